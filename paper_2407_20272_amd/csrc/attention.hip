@@ -8,6 +8,7 @@
 // Lanes that share a token add their partial dot products with a butterfly; every group of lanes keeps its own
 // running softmax (max, sum, weighted V) over the tokens it sees, and the groups, then the wavefronts, are merged
 // once at the end.  No score is ever written to memory.
+#include <atomic>
 #include <type_traits>
 
 #include "ee_common.h"
@@ -477,254 +478,498 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a, Pred pred) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Sixteen batch rows of a prompt chunk per workgroup on the matrix cores (bf16 cache).  A workgroup owns 16
-// consecutive batch rows of one head; rows of one sequence form a run whose K/V blocks are streamed ONCE, 32
-// tokens per wavefront step, and multiplied against all 16 rows with v_mfma_f32_16x16x32_bf16:
-//   scores^T [token][row] = K [token][dh] . q^T [dh][row]      (K straight from the cache as the A operand)
-//   out^T    [dh][row]   += V^T [dh][token] . p^T [token][row]  (V transposed through a per-wavefront LDS tile)
-// With the transposed products a lane holds everything of ONE row (row = lane % 16): its 8 scores of the step,
-// its running maximum and its slice of the output, so the online softmax needs two shuffles per step and the
-// probabilities go from the score registers into the next product without leaving the lane (the contraction
-// slots of the second product are simply numbered in the order the first one delivers the tokens).
-// q and the probabilities stay float in effect: each is split into a bf16 head and a bf16 remainder and
-// multiplied twice.  Rows outside the current run, and positions after a row's own, are masked.
+// Rows of a prompt chunk on the matrix cores (bf16 cache).  A workgroup of eight wavefronts owns up to R <= 64
+// consecutive batch rows of one head, in one or two groups of 32; rows of one sequence form a run, and the 32-token steps
+// of all its runs' contexts, one after the other, are dealt out to the slices (each wavefront a slice, or each pair with
+// two groups).  A wavefront multiplies its steps against its group's rows with v_mfma_f32_32x32x16_bf16; rows of other
+// runs, and positions after a row's own, are masked:
+//   scores^T [token][row] = K [token][dh] . q^T [dh][row]
+//   out^T    [dh][row]   += V^T [dh][token] . p^T [token][row]
+// With the transposed products a lane holds 16 of the 32 scores of ONE row (row = lane % 32; lane ^ 32 holds the others),
+// so the online softmax needs one shuffle per step, and the probabilities go from the score registers into the next
+// product without leaving the lane (its contraction slots are numbered in the order the first product delivers tokens).
+// q and the probabilities stay float in effect: each is split into a bf16 head and a bf16 remainder and multiplied twice.
+//
+// What bounds it is the compute unit's intake of K and V (about 55 bytes a nanosecond, whatever cache they come from), so
+// the two groups share every tile: each of a slice's two wavefronts brings one of the step's two blocks, from memory to
+// LDS directly in whole kilobytes, into the slice's other buffer while this step is multiplied; one barrier per step.
+// The lanes of a load choose WHICH 16 bytes of a token they fetch, which permutes a token's channels in LDS so that
+// neither the fragment reads of K nor the transposing reads of V (ds_read_b64_tr_b16: four tokens x 16 channels per 16
+// lanes) meet in one bank.
+// 512 rows of four sequences at 0 to 3128 positions, 32 heads x 128: 129 us with 16 rows per workgroup, each streaming
+// the whole context, and V transposed through 2-byte LDS stores; 56 us now (a step costs a wavefront about 3200 cycles:
+// 1024 of multiplies, the rest softmax, LDS and the meeting).  16 rows of 12 sequences at up to 1000 positions: 141 us
+// (runs one after the other, each through all four wavefronts) -> 28 us; 200 rows of four at up to 100: 16 -> 12 us.
 // ---------------------------------------------------------------------------------------------------------
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
+typedef __attribute__((address_space(3))) unsigned char* lds_uchar_ptr;
+typedef __attribute__((address_space(1))) const void* global_void_ptr;
 
-constexpr int CHUNK_ROWS = 16;
-constexpr int VPITCH = 34;   // bf16 per transposed V row in LDS: 32 tokens + 2 (keeps the 8 writes of a lane group on separate banks)
+constexpr int PW = 8;            // wavefronts per workgroup
+constexpr int PROMPT_ROWS = 64;  // most batch rows a workgroup owns
+
+// Two floats rounded to bf16 (nearest even), the first in the low half.
+__device__ inline unsigned pack_bf16(float a, float b) {
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned, bf16x2_t{(__bf16)a, (__bf16)b});
+}
+
+// Transposing LDS reads at four (or two) lane addresses, two rows of tokens each (the second 8 tokens on), and the wait for
+// them.  (In asm: in front of the builtin the compiler waits for every direct-to-LDS load in flight, the next K tile's too.)
+template <int OFF, int STEP>
+__device__ inline void read_tr(const unsigned (&at)[4], s16x4_t (&p)[4][2]) {
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8 offset:%12\n\tds_read_b64_tr_b16 %1, %8 offset:%13\n\t"
+      "ds_read_b64_tr_b16 %2, %9 offset:%12\n\tds_read_b64_tr_b16 %3, %9 offset:%13\n\t"
+      "ds_read_b64_tr_b16 %4, %10 offset:%12\n\tds_read_b64_tr_b16 %5, %10 offset:%13\n\t"
+      "ds_read_b64_tr_b16 %6, %11 offset:%12\n\tds_read_b64_tr_b16 %7, %11 offset:%13\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(p[0][0]), "=&v"(p[0][1]), "=&v"(p[1][0]), "=&v"(p[1][1]), "=&v"(p[2][0]), "=&v"(p[2][1]), "=&v"(p[3][0]), "=&v"(p[3][1])
+      : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "n"(OFF), "n"(OFF + STEP)
+      : "memory");
+}
+template <int OFF, int STEP>
+__device__ inline void read_tr(const unsigned (&at)[2], s16x4_t (&p)[2][2]) {
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %4 offset:%6\n\tds_read_b64_tr_b16 %1, %4 offset:%7\n\t"
+      "ds_read_b64_tr_b16 %2, %5 offset:%6\n\tds_read_b64_tr_b16 %3, %5 offset:%7\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(p[0][0]), "=&v"(p[0][1]), "=&v"(p[1][0]), "=&v"(p[1][1])
+      : "v"(at[0]), "v"(at[1]), "n"(OFF), "n"(OFF + STEP)
+      : "memory");
+}
+
+template <int DH>
+constexpr int prompt_lds_bytes() { return PW * 2 * 32 * DH * 2; }
 
 template <int DH, bool OUT_XT>
-__global__ __launch_bounds__(256) void attn_chunk_kernel(AttnArgs a, Pred pred) {
-  constexpr int CH = DH / 32;   // 32-channel contraction steps of q . K
-  constexpr int DT = DH / 16;   // 16-channel tiles of the output
-  constexpr int VS_BYTES = NW * DH * VPITCH * 2;
-  constexpr int SO_BYTES = NW * CHUNK_ROWS * DH * 4;
-  extern __shared__ int32_t tbl[];
-  __shared__ __align__(16) unsigned char smem[VS_BYTES > SO_BYTES ? VS_BYTES : SO_BYTES];
-  __shared__ int s_seq[CHUNK_ROWS], s_npos[CHUNK_ROWS];
-  __shared__ float sm[NW][CHUNK_ROWS], sl[NW][CHUNK_ROWS];
+__global__ __launch_bounds__(PW * 64) void attn_prompt_kernel(AttnArgs a, int R, Pred pred) {
+  constexpr int CS = DH / 16;            // contraction steps of q . K
+  constexpr int CT = DH / 32;            // 32-channel tiles of the output
+  constexpr int CPT = DH / 8;            // 16-byte pieces of a token
+  constexpr int TPI = 64 / CPT;          // tokens per load instruction
+  constexpr int JB = 16 / TPI;           // load instructions per 16-token block
+  constexpr int TILE = 32 * DH * 2;      // bytes of a 32-token tile
+  // two groups: [slice][buffer][K, V]; one group: [wavefront][K, V]; at the end [wavefront][32 rows][DH] floats
+  extern __shared__ __align__(16) unsigned char psm[];
+  __shared__ int s_first[PROMPT_ROWS + 1];                        // first step of every run, and their total
+  __shared__ int s_seq[PROMPT_ROWS], s_ctx[PROMPT_ROWS], s_rows[PROMPT_ROWS];   // of every run: sequence, positions, begin | end << 8
+  __shared__ float sm[PW][32], sl[PW][32];
+  __shared__ int s_meet[PW];
   if (pred_skip(pred)) return;
 
-  const int head = blockIdx.x, row0 = blockIdx.y * CHUNK_ROWS;
-  const int nrows = min(CHUNK_ROWS, a.B - row0);
+  const int head = blockIdx.x, row0 = blockIdx.y * R;
+  const int nrows = min(R, a.B - row0);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int i16 = lane & 15, g = lane >> 4;
-  const int my_row = row0 + i16;
-  const bool row_ok = i16 < nrows;
-  const int my_seq = row_ok ? safe_row(a.row_table[my_row], a.B) : -1;
-  const int my_npos = row_ok ? min(a.context_lens[my_row] + 1, a.max_blocks * 16) : 0;
-  if (threadIdx.x < CHUNK_ROWS) {
-    s_seq[i16] = my_seq;
-    s_npos[i16] = my_npos;
+  const int l32 = lane & 31, h = lane >> 5;
+  // More than 32 rows: wavefront (slice, group) of four slices, each wavefront bringing block `group` of every step for
+  // both.  Otherwise eight slices of one group, each wavefront on its own.
+  const bool two = nrows > 32;
+  const int nsl = two ? PW / 2 : PW, slice = two ? wave >> 1 : wave, grp = two ? wave & 1 : 0;
+  const int my = grp * 32 + l32;                                  // this lane's row (of the workgroup's)
+  const bool row_ok = my < nrows;
+
+  const int seq_l = lane < nrows ? safe_row(a.row_table[row0 + lane], a.B) : -1;
+  const int npos_l = lane < nrows ? min(a.context_lens[row0 + lane] + 1, a.max_blocks * 16) : 0;
+  // q of this lane's row, channels c*16 + h*8 .. +8 of every contraction step, scaled, as bf16 head + remainder
+  u32x4_t qh[CS], ql[CS];
+  {
+    const float sc = row_ok ? 1.4426950408889634f / sqrtf((float)DH) : 0.0f;
+    const float* qp = a.q + ((size_t)(row0 + (row_ok ? my : 0)) * a.n_heads + head) * DH + h * 8;
+#pragma unroll
+    for (int c = 0; c < CS; ++c) {
+      const float4 lo = *reinterpret_cast<const float4*>(qp + c * 16);
+      const float4 hi = *reinterpret_cast<const float4*>(qp + c * 16 + 4);
+      const float v[8] = {lo.x * sc, lo.y * sc, lo.z * sc, lo.w * sc, hi.x * sc, hi.y * sc, hi.z * sc, hi.w * sc};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned hd = pack_bf16(v[2 * e], v[2 * e + 1]);
+        qh[c][e] = hd;
+        ql[c][e] = pack_bf16(v[2 * e] - __uint_as_float(hd << 16), v[2 * e + 1] - __uint_as_float(hd & 0xffff0000u));
+      }
+    }
   }
 
-  // q of this lane's row, channels c*32 + g*8 .. +8 of every contraction step, scaled, as bf16 head + remainder
-  const float sc = 1.4426950408889634f / sqrtf((float)DH);
-  bf16x8_t qh[CH], ql[CH];
-  {
-    const float* qp = a.q + ((size_t)(row_ok ? my_row : row0) * a.n_heads + head) * DH + g * 8;
+  // The runs: every lane that starts one finds its end, its longest row and the steps before it (the same in every wavefront).
+  const int n_runs = [&] {
+    const int before = __shfl_up(seq_l, 1);   // (outside the condition: a shuffle reads nothing from a lane that is masked off)
+    const bool starts = lane < nrows && (lane == 0 || before != seq_l);
+    const unsigned long long bal = __ballot(starts);
+    const unsigned long long after = lane < 63 ? bal >> (lane + 1) : 0;
+    const int end = after ? lane + 1 + __builtin_ctzll(after) : nrows;
+    int ctx = npos_l;
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const float4 lo = *reinterpret_cast<const float4*>(qp + c * 32);
-      const float4 hi = *reinterpret_cast<const float4*>(qp + c * 32 + 4);
-      const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    for (int x = 1; x < 64; x <<= 1) {
+      const int o = __shfl_down(ctx, x);
+      if (lane + x < end) ctx = max(ctx, o);
+    }
+    const int steps = starts ? (ctx + 31) >> 5 : 0;
+    int upto = steps;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float x = row_ok ? v[e] * sc : 0.0f;
-        const __bf16 h = (__bf16)x;
-        qh[c][e] = h;
-        ql[c][e] = (__bf16)(x - (float)h);
+    for (int x = 1; x < 64; x <<= 1) {
+      const int o = __shfl_up(upto, x);
+      if (lane >= x) upto += o;
+    }
+    if (wave == 0) {
+      if (starts) {
+        const int j = __popcll(bal & ((1ull << lane) - 1ull));
+        s_first[j] = upto - steps;
+        s_seq[j] = seq_l;
+        s_ctx[j] = ctx;
+        s_rows[j] = lane | end << 8;
       }
+      if (lane == 63) s_first[__popcll(bal)] = upto;
+      if (lane < PW) s_meet[lane] = 0;
+    }
+    return __popcll(bal);
+  }();
+  __syncthreads();
+  const int n_steps = __builtin_amdgcn_readfirstlane(s_first[n_runs]);
+  // Steps of this wavefront, over all runs one after the other; both wavefronts of a pair take part in every step of
+  // their slice.  One past the end repeats the last.
+  const int nk = slice < n_steps ? (n_steps - slice + nsl - 1) / nsl : 0;
+
+  const size_t block_elems = (size_t)a.n_heads * 16 * DH;
+  const bf16_t* kpool = reinterpret_cast<const bf16_t*>(a.k_pool) + (size_t)head * 16 * DH;
+  const bf16_t* vpool = reinterpret_cast<const bf16_t*>(a.v_pool) + (size_t)head * 16 * DH;
+  // piece c of token t lies at piece c ^ perm(t) of its row: K t % CPT, V 2 * (t % (CPT / 2))
+  int koff[JB], voff[JB];
+#pragma unroll
+  for (int j = 0; j < JB; ++j) {
+    const int t = j * TPI + lane / CPT, c = lane % CPT;
+    koff[j] = t * DH + (c ^ (t & (CPT - 1))) * 8;
+    voff[j] = t * DH + (c ^ (2 * (t & (CPT / 2 - 1)))) * 8;
+  }
+  // lane offsets of the transposing reads: token h*4 + (lane%16)/4 (+ 8, 16, 24), channels d*32 + (lane/16%2)*16 + lane%4*4
+  unsigned voff_tr[CT];
+#pragma unroll
+  for (int d = 0; d < CT; ++d) {
+    const int t = h * 4 + ((lane & 15) >> 2);
+    const int piece = (d * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ (2 * (t & (CPT / 2 - 1)));
+    voff_tr[d] = t * (DH * 2) + piece * 16 + (lane & 1) * 8;
+  }
+
+  // The blocks of 32 steps at a time sit in one pair of registers (bytes from the pool's start), two lanes per step.  An
+  // odd block count reads the last block twice (its second copy is masked).
+  int off_lo = 0, off_hi = 0, ids_from = 0;
+  auto step_of = [&](int k) { return min(slice + k * nsl, n_steps - 1); };
+  auto load_ids = [&](int k0) {
+    const int g = step_of(k0 + (lane >> 1));
+    int j = 0;
+    while (j + 1 < n_runs && s_first[j + 1] <= g) ++j;
+    const int lb = min(2 * (g - s_first[j]) + (lane & 1), ((s_ctx[j] + 15) >> 4) - 1);
+    const int blk = safe_block(a.block_tables[(size_t)s_seq[j] * a.max_blocks + lb], a.num_blocks);
+    const size_t off = (size_t)blk * (block_elems * sizeof(bf16_t));
+    off_lo = (int)(unsigned)off;
+    off_hi = (int)(unsigned)(off >> 32);
+    ids_from = k0;
+  };
+  auto block_at = [&](const bf16_t* pool, int k, int hb) {
+    const int i = 2 * (k - ids_from) + hb;
+    const unsigned lo = __builtin_amdgcn_readlane(off_lo, i), hi = __builtin_amdgcn_readlane(off_hi, i);
+    return reinterpret_cast<const bf16_t*>(reinterpret_cast<const char*>(pool) + ((size_t)hi << 32 | lo));
+  };
+  // The run of the step that is loaded / multiplied (both only move forward).
+  struct Run {
+    int j, first, next, ctx, rows;
+  };
+  auto run_at = [&](int j) {
+    Run r;
+    r.j = j;
+    r.first = __builtin_amdgcn_readfirstlane(s_first[j]);
+    r.next = __builtin_amdgcn_readfirstlane(s_first[j + 1]);
+    r.ctx = __builtin_amdgcn_readfirstlane(s_ctx[j]);
+    r.rows = __builtin_amdgcn_readfirstlane(s_rows[j]);
+    return r;
+  };
+  Run ld = run_at(0);
+  // block hb (0 / 1) of step k: K tile to kt, V tile to kt + TILE
+  auto issue_k = [&](int k, int hb, unsigned char* kt) {
+    const bf16_t* kb = block_at(kpool, k, hb);
+#pragma unroll
+    for (int j = 0; j < JB; ++j)
+      __builtin_amdgcn_global_load_lds((global_void_ptr)(kb + koff[j]), (lds_void_ptr)(kt + hb * (TILE / 2) + j * 1024), 16, 0, 0);
+  };
+  auto issue_v = [&](int k, int hb, unsigned char* kt) {
+    const bf16_t* vb = block_at(vpool, k, hb);
+    const int g = step_of(k);
+    while (g >= ld.next) ld = run_at(ld.j + 1);
+    const int t0 = (g - ld.first) * 32 + hb * 16;
+    unsigned char* vt = kt + TILE + hb * (TILE / 2);
+    if (t0 + 16 <= ld.ctx) {
+#pragma unroll
+      for (int j = 0; j < JB; ++j)
+        __builtin_amdgcn_global_load_lds((global_void_ptr)(vb + voff[j]), (lds_void_ptr)(vt + j * 1024), 16, 0, 0);
+    } else {   // positions from the run's end on (also the second copy of a repeated last block) come from the zeros
+      for (int j = 0; j < JB; ++j) {
+        const int t = j * TPI + lane / CPT, c = lane % CPT;
+        const bf16_t* src = vb + t * DH + (c ^ (2 * (t & (CPT / 2 - 1)))) * 8;
+        if (t0 + t >= ld.ctx) src = reinterpret_cast<const bf16_t*>(&k_zero16);
+        __builtin_amdgcn_global_load_lds((global_void_ptr)src, (lds_void_ptr)(vt + j * 1024), 16, 0, 0);
+      }
+    }
+  };
+  unsigned char* ring = psm + (size_t)(two ? slice * 4 : wave * 2) * TILE;
+  if (nk > 0) {
+    load_ids(0);
+    if (two) {
+      issue_k(0, grp, ring);
+      issue_v(0, grp, ring);
+    } else {
+      issue_k(0, 0, ring);
+      issue_k(0, 1, ring);
+      issue_v(0, 0, ring);
+      issue_v(0, 1, ring);
     }
   }
 
   float m_run = NEG_BIG, l_run = 0.0f;
-  f32x4_t o[DT];
+  f32x16 o[CT];
 #pragma unroll
-  for (int d = 0; d < DT; ++d) o[d] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-
-  const size_t block_elems = (size_t)a.n_heads * 16 * DH;
-  const size_t lane_off = (size_t)head * 16 * DH + (size_t)i16 * DH + g * 8;   // token i16 of a block, channels g*8..
-  const bf16_t* kbase = reinterpret_cast<const bf16_t*>(a.k_pool) + lane_off;
-  const bf16_t* vbase = reinterpret_cast<const bf16_t*>(a.v_pool) + lane_off;
-  __bf16 (*vw)[VPITCH] = reinterpret_cast<__bf16 (*)[VPITCH]>(smem + (size_t)wave * DH * VPITCH * 2);
-
-  __syncthreads();
-  int r_begin = 0;
-  while (r_begin < nrows) {
-    // the run: rows r_begin .. r_end-1 of one sequence (uniform over the workgroup)
-    const int run_seq = __builtin_amdgcn_readfirstlane(s_seq[r_begin]);
-    int r_end = r_begin + 1;
-    while (r_end < nrows && __builtin_amdgcn_readfirstlane(s_seq[r_end]) == run_seq) ++r_end;
-    int run_ctx = 0;
-    for (int r = r_begin; r < r_end; ++r) run_ctx = max(run_ctx, __builtin_amdgcn_readfirstlane(s_npos[r]));
-    const int n_blocks = (run_ctx + 15) >> 4;
-    const int n_steps = (n_blocks + 1) >> 1;
-    const int32_t* table = a.block_tables + (size_t)run_seq * a.max_blocks;
-    __syncthreads();   // the previous run's table is no longer read
-    for (int x = threadIdx.x; x < n_blocks; x += blockDim.x) tbl[x] = safe_block(table[x], a.num_blocks);
-    __syncthreads();
-    const int npos_eff = (i16 >= r_begin && i16 < r_end) ? my_npos : 0;
-
-    for (int s = wave; s < n_steps; s += NW) {
-      // two 16-token blocks; an odd block count reads the last block twice (its second copy is masked)
-      const int lb1 = min(2 * s + 1, n_blocks - 1);
-      const size_t off[2] = {(size_t)__builtin_amdgcn_readfirstlane(tbl[2 * s]) * block_elems,
-                             (size_t)__builtin_amdgcn_readfirstlane(tbl[lb1]) * block_elems};
-      u32x4_t kt[2][CH], vt[2][CH];
+  for (int d = 0; d < CT; ++d)
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int i = 0; i < 16; ++i) o[d][i] = 0.0f;
+
+  auto walk = [&](auto two_c) {
+    constexpr bool TWO = decltype(two_c)::value;
+    Run mu = run_at(0);
+    mu.next = -1;                 // taken up at the first step
+    mu.j = -1;
+    int npos = 0;                 // positions this lane's row attends of the run (0: the row is another run's)
+    int longest = 0, full = 0;    // longest / shortest row of the group (shortest: 0 if not all of its rows are the run's)
+    int meet = 0;
+    for (int k = 0; k < nk; ++k) {
+      const int g = slice + k * nsl;
+      if (g >= mu.next) {
+        do mu = run_at(mu.j + 1);
+        while (g >= mu.next);
+        const int rb = mu.rows & 255, re = mu.rows >> 8;
+        npos = __shfl(npos_l, my);
+        if (my < rb || my >= re) npos = 0;
+        longest = npos;
+        full = row_ok ? npos : 0x7fffffff;
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          kt[t][c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(kbase + off[t] + c * 32));
-          // positions from the run's end on (also the second copy of a repeated last block) come from the zeros
-          vt[t][c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(
-              s * 32 + t * 16 + i16 < run_ctx ? vbase + off[t] + c * 32 : reinterpret_cast<const bf16_t*>(&k_zero16)));
+        for (int x = 1; x < 32; x <<= 1) {
+          longest = max(longest, __shfl_xor(longest, x));
+          full = min(full, __shfl_xor(full, x));
         }
-      // scores^T of the 32 tokens: lane (i16, g) gets tokens 4g..4g+3 of each block for row i16
-      f32x4_t st[2];
+        longest = __builtin_amdgcn_readfirstlane(longest);
+        full = __builtin_amdgcn_readfirstlane(full);
+      }
+      if (k + 1 - ids_from == 32) load_ids(k + 1);
+      const unsigned char* kt = ring;
+      if constexpr (TWO) {
+        // This wavefront's half of step k is in LDS and it has read step k-1: say so, and wait for the other's word.
+        // (Only the pair meets, and both make every step, so the wait ends; the slices run free of each other.)
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        ++meet;
+        __hip_atomic_store(&s_meet[wave], meet, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        while (__hip_atomic_load(&s_meet[wave ^ 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < meet) {
+        }
+        asm volatile("" ::: "memory");
+        unsigned char* other = ring + ((k + 1) & 1) * 2 * TILE;
+        issue_k(k + 1, grp, other);                  // (the one past the end is never used)
+        issue_v(k + 1, grp, other);
+        kt = ring + (k & 1) * 2 * TILE;
+      } else {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * JB) : "memory");   // K of step k is in LDS, V may still be on its way
+      }
+      const int tok0 = (g - mu.first) * 32;
+      if (TWO && tok0 >= longest) continue;          // nothing for this group
+      f32x16 st;
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        st[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int i = 0; i < 16; ++i) st[i] = 0.0f;
+      {
+        bf16x8_t kk[CS];
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          const bf16x8_t kk = __builtin_bit_cast(bf16x8_t, kt[t][c]);
-          st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, qh[c], st[t], 0, 0, 0);
-          st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, ql[c], st[t], 0, 0, 0);
+        for (int c = 0; c < CS; ++c)
+          kk[c] = *reinterpret_cast<const bf16x8_t*>(kt + l32 * (DH * 2) + ((2 * c + h) ^ (l32 & (CPT - 1))) * 16);
+#pragma unroll
+        for (int c = 0; c < CS; ++c) {
+          st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[c], __builtin_bit_cast(bf16x8_t, qh[c]), st, 0, 0, 0);
+          st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[c], __builtin_bit_cast(bf16x8_t, ql[c]), st, 0, 0, 0);
         }
       }
-      float sv[8];
+      if constexpr (!TWO) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the K tile has been read: its space takes the next one
+        issue_k(k + 1, 0, ring);
+        issue_k(k + 1, 1, ring);
+      }
+      // accumulator i of a lane is token (i/4)*8 + h*4 + i%4 of the step
+      const bool masked = tok0 + 32 > full;
+      if (masked) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) st[i] = tok0 + (i >> 2) * 8 + h * 4 + (i & 3) < npos ? st[i] : NEG_BIG;
+      }
       float mx = m_run;
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int tok = s * 32 + t * 16 + 4 * g + r;
-          sv[t * 4 + r] = tok < npos_eff ? st[t][r] : NEG_BIG;
-          mx = fmaxf(mx, sv[t * 4 + r]);
-        }
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, st[i]);
       mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float alpha = __builtin_amdgcn_exp2f(m_run - mx);
-      m_run = mx;
-      l_run *= alpha;
+      // The sums are taken relative to m_run, which follows the maximum only when some row's has grown by more than 2^8:
+      // until then probabilities up to 256 lose nothing in float, and the output need not be rescaled.
+      if (__any(mx > m_run + 8.0f)) {
+        const float alpha = __builtin_amdgcn_exp2f(m_run - mx);
+        m_run = mx;
+        l_run *= alpha;
 #pragma unroll
-      for (int d = 0; d < DT; ++d) o[d] *= alpha;
-      bf16x8_t ph, pl;
+        for (int d = 0; d < CT; ++d)
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+          for (int i = 0; i < 16; ++i) o[d][i] *= alpha;
+      }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int tok = s * 32 + t * 16 + 4 * g + r;
-          const float p = tok < npos_eff ? __builtin_amdgcn_exp2f(sv[t * 4 + r] - mx) : 0.0f;
-          l_run += p;
-          const __bf16 h = (__bf16)p;
-          ph[t * 4 + r] = h;
-          pl[t * 4 + r] = (__bf16)(p - (float)h);
+      for (int i = 0; i < 16; ++i) st[i] = __builtin_amdgcn_exp2f(st[i] - m_run);
+      if (masked) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) st[i] = tok0 + (i >> 2) * 8 + h * 4 + (i & 3) < npos ? st[i] : 0.0f;
+      }
+      u32x4_t ph[2], pl[2];
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        l_run += st[i];
+        l_run += st[i + 1];
+        const unsigned hd = pack_bf16(st[i], st[i + 1]);
+        ph[i >> 3][(i & 7) >> 1] = hd;
+        pl[i >> 3][(i & 7) >> 1] = pack_bf16(st[i] - __uint_as_float(hd << 16), st[i + 1] - __uint_as_float(hd & 0xffff0000u));
+      }
+      if constexpr (!TWO) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * JB) : "memory");   // V of step k is in LDS
+      // contraction slot 8h + e of 16 tokens is token (e/4)*8 + 4h + e%4: the order ph / pl hold them in
+      unsigned va[CT];
+#pragma unroll
+      for (int d = 0; d < CT; ++d) va[d] = (unsigned)(size_t)(lds_uchar_ptr)(kt + TILE) + voff_tr[d];
+      auto output_product = [&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        typedef short s16x8_t __attribute__((ext_vector_type(8)));
+        s16x4_t part[CT][2];
+        read_tr<u * 16 * DH * 2, 8 * DH * 2>(va, part);
+#pragma unroll
+        for (int d = 0; d < CT; ++d) {
+          const s16x8_t v8 = __builtin_shufflevector(part[d][0], part[d][1], 0, 1, 2, 3, 4, 5, 6, 7);
+          o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v8), __builtin_bit_cast(bf16x8_t, ph[u]), o[d], 0, 0, 0);
+          o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v8), __builtin_bit_cast(bf16x8_t, pl[u]), o[d], 0, 0, 0);
         }
-      // V of the 32 tokens, transposed into this wavefront's LDS tile: vw[channel][token]
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          const bf16x8_t vv = __builtin_bit_cast(bf16x8_t, vt[t][c]);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) vw[c * 32 + g * 8 + e][t * 16 + i16] = vv[e];
-        }
-      // out^T += V^T . p^T; contraction slot e of lane group g is token 4g+e of the first block (e < 4) or
-      // token 4g+e-4 of the second: the order in which ph / pl hold the probabilities
-#pragma unroll
-      for (int d = 0; d < DT; ++d) {
-        const __bf16* rowp = &vw[16 * d + i16][0];
-        bf16x8_t va;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          va[e] = rowp[4 * g + e];
-          va[4 + e] = rowp[16 + 4 * g + e];
-        }
-        o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, ph, o[d], 0, 0, 0);
-        o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pl, o[d], 0, 0, 0);
+      };
+      output_product(std::integral_constant<int, 0>{});
+      output_product(std::integral_constant<int, 1>{});
+      if constexpr (!TWO) {   // (the V tile has been read: read_tr waits)
+        issue_v(k + 1, 0, ring);
+        issue_v(k + 1, 1, ring);
       }
     }
-    r_begin = r_end;
-  }
+  };
+  if (two)
+    walk(std::true_type{});
+  else
+    walk(std::false_type{});
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the end still target LDS
+  __syncthreads();                                   // every tile has been read: the space now holds the partial outputs
 
-  // the four lane groups of a row hold partial sums of the same maximum; then merge the wavefronts row by row
-  l_run += __shfl_xor(l_run, 16);
+  // the two lanes of a row hold partial sums of the same maximum; then the slices are added in slice order
   l_run += __shfl_xor(l_run, 32);
-  __syncthreads();   // every wavefront is done with its V tile: the space now holds the partial outputs
-  float (*so)[CHUNK_ROWS][DH] = reinterpret_cast<float (*)[CHUNK_ROWS][DH]>(smem);
+  if (nk > 0) {
+    float* so = reinterpret_cast<float*>(psm + (size_t)wave * 2 * TILE);   // [32 rows][DH], pieces of four channels permuted by row
 #pragma unroll
-  for (int d = 0; d < DT; ++d)
-    *reinterpret_cast<float4*>(&so[wave][i16][16 * d + 4 * g]) = make_float4(o[d][0], o[d][1], o[d][2], o[d][3]);
-  if (g == 0) {
-    sm[wave][i16] = m_run;
-    sl[wave][i16] = l_run;
+    for (int d = 0; d < CT; ++d)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int piece = (d * 8 + q4 * 2 + h) ^ (l32 & (DH / 4 - 1));
+        *reinterpret_cast<float4*>(so + l32 * DH + piece * 4) = make_float4(o[d][4 * q4], o[d][4 * q4 + 1], o[d][4 * q4 + 2], o[d][4 * q4 + 3]);
+      }
+    if (h == 0) {
+      sm[wave][l32] = m_run;
+      sl[wave][l32] = l_run;
+    }
   }
   __syncthreads();
-  // one thread per (row, 8 consecutive channels): 16-byte (bf16 operand order) or 2 x 16-byte (float) stores
-  {
-    constexpr int G8 = DH / 8;
-    const int r = threadIdx.x / G8, c0 = (threadIdx.x % G8) * 8;
-    if (r < nrows) {
-      float M = sm[0][r];
+  const int ng = two ? 2 : 1, n_live = min(nsl, n_steps);   // slices that had a step
+  for (int t = threadIdx.x; t < ng * 32 * CPT; t += PW * 64) {   // thread -> (group, row, 8 channels)
+    const int g = t / (32 * CPT), u = t % (32 * CPT);
+    const int r = OUT_XT ? u % 32 : u / CPT, c8 = OUT_XT ? u / 32 : u % CPT;
+    if (g * 32 + r >= nrows) continue;
+    float M = NEG_BIG;
+    for (int i = 0; i < n_live; ++i) M = fmaxf(M, sm[i * ng + g][r]);
+    float L = 0.0f, acc[8];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) M = fmaxf(M, sm[w][r]);
-      float L = 0.0f, acc[8];
+    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+    for (int i = 0; i < n_live; ++i) {
+      const int w = i * ng + g;
+      const float wgt = __builtin_amdgcn_exp2f(sm[w][r] - M);
+      L += sl[w][r] * wgt;
+      const float* sp = reinterpret_cast<const float*>(psm + (size_t)w * 2 * TILE) + r * DH;
+      const float4 lo = *reinterpret_cast<const float4*>(sp + ((2 * c8) ^ (r & (DH / 4 - 1))) * 4);
+      const float4 hi = *reinterpret_cast<const float4*>(sp + ((2 * c8 + 1) ^ (r & (DH / 4 - 1))) * 4);
+      const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+      for (int e = 0; e < 8; ++e) acc[e] += v[e] * wgt;
+    }
+    const float inv = 1.0f / L;
+    const int row = row0 + g * 32 + r, col = head * DH + c8 * 8;
+    if constexpr (OUT_XT) {
+      bf16x8_t o8;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const float wgt = __builtin_amdgcn_exp2f(sm[w][r] - M);
-        L += sl[w][r] * wgt;
-        const float4 lo = *reinterpret_cast<const float4*>(&so[w][r][c0]);
-        const float4 hi = *reinterpret_cast<const float4*>(&so[w][r][c0 + 4]);
-        const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += v[e] * wgt;
-      }
-      const float inv = 1.0f / L;
-      const int col = head * DH + c0;
-      if constexpr (OUT_XT) {
-        bf16x8_t o8;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o8[e] = (__bf16)(acc[e] * inv);
-        *reinterpret_cast<bf16x8_t*>(reinterpret_cast<bf16_t*>(a.out) + xt_index(row0 + r, col, a.n_heads * DH)) = o8;
-      } else {
-        float* op = reinterpret_cast<float*>(a.out) + (size_t)(row0 + r) * a.n_heads * DH + col;
-        *reinterpret_cast<float4*>(op) = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
-        *reinterpret_cast<float4*>(op + 4) = make_float4(acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv);
-      }
+      for (int e = 0; e < 8; ++e) o8[e] = (__bf16)(acc[e] * inv);
+      *reinterpret_cast<bf16x8_t*>(reinterpret_cast<bf16_t*>(a.out) + xt_index(row, col, a.n_heads * DH)) = o8;
+    } else {
+      float* op = reinterpret_cast<float*>(a.out) + (size_t)row * a.n_heads * DH + col;
+      *reinterpret_cast<float4*>(op) = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+      *reinterpret_cast<float4*>(op + 4) = make_float4(acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv);
     }
   }
+}
+
+// Batch rows per workgroup: as many as it takes for one round of workgroups (one per compute unit: 128 KiB of LDS each);
+// a workgroup's time hangs on its longest context, not on its rows, so fewer workgroups than that leave the chip idle
+// and a second round costs as much as the first.
+int prompt_rows(int B, int n_heads) {
+  const int blocks = n_heads < 256 ? 256 / n_heads : 1;
+  const int R = (B + blocks - 1) / blocks;
+  return R < 4 ? 4 : R > PROMPT_ROWS ? PROMPT_ROWS : R;
+}
+
+// More than 64 KiB of LDS per workgroup has to be asked for, once per device.
+template <int DH, bool OUT_XT>
+bool prompt_lds_allowed() {
+  static std::atomic<unsigned long long> asked{0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  const unsigned long long bit = 1ull << (dev & 63);
+  if (asked.load(std::memory_order_relaxed) & bit) return true;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prompt_kernel<DH, OUT_XT>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          prompt_lds_bytes<DH>()) != hipSuccess)
+    return false;
+  asked.fetch_or(bit, std::memory_order_relaxed);
+  return true;
+}
+
+template <int DH, bool OUT_XT>
+int launch_prompt(const AttnArgs& a, Pred pred, hipStream_t st) {
+  if (!prompt_lds_allowed<DH, OUT_XT>()) EE_FAIL(EE_ERR_HIP, "attention: %d bytes of LDS refused", prompt_lds_bytes<DH>());
+  const int R = prompt_rows(a.B, a.n_heads);
+  hipLaunchKernelGGL((attn_prompt_kernel<DH, OUT_XT>), dim3(a.n_heads, (a.B + R - 1) / R), dim3(PW * 64), prompt_lds_bytes<DH>(), st,
+                     a, R, pred);
+  return EE_OK;
 }
 
 // Four rows per workgroup measured best at the 7B shape (eight: 300 registers, one wavefront per SIMD, slower).
 constexpr int ROWS_PER_GROUP = 4;
 
 template <class T, int DH>
-void launch_t(const AttnArgs& a, Pred pred, hipStream_t st) {
+int launch_t(const AttnArgs& a, Pred pred, hipStream_t st) {
   dim3 block(256);
   const size_t lds = (size_t)a.max_blocks * sizeof(int32_t);
   if (a.row_table) {   // rows share sequences: stream every sequence's K/V once per group of rows
     if constexpr (std::is_same<T, bf16_t>::value) {
-      dim3 grid16(a.n_heads, (a.B + CHUNK_ROWS - 1) / CHUNK_ROWS);
-      if (a.out_xt)
-        hipLaunchKernelGGL((attn_chunk_kernel<DH, true>), grid16, block, lds, st, a, pred);
-      else
-        hipLaunchKernelGGL((attn_chunk_kernel<DH, false>), grid16, block, lds, st, a, pred);
-      return;
+      return a.out_xt ? launch_prompt<DH, true>(a, pred, st) : launch_prompt<DH, false>(a, pred, st);
     }
     dim3 grid(a.n_heads, (a.B + ROWS_PER_GROUP - 1) / ROWS_PER_GROUP);
     if (a.out_xt)
       hipLaunchKernelGGL((attn_rows_kernel<T, DH, ROWS_PER_GROUP, true>), grid, block, lds, st, a, pred);
     else
       hipLaunchKernelGGL((attn_rows_kernel<T, DH, ROWS_PER_GROUP, false>), grid, block, lds, st, a, pred);
-    return;
+    return EE_OK;
   }
   if (a.split_ws && a.split_parts > 1) {
     // the output form only matters to the merge launch; the parts always leave as floats
@@ -735,13 +980,14 @@ void launch_t(const AttnArgs& a, Pred pred, hipStream_t st) {
       hipLaunchKernelGGL((attn_merge_kernel<DH, true>), gridm, dim3(DH), 0, st, a, pred);
     else
       hipLaunchKernelGGL((attn_merge_kernel<DH, false>), gridm, dim3(DH), 0, st, a, pred);
-    return;
+    return EE_OK;
   }
   dim3 grid(a.n_heads, a.B);
   if (a.out_xt)
     hipLaunchKernelGGL((attn_decode_kernel<T, DH, true, false>), grid, block, lds, st, a, pred);
   else
     hipLaunchKernelGGL((attn_decode_kernel<T, DH, false, false>), grid, block, lds, st, a, pred);
+  return EE_OK;
 }
 
 }  // namespace
@@ -768,15 +1014,14 @@ int launch_attention(const AttnArgs& a, int dtype, Pred pred, hipStream_t st) {
     EE_FAIL(EE_ERR_UNSUPPORTED, "attention: max_blocks %d outside 1..%d", a.max_blocks, TABLE_LDS_MAX);
   if (a.out_pos && a.row_table) EE_FAIL(EE_ERR_UNSUPPORTED, "attention: out_pos does not go with row_table");
   if (dtype == EE_FP32) {
-    if (a.head_dim == 64) launch_t<float, 64>(a, pred, st);
-    else if (a.head_dim == 128) launch_t<float, 128>(a, pred, st);
+    if (a.head_dim == 64) return launch_t<float, 64>(a, pred, st);
+    else if (a.head_dim == 128) return launch_t<float, 128>(a, pred, st);
     else EE_FAIL(EE_ERR_UNSUPPORTED, "attention: head_dim %d not supported for fp32 (64 or 128)", a.head_dim);
   } else {
-    if (a.head_dim == 64) launch_t<bf16_t, 64>(a, pred, st);
-    else if (a.head_dim == 128) launch_t<bf16_t, 128>(a, pred, st);
+    if (a.head_dim == 64) return launch_t<bf16_t, 64>(a, pred, st);
+    else if (a.head_dim == 128) return launch_t<bf16_t, 128>(a, pred, st);
     else EE_FAIL(EE_ERR_UNSUPPORTED, "attention: head_dim %d not supported for bf16 (64 or 128)", a.head_dim);
   }
-  return EE_OK;
 }
 
 }  // namespace ee

@@ -156,6 +156,47 @@ def test_attention_rows_of_several_sequences_across_row_groups(dh):
         assert_close_scaled(out[r].cpu(), want, tol_of(cfg), f"row {r}: sequence {s_} at position {p_}")
 
 
+@pytest.mark.parametrize("dh,n_heads,runs", [
+    (128, 2, [(1, 0), (3, 31), (1, 40), (2, 15)]),                    # four rows a workgroup, runs of one to three rows
+    (128, 40, [(33, 0), (64, 95), (5, 17), (90, 500)]),               # six blocks of rows: one group of 32, runs straddle them
+    (64, 40, [(200, 0), (1, 300), (120, 33), (59, 130)]),             # two groups of 32, a last block of few rows
+    (128, 32, [(250, 4200), (262, 0)]),                               # two groups, more steps per slice than one look-up of ids
+    (64, 2, [(7, 8300)]),                                             # one group, likewise
+])
+def test_attention_prompt_rows_run_structure(dh, n_heads, runs):
+    """Prompt rows as (rows, first position) per sequence, consecutive positions, NaN behind every sequence's end: group
+    sizes, runs that straddle groups and workgroups, odd block counts, long slices.  q and the probabilities are carried
+    with 16 significant bits or more (bf16 head + remainder), so a score of magnitude 8 is off by at most 8 * 2^-17 and a
+    result by about as much: 6e-5 at worst, averaged well below over a row; asserted on the 2-norm at 2e-5."""
+    cfg = cfg_of("bf16", dh, n_heads, n_layers=1).with_(batch=len(runs), shuffled_blocks=True)
+    lens = torch.tensor([b + n - 1 for n, b in runs], dtype=torch.int32)
+    Lmax = int(lens.max()) + 1
+    Ks, Vs = W.make_dense_kv(cfg, lens + 1, Lmax, seed=18, device="cuda")
+    bt, nb = W.make_block_tables(lens, 1, 16, True, 18, spare_blocks=2)
+    cache = B.PagedKV(cfg, nb)
+    cache.k[0] = W.dense_to_paged(Ks[0], bt, nb, 16)
+    cache.v[0] = W.dense_to_paged(Vs[0], bt, nb, 16)
+    poison_unwritten_slots(cache, bt, lens + 1)
+    rows = [(s, b + i) for s, (n, b) in enumerate(runs) for i in range(n)]
+    pos = torch.tensor([p for _, p in rows], dtype=torch.int32)
+    seq = torch.tensor([s for s, _ in rows], dtype=torch.int32)
+    q = torch.randn(len(rows), n_heads, dh, generator=torch.Generator().manual_seed(18)) * 1.3
+    out = torch.zeros(len(rows), n_heads, dh, device="cuda")
+    batch = B.make_batch(None, pos.cuda(), bt.cuda(), Lmax, seq.cuda())
+    B.ee_paged_attention_decode(B.make_desc(cfg), cache, 1, q.cuda(), batch, out)
+    torch.cuda.synchronize()
+    want = torch.empty(len(rows), n_heads, dh, dtype=F64)
+    for s, (n, b) in enumerate(runs):   # every head a plain 2-D product in float64
+        mask = torch.arange(b + n)[None, :] > torch.arange(b, b + n)[:, None]
+        at = [r for r, (t, _) in enumerate(rows) if t == s]
+        for h in range(n_heads):
+            K, V = Ks[0][s, :b + n, h].cpu().to(F64), Vs[0][s, :b + n, h].cpu().to(F64)
+            z = (q[at, h].to(F64) @ K.T / math.sqrt(dh)).masked_fill(mask, -math.inf)
+            want[at, h] = z.softmax(-1) @ V
+    err = ((out.cpu().to(F64) - want).flatten(1).norm(dim=1) / want.flatten(1).norm(dim=1)).max().item()
+    assert err <= 2e-5, f"relative error of a row: {err}"
+
+
 def test_attention_single_sequence_and_sequential_blocks():
     run_attention(cfg_of("bf16", 128, 2), [300], seed=12, shuffled=False)
     run_attention(cfg_of("fp32", 64, 4), [47], seed=13, shuffled=False)
