@@ -435,6 +435,14 @@ __device__ inline void finish_from_registers(const f32x16& acc, int nt, int mtil
   }
 }
 
+// 16 bytes of a packed weight tile: streamed past the caches (nt) when one workgroup reads it, kept for the others when
+// several do.
+template <bool KEEP>
+__device__ inline u32x4 weight_load(const u32x4* p) {
+  if constexpr (KEEP) return *p;
+  else return __builtin_nontemporal_load(p);
+}
+
 template <int MT>
 struct TiledLds {
   u32x4 b[2][UT][MT][64];
@@ -525,10 +533,11 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pre
   // outstanding load where the branches meet): the group count is rounded up to the rotation period and
   // groups past the end load a clamped weight tile against zero activations.
   const int n = (ks1 - ks0 + UT - 1) / UT;
-  // The main loop exists twice, chosen once per wavefront: with and without a weight stream.  Both take the same
-  // barriers.
-  auto main_loop = [&](auto streams_c) {
+  // The main loop exists in three forms, chosen once per wavefront: without a weight stream, with one that nobody else
+  // reads, with one that the other row chunks read too.  All take the same barriers.
+  auto main_loop = [&](auto streams_c, auto keep_c) {
     constexpr bool STREAMS = decltype(streams_c)::value;
+    constexpr bool KEEP = decltype(keep_c)::value;
     u32x4 W[4][NTW][UT], X[2][XR];
     auto gload = [&](int grp, u32x4 (&wr)[NTW][UT], u32x4 (&xr)[XR]) {
       const int kbase = ks0 + grp * UT;
@@ -537,7 +546,7 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pre
         for (int u = 0; u < UT; ++u) {
           const int kk = kbase + u < ks1 ? kbase + u : ks1 - 1;
 #pragma unroll
-          for (int t = 0; t < NTW; ++t) wr[t][u] = __builtin_nontemporal_load(wp + t * w_tile_stride + (size_t)kk * 64);
+          for (int t = 0; t < NTW; ++t) wr[t][u] = weight_load<KEEP>(wp + t * w_tile_stride + (size_t)kk * 64);
         }
       }
 #pragma unroll
@@ -606,10 +615,12 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pre
     }
     __syncthreads();
   };
-  if (active) {
-    main_loop(std::true_type{});
+  if (active && MT == 4 && g.keep_chunks > 0 && M_eff > (g.keep_chunks - 1) * MT * 32) {
+    main_loop(std::true_type{}, std::integral_constant<bool, MT == 4>{});
+  } else if (active) {
+    main_loop(std::true_type{}, std::false_type{});
   } else {
-    main_loop(std::false_type{});
+    main_loop(std::false_type{}, std::false_type{});
     return;       // nothing to finish; the epilogues below take no workgroup barrier
   }
 
@@ -839,8 +850,14 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
         return;
       }
     }
+    // From how many working row chunks on the weights are loaded to stay in the L2 that the chunks share, instead of past
+    // it: with one reader the plain load costs 10 % (LM head, 128 rows: 53 against 59 us), with two the second one's misses
+    // are worth more (gate/up of the 7B shape at 256 rows: 90 -> 77 us, at 384: 116 -> 95; LM head of 256 compacted rows:
+    // 105 -> 94).  QKV, one workgroup of the grid per unit and fewer, gains from three on (256 rows: 48.5 against 50.5 us,
+    // 384 rows: 80 -> 74).  The sliced projections and the LM head with two tiles per wavefront gain nothing.
     GemmShape g4 = g;
     g4.grid_y = chunks * ksplit;
+    g4.keep_chunks = ACC ? 0 : std::is_same<Epi, QkvEpi>::value ? 3 : 2;
     if constexpr (!FILL && std::is_same<Epi, LmEpi>::value) {
       // LM head: two output tiles per wavefront (each LDS operand read feeds two MFMAs, half the workgroups):
       // 161 -> 153 us at 512 rows.  The same arrangement is slower for gate/up (119 -> 135 us) and is not used there.
@@ -848,6 +865,7 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
       // reason not with a compacted operand, where often only the first chunk holds rows)
       if (g.n_tiles % (2 * NW) == 0 && chunks >= 2 && !g.n_rows_dev) {
         const int groups2 = g.n_tiles / (2 * NW);
+        g4.keep_chunks = 0;
         dim3 grid2((groups2 + 7) / 8 * 8 * chunks * ksplit, 1, nz);
         hipLaunchKernelGGL((gemm_tiled_kernel<4, 2, Epi, FILL>), grid2, block, 0, st, g4, e, pred, fc);
         return;
