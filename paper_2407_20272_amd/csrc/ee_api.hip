@@ -538,14 +538,32 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   auto rs = [&](int slot) { return w.rowsq + (size_t)slot * Mpad; };
   {
     ProfScope ps(EE_K_OTHER, 0, st);
-    launch_iter_init(s, B, n, out_conf, st);
-    launch_rope_table(batch->context_lens, w.rope, B, D.head_dim, D.rope_theta, st);
+    BeginArgs ba{};
+    ba.s = s;
+    ba.conf_out = out_conf;
+    ba.context_lens = batch->context_lens;
+    ba.tokens = batch->tokens;
+    ba.rope = w.rope;
+    ba.h = w.h;
+    ba.snapshot = simmode ? w.hprev : nullptr;   // h_0, the "previous" hidden state of layer 1
+    ba.theta = D.rope_theta;
+    ba.eps = D.rms_eps;
+    ba.B = B;
+    ba.Mpad = Mpad;
+    ba.d = d;
+    ba.vocab = D.vocab;
+    ba.n_layers = n;
+    ba.head_dim = D.head_dim;
     if (bf) {
-      launch_embed_bf16(reinterpret_cast<const bf16_t*>(model->embed), batch->tokens, w.h, B, Mpad, d, D.vocab, st);
-      if (compact) launch_compact(w.status, B, rmap, always, st);   // nobody has left: identity
+      ba.embed = reinterpret_cast<const bf16_t*>(model->embed);
+      ba.gain = reinterpret_cast<const bf16_t*>(model->layers[0].g_attn);
+      ba.x = w.xT;
+      ba.rowsq_out = rs(0);
+      ba.rm = rmap;
+      launch_iter_begin(ba, st);
     } else {
-      launch_embed_f32(reinterpret_cast<const float*>(model->embed), batch->tokens, w.h, B, d, D.vocab, st);
-      if (simmode) launch_copy_f32(w.h, w.hprev, (size_t)B * d, st);   // h_0, the "previous" state of layer 1
+      ba.embed_f32 = reinterpret_cast<const float*>(model->embed);
+      launch_iter_begin_f32(ba, st);
     }
   }
   // bf16 path: the residual update of a projection and the RMSNorm that follows it are one launch (NormArgs):
@@ -554,7 +572,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   auto norm_args = [&](int n_slices, int slot) {
     NormArgs a{};
     a.h_in = w.h;
-    a.h_out = n_slices ? w.h : nullptr;
+    a.h_out = w.h;
     a.y = w.y;
     a.S = n_slices;
     a.skip = compact ? nullptr : left;   // with a row map, a sequence that has left has no position in it
@@ -588,14 +606,6 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
     }
     const bool head_here = use_exit_heads && has_head(D, i);
     if (bf) {
-      if (i == 1) {   // operand of the first layer from the embedding (also h_0, the "previous" hidden state of layer 1)
-        ProfScope ps(EE_K_NORM, i, st);
-        NormArgs na = norm_args(0, 0);
-        na.gain[0] = reinterpret_cast<const bf16_t*>(L.g_attn);
-        na.x[0] = w.xT;
-        if (simmode) na.rd = RowDot{nullptr, w.hprev, nullptr, 1};
-        launch_finish_norm(na, run_layers, st);
-      }
       {
         ProfScope ps(EE_K_QKV, i, st);
         GemmShape gq{L.w_qkv, w.xT, d, B, 0, 3 * d / 32, D.head_dim / 2, 1};
@@ -775,10 +785,8 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
     }
     CombineArgs ca{w.partials, bf ? D.vocab / 32 : 1, B, 0, 0.0f, 0.0f, 0, nullptr, s, out_tokens, nullptr};
     ProfScope ps(EE_K_COMBINE, n, st);
-    launch_combine(ca, final_pred, st);
+    launch_combine_copy(ca, final_pred, w.h, out_hidden, d, st);
   }
-  if (out_hidden) launch_copy_f32(w.h, out_hidden, (size_t)B * d, st);
-  (void)always;
   EE_HIP(hipGetLastError());
   return EE_OK;
 }

@@ -128,9 +128,6 @@ struct Pred {
 };
 
 // misc.hip
-void launch_iter_init(const IterState& s, int B, int n_layers, float* conf_out, hipStream_t st);
-void launch_embed_bf16(const bf16_t* E, const int32_t* tokens, float* h, int B, int Mpad, int d, int vocab, hipStream_t st);
-void launch_embed_f32(const float* E, const int32_t* tokens, float* h, int B, int d, int vocab, hipStream_t st);
 void launch_copy_f32(const float* src, float* dst, size_t n, hipStream_t st);
 void launch_rope_table(const int32_t* context_lens, float2* table, int B, int head_dim, float theta, hipStream_t st);
 struct GainTable {
@@ -168,6 +165,27 @@ struct NormArgs {
   int B, Mpad, d;
 };
 void launch_finish_norm(const NormArgs& a, Pred pred, hipStream_t st);
+// Start of an iteration: state reset, embedding (residual rows [B][d]), rotary table, and on the bf16 path the first
+// layer's operand x (RMSNorm with `gain`), the rows' sums of squares and the identity row map.
+struct BeginArgs {
+  IterState s;
+  float* conf_out;        // nullptr or [n_layers][B]
+  const int32_t* context_lens;
+  const int32_t* tokens;
+  float2* rope;
+  const bf16_t* embed;    // bf16 path
+  const float* embed_f32; // fp32 path
+  const bf16_t* gain;
+  float* h;
+  float* snapshot;        // nullptr, or a copy of h (h_0 of the similarity measure)
+  bf16_t* x;
+  float* rowsq_out;
+  RowMap rm;              // perm == nullptr: none
+  float theta, eps;
+  int B, Mpad, d, vocab, n_layers, head_dim;
+};
+void launch_iter_begin(const BeginArgs& a, hipStream_t st);
+void launch_iter_begin_f32(const BeginArgs& a, hipStream_t st);
 // KV filling: x slab of layer l = bf16(RMSNorm(h; gains.g[l-1])) for every layer some row needs (fill_from < l).
 void launch_fill_prep(const float* h, const GainTable& gains, int n_layers, bf16_t* x_slabs, float eps,
                       const int32_t* fill_from, int fill_from_stride, int B, int Mpad, int d, Pred pred, hipStream_t st);
@@ -192,6 +210,8 @@ struct CombineArgs {
   const int32_t* left;  // nullptr, or [B]: rows with left[m] != 0 are not touched (per-sequence exit: token and state stay)
 };
 void launch_combine(const CombineArgs& a, Pred pred, hipStream_t st);
+// The same where the predicate holds, and always dst[m][..] = src[m][..] over d floats for every row (dst may be nullptr).
+void launch_combine_copy(const CombineArgs& a, Pred pred, const float* src, float* dst, int d, hipStream_t st);
 // Exit decision from a measure that is one dot product per row (conf_mode 2: cosine of consecutive hidden
 // states = dots / sqrt(sq_a * sq_b); conf_mode 3: logistic function of dots * rsqrt(sq_b / d + eps) + bias[0],
 // the classifier's unit applied to the hidden state at unit root mean square).

@@ -7,52 +7,33 @@ namespace ee {
 namespace {
 
 // ---------------------------------------------------------------------------------------------------
-// Status <- False for every sequence (Algorithm 1, initialisation), counters.
+// Status <- False for sequence m (Algorithm 1, initialisation), no confidence yet; row 0: the counters.  One workgroup a row.
 // ---------------------------------------------------------------------------------------------------
-__global__ void iter_init_kernel(IterState s, int B, int n_layers, float* conf_out) {
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = t; i < (size_t)B; i += stride) {
-    s.status[i] = 0;
-    s.exit_layer[i] = n_layers;
+__device__ inline void init_row(const IterState& s, int m, int B, int n_layers, float* conf_out) {
+  if (threadIdx.x == 0) {
+    s.status[m] = 0;
+    s.exit_layer[m] = n_layers;
+    if (m == 0) {
+      *s.n_exited = 0;
+      *s.done = 0;
+      *s.batch_exit_layer = n_layers;
+    }
   }
-  if (t == 0) {
-    *s.n_exited = 0;
-    *s.done = 0;
-    *s.batch_exit_layer = n_layers;
-  }
-  if (conf_out)
-    for (size_t i = t; i < (size_t)B * n_layers; i += stride) conf_out[i] = __builtin_nanf("");
-}
-
-// hidden_states <- Embed(input_tokens): one row gather per sequence; padding rows of the last tile are zero.
-// A token id outside 0..vocab-1 reads row 0 (the result is unspecified, the access stays inside the table).
-__global__ __launch_bounds__(256) void embed_bf16_kernel(const bf16_t* E, const int32_t* tokens, float* h, int B, int d, int vocab) {
-  const int m = blockIdx.x;
-  const bf16_t* row = nullptr;
-  if (m < B) {
-    const int tok = tokens[m];
-    row = E + (size_t)((unsigned)tok < (unsigned)vocab ? tok : 0) * d;
-  }
-  for (int k = threadIdx.x; k < d; k += blockDim.x) h[(size_t)m * d + k] = row ? (float)row[k] : 0.0f;
-}
-__global__ void embed_f32_kernel(const float* E, const int32_t* tokens, float* h, int B, int d, int vocab) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  const int m = blockIdx.y;
-  const int tok = tokens[m];
-  if (k < d) h[(size_t)m * d + k] = E[(size_t)((unsigned)tok < (unsigned)vocab ? tok : 0) * d + k];
+  if (conf_out && (int)threadIdx.x < n_layers) conf_out[(size_t)threadIdx.x * B + m] = __builtin_nanf("");
 }
 
 // (cos, sin) of pos_m * theta^(-2j/dh) for every sequence m and channel pair j, angles formed in double.
-__global__ void rope_table_kernel(const int32_t* context_lens, float2* table, int B, int head_dim, float theta) {
+__device__ inline void rope_entry(const int32_t* context_lens, float2* table, int idx, int B, int head_dim, float theta) {
   const int half = head_dim >> 1;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= B * half) return;
   const int m = idx / half, j = idx - m * half;
   const double ang = (double)context_lens[m] * exp2(-2.0 * (double)j / (double)head_dim * log2((double)theta));
   double sn, cs;
   sincos(ang, &sn, &cs);
   table[idx] = make_float2((float)cs, (float)sn);
+}
+__global__ void rope_table_kernel(const int32_t* context_lens, float2* table, int B, int head_dim, float theta) {
+  rope_entry(context_lens, table, blockIdx.x * blockDim.x + threadIdx.x, B, head_dim, theta);
 }
 __global__ void copy_f32_kernel(const float* src, float* dst, size_t n) {
   const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -192,6 +173,61 @@ __global__ __launch_bounds__(NORM_THREADS) void finish_norm_kernel(NormArgs a, P
   }
 }
 
+// Everything before the first projection of an iteration in one launch: workgroup m < Mpad resets the state of row m,
+// gathers its embedding (float residual row, sum of squares) and writes the first layer's operand with the arithmetic of
+// finish_norm_kernel; the workgroups from Mpad on tabulate the rotary angles.  (Four or five dependent launches before, about
+// 3.3 us each whatever they did; one now.)
+__global__ __launch_bounds__(NORM_THREADS) void iter_begin_kernel(BeginArgs a) {
+  __shared__ float red[NORM_THREADS / 64];
+  const int m = blockIdx.x, d = a.d;
+  if (m >= a.Mpad) {
+    rope_entry(a.context_lens, a.rope, (m - a.Mpad) * NORM_THREADS + threadIdx.x, a.B, a.head_dim, a.theta);
+    return;
+  }
+  if (m >= a.B) {
+    zero_x_row(a.x, m, d);
+    return;
+  }
+  const int tok = a.tokens[m];
+  const bf16_t* row = a.embed + (size_t)((unsigned)tok < (unsigned)a.vocab ? tok : 0) * d;   // never outside the table
+  bf16x8 gv[NORM_CHUNKS];
+  load_gain(a.gain, d, gv);
+  init_row(a.s, m, a.B, a.n_layers, a.conf_out);
+  if (a.rm.perm && threadIdx.x == 0) {   // nobody has left: the row map is the identity
+    a.rm.perm[m] = m;
+    a.rm.cpos[m] = m;
+    if (m == 0) a.rm.n_active[0] = a.B;
+  }
+  const bool wide = (reinterpret_cast<uintptr_t>(a.embed) & 15) == 0;
+  float v[NORM_CHUNKS][8];
+  float ss = 0.0f;
+#pragma unroll
+  for (int c = 0; c < NORM_CHUNKS; ++c) {
+    const int k0 = (c * NORM_THREADS + threadIdx.x) * 8;
+    if (k0 < d) {
+      bf16x8 e;
+      if (wide) {
+        e = *reinterpret_cast<const bf16x8*>(row + k0);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = row[k0 + i];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[c][i] = (float)e[i];
+      store8(a.h + (size_t)m * d + k0, v[c]);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) ss = fmaf(v[c][i], v[c][i], ss);
+      if (a.snapshot) store8(a.snapshot + (size_t)m * d + k0, v[c]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[c][i] = 0.0f;
+    }
+  }
+  ss = block_sum(ss, red);
+  if (threadIdx.x == 0) a.rowsq_out[m] = ss;
+  write_x_row(a.x, m, d, v, rsqrtf(ss / (float)d + a.eps), gv);
+}
+
 // KV filling: grid (Mpad, n_layers); workgroup (m, l-1) normalises row m with layer l's attention gain into slab
 // l-1.  Same arithmetic, thread for thread, as finish_norm_kernel, so that what is filled for a layer equals bit
 // for bit the operand that layer's own pass would have built from the same hidden state.
@@ -229,6 +265,23 @@ __global__ __launch_bounds__(NORM_THREADS) void fill_prep_kernel(const float* h,
   }
   ss = block_sum(ss, red);
   write_x_row(x, m, d, v, rsqrtf(ss / (float)d + eps), gv);
+}
+
+// fp32 path: the same, without the operand (the projections normalise for themselves).
+__global__ __launch_bounds__(256) void iter_begin_f32_kernel(BeginArgs a) {
+  const int m = blockIdx.x, d = a.d;
+  if (m >= a.B) {
+    rope_entry(a.context_lens, a.rope, (m - a.B) * 256 + threadIdx.x, a.B, a.head_dim, a.theta);
+    return;
+  }
+  init_row(a.s, m, a.B, a.n_layers, a.conf_out);
+  const int tok = a.tokens[m];
+  const float* row = a.embed_f32 + (size_t)((unsigned)tok < (unsigned)a.vocab ? tok : 0) * d;   // never outside the table
+  for (int k = threadIdx.x; k < d; k += 256) {
+    const float v = row[k];
+    a.h[(size_t)m * d + k] = v;
+    if (a.snapshot) a.snapshot[(size_t)m * d + k] = v;
+  }
 }
 
 // fp32 path: the three sums a one-dot-product confidence measure needs, one workgroup per row.
@@ -307,6 +360,24 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, Pred pred) 
   combine_row(a, blockIdx.x, red);
 }
 
+// The last launch of an iteration: the final tokens (where the predicate holds) and, always, the hidden states the caller
+// asked for, one workgroup per row.
+__global__ __launch_bounds__(256) void combine_copy_kernel(CombineArgs a, Pred pred, const float* src, float* dst, int d) {
+  const int m = blockIdx.x;
+  if (dst) {
+    const float* sp = src + (size_t)m * d;
+    float* dp = dst + (size_t)m * d;
+    if ((d & 3) == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
+      for (int k = threadIdx.x * 4; k < d; k += 1024) *reinterpret_cast<float4*>(dp + k) = *reinterpret_cast<const float4*>(sp + k);
+    } else {
+      for (int k = threadIdx.x; k < d; k += 256) dp[k] = sp[k];
+    }
+  }
+  if (pred_skip(pred)) return;
+  __shared__ float4 red[256];
+  combine_row(a, m, red);
+}
+
 // Row map of the sequences that are still active, in batch order (one workgroup walks the batch 256 rows at a
 // time).
 __global__ __launch_bounds__(256) void compact_kernel(const int32_t* status, int B, RowMap rm, Pred pred) {
@@ -345,18 +416,13 @@ __global__ __launch_bounds__(256) void decide_kernel(DecideArgs a, Pred pred) {
 
 }  // namespace
 
-void launch_iter_init(const IterState& s, int B, int n_layers, float* conf_out, hipStream_t st) {
-  size_t work = (size_t)B * n_layers;
-  int blocks = (int)((work + 255) / 256);
-  if (blocks < 1) blocks = 1;
-  if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(iter_init_kernel, dim3(blocks), dim3(256), 0, st, s, B, n_layers, conf_out);
+void launch_iter_begin(const BeginArgs& a, hipStream_t st) {
+  const int rope_wgs = a.theta > 0.0f ? (a.B * (a.head_dim / 2) + NORM_THREADS - 1) / NORM_THREADS : 0;
+  hipLaunchKernelGGL(iter_begin_kernel, dim3(a.Mpad + rope_wgs), dim3(NORM_THREADS), 0, st, a);
 }
-void launch_embed_bf16(const bf16_t* E, const int32_t* tokens, float* h, int B, int Mpad, int d, int vocab, hipStream_t st) {
-  hipLaunchKernelGGL(embed_bf16_kernel, dim3(Mpad), dim3(256), 0, st, E, tokens, h, B, d, vocab);
-}
-void launch_embed_f32(const float* E, const int32_t* tokens, float* h, int B, int d, int vocab, hipStream_t st) {
-  hipLaunchKernelGGL(embed_f32_kernel, dim3((d + 255) / 256, B), dim3(256), 0, st, E, tokens, h, B, d, vocab);
+void launch_iter_begin_f32(const BeginArgs& a, hipStream_t st) {
+  const int rope_wgs = a.theta > 0.0f ? (a.B * (a.head_dim / 2) + 255) / 256 : 0;
+  hipLaunchKernelGGL(iter_begin_f32_kernel, dim3(a.B + rope_wgs), dim3(256), 0, st, a);
 }
 void launch_rope_table(const int32_t* context_lens, float2* table, int B, int head_dim, float theta, hipStream_t st) {
   if (theta <= 0.0f || B == 0) return;
@@ -403,6 +469,9 @@ void launch_measure_f32(const float* h, float* other, int per_row, float* out, i
 }
 void launch_decide(const DecideArgs& a, Pred pred, hipStream_t st) {
   hipLaunchKernelGGL(decide_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, a, pred);
+}
+void launch_combine_copy(const CombineArgs& a, Pred pred, const float* src, float* dst, int d, hipStream_t st) {
+  hipLaunchKernelGGL(combine_copy_kernel, dim3(a.B), dim3(256), 0, st, a, pred, src, dst, d);
 }
 void launch_combine(const CombineArgs& a, Pred pred, hipStream_t st) {
   hipLaunchKernelGGL(combine_kernel, dim3(a.B), dim3(256), 0, st, a, pred);
