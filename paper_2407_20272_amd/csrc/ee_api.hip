@@ -83,7 +83,7 @@ struct Workspace {
   float* q;           // [B][d]
   float* attn_split;  // [B][H][8][head_dim + 2] partial attention results, only for batches of at most 64 (sequence, head) pairs
   float2* rope;       // [B][head_dim/2] (cos, sin) of this iteration's rotary angles
-  float4* partials;   // bf16: [Mpad][vocab/32]; fp32: [B]
+  float4* partials;   // bf16: [Mpad][vocab/32]
   float* h;           // residual stream: bf16 [Mpad][d], fp32 [B][d]
   // bf16 path
   float* y;           // [slices][Mpad][d] partial results of the output / down projection
@@ -95,10 +95,9 @@ struct Workspace {
   bf16_t* fill_x;     // [n][Mpad][d]
   float* dots;        // [n][Mpad] per-layer row dot products of the head-less confidence measures
   float* hprev;       // bf16: [Mpad][d], fp32: [B][d]: hidden state before the current layer (similarity measure)
-  float* msr;         // fp32: [3][B] sums of the head-less confidence measures
   RowMap rowmap;      // bf16: [Mpad] + [Mpad] + [1] row map of the sequences still active (per-sequence exit)
   // fp32 path
-  float *x, *ao, *act, *logits;
+  float *ao, *act, *logits;
   size_t bytes;
 };
 
@@ -141,14 +140,11 @@ Workspace carve(const ee_model_desc& D, int B, void* base) {
     w.rowmap.cpos = c.take<int32_t>(Mpad);
     w.rowmap.n_active = c.take<int32_t>(1);
   } else {
-    w.partials = c.take<float4>(Bp);
     w.h = c.take<float>(Bp * d);
-    w.x = c.take<float>(Bp * d);
     w.ao = c.take<float>(Bp * d);
     w.act = c.take<float>(Bp * f);
     w.logits = c.take<float>(Bp * V);
     w.hprev = c.take<float>(Bp * d);
-    w.msr = c.take<float>(3 * Bp);
   }
   w.bytes = (c.off + 255) & ~(size_t)255;
   return w;
@@ -171,8 +167,6 @@ Workspace carve_exit_check(const ee_model_desc& D, int B, void* base) {
     w.partials = c.take<float4>((size_t)Mpad * (V / 32));
     w.xH = c.take<bf16_t>(d * Mpad);
   } else {
-    w.partials = c.take<float4>(Bp);
-    w.x = c.take<float>(Bp * d);
     w.logits = c.take<float>(Bp * V);
   }
   w.bytes = (c.off + 255) & ~(size_t)255;
@@ -306,15 +300,13 @@ NormArgs plain_norm(const ee_model_desc& D, const float* h, const void* gain, bf
   a.d = D.d_model;
   return a;
 }
-void enqueue_head_f32(const ee_model& M, const Workspace& w, const float* h, int B, float scale, int layer, Pred pred,
-                      hipStream_t st) {
+// Logits of RMSNorm(h; g_final); the decision (launch_head_decide_f32) reads them.
+void enqueue_head_f32(const ee_model& M, const Workspace& w, const float* h, int B, int layer, Pred pred, hipStream_t st) {
   const ee_model_desc& D = M.desc;
   ProfScope ps(EE_K_HEAD, layer, st);
-  launch_rmsnorm_f32(h, reinterpret_cast<const float*>(M.g_final), w.x, B, D.d_model, D.rms_eps, pred, st);
-  SimpleShape g{reinterpret_cast<const float*>(M.w_lm), w.x, D.d_model, B, 0, D.vocab, 1};
-  LmEpi e{w.partials, w.logits, 1, D.vocab, scale, nullptr, D.rms_eps, D.d_model};
+  SimpleShape g{reinterpret_cast<const float*>(M.w_lm), h, reinterpret_cast<const float*>(M.g_final), D.rms_eps, D.d_model, B, 0, D.vocab, 1};
+  LmEpi e{nullptr, w.logits, 1, D.vocab, 0.0f, nullptr, D.rms_eps, D.d_model};
   launch_simple_lm(g, e, pred, st);
-  launch_head_stats_f32(w.logits, w.partials, B, D.vocab, scale, pred, st);
 }
 
 // --- KV filling for layers above fill_from ----------------------------------------------------------------
@@ -340,16 +332,17 @@ void enqueue_fill_f32(const ee_model& M, const ee_kv_cache& C, const ee_batch& B
                       const int32_t* fill_from, int stride, Pred pred, hipStream_t st) {
   const ee_model_desc& D = M.desc;
   ProfScope ps(EE_K_KVFILL, 0, st);
-  for (int i = 1; i <= D.n_layers; ++i) {
-    const ee_layer_weights& L = M.layers[i - 1];
-    launch_rmsnorm_f32(h, reinterpret_cast<const float*>(L.g_attn), w.x, Bt.batch, D.d_model, D.rms_eps, pred, st);
-    SimpleShape g{reinterpret_cast<const float*>(L.w_qkv), w.x, D.d_model, Bt.batch, D.d_model, 2 * D.d_model,
-                  D.head_dim / 2};
-    QkvEpi e = make_qkv_epi(D, C, Bt, w, i, nullptr);
-    e.fill_from = fill_from;
-    e.fill_from_stride = stride;
-    launch_simple_qkv(g, e, pred, st);
+  SimpleFill fill{};
+  for (int i = 0; i < D.n_layers; ++i) {
+    fill.layers.w_qkv[i] = M.layers[i].w_qkv;
+    fill.gains.g[i] = M.layers[i].g_attn;
   }
+  fill.pool_layer_bytes = pool_layer_elems(D, C) * elem_bytes(D);
+  SimpleShape g{nullptr, h, nullptr, D.rms_eps, D.d_model, Bt.batch, D.d_model, 2 * D.d_model, D.head_dim / 2};
+  QkvEpi e = make_qkv_epi(D, C, Bt, w, 1, nullptr);
+  e.fill_from = fill_from;
+  e.fill_from_stride = stride;
+  launch_simple_kvfill(fill, D.n_layers, g, e, pred, st);
 }
 
 // --- stand-alone exit check: validation and launch sequence shared by the two entry points -----------------
@@ -377,16 +370,16 @@ int enqueue_exit_check(const ee_model& M, int32_t layer, const float* hidden, in
   const ee_model_desc& D = M.desc;
   const Pred always{nullptr, 0};
   const float scale = D.logit_scale * (float)layer;
+  IterState s{status, exit_layer, n_exited, done_flag, batch_exit_layer};
+  CombineArgs ca{w.partials, D.vocab / 32, batch, layer, scale, threshold, D.conf_mode, forced_exit_layer, s, argmax, conf};
   if (D.dtype == EE_BF16) {
     launch_finish_norm(plain_norm(D, hidden, M.g_final, w.xH, batch), always, st);
     enqueue_head_bf16(M, w, batch, scale, layer, RowMap{}, always, st);
+    launch_combine(ca, always, st);
   } else {
-    enqueue_head_f32(M, w, hidden, batch, scale, layer, always, st);
+    enqueue_head_f32(M, w, hidden, batch, layer, always, st);
+    launch_head_decide_f32(w.logits, D.vocab, ca, always, nullptr, nullptr, D.d_model, st);
   }
-  IterState s{status, exit_layer, n_exited, done_flag, batch_exit_layer};
-  CombineArgs ca{w.partials, D.dtype == EE_BF16 ? D.vocab / 32 : 1, batch, layer, scale, threshold, D.conf_mode,
-                 forced_exit_layer, s, argmax, conf};
-  launch_combine(ca, always, st);
   EE_HIP(hipGetLastError());
   return EE_OK;
 }
@@ -677,8 +670,8 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
     } else {
       {
         ProfScope ps(EE_K_QKV, i, st);
-        launch_rmsnorm_f32(w.h, reinterpret_cast<const float*>(L.g_attn), w.x, B, d, D.rms_eps, run_layers, st);
-        SimpleShape gq{reinterpret_cast<const float*>(L.w_qkv), w.x, d, B, 0, 3 * d, D.head_dim / 2};
+        SimpleShape gq{reinterpret_cast<const float*>(L.w_qkv), w.h, reinterpret_cast<const float*>(L.g_attn), D.rms_eps, d, B, 0, 3 * d,
+                       D.head_dim / 2};
         QkvEpi qe = make_qkv_epi(D, *cache, *batch, w, i, w.q);
         launch_simple_qkv(gq, qe, run_layers, st);
       }
@@ -690,18 +683,17 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       }
       {
         ProfScope ps(EE_K_OPROJ, i, st);
-        SimpleShape go{reinterpret_cast<const float*>(L.w_o), w.ao, d, B, 0, d, 1};
+        SimpleShape go{reinterpret_cast<const float*>(L.w_o), w.ao, nullptr, 0.0f, d, B, 0, d, 1};
         launch_simple_acc(go, AccEpi{w.h, 0, d, left}, run_layers, st);
       }
       {
         ProfScope ps(EE_K_GATEUP, i, st);
-        launch_rmsnorm_f32(w.h, reinterpret_cast<const float*>(L.g_ffn), w.x, B, d, D.rms_eps, run_layers, st);
-        SimpleShape gg{reinterpret_cast<const float*>(L.w_gate_up), w.x, d, B, 0, 2 * f, f};
+        SimpleShape gg{reinterpret_cast<const float*>(L.w_gate_up), w.h, reinterpret_cast<const float*>(L.g_ffn), D.rms_eps, d, B, 0, 2 * f, f};
         launch_simple_gateup(gg, GateUpEpi{w.act, f, nullptr, D.rms_eps, d}, run_layers, st);
       }
       {
         ProfScope ps(EE_K_DOWN, i, st);
-        SimpleShape gd{reinterpret_cast<const float*>(L.w_down), w.act, f, B, 0, d, 1};
+        SimpleShape gd{reinterpret_cast<const float*>(L.w_down), w.act, nullptr, 0.0f, f, B, 0, d, 1};
         launch_simple_acc(gd, AccEpi{w.h, 0, d, left}, run_layers, st);
       }
     }
@@ -712,13 +704,6 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
         da.dots = w.dots + (size_t)(i - 1) * Mpad;
         da.sq_a = rs(2 * i - 2);
         da.sq_b = rs(2 * i);
-      } else {
-        ProfScope ps(EE_K_HEAD, i, st);
-        float* other = simmode ? w.hprev : const_cast<float*>(model->w_cls) + (size_t)(i - 1) * d;
-        launch_measure_f32(w.h, other, simmode ? 1 : 0, w.msr, B, d, run_layers, st);
-        da.dots = w.msr;
-        da.sq_a = w.msr + B;
-        da.sq_b = w.msr + 2 * (size_t)B;
       }
       da.bias = D.conf_mode == 3 ? model->b_cls + (i - 1) : nullptr;
       da.d = d;
@@ -730,7 +715,11 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       da.forced_exit_layer = forced_exit_layer;
       da.s = s;
       da.conf_out = out_conf ? out_conf + (size_t)(i - 1) * B : nullptr;
-      if (carry_decide) {   // decided inside the next layer's QKV projection launch
+      if (!bf) {
+        ProfScope ps(EE_K_COMBINE, i, st);
+        float* other = simmode ? w.hprev : const_cast<float*>(model->w_cls) + (size_t)(i - 1) * d;
+        launch_measure_decide_f32(w.h, other, simmode ? 1 : 0, da, run_layers, st);
+      } else if (carry_decide) {   // decided inside the next layer's QKV projection launch
         pending_dot = da;
         have_pending_dot = true;
       } else {
@@ -740,18 +729,17 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       if (compact) launch_compact(w.status, B, rmap, run_layers, st);
     } else if (head_here) {
       const float scale = D.logit_scale * (float)i;
-      if (bf)
-        enqueue_head_bf16(*model, w, B, scale, i, rmap, run_layers, st);
-      else
-        enqueue_head_f32(*model, w, w.h, B, scale, i, run_layers, st);
-      CombineArgs ca{w.partials, bf ? D.vocab / 32 : 1, B, i, scale, thresholds[i - 1], D.conf_mode, forced_exit_layer, s,
-                     out_tokens, out_conf ? out_conf + (size_t)(i - 1) * B : nullptr, left};
+      CombineArgs ca{w.partials, D.vocab / 32, B, i, scale, thresholds[i - 1], D.conf_mode, forced_exit_layer, s, out_tokens,
+                     out_conf ? out_conf + (size_t)(i - 1) * B : nullptr, left};
+      if (bf) enqueue_head_bf16(*model, w, B, scale, i, rmap, run_layers, st);
+      else enqueue_head_f32(*model, w, w.h, B, i, run_layers, st);
       if (carry_combine) {   // decided inside the next layer's QKV projection launch (i < n: there is one)
         pending = ca;
         have_pending = true;
       } else {
         ProfScope ps(EE_K_COMBINE, i, st);
-        launch_combine(ca, run_layers, st);
+        if (bf) launch_combine(ca, run_layers, st);
+        else launch_head_decide_f32(w.logits, D.vocab, ca, run_layers, nullptr, nullptr, d, st);
       }
       if (compact) launch_compact(w.status, B, rmap, run_layers, st);
     }
@@ -781,11 +769,12 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
     } else if (bf) {
       enqueue_head_bf16(*model, w, B, 0.0f, n, RowMap{}, run_layers, st);
     } else {
-      enqueue_head_f32(*model, w, w.h, B, 0.0f, n, final_pred, st);
+      enqueue_head_f32(*model, w, w.h, B, n, final_pred, st);
     }
-    CombineArgs ca{w.partials, bf ? D.vocab / 32 : 1, B, 0, 0.0f, 0.0f, 0, nullptr, s, out_tokens, nullptr};
+    CombineArgs ca{w.partials, D.vocab / 32, B, 0, 0.0f, 0.0f, 0, nullptr, s, out_tokens, nullptr};
     ProfScope ps(EE_K_COMBINE, n, st);
-    launch_combine_copy(ca, final_pred, w.h, out_hidden, d, st);
+    if (bf) launch_combine_copy(ca, final_pred, w.h, out_hidden, d, st);
+    else launch_head_decide_f32(w.logits, D.vocab, ca, final_pred, w.h, out_hidden, d, st);
   }
   EE_HIP(hipGetLastError());
   return EE_OK;

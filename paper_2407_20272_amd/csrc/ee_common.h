@@ -189,12 +189,6 @@ void launch_iter_begin_f32(const BeginArgs& a, hipStream_t st);
 // KV filling: x slab of layer l = bf16(RMSNorm(h; gains.g[l-1])) for every layer some row needs (fill_from < l).
 void launch_fill_prep(const float* h, const GainTable& gains, int n_layers, bf16_t* x_slabs, float eps,
                       const int32_t* fill_from, int fill_from_stride, int B, int Mpad, int d, Pred pred, hipStream_t st);
-void launch_rmsnorm_f32(const float* h, const float* gain, float* x, int B, int d, float eps, Pred pred, hipStream_t st);
-// fp32 path: out[0][m] = h[m] . other, out[1][m] = |other|^2, out[2][m] = |h[m]|^2 (out is [3][B]); other is
-// the previous hidden state [B][d] (per_row) or one row [d]; with per_row, h is then copied over other.
-void launch_measure_f32(const float* h, float* other, int per_row, float* out, int B, int d, Pred pred, hipStream_t st);
-void launch_head_stats_f32(const float* logits, float4* partials, int B, int vocab, float scale, Pred pred,
-                           hipStream_t st);
 struct CombineArgs {
   const float4* partials;
   int n_parts;
@@ -216,8 +210,8 @@ void launch_combine_copy(const CombineArgs& a, Pred pred, const float* src, floa
 // states = dots / sqrt(sq_a * sq_b); conf_mode 3: logistic function of dots * rsqrt(sq_b / d + eps) + bias[0],
 // the classifier's unit applied to the hidden state at unit root mean square).
 struct DecideArgs {
-  const float* dots;   // [B]
-  const float* sq_a;   // [B] squared norms (conf_mode 2)
+  const float* dots;   // [B] (bf16 path)
+  const float* sq_a;   // [B] squared norms (conf_mode 2; bf16 path)
   const float* sq_b;
   const float* bias;   // device, this layer's bias (conf_mode 3)
   int d;               // width of the hidden state
@@ -231,6 +225,13 @@ struct DecideArgs {
   float* conf_out;
 };
 void launch_decide(const DecideArgs& a, Pred pred, hipStream_t st);
+// fp32 path: the decision of every row from its own logits [B][vocab] (conf_mode 0, 1; layer 0: token selection), one
+// launch; dst as in launch_combine_copy.
+void launch_head_decide_f32(const float* logits, int vocab, const CombineArgs& a, Pred pred, const float* src, float* dst, int d,
+                            hipStream_t st);
+// fp32 path: the sums of a one-dot-product measure and the decision from them; other is the previous hidden state [B][d]
+// (per_row; it becomes h) or one row [d].
+void launch_measure_decide_f32(const float* h, float* other, int per_row, const DecideArgs& a, Pred pred, hipStream_t st);
 // The exit decision of layer i may ride along with the QKV projection launch of layer i+1 instead of taking a
 // launch of its own (see launch_gemm_qkv_bf16): n_wg leading workgroups of that launch (a multiple of 8) take it.
 // kind 1: softmax-response measures, workgroup m < a.B runs combine_row for batch row m.
@@ -289,10 +290,13 @@ struct FillLayers {
 void launch_gemm_kvfill_bf16(const FillLayers& fl, int n_layers, const bf16_t* x_slabs, size_t x_slab_elems,
                              size_t pool_layer_elems, const GemmShape& g, const QkvEpi& e, Pred pred, hipStream_t st);
 
-// gemm_simple.hip (fp32 path).  w: plain [n_out][K]; x: plain [M][K].
+// gemm_simple.hip (fp32 path).  w: plain [n_out][K]; x: plain [M][K]; QKV, gate/up and the LM head take the residual rows
+// as x and multiply RMSNorm(x; gain), the accumulate projections take x as it is (gain unused).
 struct SimpleShape {
   const float* w;
   const float* x;
+  const float* gain;
+  float eps;
   int K, M;
   int row_begin;    // first output row
   int n_rows;       // output rows to compute (even)
@@ -302,6 +306,13 @@ void launch_simple_qkv(const SimpleShape& g, const QkvEpi& e, Pred pred, hipStre
 void launch_simple_acc(const SimpleShape& g, const AccEpi& e, Pred pred, hipStream_t st);
 void launch_simple_gateup(const SimpleShape& g, const GateUpEpi& e, Pred pred, hipStream_t st);
 void launch_simple_lm(const SimpleShape& g, const LmEpi& e, Pred pred, hipStream_t st);
+// KV filling over layers 1..n_layers in one launch (e.fill_from set; e.k_pool / e.v_pool: pools of layer 1).
+struct SimpleFill {
+  FillLayers layers;
+  GainTable gains;
+  size_t pool_layer_bytes;
+};
+void launch_simple_kvfill(const SimpleFill& fill, int n_layers, const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st);
 
 // attention.hip
 // Block ids and positions come from device memory the caller filled in; the kernels never let them reach outside

@@ -27,6 +27,15 @@ __device__ inline void decide_row(const IterState& s, int m, int B, int layer, f
   }
 }
 
+// Confidence and arg max of row m from its softmax statistics, then the status rule.  One thread.
+__device__ inline void decide_from_stat(const CombineArgs& a, int m, const HeadStat& s) {
+  if (a.argmax_out) a.argmax_out[m] = s.idx;
+  if (a.layer == 0) return;
+  float conf = 1.0f / s.sum;                                          // largest softmax probability
+  if (a.conf_mode == 1) conf = (1.0f - expf(a.scale * (s.z2 - s.zmax))) / s.sum;  // top-1 minus top-2
+  decide_row(a.s, m, a.B, a.layer, conf, a.threshold, a.forced_exit_layer, a.conf_out);
+}
+
 // One workgroup of 256 threads merges the per-tile softmax statistics of row m into the confidence and applies
 // the status rule.  red: 256 float4 of LDS.  layer == 0: final token selection only.
 __device__ inline void combine_row(const CombineArgs& a, int m, float4* red) {
@@ -41,24 +50,21 @@ __device__ inline void combine_row(const CombineArgs& a, int m, float4* red) {
       red[threadIdx.x] = stat_pack(stat_merge(stat_unpack(red[threadIdx.x]), stat_unpack(red[threadIdx.x + w]), a.scale));
     __syncthreads();
   }
-  if (threadIdx.x != 0) return;
-  s = stat_unpack(red[0]);
-  if (a.argmax_out) a.argmax_out[m] = s.idx;
-  if (a.layer == 0) return;
-  float conf = 1.0f / s.sum;                                          // largest softmax probability
-  if (a.conf_mode == 1) conf = (1.0f - expf(a.scale * (s.z2 - s.zmax))) / s.sum;  // top-1 minus top-2
-  decide_row(a.s, m, a.B, a.layer, conf, a.threshold, a.forced_exit_layer, a.conf_out);
+  if (threadIdx.x == 0) decide_from_stat(a, m, stat_unpack(red[0]));
 }
 
 // Confidence of row m from one dot product (hidden states similarity, dedicated classifier) and the status rule.
-__device__ inline void decide_from_dot(const DecideArgs& a, int m) {
+__device__ inline void decide_from_sums(const DecideArgs& a, int m, float dot, float sq_a, float sq_b) {
   float conf;
   if (a.conf_mode == 2) {
-    conf = a.dots[m] / (sqrtf(a.sq_a[m]) * sqrtf(a.sq_b[m]));
+    conf = dot / (sqrtf(sq_a) * sqrtf(sq_b));
   } else {
-    conf = 1.0f / (1.0f + expf(-(a.dots[m] * rsqrtf(a.sq_b[m] / (float)a.d + a.eps) + a.bias[0])));
+    conf = 1.0f / (1.0f + expf(-(dot * rsqrtf(sq_b / (float)a.d + a.eps) + a.bias[0])));
   }
   decide_row(a.s, m, a.B, a.layer, conf, a.threshold, a.forced_exit_layer, a.conf_out);
+}
+__device__ inline void decide_from_dot(const DecideArgs& a, int m) {
+  decide_from_sums(a, m, a.dots[m], a.conf_mode == 2 ? a.sq_a[m] : 0.0f, a.sq_b[m]);
 }
 
 }  // namespace ee

@@ -164,10 +164,6 @@ __device__ inline HeadStat stat_merge(const HeadStat& a, const HeadStat& b, floa
   o.sum = wa + wb;
   return o;
 }
-__device__ inline HeadStat stat_push(const HeadStat& a, float z, int idx, float scale) {
-  HeadStat b = {z, 1.0f, -INFINITY, idx};
-  return stat_merge(a, b, scale);
-}
 // Statistics of 32 logits of one row that sit four each in eight neighbouring lanes (lane & 7 = which four):
 // two short passes (largest with its index, then the sum of exponentials and the runner-up) instead of 32
 // dependent pushes.  z[i] has vocabulary index idx0 + i.  Every one of the eight lanes returns the result.

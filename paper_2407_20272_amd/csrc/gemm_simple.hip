@@ -1,6 +1,11 @@
 // fp32 projections (plain row-major weights): the small reference-shaped workload runs entirely in float.
-// One wavefront computes one pair of output rows for every batch row: lanes stride over the contraction
-// and a butterfly adds the 64 partial sums.  Not a throughput kernel; the bf16 path is.
+// One wavefront computes one pair of output rows for MC batch rows (blockIdx.y picks them): lanes stride over the
+// contraction, 16 bytes at a time where the operands allow it, and a halving exchange adds the 64 partial sums, so that
+// four lanes finish the four batch rows side by side.  A projection of a normalised operand takes the residual rows
+// themselves: every wavefront sums the squares of its rows beside the products (the rows are a few kilobytes in L1) and the
+// separate normalisation launches are gone.  What bounds this path is the number of dependent launches, about 3.3 us each:
+// one iteration of four layers of width 256 took 65 launches and 216 us,
+// 30 launches and 115 us in this form.
 #include <type_traits>
 
 #include "ee_common.h"
@@ -9,11 +14,59 @@
 namespace ee {
 namespace {
 
-constexpr int MC = 4;  // batch rows per pass
+constexpr int MC = 4;  // batch rows per wavefront
 
-template <class Epi>
-__global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, Pred pred) {
+// Sums of v[0..7] over the wavefront: the lane of bits 5, 4, 3 = i gets sum i in every lane of its eight.
+__device__ inline float wave_sums8(float (&v)[8], int lane) {
+#pragma unroll
+  for (int n = 4, bit = 32; n >= 1; n >>= 1, bit >>= 1) {
+    const bool up = (lane & bit) != 0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      const float keep = up ? v[i + n] : v[i], give = up ? v[i] : v[i + n];
+      v[i] = keep + __shfl_xor(give, bit);
+    }
+  }
+  float s = v[0];
+#pragma unroll
+  for (int x = 4; x >= 1; x >>= 1) s += __shfl_xor(s, x);
+  return s;
+}
+// The same for four sums, lane bits 5, 4.
+__device__ inline float wave_sums4(float (&v)[4], int lane) {
+#pragma unroll
+  for (int n = 2, bit = 32; n >= 1; n >>= 1, bit >>= 1) {
+    const bool up = (lane & bit) != 0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      const float keep = up ? v[i + n] : v[i], give = up ? v[i] : v[i + n];
+      v[i] = keep + __shfl_xor(give, bit);
+    }
+  }
+  float s = v[0];
+#pragma unroll
+  for (int x = 8; x >= 1; x >>= 1) s += __shfl_xor(s, x);
+  return s;
+}
+
+struct NoFill {};   // (a launch that fills nothing does not carry a kilobyte of layer tables)
+
+template <class Epi, bool NORM, bool VEC, class Fill>
+__global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, Pred pred, Fill fill) {
+  constexpr bool FILL = std::is_same<Fill, SimpleFill>::value;
   if (pred_skip(pred)) return;
+  const int m0 = blockIdx.y * MC;
+  if constexpr (FILL) {   // one slice of the grid per layer; nothing to do where every row has been cached already
+    const int layer = blockIdx.z + 1;
+    bool need = false;
+    for (int m = m0; m < min(m0 + MC, g.M); ++m) need |= ctl_load(e.fill_from + (size_t)m * e.fill_from_stride) < layer;
+    if (!need) return;
+    g.w = reinterpret_cast<const float*>(fill.layers.w_qkv[layer - 1]);
+    g.gain = reinterpret_cast<const float*>(fill.gains.g[layer - 1]);
+    e.layer = layer;
+    e.k_pool = reinterpret_cast<char*>(e.k_pool) + (size_t)(layer - 1) * fill.pool_layer_bytes;
+    e.v_pool = reinterpret_cast<char*>(e.v_pool) + (size_t)(layer - 1) * fill.pool_layer_bytes;
+  }
   const int lane = threadIdx.x & 63;
   const int pair = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (pair >= g.n_rows / 2) return;
@@ -22,58 +75,76 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, 
   const int f_hi = f_lo + s;
   const float* w_lo = g.w + (size_t)f_lo * g.K;
   const float* w_hi = g.w + (size_t)f_hi * g.K;
-  for (int m0 = 0; m0 < g.M; m0 += MC) {
-    float lo[MC], hi[MC];
+  const float* x[MC];
 #pragma unroll
-    for (int i = 0; i < MC; ++i) lo[i] = hi[i] = 0.0f;
-    for (int k = lane; k < g.K; k += 64) {
-      const float a = w_lo[k], b = w_hi[k];
+  for (int i = 0; i < MC; ++i) x[i] = g.x + (size_t)min(m0 + i, g.M - 1) * g.K;   // rows past the last repeat it, never written
+  float sum[2 * MC], sq[MC];   // sum[2 i + hi]
 #pragma unroll
-      for (int i = 0; i < MC; ++i) {
-        const float x = m0 + i < g.M ? g.x[(size_t)(m0 + i) * g.K + k] : 0.0f;
-        lo[i] = fmaf(a, x, lo[i]);
-        hi[i] = fmaf(b, x, hi[i]);
-      }
-    }
+  for (int i = 0; i < MC; ++i) sum[2 * i] = sum[2 * i + 1] = sq[i] = 0.0f;
+  constexpr int N = VEC ? 4 : 1;
+  typedef float vec_t __attribute__((ext_vector_type(N)));
+#pragma unroll 2
+  for (int k = lane * N; k < g.K; k += 64 * N) {
+    const vec_t a = *reinterpret_cast<const vec_t*>(w_lo + k), b = *reinterpret_cast<const vec_t*>(w_hi + k);
+    vec_t gn = vec_t(1.0f);
+    if constexpr (NORM) gn = *reinterpret_cast<const vec_t*>(g.gain + k);
+    vec_t xv[MC];
+#pragma unroll
+    for (int i = 0; i < MC; ++i) xv[i] = *reinterpret_cast<const vec_t*>(x[i] + k);
 #pragma unroll
     for (int i = 0; i < MC; ++i)
 #pragma unroll
-      for (int x = 1; x < 64; x <<= 1) {
-        lo[i] += __shfl_xor(lo[i], x);
-        hi[i] += __shfl_xor(hi[i], x);
+      for (int j = 0; j < N; ++j) {
+        const float v = xv[i][j], u = NORM ? v * gn[j] : v;
+        if constexpr (NORM) sq[i] = fmaf(v, v, sq[i]);
+        sum[2 * i] = fmaf(a[j], u, sum[2 * i]);
+        sum[2 * i + 1] = fmaf(b[j], u, sum[2 * i + 1]);
       }
-    if (lane == 0) {
-#pragma unroll
-      for (int i = 0; i < MC; ++i) {
-        const int m = m0 + i;
-        if (m >= g.M) break;
-        if constexpr (std::is_same<Epi, QkvEpi>::value) {
-          epi_qkv<float>(e, m, f_lo, lo[i], hi[i]);
-        } else if constexpr (std::is_same<Epi, AccEpi>::value) {
-          epi_acc(e, m, f_lo, lo[i]);
-          epi_acc(e, m, f_hi, hi[i]);
-        } else if constexpr (std::is_same<Epi, GateUpEpi>::value) {
-          epi_gateup<float>(e, m, f_lo, lo[i], hi[i]);
-        } else {
-          e.logits[(size_t)m * e.vocab + f_lo] = lo[i];
-          e.logits[(size_t)m * e.vocab + f_hi] = hi[i];
-        }
-      }
-    }
+  }
+  static_assert(MC == 4, "eight sums, four squares");
+  float r = wave_sums8(sum, lane);      // lane bits 5, 4: batch row, bit 3: lo / hi
+  if constexpr (NORM) r *= 1.0f / sqrtf(wave_sums4(sq, lane) / (float)g.K + g.eps);
+  const float lo = r, hi = __shfl_xor(r, 8);
+  const int m = m0 + (lane >> 4);
+  if ((lane & 15) != 0 || m >= g.M) return;
+  if constexpr (std::is_same<Epi, QkvEpi>::value) {
+    epi_qkv<float>(e, m, f_lo, lo, hi);
+  } else if constexpr (std::is_same<Epi, AccEpi>::value) {
+    epi_acc(e, m, f_lo, lo);
+    epi_acc(e, m, f_hi, hi);
+  } else if constexpr (std::is_same<Epi, GateUpEpi>::value) {
+    epi_gateup<float>(e, m, f_lo, lo, hi);
+  } else {
+    e.logits[(size_t)m * e.vocab + f_lo] = lo;
+    e.logits[(size_t)m * e.vocab + f_hi] = hi;
   }
 }
 
-template <class Epi>
-void launch(const SimpleShape& g, const Epi& e, Pred pred, hipStream_t st) {
-  const int pairs = g.n_rows / 2;
-  hipLaunchKernelGGL((gemm_simple_kernel<Epi>), dim3((pairs + 3) / 4), dim3(256), 0, st, g, e, pred);
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+template <class Epi, bool NORM, class Fill = NoFill>
+void launch(const SimpleShape& g, const Epi& e, Pred pred, hipStream_t st, const Fill& fill = Fill{}, int n_layers = 1) {
+  const dim3 grid((g.n_rows / 2 + 3) / 4, (g.M + MC - 1) / MC, n_layers);
+  // 16-byte loads need rows that keep the alignment and operands that start on it (the library asks no caller for that)
+  bool vec = g.K % 4 == 0 && aligned16(g.w) && aligned16(g.x) && aligned16(g.gain);
+  if constexpr (std::is_same<Fill, SimpleFill>::value)
+    for (int i = 0; i < n_layers; ++i) vec = vec && aligned16(fill.layers.w_qkv[i]) && aligned16(fill.gains.g[i]);
+  if (vec)
+    hipLaunchKernelGGL((gemm_simple_kernel<Epi, NORM, true, Fill>), grid, dim3(256), 0, st, g, e, pred, fill);
+  else
+    hipLaunchKernelGGL((gemm_simple_kernel<Epi, NORM, false, Fill>), grid, dim3(256), 0, st, g, e, pred, fill);
 }
 
 }  // namespace
 
-void launch_simple_qkv(const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st) { launch(g, e, pred, st); }
-void launch_simple_acc(const SimpleShape& g, const AccEpi& e, Pred pred, hipStream_t st) { launch(g, e, pred, st); }
-void launch_simple_gateup(const SimpleShape& g, const GateUpEpi& e, Pred pred, hipStream_t st) { launch(g, e, pred, st); }
-void launch_simple_lm(const SimpleShape& g, const LmEpi& e, Pred pred, hipStream_t st) { launch(g, e, pred, st); }
+void launch_simple_qkv(const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st) { launch<QkvEpi, true>(g, e, pred, st); }
+void launch_simple_acc(const SimpleShape& g, const AccEpi& e, Pred pred, hipStream_t st) { launch<AccEpi, false>(g, e, pred, st); }
+void launch_simple_gateup(const SimpleShape& g, const GateUpEpi& e, Pred pred, hipStream_t st) {
+  launch<GateUpEpi, true>(g, e, pred, st);
+}
+void launch_simple_lm(const SimpleShape& g, const LmEpi& e, Pred pred, hipStream_t st) { launch<LmEpi, true>(g, e, pred, st); }
+void launch_simple_kvfill(const SimpleFill& fill, int n_layers, const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st) {
+  launch<QkvEpi, true>(g, e, pred, st, fill, n_layers);
+}
 
 }  // namespace ee

@@ -284,69 +284,92 @@ __global__ __launch_bounds__(256) void iter_begin_f32_kernel(BeginArgs a) {
   }
 }
 
-// fp32 path: the three sums a one-dot-product confidence measure needs, one workgroup per row.
-__global__ __launch_bounds__(256) void measure_f32_kernel(const float* h, float* other, int per_row, float* out, int B,
-                                                          int d, Pred pred) {
+// Copies row m of src to dst (either alignment), all threads of a 256-thread workgroup.
+__device__ inline void copy_row(const float* src, float* dst, int m, int d) {
+  if (!dst) return;
+  const float* sp = src + (size_t)m * d;
+  float* dp = dst + (size_t)m * d;
+  if ((d & 3) == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
+    for (int k = threadIdx.x * 4; k < d; k += 1024) *reinterpret_cast<float4*>(dp + k) = *reinterpret_cast<const float4*>(sp + k);
+  } else {
+    for (int k = threadIdx.x; k < d; k += 256) dp[k] = sp[k];
+  }
+}
+
+// fp32 path: the three sums a one-dot-product confidence measure needs and the decision, one workgroup per row.
+__global__ __launch_bounds__(256) void measure_decide_f32_kernel(const float* h, float* other, int per_row, DecideArgs a, Pred pred) {
   if (pred_skip(pred)) return;
-  const int m = blockIdx.x;
+  const int m = blockIdx.x, d = a.d;
   const float* hp = h + (size_t)m * d;
   float* op = per_row ? other + (size_t)m * d : other;
   float dot = 0.0f, so = 0.0f, sh = 0.0f;
   for (int k = threadIdx.x; k < d; k += blockDim.x) {
-    const float a = hp[k], b = op[k];
-    dot = fmaf(a, b, dot);
-    so = fmaf(b, b, so);
-    sh = fmaf(a, a, sh);
-    if (per_row) op[k] = a;   // this hidden state is the next layer's previous one
+    const float x = hp[k], y = op[k];
+    dot = fmaf(x, y, dot);
+    so = fmaf(y, y, so);
+    sh = fmaf(x, x, sh);
+    if (per_row) op[k] = x;   // this hidden state is the next layer's previous one
   }
-  __shared__ float red[3][256];
-  red[0][threadIdx.x] = dot;
-  red[1][threadIdx.x] = so;
-  red[2][threadIdx.x] = sh;
+  __shared__ float red[3][4];
+#pragma unroll
+  for (int x = 32; x > 0; x >>= 1) {
+    dot += __shfl_xor(dot, x);
+    so += __shfl_xor(so, x);
+    sh += __shfl_xor(sh, x);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = dot;
+    red[1][threadIdx.x >> 6] = so;
+    red[2][threadIdx.x >> 6] = sh;
+  }
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s)
-      for (int j = 0; j < 3; ++j) red[j][threadIdx.x] += red[j][threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x < 3) out[(size_t)threadIdx.x * B + m] = red[threadIdx.x][0];
+  if (threadIdx.x == 0)
+    decide_from_sums(a, m, red[0][0] + red[0][1] + red[0][2] + red[0][3], red[1][0] + red[1][1] + red[1][2] + red[1][3],
+                     red[2][0] + red[2][1] + red[2][2] + red[2][3]);
 }
 
-// fp32 path: plain RMSNorm, one workgroup per row.
-__global__ __launch_bounds__(256) void rmsnorm_f32_kernel(const float* h, const float* gain, float* x, int d, float eps,
-                                                          Pred pred) {
-  if (pred_skip(pred)) return;
+// fp32 path: softmax statistics of one row of materialised logits and the decision from them, one workgroup per row; src /
+// dst: the hidden states the caller asked for (last launch of an iteration), copied whatever the predicate says.
+__global__ __launch_bounds__(256) void head_decide_f32_kernel(const float* logits, int vocab, CombineArgs a, Pred pred, const float* src,
+                                                              float* dst, int d) {
   const int m = blockIdx.x;
-  const float* hp = h + (size_t)m * d;
-  float ss = 0.0f;
-  for (int k = threadIdx.x; k < d; k += blockDim.x) ss = fmaf(hp[k], hp[k], ss);
-  __shared__ float red[256];
-  red[threadIdx.x] = ss;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  const float r = 1.0f / sqrtf(red[0] / (float)d + eps);
-  for (int k = threadIdx.x; k < d; k += blockDim.x) x[(size_t)m * d + k] = hp[k] * r * gain[k];
-}
-
-// fp32 path: softmax statistics of one row of materialised logits -> one partial record.
-__global__ __launch_bounds__(256) void head_stats_f32_kernel(const float* logits, float4* partials, int vocab, float scale,
-                                                             Pred pred) {
+  copy_row(src, dst, m, d);
   if (pred_skip(pred)) return;
-  const int m = blockIdx.x;
+  if (a.left && ctl_load(a.left + m) != 0) return;   // left at an earlier layer: its token and exit layer stand
+  // largest logit with its index and the runner-up first, the exponentials relative to the wavefront's largest after
   HeadStat s = stat_empty();
-  for (int v = threadIdx.x; v < vocab; v += blockDim.x) s = stat_push(s, logits[(size_t)m * vocab + v], v, scale);
-  __shared__ float4 red[256];
-  red[threadIdx.x] = stat_pack(s);
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w)
-      red[threadIdx.x] = stat_pack(stat_merge(stat_unpack(red[threadIdx.x]), stat_unpack(red[threadIdx.x + w]), scale));
-    __syncthreads();
+  const float* z = logits + (size_t)m * vocab;
+  for (int v = threadIdx.x; v < vocab; v += 256) {
+    const float x = z[v];
+    if (x > s.zmax || s.idx == 0x7fffffff) {   // strict: the lowest index wins among equals
+      s.z2 = fmaxf(s.z2, s.zmax);
+      s.zmax = x;
+      s.idx = v;
+    } else {
+      s.z2 = fmaxf(s.z2, x);
+    }
   }
-  if (threadIdx.x == 0) partials[m] = red[0];
+#pragma unroll
+  for (int x = 1; x < 64; x <<= 1) {
+    const float ob = __shfl_xor(s.zmax, x), o2 = __shfl_xor(s.z2, x);
+    const int oi = __shfl_xor(s.idx, x);
+    const bool take = ob > s.zmax || (ob == s.zmax && oi < s.idx);
+    s.z2 = fmaxf(fmaxf(s.z2, o2), take ? s.zmax : ob);
+    if (take) {
+      s.zmax = ob;
+      s.idx = oi;
+    }
+  }
+  for (int v = threadIdx.x; v < vocab; v += 256) s.sum += stat_exp(a.scale * (z[v] - s.zmax));
+#pragma unroll
+  for (int x = 1; x < 64; x <<= 1) s.sum += __shfl_xor(s.sum, x);
+  __shared__ float4 red[4];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = stat_pack(s);
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+#pragma unroll
+  for (int w = 1; w < 4; ++w) s = stat_merge(s, stat_unpack(red[w]), a.scale);
+  decide_from_stat(a, m, s);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -364,15 +387,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, Pred pred) 
 // asked for, one workgroup per row.
 __global__ __launch_bounds__(256) void combine_copy_kernel(CombineArgs a, Pred pred, const float* src, float* dst, int d) {
   const int m = blockIdx.x;
-  if (dst) {
-    const float* sp = src + (size_t)m * d;
-    float* dp = dst + (size_t)m * d;
-    if ((d & 3) == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
-      for (int k = threadIdx.x * 4; k < d; k += 1024) *reinterpret_cast<float4*>(dp + k) = *reinterpret_cast<const float4*>(sp + k);
-    } else {
-      for (int k = threadIdx.x; k < d; k += 256) dp[k] = sp[k];
-    }
-  }
+  copy_row(src, dst, m, d);
   if (pred_skip(pred)) return;
   __shared__ float4 red[256];
   combine_row(a, m, red);
@@ -457,15 +472,12 @@ void launch_fill_prep(const float* h, const GainTable& gains, int n_layers, bf16
 void launch_compact(const int32_t* status, int B, const RowMap& rm, Pred pred, hipStream_t st) {
   hipLaunchKernelGGL(compact_kernel, dim3(1), dim3(256), 0, st, status, B, rm, pred);
 }
-void launch_rmsnorm_f32(const float* h, const float* gain, float* x, int B, int d, float eps, Pred pred, hipStream_t st) {
-  hipLaunchKernelGGL(rmsnorm_f32_kernel, dim3(B), dim3(256), 0, st, h, gain, x, d, eps, pred);
+void launch_head_decide_f32(const float* logits, int vocab, const CombineArgs& a, Pred pred, const float* src, float* dst, int d,
+                            hipStream_t st) {
+  hipLaunchKernelGGL(head_decide_f32_kernel, dim3(a.B), dim3(256), 0, st, logits, vocab, a, pred, src, dst, d);
 }
-void launch_head_stats_f32(const float* logits, float4* partials, int B, int vocab, float scale, Pred pred,
-                           hipStream_t st) {
-  hipLaunchKernelGGL(head_stats_f32_kernel, dim3(B), dim3(256), 0, st, logits, partials, vocab, scale, pred);
-}
-void launch_measure_f32(const float* h, float* other, int per_row, float* out, int B, int d, Pred pred, hipStream_t st) {
-  hipLaunchKernelGGL(measure_f32_kernel, dim3(B), dim3(256), 0, st, h, other, per_row, out, B, d, pred);
+void launch_measure_decide_f32(const float* h, float* other, int per_row, const DecideArgs& a, Pred pred, hipStream_t st) {
+  hipLaunchKernelGGL(measure_decide_f32_kernel, dim3(a.B), dim3(256), 0, st, h, other, per_row, a, pred);
 }
 void launch_decide(const DecideArgs& a, Pred pred, hipStream_t st) {
   hipLaunchKernelGGL(decide_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, a, pred);

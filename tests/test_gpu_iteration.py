@@ -65,6 +65,17 @@ def test_two_sequences_long_prompts_attention_split_among_workgroups(dtype):
     assert stats["near_threshold"] + stats["near_tie"] <= max(2, total // 20), stats
 
 
+@pytest.mark.parametrize("batch,d_ffn,vocab,conf_mode", [(1, 257, 130, 0), (5, 258, 514, 1), (9, 1028, 64, 2), (4, 62, 2, 3)])
+def test_fp32_odd_widths(batch, d_ffn, vocab, conf_mode):
+    """The float projections take four batch rows a wavefront and 16 bytes a load where a contraction divides by four: rows
+    that do not divide by four, widths that do not, a contraction and a vocabulary narrower than a workgroup, every
+    confidence measure (the sums of a measure and its decision share a launch)."""
+    cfg = TINY.with_(batch=batch, d_ffn=d_ffn, vocab=vocab, conf_mode=conf_mode, prompt_len=12, min_prompt_len=5, weight_std=0.05,
+                     logit_scale=1.0, threshold=0.99 if conf_mode == 2 else 0.5, shuffled_blocks=True, tied_head=False)
+    stats = lockstep(cfg, seed=7, steps=4)
+    assert stats["near_threshold"] + stats["near_tie"] <= 1
+
+
 def test_fp32_ragged_prompts_shuffled_blocks_conf_mode1():
     cfg = TINY.with_(batch=6, prompt_len=21, min_prompt_len=3, shuffled_blocks=True, conf_mode=1, weight_std=0.05,
                      logit_scale=2.0, threshold=0.2, n_layers=5, exit_every=2)

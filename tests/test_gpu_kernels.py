@@ -309,6 +309,27 @@ def test_exit_check_matches_oracle(dtype, conf_mode):
         run_exit_check(cfg, seed=20 + layer, layer=layer, threshold=thr, hidden_scale=3.0)
 
 
+def test_exit_check_fp32_hidden_rows_off_a_16_byte_boundary():
+    """The float head reads the caller's hidden rows itself, 16 bytes at a time only where they start on a boundary: rows
+    one float further on give the same arg max and, to float rounding of another summation order, the same confidence."""
+    cfg = cfg_of("fp32", 64, 4, n_layers=6, vocab=514, logit_scale=2.0, batch=7)
+    w = W.make_weights(cfg, seed=19, gain_jitter=0.2)
+    model = B.DeviceModel(cfg, w)
+    ws = B.Workspace(model.desc, cfg.batch, 16)
+    hidden = torch.randn(cfg.batch, cfg.d_model, generator=torch.Generator().manual_seed(19)).mul_(3.0).cuda()
+    store = torch.empty(cfg.batch * cfg.d_model + 1, device="cuda")
+    off = store[1:].view(cfg.batch, cfg.d_model).copy_(hidden)
+    got = []
+    for h in (hidden, off):
+        z = lambda *s: torch.zeros(*s, dtype=torch.int32, device="cuda")  # noqa: E731
+        argmax, conf = z(cfg.batch), torch.zeros(cfg.batch, device="cuda")
+        B.ee_exit_check(model, 2, h, 2.0, None, z(cfg.batch), z(cfg.batch), z(1), z(1), z(1), argmax, conf, ws)
+        torch.cuda.synchronize()
+        got.append((argmax.cpu(), conf.cpu()))
+    assert got[0][0].equal(got[1][0])
+    assert torch.allclose(got[0][1], got[1][1], rtol=1e-5, atol=0)   # logits of magnitude 10 to 1e-6, scale 4
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_exit_check_sticky_forced_and_done_flag(dtype):
     cfg = cfg_of(dtype, 64, 4, n_layers=6, vocab=512, logit_scale=2.0, batch=5)
