@@ -193,17 +193,19 @@ __device__ inline void tile_finish(const f32x16& acc, int nt, int mt_global, con
 // ---------------------------------------------------------------------------------------------------------
 // Main loop 1: bf16 operand tiles on both sides
 // ---------------------------------------------------------------------------------------------------------
-template <int MT, int U>
+template <int MT, int NT, int U>
 struct Frag {
-  u32x4 w[U];
+  u32x4 w[NT][U];
   u32x4 x[MT][U];
 };
 
-template <int MT, int U>
-__device__ inline void frag_load(Frag<MT, U>& f, const u32x4* __restrict__ wp, const u32x4* __restrict__ xp,
+template <int MT, int NT, int U>
+__device__ inline void frag_load(Frag<MT, NT, U>& f, const u32x4* const (&wp)[NT], const u32x4* __restrict__ xp,
                                  size_t x_tile_stride, int ks) {
 #pragma unroll
-  for (int u = 0; u < U; ++u) f.w[u] = __builtin_nontemporal_load(wp + (size_t)(ks + u) * 64);
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) f.w[t][u] = __builtin_nontemporal_load(wp[t] + (size_t)(ks + u) * 64);
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -211,14 +213,15 @@ __device__ inline void frag_load(Frag<MT, U>& f, const u32x4* __restrict__ wp, c
 }
 
 // Last, partial group: steps past ks1 re-read the last valid weight tile against a zero activation tile.
-template <int MT, int U>
-__device__ inline void frag_load_tail(Frag<MT, U>& f, const u32x4* __restrict__ wp, const u32x4* __restrict__ xp,
+template <int MT, int NT, int U>
+__device__ inline void frag_load_tail(Frag<MT, NT, U>& f, const u32x4* const (&wp)[NT], const u32x4* __restrict__ xp,
                                       size_t x_tile_stride, int ks, int ks1) {
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const bool ok = ks + u < ks1;
     const int kk = ok ? ks + u : ks1 - 1;
-    f.w[u] = __builtin_nontemporal_load(wp + (size_t)kk * 64);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) f.w[t][u] = __builtin_nontemporal_load(wp[t] + (size_t)kk * 64);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       u32x4 v = xp[mt * x_tile_stride + (size_t)kk * 64];
@@ -227,17 +230,22 @@ __device__ inline void frag_load_tail(Frag<MT, U>& f, const u32x4* __restrict__ 
   }
 }
 
-template <int MT, int U>
-__device__ inline void frag_mma(const Frag<MT, U>& f, f32x16 (&acc)[MT]) {
+template <int MT, int NT, int U>
+__device__ inline void frag_mma(const Frag<MT, NT, U>& f, f32x16 (&acc)[NT][MT]) {
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
-      acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.w[u]),
-                                                        __builtin_bit_cast(bf16x8, f.x[mt][u]), acc[mt], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        acc[t][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.w[t][u]),
+                                                             __builtin_bit_cast(bf16x8, f.x[mt][u]), acc[t][mt], 0, 0, 0);
 }
 
-template <int MT, int U, class Epi, bool FILL>
+// NT = 2: a workgroup streams two output tiles, so the activation operand, which otherwise costs a compute unit as many
+// bytes from L2 as the weights do from memory at 64 rows (half as many at 32), is fetched once for both: two neighbouring
+// tiles, or, with one batch tile (QKV), a whole Q/K tile and half a V tile (g.split_tiles = 2 x as many whole tiles).
+template <int MT, int NT, int U, class Epi, bool FILL>
 __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred pred, FillCtl fc, CombineJob cj) {
   __shared__ Lds s;
 
@@ -287,26 +295,47 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred
   // of every weight tile that holds those rows (two 256-byte pieces of each kilobyte).  Both halves are complete
   // results: the workgroups share nothing and never meet.  With 384 tiles on 256 compute units this turns two rounds
   // of workgroups into one and a half.  Only tiles without a rotation may be split (V: the host sees to that).
-  const bool half_tile = bx < 2 * g.split_tiles;
-  int tl = half_tile ? bx >> 1 : bx - 2 * g.split_tiles;   // tile within its class (halved / whole)
-  int rhalf = bx & 1;
-  if constexpr (std::is_same<Epi, QkvEpi>::value) {
-    // Four consecutive tiles hold the 128 channels of one head (or two heads of 64): each writes 32-byte runs of
-    // the same cache lines of the paged cache (64-byte runs of q).  Workgroup ids congruent modulo 8 run on the
-    // same XCD behind the same L2, so the four tiles of a head get ids 8 apart: their partial lines meet in that
-    // L2 before they go to memory.  Only whole groups are rearranged (32 whole tiles = 8 heads x 4 tiles; 64 half
-    // tiles = 8 heads x 4 tiles x 2 halves, both halves of a tile on one XCD as well).
-    if (half_tile) {
-      if (bx < ((2 * g.split_tiles) & ~63)) {
-        const int q = (bx >> 3) & 7;
-        tl = (((bx >> 6) << 3) + (bx & 7)) * 4 + (q >> 1);
-        rhalf = q & 1;
+  int nt[NT], rhalf[NT];   // this workgroup's tiles; rhalf: which half of the tile's rows, -1 = all
+  if constexpr (NT == 1) {
+    const bool half_tile = bx < 2 * g.split_tiles;
+    int tl = half_tile ? bx >> 1 : bx - 2 * g.split_tiles;   // tile within its class (halved / whole)
+    rhalf[0] = half_tile ? bx & 1 : -1;
+    if constexpr (std::is_same<Epi, QkvEpi>::value) {
+      // Four consecutive tiles hold the 128 channels of one head (or two heads of 64): each writes 32-byte runs of
+      // the same cache lines of the paged cache (64-byte runs of q).  Workgroup ids congruent modulo 8 run on the
+      // same XCD behind the same L2, so the four tiles of a head get ids 8 apart: their partial lines meet in that
+      // L2 before they go to memory.  Only whole groups are rearranged (32 whole tiles = 8 heads x 4 tiles; 64 half
+      // tiles = 8 heads x 4 tiles x 2 halves, both halves of a tile on one XCD as well).
+      if (half_tile) {
+        if (bx < ((2 * g.split_tiles) & ~63)) {
+          const int q = (bx >> 3) & 7;
+          tl = (((bx >> 6) << 3) + (bx & 7)) * 4 + (q >> 1);
+          rhalf[0] = q & 1;
+        }
+      } else if (tl < ((g.n_tiles - g.split_tiles) & ~31)) {
+        tl = (tl & ~31) + ((tl & 7) << 2) + ((tl >> 3) & 3);
       }
-    } else if (tl < ((g.n_tiles - g.split_tiles) & ~31)) {
-      tl = (tl & ~31) + ((tl & 7) << 2) + ((tl >> 3) & 3);
     }
+    nt[0] = half_tile ? g.tile_begin + g.n_tiles - g.split_tiles + tl : g.tile_begin + tl;
+  } else if (g.split_tiles) {   // a whole tile and half of one of the last split_tiles (grid: 2 * split_tiles = the others)
+    int tl = bx, hl = bx >> 1;
+    rhalf[0] = -1;
+    rhalf[1] = bx & 1;
+    if (bx < ((2 * g.split_tiles) & ~63)) {   // heads stay on one XCD, as above
+      const int q = (bx >> 3) & 7;
+      tl = (bx & ~31) + ((bx & 7) << 2) + ((bx >> 3) & 3);
+      hl = (((bx >> 6) << 3) + (bx & 7)) * 4 + (q >> 1);
+      rhalf[1] = q & 1;
+    }
+    nt[0] = g.tile_begin + tl;
+    nt[1] = g.tile_begin + 2 * g.split_tiles + hl;
+  } else {
+    int pr = bx;   // two neighbouring tiles; the two pairs of a head get ids 8 apart
+    if (std::is_same<Epi, QkvEpi>::value && bx < ((g.n_tiles >> 1) & ~15)) pr = (bx & ~15) + ((bx & 7) << 1) + ((bx >> 3) & 1);
+    nt[0] = g.tile_begin + 2 * pr;
+    nt[1] = nt[0] + 1;
+    rhalf[0] = rhalf[1] = -1;
   }
-  const int nt = half_tile ? g.tile_begin + g.n_tiles - g.split_tiles + tl : g.tile_begin + tl;
   const int k_steps = g.K >> 4;
   const int chunks = gridDim.y * NW;
   const int c = blockIdx.y * NW + wave;
@@ -317,19 +346,23 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred
 
   // Lane l of a weight tile holds row l % 32.  In a halved tile the lanes of the other 16 rows fetch what their
   // partner lanes fetch (the same bytes, no further memory traffic): their result rows are duplicates, never written.
-  const int wlane = half_tile ? ((lane & ~16) | (rhalf << 4)) : lane;
-  const u32x4* wp = reinterpret_cast<const u32x4*>(g.w) + (size_t)nt * k_steps * 64 + wlane;
+  const u32x4* wp[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+    wp[t] = reinterpret_cast<const u32x4*>(g.w) + (size_t)nt[t] * k_steps * 64 + (rhalf[t] >= 0 ? ((lane & ~16) | (rhalf[t] << 4)) : lane);
 
   for (int mt0 = 0; mt0 < m_tiles; mt0 += MT) {
     const u32x4* xp = reinterpret_cast<const u32x4*>(g.x) + (size_t)mt0 * x_tile_stride + lane;
-    f32x16 acc[MT];
+    f32x16 acc[NT][MT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[mt][i] = 0.0f;
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[t][mt][i] = 0.0f;
 
     // double-buffered stream over this wavefront's share of the contraction
-    Frag<MT, U> A, B;
+    Frag<MT, NT, U> A, B;
     const int n = (ks1 - ks0) / U;
     int k = ks0;
     if (n > 0) frag_load(A, wp, xp, x_tile_stride, k);
@@ -352,7 +385,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred
       frag_mma(A, acc);
     }
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) tile_finish(acc[mt], nt, mt0 + mt, g, e, s, wave, lane, half_tile ? rhalf : -1);
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) tile_finish(acc[t][mt], nt[t], mt0 + mt, g, e, s, wave, lane, rhalf[t]);
   }
 }
 
@@ -777,7 +812,8 @@ bool tiled(int M, int n_tiles) { return (M + 31) / 32 >= 3 && n_tiles % NW == 0;
 // contraction of K runs in, and how many contraction slices it writes.  Every slice is one more partial result for
 // the normalisation launch to read, so the count stays as small as filling the chip allows.
 struct AccPlan {
-  int kind;     // 0: streaming kernel, 1: tiled kernel with 128-row chunks, 2: tiled kernel, one chunk of one or two tiles
+  int kind;     // 0: streaming kernel, 1: tiled kernel with 128-row chunks, 2: tiled kernel, one chunk of one or two tiles,
+                // 3: streaming kernel, two output tiles per workgroup
   int ksplit;
 };
 AccPlan acc_plan(int M, int n_tiles, int K) {
@@ -791,6 +827,12 @@ AccPlan acc_plan(int M, int n_tiles, int K) {
   } else if (m_tiles <= 2 && n_tiles % NW == 0 && k_steps >= 512) {
     p.kind = 2;
     p.ksplit = 256 / (n_tiles / NW);
+  } else if (m_tiles <= 2 && n_tiles % 2 == 0 && n_tiles > 128 && n_tiles < 256 && k_steps / 64 >= 512 / n_tiles) {
+    // One tile per workgroup would need two slices and a second round of workgroups for the remainder: two tiles and up to
+    // three slices fit one round (13B output projection, 160 tiles: 22.1 -> 16.7 us at 64 rows, 16.1 -> 13.8 at 32).  At 128 tiles
+    // two slices fill the chip exactly, and four of two tiles cost the normalisation more than they gain (12.6 against 13.0).
+    p.kind = 3;
+    p.ksplit = 512 / n_tiles;
   } else {
     // streaming kernel (its four wavefronts already split the slice four ways): enough workgroups for every
     // compute unit, no more
@@ -902,17 +944,34 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
       return;
     }
   }
+  // Two tiles per workgroup where they fill the chip in one round: QKV of one batch tile as 2 * split_tiles whole tiles with a
+  // half each (7B, 256 workgroups, 32 rows: 24.2 -> 22.7 us), else pairs of tiles on 129 to 256 workgroups (13B: 45 -> 38 us at
+  // 64 rows, 39 -> 31 at 32; 7B at 64 rows: 34 -> 31).
+  if constexpr (!FILL) {
+    const bool one_half = m_tiles == 1 && g.split_tiles && 3 * g.split_tiles == g.n_tiles && g.split_tiles > 96 && g.split_tiles <= 128;
+    const bool pairs = ACC ? ap.kind == 3 : m_tiles <= 2 && g.n_tiles % 2 == 0 && g.n_tiles > 256 && g.n_tiles <= 512;
+    if (one_half || pairs) {
+      GemmShape g2 = g;
+      if (!one_half) g2.split_tiles = 0;
+      const dim3 grid2((one_half ? 2 * g.split_tiles : g.n_tiles / 2) + cj.n_wg, ACC ? ap.ksplit : 1, nz);
+      if (m_tiles == 1)
+        hipLaunchKernelGGL((gemm_mfma_kernel<1, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
+      else
+        hipLaunchKernelGGL((gemm_mfma_kernel<2, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
+      return;
+    }
+  }
   // split tiles take two workgroups each (one batch tile only); the workgroups of a combine job come first
   dim3 grid(g.n_tiles + g.split_tiles + cj.n_wg, ACC ? ap.ksplit : 1, nz);
   switch (pick_mt(g.M, 4)) {
     case 4:
-      hipLaunchKernelGGL((gemm_mfma_kernel<4, 2, Epi, FILL>), grid, block, 0, st, g, e, pred, fc, cj);
+      hipLaunchKernelGGL((gemm_mfma_kernel<4, 1, 2, Epi, FILL>), grid, block, 0, st, g, e, pred, fc, cj);
       break;
     case 2:
-      hipLaunchKernelGGL((gemm_mfma_kernel<2, 4, Epi, FILL>), grid, block, 0, st, g, e, pred, fc, cj);
+      hipLaunchKernelGGL((gemm_mfma_kernel<2, 1, 4, Epi, FILL>), grid, block, 0, st, g, e, pred, fc, cj);
       break;
     default:
-      hipLaunchKernelGGL((gemm_mfma_kernel<1, 8, Epi, FILL>), grid, block, 0, st, g, e, pred, fc, cj);
+      hipLaunchKernelGGL((gemm_mfma_kernel<1, 1, 8, Epi, FILL>), grid, block, 0, st, g, e, pred, fc, cj);
   }
 }
 

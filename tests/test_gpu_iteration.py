@@ -312,6 +312,20 @@ def test_bf16_row_counts_with_a_short_last_chunk(batch, heads):
     assert stats["near_threshold"] + stats["near_tie"] <= max(2, total // 20), stats
 
 
+@pytest.mark.parametrize("heads,dh,batch", [
+    (25, 128, 7),      # QKV as 200 whole tiles with half a V tile each: the last 8 past the groups that are rearranged
+    (44, 64, 31),      # 264 tiles as 132 pairs (88 halves would leave units idle), one batch tile
+    (22, 128, 33),     # the same in two batch tiles, the second of one row
+    (33, 128, 64),     # 396 tiles as 198 pairs; output projection of 132 tiles: pairs, three slices of 88 steps
+    (33, 128, 2),      # ... in one batch tile
+])
+def test_bf16_two_output_tiles_per_workgroup(heads, dh, batch):
+    cfg = small_bf16(n_layers=2, d_model=heads * dh, n_heads=heads, head_dim=dh, d_ffn=96, vocab=512, batch=batch, prompt_len=3,
+                     min_prompt_len=2, weight_std=0.02, shuffled_blocks=True, threshold=2.0)
+    stats = lockstep(cfg, seed=61, steps=2)
+    assert stats["near_threshold"] + stats["near_tie"] <= max(2, stats["tokens"] // 20), stats
+
+
 @pytest.mark.parametrize("exit_every", [1, 2])
 def test_per_sequence_compaction_across_chunk_boundaries(exit_every):
     """Forced exits that take the number of active rows through 129, 128, 127, 1 and 0 (the projections work on
