@@ -312,7 +312,7 @@ void enqueue_head_f32(const ee_model& M, const Workspace& w, const float* h, int
 // --- KV filling for layers above fill_from ----------------------------------------------------------------
 // h: hidden rows [B][d] (inside an iteration: the residual stream, final at the batch exit layer).
 void enqueue_fill_bf16(const ee_model& M, const ee_kv_cache& C, const ee_batch& Bt, const Workspace& w, const float* h,
-                       int Mpad, const int32_t* fill_from, int stride, Pred pred, hipStream_t st) {
+                       int Mpad, const int32_t* fill_from, int stride, Pred pred, const RopeJob& rope, hipStream_t st) {
   const ee_model_desc& D = M.desc;
   GainTable gt{};
   FillLayers fl{};
@@ -321,7 +321,7 @@ void enqueue_fill_bf16(const ee_model& M, const ee_kv_cache& C, const ee_batch& 
     fl.w_qkv[i] = M.layers[i].w_qkv;
   }
   ProfScope ps(EE_K_KVFILL, 0, st);
-  launch_fill_prep(h, gt, D.n_layers, w.fill_x, D.rms_eps, fill_from, stride, Bt.batch, Mpad, D.d_model, pred, st);
+  launch_fill_prep(h, gt, D.n_layers, w.fill_x, D.rms_eps, fill_from, stride, Bt.batch, Mpad, D.d_model, pred, rope, st);
   GemmShape g{nullptr, nullptr, D.d_model, Bt.batch, D.d_model / 32, 2 * D.d_model / 32, D.head_dim / 2, 1};
   QkvEpi e = make_qkv_epi(D, C, Bt, w, 1, nullptr);
   e.fill_from = fill_from;
@@ -750,7 +750,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // layers' own QKV projections (see above); every column of the residual stream is that sequence's exit state.
   if (use_exit_heads) {
     if (bf)
-      enqueue_fill_bf16(*model, *cache, *batch, w, w.h, Mpad, out_batch_exit_layer, 0, run_fill, st);
+      enqueue_fill_bf16(*model, *cache, *batch, w, w.h, Mpad, out_batch_exit_layer, 0, run_fill, RopeJob{}, st);
     else
       enqueue_fill_f32(*model, *cache, *batch, w, w.h, out_batch_exit_layer, 0, run_fill, st);
   }
@@ -836,11 +836,13 @@ int ee_kv_fill(const ee_model* model, const ee_kv_cache* cache, const ee_batch* 
   const Workspace w = carve(D, B, workspace);
   const int Mpad = round_up(B, 32);
   const Pred always{nullptr, 0};
-  launch_rope_table(batch->context_lens, w.rope, B, D.head_dim, D.rope_theta, st);
-  if (D.dtype == EE_BF16)
-    enqueue_fill_bf16(*model, *cache, *batch, w, hidden, Mpad, fill_from_layer, 1, always, st);
-  else
+  if (D.dtype == EE_BF16) {
+    enqueue_fill_bf16(*model, *cache, *batch, w, hidden, Mpad, fill_from_layer, 1, always,
+                      RopeJob{batch->context_lens, w.rope, D.head_dim, D.rope_theta}, st);
+  } else {
+    launch_rope_table(batch->context_lens, w.rope, B, D.head_dim, D.rope_theta, st);
     enqueue_fill_f32(*model, *cache, *batch, w, hidden, fill_from_layer, 1, always, st);
+  }
   EE_HIP(hipGetLastError());
   return EE_OK;
 }

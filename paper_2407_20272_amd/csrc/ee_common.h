@@ -187,8 +187,16 @@ struct BeginArgs {
 void launch_iter_begin(const BeginArgs& a, hipStream_t st);
 void launch_iter_begin_f32(const BeginArgs& a, hipStream_t st);
 // KV filling: x slab of layer l = bf16(RMSNorm(h; gains.g[l-1])) for every layer some row needs (fill_from < l).
+// rope.table != nullptr: the same launch also tabulates the rotary angles.
+struct RopeJob {
+  const int32_t* context_lens;
+  float2* table;
+  int head_dim;
+  float theta;
+};
 void launch_fill_prep(const float* h, const GainTable& gains, int n_layers, bf16_t* x_slabs, float eps,
-                      const int32_t* fill_from, int fill_from_stride, int B, int Mpad, int d, Pred pred, hipStream_t st);
+                      const int32_t* fill_from, int fill_from_stride, int B, int Mpad, int d, Pred pred, const RopeJob& rope,
+                      hipStream_t st);
 struct CombineArgs {
   const float4* partials;
   int n_parts;
