@@ -284,7 +284,7 @@ void enqueue_head_bf16(const ee_model& M, const Workspace& w, int B, float scale
   const ee_model_desc& D = M.desc;
   GemmShape g{M.w_lm, w.xH, D.d_model, B, 0, D.vocab / 32, 16, 1};
   g.n_rows_dev = rm.n_active;   // compacted operand (prepared by the caller through the same map)
-  LmEpi e{w.partials, nullptr, D.vocab / 32, D.vocab, scale, nullptr, D.rms_eps, D.d_model, rm.perm};
+  LmEpi e{w.partials, nullptr, D.vocab / 32, D.vocab, scale, rm.perm};
   ProfScope ps(EE_K_HEAD, layer, st);
   launch_gemm_lm_bf16(g, e, pred, st);
 }
@@ -305,7 +305,7 @@ void enqueue_head_f32(const ee_model& M, const Workspace& w, const float* h, int
   const ee_model_desc& D = M.desc;
   ProfScope ps(EE_K_HEAD, layer, st);
   SimpleShape g{reinterpret_cast<const float*>(M.w_lm), h, reinterpret_cast<const float*>(M.g_final), D.rms_eps, D.d_model, B, 0, D.vocab, 1};
-  LmEpi e{nullptr, w.logits, 1, D.vocab, 0.0f, nullptr, D.rms_eps, D.d_model};
+  LmEpi e{nullptr, w.logits, 1, D.vocab, 0.0f, nullptr};
   launch_simple_lm(g, e, pred, st);
 }
 

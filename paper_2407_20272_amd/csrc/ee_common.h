@@ -112,9 +112,6 @@ struct LmEpi {                  // per-tile softmax statistics of the scaled log
   int n_parts;
   int vocab;
   float scale;                  // logit_scale * layer
-  const float* rowsq;
-  float eps;
-  int d_model;
   const int32_t* perm;          // nullptr, or [M]: operand row m is batch row perm[m] (compacted operand, tiled kernel only)
 };
 

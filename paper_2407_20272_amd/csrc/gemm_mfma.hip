@@ -87,11 +87,10 @@ __device__ inline void tile_finish(const f32x16& acc, int nt, int mt_global, con
     r16[ai] = (a >> 2) * 8 + (l2 >> 5) * 4 + (a & 3);
   }
   if constexpr (std::is_same<Epi, LmEpi>::value) {
-    const float r = m < g.M ? row_rinv(e.rowsq, m, e.d_model, e.eps) : 0.0f;
 #pragma unroll
     for (int ai = 0; ai < 2; ++ai) {
-      s.zt[r16[ai]][l2 & 31] = vlo[ai] * r;
-      s.zt[r16[ai] + 16][l2 & 31] = vhi[ai] * r;
+      s.zt[r16[ai]][l2 & 31] = vlo[ai];
+      s.zt[r16[ai] + 16][l2 & 31] = vhi[ai];
     }
     __syncthreads();
     {   // eight neighbouring lanes share one batch row: four logits each
@@ -403,6 +402,57 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred
 constexpr int UT = 4;
 __device__ u32x4 k_zero_tile[64];   // one operand tile of zeros, never written (activation rows past the contraction range; not const: it must live in the same address space as the operands)
 
+// Exit-head epilogue of NT neighbouring 32-column tiles of one batch tile, from registers: the statistics of all their logits
+// of a row as one record in the first tile's place (the others' are empty).  Accumulators as in finish_from_registers below.
+// Nothing hides this work (one or two wavefronts per SIMD, all in the same phase), so it is as few instructions as it can
+// be: largest and runner-up as a maximum and a median of three, the row's largest settled between its two lanes before the
+// exponentials, so that merging them takes none.  The statistics were about 20 us of the ring kernel's 120 at 500 rows; exit
+// check 128.8 -> 125.1 us there, 160 -> 148 at 300 rows (tiled kernel, two tiles), 99 -> 93 for 256 compacted rows.
+template <int NT, class Get>
+__device__ inline void finish_lm(Get acc, int nt, int mtile, int M_eff, const GemmShape& g, const LmEpi& e, int lane) {
+  constexpr int N = NT * 16;
+  const int half = lane >> 5, m = mtile * 32 + (lane & 31);
+  float m1[NT], m2[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    m1[t] = acc(t, 0);
+    m2[t] = -INFINITY;
+#pragma unroll
+    for (int a = 1; a < 16; ++a) {
+      const float z = acc(t, a);
+      m2[t] = __builtin_amdgcn_fmed3f(m1[t], m2[t], z);
+      m1[t] = fmaxf(m1[t], z);
+    }
+  }
+  float lane_best = m1[0], z2 = m2[0];
+#pragma unroll
+  for (int t = 1; t < NT; ++t) {
+    z2 = fmaxf(fminf(lane_best, m1[t]), fmaxf(z2, m2[t]));
+    lane_best = fmaxf(lane_best, m1[t]);
+  }
+  const float other = __shfl_xor(lane_best, 32);
+  z2 = fmaxf(fminf(lane_best, other), fmaxf(z2, __shfl_xor(z2, 32)));
+  const float best = fmaxf(lane_best, other);
+  // number of the lane's first logit (they are in vocabulary order) that is the row's largest
+  int at = N;
+#pragma unroll
+  for (int i = N - 1; i >= 0; --i) at = acc(i >> 4, i & 15) == best ? i : at;
+  int idx = at < N ? (nt + (at >> 4)) * 32 + ((at >> 3) & 1) * 16 + ((at >> 2) & 1) * 8 + half * 4 + (at & 3) : 0x7fffffff;
+  idx = min(idx, __shfl_xor(idx, 32));
+  const float c = e.scale * 1.4426950408889634f;
+  float sum[2] = {0.0f, 0.0f};
+#pragma unroll
+  for (int i = 0; i < N; ++i) sum[i & 1] += __builtin_amdgcn_exp2f(c * (acc(i >> 4, i & 15) - best));
+  float total = sum[0] + sum[1];
+  total += __shfl_xor(total, 32);
+  if (half == 0 && m < M_eff) {
+    float4* rec = e.partials + (size_t)(e.perm ? e.perm[m] : m) * e.n_parts + (nt - g.tile_begin);
+    rec[0] = stat_pack(HeadStat{best, total, z2, idx});
+#pragma unroll
+    for (int t = 1; t < NT; ++t) rec[t] = stat_pack(stat_empty());
+  }
+}
+
 // Epilogue of one finished 32 x 32 result tile held in a wavefront's registers (tiled and ring kernels): accumulator a
 // (< 8) of a lane is result row r16 = (a/4)*8 + (lane/32)*4 + a%4 of column lane%32, accumulator a+8 is row r16+16 (its
 // partner row in the packed order).  nt: packed weight tile, mtile: 32-row batch tile, M_eff: valid rows, ksl: the
@@ -412,31 +462,7 @@ __device__ inline void finish_from_registers(const f32x16& acc, int nt, int mtil
                                              const Epi& e, int lane) {
   const int half = lane >> 5, ml = lane & 31;
   const int m = mtile * 32 + ml;
-  if constexpr (std::is_same<Epi, LmEpi>::value) {
-    // this lane's 16 logits of the row in ascending vocabulary order: rows r16(a), a = 0..7, then r16(a)+16
-    float z[16];
-    int zi[16];
-    const float rs = m < M_eff ? row_rinv(e.rowsq, e.perm ? e.perm[m] : m, e.d_model, e.eps) : 0.0f;
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
-      const int r16 = (a >> 2) * 8 + half * 4 + (a & 3);
-      z[a] = acc[a] * rs;
-      zi[a] = nt * 32 + r16;
-      z[a + 8] = acc[a + 8] * rs;
-      zi[a + 8] = nt * 32 + r16 + 16;
-    }
-    HeadStat st = stat_of<16>(z, zi, e.scale);
-    HeadStat o;
-    o.zmax = __shfl_xor(st.zmax, 32);
-    o.sum = __shfl_xor(st.sum, 32);
-    o.z2 = __shfl_xor(st.z2, 32);
-    o.idx = __shfl_xor(st.idx, 32);
-    st = stat_merge(st, o, e.scale);
-    if (half == 0 && m < M_eff) {
-      const int row = e.perm ? e.perm[m] : m;
-      e.partials[(size_t)row * e.n_parts + (nt - g.tile_begin)] = stat_pack(st);
-    }
-  } else if constexpr (std::is_same<Epi, AccEpi>::value) {
+  if constexpr (std::is_same<Epi, AccEpi>::value) {
     // this workgroup's contraction slice (ksl) of the partial results, plain 16-byte stores: a lane holds, for its
     // batch row, two runs of four consecutive channels and the two runs 16 channels further on
     if (m < M_eff) {
@@ -660,10 +686,16 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pre
   }
 
   // every wavefront finishes its own tiles from registers
+  if constexpr (std::is_same<Epi, LmEpi>::value) {
 #pragma unroll
-  for (int t = 0; t < NTW; ++t)
+    for (int mt = 0; mt < MT; ++mt)
+      finish_lm<NTW>([&](int t, int a) { return acc[t][mt][a]; }, nt0, chunk * MT + mt, M_eff, g, e, lane);
+  } else {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) finish_from_registers(acc[t][mt], nt0 + t, chunk * MT + mt, M_eff, ksl, g, e, lane);
+    for (int t = 0; t < NTW; ++t)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) finish_from_registers(acc[t][mt], nt0 + t, chunk * MT + mt, M_eff, ksl, g, e, lane);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -783,10 +815,15 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(GemmShape g, Epi e, Pred
   }
   wait_loads_but<0>();   // the repeated loads past the end still target LDS and registers
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int b = 0; b < 8; ++b) {
+    if (bm * 8 + b >= m_tiles) continue;
+    if constexpr (std::is_same<Epi, LmEpi>::value) {
+      finish_lm<2>([&](int t, int a) { return acc[t][b][a]; }, nt0, bm * 8 + b, M_eff, g, e, lane);
+    } else {
 #pragma unroll
-    for (int b = 0; b < 8; ++b)
-      if (bm * 8 + b < m_tiles) finish_from_registers(acc[a][b], nt0 + a, bm * 8 + b, M_eff, 0, g, e, lane);
+      for (int a = 0; a < 2; ++a) finish_from_registers(acc[a][b], nt0 + a, bm * 8 + b, M_eff, 0, g, e, lane);
+    }
+  }
 }
 
 // Which shapes the ring kernel serves: 385 to 512 rows (two row blocks, the second at least half full: below that the

@@ -352,6 +352,25 @@ def test_exit_check_385_to_512_rows(batch, heads):
     run_exit_check(cfg, seed=50 + heads, layer=2, threshold=0.3, hidden_scale=3.0)
 
 
+@pytest.mark.parametrize("batch", [3, 40, 100, 200, 450])
+def test_exit_check_ties_go_to_the_lowest_index(batch):
+    """Every LM-head row four times (16 rows on, in the next tile pair and half a vocabulary on): equal sums bit for bit, so the
+    arg max is the lowest of them and top-1 minus top-2 is exactly zero, in each form of the projection and its epilogue."""
+    cfg = cfg_of("bf16", 64, 4, n_layers=4, vocab=1280, logit_scale=2.0, batch=batch, conf_mode=1, tied_head=False)
+    w = W.make_weights(cfg, seed=23, gain_jitter=0.2)
+    lm = w["w_lm"].view(2, 10, 2, 2, 16, -1)
+    lm.copy_(lm[:1, :, :1, :1].clone().expand_as(lm))
+    w["w_lm"] = lm.view(1280, -1)
+    model = B.DeviceModel(cfg, w)
+    ws = B.Workspace(model.desc, batch, 16)
+    hidden = torch.randn(batch, cfg.d_model, generator=torch.Generator().manual_seed(23)).mul_(3.0).cuda()
+    z = lambda *s: torch.zeros(*s, dtype=torch.int32, device="cuda")  # noqa: E731
+    argmax, conf = z(batch), torch.full((batch,), 7.0, device="cuda")
+    B.ee_exit_check(model, 2, hidden, 2.0, None, z(batch), z(batch), z(1), z(1), z(1), argmax, conf, ws)
+    torch.cuda.synchronize()
+    assert (argmax < 640).all() and (argmax % 64 < 16).all() and (conf == 0).all()
+
+
 def test_exit_check_llama7b_width():
     """LM head of the 7B-shaped workload (vocab 32000 x d 4096, batch 32): every row's confidence and arg max."""
     cfg = W.reduced(L7B, n_layers=2, d_ffn=256)
