@@ -574,7 +574,8 @@ __global__ __launch_bounds__(PW * 64) void attn_prompt_kernel(AttnArgs a, int R,
   const bool row_ok = my < nrows;
 
   const int seq_l = lane < nrows ? safe_row(a.row_table[row0 + lane], a.B) : -1;
-  const int npos_l = lane < nrows ? min(a.context_lens[row0 + lane] + 1, a.max_blocks * 16) : 0;
+  // (a negative context attends nothing: the counts of steps below must not go backwards)
+  const int npos_l = lane < nrows ? max(0, min(a.context_lens[row0 + lane], a.max_blocks * 16 - 1) + 1) : 0;
   // q of this lane's row, channels c*16 + h*8 .. +8 of every contraction step, scaled, as bf16 head + remainder
   u32x4_t qh[CS], ql[CS];
   {

@@ -197,6 +197,27 @@ def test_attention_prompt_rows_run_structure(dh, n_heads, runs):
     assert err <= 2e-5, f"relative error of a row: {err}"
 
 
+def test_attention_prompt_rows_beside_a_negative_context():
+    """A sequence whose context lengths are garbage (negative) has no result, but its neighbours keep theirs."""
+    cfg = cfg_of("bf16", 64, 2, n_layers=1).with_(batch=3, shuffled_blocks=True)
+    lens = torch.tensor([40, 16, 70], dtype=torch.int32)
+    Ks, Vs = W.make_dense_kv(cfg, lens + 1, 71, seed=19, device="cuda")
+    bt, nb = W.make_block_tables(lens, 1, 16, True, 19, spare_blocks=1)
+    cache = B.PagedKV(cfg, nb)
+    cache.k[0], cache.v[0] = W.dense_to_paged(Ks[0], bt, nb, 16), W.dense_to_paged(Vs[0], bt, nb, 16)
+    seq = torch.tensor([0] * 3 + [1] * 5 + [2] * 4, dtype=torch.int32)
+    pos = torch.tensor([38, 39, 40] + [-100, -1, -2 ** 31, -33, -7] + [67, 68, 69, 70], dtype=torch.int32)
+    q = torch.randn(12, 2, 64, generator=torch.Generator().manual_seed(19))
+    out = torch.zeros(12, 2, 64, device="cuda")
+    batch = B.make_batch(None, pos.cuda(), bt.cuda(), 71, seq.cuda())
+    B.ee_paged_attention_decode(B.make_desc(cfg), cache, 1, q.cuda(), batch, out)
+    torch.cuda.synchronize()
+    for r in (0, 1, 2, 8, 9, 10, 11):
+        s_, n = int(seq[r]), int(pos[r]) + 1
+        want = O.attention_decode(q[r].to(F64), Ks[0][s_, :n].cpu(), Vs[0][s_, :n].cpu())
+        assert_close_scaled(out[r].cpu(), want, tol_of(cfg), f"row {r}")
+
+
 def test_attention_single_sequence_and_sequential_blocks():
     run_attention(cfg_of("bf16", 128, 2), [300], seed=12, shuffled=False)
     run_attention(cfg_of("fp32", 64, 4), [47], seed=13, shuffled=False)
