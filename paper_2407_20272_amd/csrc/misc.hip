@@ -346,7 +346,7 @@ __global__ __launch_bounds__(256) void head_decide_f32_kernel(const float* logit
   const float* z = logits + (size_t)m * vocab;
   for (int v = threadIdx.x; v < vocab; v += 256) {
     const float x = z[v];
-    if (x > s.zmax || s.idx == 0x7fffffff) {   // strict: the lowest index wins among equals
+    if (x > s.zmax || s.idx == STAT_NO_INDEX) {   // strict: the lowest index wins among equals
       s.z2 = fmaxf(s.z2, s.zmax);
       s.zmax = x;
       s.idx = v;

@@ -347,6 +347,25 @@ def test_per_sequence_compaction_across_chunk_boundaries(exit_every):
         assert stats["L"] == want
 
 
+@pytest.mark.parametrize("heads", [0, 2])
+def test_token_of_a_sequence_of_nan_among_compacted_rows(heads):
+    """A sequence whose embedding is NaN among 200 (two row chunks; with exits of their own the rows are compacted): its
+    token stays inside the vocabulary and the others' tokens are those of the batch without it."""
+    cfg = compactable_bf16(batch=200).with_(n_layers=3)
+    w = W.make_weights(cfg, seed=46, gain_jitter=0.1)
+    w["embed"][7] = float("nan")
+    lens = torch.full((200,), 3, dtype=torch.int32)
+    run = HipRun(cfg, w, lens, 2, seed=46)
+    tokens = torch.arange(200, dtype=torch.int32) + 8
+    forced = torch.arange(200) % 2 + 2 if heads else None
+    want = run.step(tokens, lens.long(), 2.0, forced=forced, heads=heads)[0]
+    tokens[150] = 7
+    got = run.step(tokens, lens.long(), 2.0, forced=forced, heads=heads)[0]
+    assert 0 <= int(got[150]) < cfg.vocab
+    keep = torch.arange(200) != 150
+    assert torch.equal(got[keep], want[keep])
+
+
 @pytest.mark.parametrize("heads", [1, 2])
 def test_batch_of_one_and_prompts_ending_on_block_boundaries(heads):
     """Degenerate sizes: a single sequence, and prompts whose next position opens a new 16-token block."""

@@ -392,6 +392,33 @@ def test_exit_check_ties_go_to_the_lowest_index(batch):
     assert (argmax < 640).all() and (argmax % 64 < 16).all() and (conf == 0).all()
 
 
+@pytest.mark.parametrize("dtype,batch,vocab", [
+    ("bf16", 5, 1280), ("bf16", 40, 1280), ("bf16", 40, 1312), ("bf16", 100, 1280), ("bf16", 100, 8448),   # one tile a record
+    ("bf16", 200, 1280), ("bf16", 450, 1280), ("bf16", 450, 8448),                                         # two
+    ("fp32", 5, 130), ("fp32", 5, 514)])
+def test_exit_check_of_a_row_of_nan(dtype, batch, vocab):
+    """A hidden state of NaN (what attention leaves for a sequence of garbage) has no largest logit, but its arg max stays
+    inside the vocabulary, in each form of the projection and its epilogue, and the rows beside it do not change a bit."""
+    cfg = cfg_of(dtype, 64, 4, n_layers=4, vocab=vocab, logit_scale=2.0, batch=batch, tied_head=False)
+    model = B.DeviceModel(cfg, W.make_weights(cfg, seed=24, gain_jitter=0.2))
+    ws = B.Workspace(model.desc, batch, 16)
+    hidden = torch.randn(batch, cfg.d_model, generator=torch.Generator().manual_seed(24)).mul_(3.0).cuda()
+    bad = torch.tensor([1, batch - 1], device="cuda")
+    z = lambda *s: torch.zeros(*s, dtype=torch.int32, device="cuda")  # noqa: E731
+    got = []
+    for nan in (False, True):
+        if nan:
+            hidden[bad] = float("nan")
+        argmax, conf = z(batch) - 1, torch.zeros(batch, device="cuda")
+        B.ee_exit_check(model, 2, hidden, 2.0, None, z(batch), z(batch), z(1), z(1), z(1), argmax, conf, ws)
+        torch.cuda.synchronize()
+        got.append((argmax, conf))
+    assert (got[1][0] >= 0).all() and (got[1][0] < vocab).all(), got[1][0][bad]
+    good = torch.ones(batch, dtype=torch.bool, device="cuda")
+    good[bad] = False
+    assert got[0][0][good].equal(got[1][0][good]) and got[0][1][good].equal(got[1][1][good])
+
+
 def test_exit_check_llama7b_width():
     """LM head of the 7B-shaped workload (vocab 32000 x d 4096, batch 32): every row's confidence and arg max."""
     cfg = W.reduced(L7B, n_layers=2, d_ffn=256)
