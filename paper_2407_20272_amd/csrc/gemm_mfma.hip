@@ -512,7 +512,8 @@ struct TiledLds {
 };
 
 template <int MT, int NTW, class Epi, bool FILL>
-__device__ __forceinline__ void tiled_body(GemmShape g, Epi e, const Pred& pred, const FillCtl& fc, TiledLds<MT>& s) {
+__global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pred pred, FillCtl fc) {
+  __shared__ TiledLds<MT> s;
   constexpr int XR = UT * MT / NW;   // activation tiles each wavefront stages per group
   static_assert(UT * MT % NW == 0, "stage must split evenly over the wavefronts");
 
@@ -695,25 +696,6 @@ __device__ __forceinline__ void tiled_body(GemmShape g, Epi e, const Pred& pred,
     for (int t = 0; t < NTW; ++t)
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) finish_from_registers(acc[t][mt], nt0 + t, chunk * MT + mt, M_eff, ksl, g, e, lane);
-  }
-}
-
-template <int MT, int NTW, class Epi, bool FILL>
-__global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pred pred, FillCtl fc) {
-  __shared__ TiledLds<MT> s;
-  tiled_body<MT, NTW, Epi, FILL>(g, e, pred, fc, s);
-}
-
-// LM head of a compacted operand, whose working row chunks only the device knows: one chunk needs a workgroup per four tiles
-// to fill the chip, from two on two tiles per wavefront are faster, as they are without a row map (7B, both chunks of 256
-// rows: 93 -> 80 us; the workgroups that the second form leaves over return at once).
-__global__ __launch_bounds__(256) void gemm_tiled_lm_rows_kernel(GemmShape g, LmEpi e, Pred pred) {
-  __shared__ TiledLds<4> s;
-  if (g.n_rows_dev[0] > 128) {
-    g.keep_chunks = 0;
-    tiled_body<4, 2, LmEpi, false>(g, e, pred, FillCtl{}, s);
-  } else {
-    tiled_body<4, 1, LmEpi, false>(g, e, pred, FillCtl{}, s);
   }
 }
 
@@ -970,12 +952,6 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
       }
     }
     dim3 grid((groups + 7) / 8 * 8 * chunks * ksplit, 1, nz);
-    if constexpr (std::is_same<Epi, LmEpi>::value) {
-      if (g.n_rows_dev && chunks >= 2 && g.n_tiles % (2 * NW) == 0) {
-        hipLaunchKernelGGL(gemm_tiled_lm_rows_kernel, grid, block, 0, st, g4, e, pred);
-        return;
-      }
-    }
     hipLaunchKernelGGL((gemm_tiled_kernel<4, 1, Epi, FILL>), grid, block, 0, st, g4, e, pred, fc);
     return;
   }
