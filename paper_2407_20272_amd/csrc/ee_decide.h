@@ -27,6 +27,19 @@ __device__ inline void decide_row(const IterState& s, int m, int B, int layer, f
   }
 }
 
+// Did layer `layer` run?  It did if the batch has not left, or left at that very layer or later.  The launch that takes the
+// layer's decision raises `done` itself, so the live flag alone would tell the workgroups (and wavefronts) that read it late
+// to leave out rows accepted at an earlier layer, whose tokens come from this one.  A `done` raised by this launch comes with
+// batch_exit_layer == layer or, not yet visible, its initial n_layers; one raised at an earlier layer with that layer's
+// number, both visible since an earlier launch.  So every reader of the launch gets the same answer, whenever it reads.
+__device__ inline bool layer_ran(const IterState& s, int layer) {
+  return ctl_load(s.done) == 0 || ctl_load(s.batch_exit_layer) >= layer;
+}
+// Whether a launch that takes layer `layer`'s decision has nothing to do (layer 0, the final token selection, raises nothing).
+__device__ inline bool decision_skip(const Pred& pred, const IterState& s, int layer) {
+  return layer > 0 && pred.flag ? !layer_ran(s, layer) : pred_skip(pred);
+}
+
 // Confidence and arg max of row m from its softmax statistics, then the status rule.  One thread.
 __device__ inline void decide_from_stat(const CombineArgs& a, int m, const HeadStat& s) {
   if (a.argmax_out) a.argmax_out[m] = s.idx;

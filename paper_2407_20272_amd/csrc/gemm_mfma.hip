@@ -250,17 +250,13 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred
 
   int bx = blockIdx.x;
   if constexpr (std::is_same<Epi, QkvEpi>::value && !FILL) {
-    // Leading workgroups: the exit decision of the previous layer, one row each.  That layer ran if the batch
-    // has not left, or left at that very layer or later (the words may already show a sibling's update of this
-    // launch; `done` set at an earlier layer comes with a smaller batch exit layer, both visible since an earlier
-    // launch).  The projection's own workgroups apply the SAME rule instead of the live flag, so every workgroup of
-    // the launch takes the same branch whatever the interleaving: the projection of the layer after the batch exit
-    // layer always runs (what it caches is what KV filling caches there anyway), and a tile that two workgroups
-    // share is never left half done.
+    // Leading workgroups: the exit decision of the previous layer, one row each.  The projection's own workgroups apply
+    // the SAME rule (layer_ran) instead of the live flag, so every workgroup of the launch takes the same branch whatever
+    // the interleaving: the projection of the layer after the batch exit layer always runs (what it caches is what KV
+    // filling caches there anyway), and a tile that two workgroups share is never left half done.
     if (cj.n_wg) {
       const IterState& cs = cj.kind == 1 ? cj.a.s : cj.d.s;
-      const int decided_layer = cj.kind == 1 ? cj.a.layer : cj.d.layer;
-      const bool ran = ctl_load(cs.done) == 0 || ctl_load(cs.batch_exit_layer) >= decided_layer;
+      const bool ran = layer_ran(cs, cj.kind == 1 ? cj.a.layer : cj.d.layer);
       if (bx < cj.n_wg) {
         if (cj.kind == 1) {
           if (bx < cj.a.B && ran) combine_row(cj.a, bx, reinterpret_cast<float4*>(&s.red[0][0][0]));

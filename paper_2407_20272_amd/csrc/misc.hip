@@ -303,7 +303,7 @@ __device__ inline void copy_row(const float* src, float* dst, int m, int d) {
 
 // fp32 path: the three sums a one-dot-product confidence measure needs and the decision, one workgroup per row.
 __global__ __launch_bounds__(256) void measure_decide_f32_kernel(const float* h, float* other, int per_row, DecideArgs a, Pred pred) {
-  if (pred_skip(pred)) return;
+  if (decision_skip(pred, a.s, a.layer)) return;
   const int m = blockIdx.x, d = a.d;
   const float* hp = h + (size_t)m * d;
   float* op = per_row ? other + (size_t)m * d : other;
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(256) void head_decide_f32_kernel(const float* logit
                                                               float* dst, int d) {
   const int m = blockIdx.x;
   copy_row(src, dst, m, d);
-  if (pred_skip(pred)) return;
+  if (decision_skip(pred, a.s, a.layer)) return;
   if (a.left && ctl_load(a.left + m) != 0) return;   // left at an earlier layer: its token and exit layer stand
   // largest logit with its index and the runner-up first, the exponentials relative to the wavefront's largest after
   HeadStat s = stat_empty();
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(256) void head_decide_f32_kernel(const float* logit
 // layer == 0: final token selection only.
 // ---------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, Pred pred) {
-  if (pred_skip(pred)) return;
+  if (decision_skip(pred, a.s, a.layer)) return;
   __shared__ float4 red[256];
   combine_row(a, blockIdx.x, red);
 }
@@ -393,7 +393,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, Pred pred) 
 __global__ __launch_bounds__(256) void combine_copy_kernel(CombineArgs a, Pred pred, const float* src, float* dst, int d) {
   const int m = blockIdx.x;
   copy_row(src, dst, m, d);
-  if (pred_skip(pred)) return;
+  if (decision_skip(pred, a.s, a.layer)) return;
   __shared__ float4 red[256];
   combine_row(a, m, red);
 }
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(256) void compact_kernel(const int32_t* status, int
 
 // One thread per row: confidence from one dot product (hidden states similarity, dedicated classifier).
 __global__ __launch_bounds__(256) void decide_kernel(DecideArgs a, Pred pred) {
-  if (pred_skip(pred)) return;
+  if (decision_skip(pred, a.s, a.layer)) return;
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= a.B) return;
   decide_from_dot(a, m);

@@ -366,6 +366,28 @@ def test_token_of_a_sequence_of_nan_among_compacted_rows(heads):
     assert torch.equal(got[keep], want[keep])
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_tokens_of_sequences_accepted_before_the_batch_leaves(dtype):
+    """Algorithm 1 takes every token from the hidden state at output_layer.  5000 sequences (more than the chip holds in one
+    round of the launch that takes a decision), all accepted at layer 1 but the first, whose acceptance at layer 2 ends
+    the iteration while later rows' workgroups have not started: their tokens are those of a batch accepted at layer 2."""
+    base = TINY if dtype == "fp32" else L7B
+    cfg = W.reduced(base, n_layers=3, d_model=128, n_heads=2, head_dim=64, d_ffn=128, vocab=256, batch=5000, prompt_len=1,
+                    min_prompt_len=1, weight_std=0.1, tied_head=False)
+    lens = torch.ones(5000, dtype=torch.int32)
+    run = HipRun(cfg, W.make_weights(cfg, seed=49, gain_jitter=0.1), lens, 1, seed=49)
+    tokens = torch.randint(0, 256, (5000,), generator=torch.Generator().manual_seed(49), dtype=torch.int32)
+    got = {}
+    for name, first, others in (("1", 1, 1), ("2", 2, 2), ("first at 2", 2, 1)):
+        forced = torch.full((5000,), others, dtype=torch.int32)
+        forced[0] = first
+        tok, exits, L, _, _ = run.step(tokens, lens.long(), 2.0, forced=forced)
+        assert torch.equal(exits, forced) and L == first
+        got[name] = tok
+    assert (got["1"] != got["2"]).sum() > 1000, "the two layers have to disagree for the comparison to say anything"
+    assert torch.equal(got["first at 2"], got["2"])
+
+
 @pytest.mark.parametrize("heads", [1, 2])
 def test_batch_of_one_and_prompts_ending_on_block_boundaries(heads):
     """Degenerate sizes: a single sequence, and prompts whose next position opens a new 16-token block."""
