@@ -542,6 +542,57 @@ __device__ inline void read_tr(const unsigned (&at)[2], s16x4_t (&p)[2][2]) {
       : "memory");
 }
 
+// The same rows one at a time, a wavefront each, every row over its own positions alone: for workgroups that met an Inf or NaN
+// (see the end of the walk below).  64 scores at a time, a token per lane; then a channel or two per lane.
+template <int DH, bool OUT_XT>
+__device__ inline void prompt_rows_alone(const AttnArgs& a, int row0, int nrows, int head, int wave, int lane) {
+  constexpr int CPL = DH / 64;   // channels per lane
+  const float sc = 1.4426950408889634f / sqrtf((float)DH);
+  const size_t block_elems = (size_t)a.n_heads * 16 * DH;
+  const bf16_t* kpool = reinterpret_cast<const bf16_t*>(a.k_pool) + (size_t)head * 16 * DH;
+  const bf16_t* vpool = reinterpret_cast<const bf16_t*>(a.v_pool) + (size_t)head * 16 * DH;
+  for (int row = row0 + wave; row < row0 + nrows; row += PW) {
+    const int32_t* table = a.block_tables + (size_t)safe_row(a.row_table[row], a.B) * a.max_blocks;
+    const int npos = max(0, min(a.context_lens[row], a.max_blocks * 16 - 1) + 1);
+    const float* q = a.q + ((size_t)row * a.n_heads + head) * DH;
+    float m = NEG_BIG, l = 0.0f, acc[CPL];
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) acc[i] = 0.0f;
+    for (int t0 = 0; t0 < npos; t0 += 64) {
+      const int n = min(64, npos - t0), t = t0 + min(lane, n - 1);
+      const size_t at = (size_t)safe_block(table[t >> 4], a.num_blocks) * block_elems + (size_t)(t & 15) * DH;
+      float z = 0.0f;
+#pragma unroll 8
+      for (int c = 0; c < DH; ++c) z = fmaf(q[c], (float)kpool[at + c], z);
+      z = lane < n ? z * sc : NEG_BIG;
+      float mx = fmaxf(m, z);
+#pragma unroll
+      for (int x = 1; x < 64; x <<= 1) mx = fmaxf(mx, __shfl_xor(mx, x));
+      const float alpha = __builtin_amdgcn_exp2f(m - mx), p = lane < n ? __builtin_amdgcn_exp2f(z - mx) : 0.0f;
+      float sum = p;
+#pragma unroll
+      for (int x = 1; x < 64; x <<= 1) sum += __shfl_xor(sum, x);
+      m = mx;
+      l = l * alpha + sum;
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) acc[i] *= alpha;
+      for (int j = 0; j < n; ++j) {
+        const float pj = __shfl(p, j);
+        const bf16_t* v = vpool + (size_t)__shfl((unsigned long long)at, j) + lane * CPL;
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) acc[i] = fmaf(pj, (float)v[i], acc[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      const int col = head * DH + lane * CPL + i;
+      const float r = acc[i] * (1.0f / l);
+      if constexpr (OUT_XT) reinterpret_cast<bf16_t*>(a.out)[xt_index(row, col, a.n_heads * DH)] = (bf16_t)r;
+      else reinterpret_cast<float*>(a.out)[(size_t)row * a.n_heads * DH + col] = r;
+    }
+  }
+}
+
 template <int DH>
 constexpr int prompt_lds_bytes() { return PW * 2 * 32 * DH * 2; }
 
@@ -558,7 +609,7 @@ __global__ __launch_bounds__(PW * 64) void attn_prompt_kernel(AttnArgs a, int R,
   __shared__ int s_first[PROMPT_ROWS + 1];                        // first step of every run, and their total
   __shared__ int s_seq[PROMPT_ROWS], s_ctx[PROMPT_ROWS], s_rows[PROMPT_ROWS];   // of every run: sequence, positions, begin | end << 8
   __shared__ float sm[PW][32], sl[PW][32];
-  __shared__ int s_meet[PW];
+  __shared__ int s_meet[PW], s_alone;
   if (pred_skip(pred)) return;
 
   const int head = blockIdx.x, row0 = blockIdx.y * R;
@@ -625,6 +676,7 @@ __global__ __launch_bounds__(PW * 64) void attn_prompt_kernel(AttnArgs a, int R,
       }
       if (lane == 63) s_first[__popcll(bal)] = upto;
       if (lane < PW) s_meet[lane] = 0;
+      if (lane == 0) s_alone = 0;
     }
     return __popcll(bal);
   }();
@@ -867,7 +919,21 @@ __global__ __launch_bounds__(PW * 64) void attn_prompt_kernel(AttnArgs a, int R,
   else
     walk(std::false_type{});
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the end still target LDS
+  // A row takes part in the steps of the group's other runs, and in what is after its own position, with probabilities of 0.
+  // That leaves its sums alone unless a V of the step is not finite: 0 times Inf is NaN, and what one sequence cached must
+  // not reach another.  So where a row's sums are not finite, the rows are done again, each by itself.  (The look at the sums
+  // costs 0 to 0.5 us a launch; leaving such rows out of each step needs registers the walk does not have.)
+  float zero = 0.0f;
+#pragma unroll
+  for (int d = 0; d < CT; ++d)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) zero = fmaf(o[d][i], 0.0f, zero);   // NaN if one of them is not finite
+  if (row_ok && zero != 0.0f) s_alone = 1;
   __syncthreads();                                   // every tile has been read: the space now holds the partial outputs
+  if (__builtin_amdgcn_readfirstlane(s_alone)) {
+    prompt_rows_alone<DH, OUT_XT>(a, row0, nrows, head, wave, lane);
+    return;
+  }
 
   // the two lanes of a row hold partial sums of the same maximum; then the slices are added in slice order
   l_run += __shfl_xor(l_run, 32);

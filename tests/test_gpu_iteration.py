@@ -6,6 +6,7 @@ import os
 import pytest
 import torch
 
+from paper_2407_20272_amd import binding as B
 from paper_2407_20272_amd import workloads as W
 from gpu_harness import HipRun, lockstep
 
@@ -386,6 +387,31 @@ def test_tokens_of_sequences_accepted_before_the_batch_leaves(dtype):
         got[name] = tok
     assert (got["1"] != got["2"]).sum() > 1000, "the two layers have to disagree for the comparison to say anything"
     assert torch.equal(got["first at 2"], got["2"])
+
+
+def test_prompt_chunk_beside_a_sequence_of_nan():
+    """A chunk of three prompts, the tokens of one embedded as NaN: the rows of the others, in the same groups of rows, end
+    with the hidden states they have without it, to the rounding of a bf16 layer."""
+    cfg = small_bf16(n_layers=2, batch=3, prompt_len=20, min_prompt_len=20)
+    w = W.make_weights(cfg, seed=48, gain_jitter=0.1)
+    w["embed"][7] = float("nan")
+    run = HipRun(cfg, w, torch.full((3,), 20, dtype=torch.int32), 1, seed=48)
+    ws = B.Workspace(run.model.desc, 60, 21)
+    seq = torch.arange(3, dtype=torch.int32).repeat_interleave(20).cuda()
+    pos = torch.arange(20, dtype=torch.int32).repeat(3).cuda()
+    tokens = torch.randint(8, cfg.vocab, (60,), generator=torch.Generator().manual_seed(48), dtype=torch.int32).cuda()
+    z = lambda *n: torch.zeros(*n, dtype=torch.int32, device="cuda")  # noqa: E731
+    got = []
+    for nan in (False, True):
+        if nan:
+            tokens[20:40] = 7
+        hidden = torch.zeros(60, cfg.d_model, device="cuda")
+        batch = B.make_batch(tokens, pos, run.bt_dev, 21, row_table=seq)
+        B.ee_decode_iteration(run.model, run.cache, batch, 2.0, None, B.EE_EXIT_NONE, z(60), z(60), z(1), None, hidden, ws)
+        torch.cuda.synchronize()
+        got.append(torch.cat([hidden[:20], hidden[40:]]).cpu())
+    assert torch.isfinite(got[1]).all()
+    assert ((got[1] - got[0]).norm(dim=1) <= 2e-2 * got[0].norm(dim=1)).all()
 
 
 @pytest.mark.parametrize("heads", [1, 2])

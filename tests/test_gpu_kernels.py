@@ -197,6 +197,48 @@ def test_attention_prompt_rows_run_structure(dh, n_heads, runs):
     assert err <= 2e-5, f"relative error of a row: {err}"
 
 
+@pytest.mark.parametrize("dh,n_heads,runs,bad_seq,bad_pos", [
+    (128, 2, [(3, 20), (1, 40), (2, 15), (4, 61)], 1, 7),                          # four rows a workgroup
+    (64, 40, [(20, 0), (0, 0), (30, 70), (60, 5)], 2, 80),                          # one group of 32, runs straddle workgroups
+    (128, 40, [(40, 300), (20, None), (50, 64), (100, 0)], 0, 0),                   # two groups, a run of no positions between
+    (64, 32, [(250, 90), (6, None), (240, 0)], 2, 239),                             # two groups, the last position of a prompt
+])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_attention_prompt_rows_beside_a_sequence_that_is_not_finite(dh, n_heads, runs, bad_seq, bad_pos, value):
+    """One cached V of one sequence is Inf or NaN: rows that do not attend that position (other sequences' rows in the same
+    group of 32, and the sequence's own earlier ones) keep their results, within the bound of the test above; rows that attend
+    it show it in that channel.  A run of garbage (negative) contexts in the middle has no result and no steps."""
+    cfg = cfg_of("bf16", dh, n_heads, n_layers=1).with_(batch=len(runs), shuffled_blocks=True)
+    lens = torch.tensor([0 if b is None else max(b + n - 1, 0) for n, b in runs], dtype=torch.int32)
+    Lmax = int(lens.max()) + 1
+    Ks, Vs = W.make_dense_kv(cfg, lens + 1, Lmax, seed=28, device="cuda")
+    Vs[0][bad_seq, bad_pos, n_heads - 1, 5] = value
+    bt, nb = W.make_block_tables(lens, 1, 16, True, 28, spare_blocks=2)
+    cache = B.PagedKV(cfg, nb)
+    cache.k[0] = W.dense_to_paged(Ks[0], bt, nb, 16)
+    cache.v[0] = W.dense_to_paged(Vs[0], bt, nb, 16)
+    poison_unwritten_slots(cache, bt, lens + 1)
+    rows = [(s, -5 if b is None else b + i) for s, (n, b) in enumerate(runs) for i in range(n)]
+    seq, pos = (torch.tensor(x, dtype=torch.int32) for x in zip(*rows))
+    q = torch.randn(len(rows), n_heads, dh, generator=torch.Generator().manual_seed(28)) * 1.3
+    out = torch.zeros(len(rows), n_heads, dh, device="cuda")
+    batch = B.make_batch(None, pos.cuda(), bt.cuda(), Lmax, seq.cuda())
+    B.ee_paged_attention_decode(B.make_desc(cfg), cache, 1, q.cuda(), batch, out)
+    torch.cuda.synchronize()
+    out = out.cpu().to(F64)
+    for r, (s, p) in enumerate(rows):
+        if p < 0:
+            continue
+        K, V = (x[0][s, :p + 1].cpu().to(F64).permute(1, 0, 2) for x in (Ks, Vs))     # [head][position][channel]
+        w = (K @ q[r].to(F64)[:, :, None] / math.sqrt(dh)).softmax(1)
+        want = (w * V).sum(1)
+        if s == bad_seq and p >= bad_pos:
+            assert not math.isfinite(float(out[r, n_heads - 1, 5]))
+            want[n_heads - 1, 5] = out[r, n_heads - 1, 5] = 0.0
+        err = ((out[r] - want).norm() / want.norm()).item()
+        assert err <= 2e-5, f"row {r} (sequence {s}, position {p}): relative error {err}"
+
+
 def test_attention_prompt_rows_beside_a_negative_context():
     """A sequence whose context lengths are garbage (negative) has no result, but its neighbours keep theirs."""
     cfg = cfg_of("bf16", 64, 2, n_layers=1).with_(batch=3, shuffled_blocks=True)
