@@ -1002,42 +1002,48 @@ template <int DH, bool OUT_XT>
 bool prompt_lds_allowed() {
   static std::atomic<unsigned long long> asked{0};
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
+  if (hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
   const unsigned long long bit = 1ull << (dev & 63);
   if (asked.load(std::memory_order_relaxed) & bit) return true;
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prompt_kernel<DH, OUT_XT>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          prompt_lds_bytes<DH>()) != hipSuccess)
+                          prompt_lds_bytes<DH>()) != hipSuccess) {
+    (void)hipGetLastError();   // not the call's error: another kernel takes the rows
     return false;
+  }
   asked.fetch_or(bit, std::memory_order_relaxed);
   return true;
 }
 
+// false: the runtime refuses the kernel its LDS, nothing has been enqueued.
 template <int DH, bool OUT_XT>
-int launch_prompt(const AttnArgs& a, Pred pred, hipStream_t st) {
-  if (!prompt_lds_allowed<DH, OUT_XT>()) EE_FAIL(EE_ERR_HIP, "attention: %d bytes of LDS refused", prompt_lds_bytes<DH>());
+bool launch_prompt(const AttnArgs& a, Pred pred, hipStream_t st) {
+  if (!prompt_lds_allowed<DH, OUT_XT>()) return false;
   const int R = prompt_rows(a.B, a.n_heads);
   hipLaunchKernelGGL((attn_prompt_kernel<DH, OUT_XT>), dim3(a.n_heads, (a.B + R - 1) / R), dim3(PW * 64), prompt_lds_bytes<DH>(), st,
                      a, R, pred);
-  return EE_OK;
+  return true;
 }
 
 // Four rows per workgroup measured best at the 7B shape (eight: 300 registers, one wavefront per SIMD, slower).
 constexpr int ROWS_PER_GROUP = 4;
 
 template <class T, int DH>
-int launch_t(const AttnArgs& a, Pred pred, hipStream_t st) {
+void launch_t(const AttnArgs& a, Pred pred, hipStream_t st) {
   dim3 block(256);
   const size_t lds = (size_t)a.max_blocks * sizeof(int32_t);
   if (a.row_table) {   // rows share sequences: stream every sequence's K/V once per group of rows
     if constexpr (std::is_same<T, bf16_t>::value) {
-      return a.out_xt ? launch_prompt<DH, true>(a, pred, st) : launch_prompt<DH, false>(a, pred, st);
+      if (a.out_xt ? launch_prompt<DH, true>(a, pred, st) : launch_prompt<DH, false>(a, pred, st)) return;
     }
     dim3 grid(a.n_heads, (a.B + ROWS_PER_GROUP - 1) / ROWS_PER_GROUP);
     if (a.out_xt)
       hipLaunchKernelGGL((attn_rows_kernel<T, DH, ROWS_PER_GROUP, true>), grid, block, lds, st, a, pred);
     else
       hipLaunchKernelGGL((attn_rows_kernel<T, DH, ROWS_PER_GROUP, false>), grid, block, lds, st, a, pred);
-    return EE_OK;
+    return;
   }
   if (a.split_ws && a.split_parts > 1) {
     // the output form only matters to the merge launch; the parts always leave as floats
@@ -1048,14 +1054,13 @@ int launch_t(const AttnArgs& a, Pred pred, hipStream_t st) {
       hipLaunchKernelGGL((attn_merge_kernel<DH, true>), gridm, dim3(DH), 0, st, a, pred);
     else
       hipLaunchKernelGGL((attn_merge_kernel<DH, false>), gridm, dim3(DH), 0, st, a, pred);
-    return EE_OK;
+    return;
   }
   dim3 grid(a.n_heads, a.B);
   if (a.out_xt)
     hipLaunchKernelGGL((attn_decode_kernel<T, DH, true, false>), grid, block, lds, st, a, pred);
   else
     hipLaunchKernelGGL((attn_decode_kernel<T, DH, false, false>), grid, block, lds, st, a, pred);
-  return EE_OK;
 }
 
 }  // namespace
@@ -1082,14 +1087,15 @@ int launch_attention(const AttnArgs& a, int dtype, Pred pred, hipStream_t st) {
     EE_FAIL(EE_ERR_UNSUPPORTED, "attention: max_blocks %d outside 1..%d", a.max_blocks, TABLE_LDS_MAX);
   if (a.out_pos && a.row_table) EE_FAIL(EE_ERR_UNSUPPORTED, "attention: out_pos does not go with row_table");
   if (dtype == EE_FP32) {
-    if (a.head_dim == 64) return launch_t<float, 64>(a, pred, st);
-    else if (a.head_dim == 128) return launch_t<float, 128>(a, pred, st);
+    if (a.head_dim == 64) launch_t<float, 64>(a, pred, st);
+    else if (a.head_dim == 128) launch_t<float, 128>(a, pred, st);
     else EE_FAIL(EE_ERR_UNSUPPORTED, "attention: head_dim %d not supported for fp32 (64 or 128)", a.head_dim);
   } else {
-    if (a.head_dim == 64) return launch_t<bf16_t, 64>(a, pred, st);
-    else if (a.head_dim == 128) return launch_t<bf16_t, 128>(a, pred, st);
+    if (a.head_dim == 64) launch_t<bf16_t, 64>(a, pred, st);
+    else if (a.head_dim == 128) launch_t<bf16_t, 128>(a, pred, st);
     else EE_FAIL(EE_ERR_UNSUPPORTED, "attention: head_dim %d not supported for bf16 (64 or 128)", a.head_dim);
   }
+  return EE_OK;
 }
 
 }  // namespace ee

@@ -1,6 +1,9 @@
 """Per-entry-point parity on the GPU: ee_paged_attention_decode, ee_exit_check, ee_kv_fill against the CPU oracle
 on seeded tensors, at sizes that span several tiles and ragged tails, plus the degenerate cases."""
 import math
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -237,6 +240,20 @@ def test_attention_prompt_rows_beside_a_sequence_that_is_not_finite(dh, n_heads,
             want[n_heads - 1, 5] = out[r, n_heads - 1, 5] = 0.0
         err = ((out[r] - want).norm() / want.norm()).item()
         assert err <= 2e-5, f"row {r} (sequence {s}, position {p}): relative error {err}"
+
+
+def test_attention_prompt_rows_without_the_lds_of_the_matrix_core_kernel(tmp_path):
+    """The runtime refuses 128 KiB of LDS (a library loaded first into the process answers hipFuncSetAttribute so): the rows
+    take another kernel, within the same bound."""
+    src, so = tmp_path / "refuse.c", tmp_path / "refuse.so"
+    src.write_text("int refused; int hipFuncSetAttribute(const void* f, int a, int v) { (void)f; (void)a; (void)v; ++refused; return 1; }\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
+    code = ("import ctypes, sys; L = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL); sys.path[:0] = sys.argv[2:]; import test_gpu_kernels as T\n"
+            "T.test_attention_prompt_rows_run_structure(128, 2, [(1, 0), (3, 31), (1, 40), (2, 15)])\n"
+            "T.test_attention_prompt_rows_run_structure(64, 3, [(7, 300), (20, 5)])\n"
+            "assert ctypes.c_int.in_dll(L, 'refused').value >= 2\n")
+    here = os.path.dirname(os.path.abspath(__file__))
+    subprocess.run([sys.executable, "-c", code, str(so), here, os.path.dirname(here)], check=True, timeout=100)
 
 
 def test_attention_prompt_rows_beside_a_negative_context():

@@ -1,0 +1,91 @@
+"""What the host side enqueues when the runtime refuses something, without a GPU: a small C program brings its own
+hipLaunchKernel, hipFuncSetAttribute, .. (a program's symbols come before those of the libraries it loads), calls the library with
+made-up device pointers, which the host never follows, and prints every launch."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2407_20272_amd import binding as B
+from paper_2407_20272_amd import build
+
+PROGRAM = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+#include "ee_decode.h"
+
+typedef struct { unsigned x, y, z; } dim;
+static int refuse, pending;
+static dim grid, block;
+static size_t lds;
+
+int hipGetDevice(int* d) { *d = 0; return 0; }
+int hipGetLastError(void) { int e = pending; pending = 0; return e; }
+int hipFuncSetAttribute(const void* f, int attr, int value) {
+  (void)f; (void)attr;
+  if (refuse && value > 65536) return pending = 1;   /* like the runtime: the error also waits for hipGetLastError */
+  return 0;
+}
+int __hipPushCallConfiguration(dim g, dim b, size_t s, void* st) { (void)st; grid = g; block = b; lds = s; return 0; }
+int __hipPopCallConfiguration(dim* g, dim* b, size_t* s, void** st) { *g = grid; *b = block; *s = lds; *st = 0; return 0; }
+int hipLaunchKernel(const void* f, dim g, dim b, void** args, size_t s, void* st) {
+  (void)f; (void)args; (void)st;
+  printf("launch %u %u %u %u %zu\n", g.x, g.y, g.z, b.x, s);
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  void* p = (void*)0x10000;                          /* any aligned address */
+  const int B = atoi(argv[3]);
+  refuse = atoi(argv[2]);
+  ee_layer_weights w[2] = {{p, p, p, p, p, p}, {p, p, p, p, p, p}};
+  ee_model m = {{2, 256, 2, 128, 512, 1024, EE_BF16, 1e-5f, 1e4f, 1, 1.0f, 0}, p, p, p, w, 0, 0};
+  ee_kv_cache c = {p, p, 64, 16};
+  ee_batch b = {B, p, p, p, 20, 300, p};
+  const size_t n = ee_workspace_bytes(&m.desc, B, 300);
+  int rc;
+  if (!strcmp(argv[1], "iteration"))
+    rc = ee_decode_iteration(&m, &c, &b, 0, 0, EE_EXIT_NONE, p, p, p, 0, 0, p, n, 0);
+  else if (!strcmp(argv[1], "attention"))
+    rc = ee_paged_attention_decode(&m.desc, &c, 1, p, &b, p, 0, 0, 0);
+  else
+    rc = ee_exit_check(&m, 1, p, B, 0.5f, 0, p, p, p, p, p, 0, 0, p, n, 0);
+  printf("rc %d %s\n", rc, rc ? ee_last_error() : "");
+  fflush(stdout);
+  _Exit(argc < 0);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    B.lib()
+    d = tmp_path_factory.mktemp("host_launches")
+    src, exe = d / "program.c", d / "program"
+    src.write_text(PROGRAM)
+    subprocess.run(["gcc", "-O1", "-rdynamic", "-I" + os.path.join(build.ROOT, "include"), str(src), "-o", str(exe), B.LIB_PATH,
+                    "-Wl,-rpath-link,/opt/rocm/lib"], check=True, capture_output=True, text=True)
+
+    def run(*args):
+        out = subprocess.run([str(exe), *map(str, args)], check=True, capture_output=True, text=True, timeout=60).stdout.split("\n")
+        launches = [tuple(int(x) for x in line.split()[1:]) for line in out if line.startswith("launch")]
+        return launches, [line for line in out if line.startswith("rc")][0]
+
+    return run
+
+
+@pytest.mark.parametrize("call,refused_before", [("attention", 0), ("iteration", 2)])
+def test_prompt_attention_without_its_lds(program, call, refused_before):
+    """128 KiB of LDS refused: the call succeeds all the same, and four rows a workgroup over a block table in LDS take the
+    place of the matrix-core kernel; nothing else in the sequence of launches changes."""
+    rows = 30
+    want, rc = program(call, 0, rows)
+    assert rc.strip() == "rc 0"
+    prompt = [i for i, x in enumerate(want) if x[3:] == (512, 131072)]
+    assert prompt[0] == refused_before and len(prompt) == (1 if call == "attention" else 2)
+    got, rc = program(call, 1, rows)
+    assert rc.strip() == "rc 0"
+    for i in prompt:
+        want[i] = (2, (rows + 3) // 4, 1, 256, 20 * 4)
+    assert got == want
