@@ -883,9 +883,11 @@ AccPlan acc_plan(int M, int n_tiles, int K) {
 template <class Epi>
 bool ring_allowed() {
   static int ok = -1;
-  if (ok < 0)
+  if (ok < 0) {
     ok = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_kernel<Epi>), hipFuncAttributeMaxDynamicSharedMemorySize,
                              RING_LDS_BYTES) == hipSuccess;
+    if (!ok) (void)hipGetLastError();   // not the call's error: the tiled kernel takes the shape
+  }
   return ok > 0;
 }
 

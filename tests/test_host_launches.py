@@ -89,3 +89,12 @@ def test_prompt_attention_without_its_lds(program, call, refused_before):
     for i in prompt:
         want[i] = (2, (rows + 3) // 4, 1, 256, 20 * 4)
     assert got == want
+
+
+def test_exit_check_without_the_lds_of_the_ring_kernel(program):
+    """385 to 512 rows with 128 KiB of LDS refused: the tiled kernel's blocks of 128 rows, and no error left behind."""
+    want, rc = program("check", 0, 450)
+    assert rc.strip() == "rc 0" and [x[3:] for x in want] == [(512, 0), (256, 131072), (256, 0)]
+    got, rc = program("check", 1, 450)
+    assert rc.strip() == "rc 0"
+    assert got == [want[0], (8 * 4, 1, 1, 256, 0), want[2]]
