@@ -478,6 +478,14 @@ def test_exit_check_of_a_row_of_nan(dtype, batch, vocab):
     assert got[0][0][good].equal(got[1][0][good]) and got[0][1][good].equal(got[1][1][good])
 
 
+@pytest.mark.parametrize("batch,vocab", [(33, 64), (37, 66), (70, 1030)])
+def test_exit_check_fp32_several_row_blocks(batch, vocab):
+    """The float projections deal (four batch rows, eight weight rows) out to the workgroups in one list: fewer groups of weight
+    rows than XCDs, one more than a multiple, and a last block of few rows."""
+    cfg = cfg_of("fp32", 64, 4, n_layers=6, vocab=vocab, logit_scale=2.0, batch=batch)
+    run_exit_check(cfg, seed=60 + batch, layer=3, threshold=0.2, hidden_scale=3.0)
+
+
 def test_exit_check_llama7b_width():
     """LM head of the 7B-shaped workload (vocab 32000 x d 4096, batch 32): every row's confidence and arg max."""
     cfg = W.reduced(L7B, n_layers=2, d_ffn=256)
