@@ -344,8 +344,18 @@ __global__ __launch_bounds__(256) void head_decide_f32_kernel(const float* logit
   // largest logit with its index and the runner-up first, the exponentials relative to the wavefront's largest after
   HeadStat s = stat_empty();
   const float* z = logits + (size_t)m * vocab;
-  for (int v = threadIdx.x; v < vocab; v += 256) {
-    const float x = z[v];
+  constexpr int AHEAD = 8;   // loads in flight: one at a time a row of 32000 took 53 us, now 24
+  auto each = [&](auto take) {
+    for (int v0 = threadIdx.x; v0 < vocab; v0 += 256 * AHEAD) {
+      float x[AHEAD];
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) x[i] = z[min(v0 + 256 * i, vocab - 1)];
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i)
+        if (v0 + 256 * i < vocab) take(v0 + 256 * i, x[i]);
+    }
+  };
+  each([&](int v, float x) {
     if (x > s.zmax || s.idx == STAT_NO_INDEX) {   // strict: the lowest index wins among equals
       s.z2 = fmaxf(s.z2, s.zmax);
       s.zmax = x;
@@ -353,7 +363,7 @@ __global__ __launch_bounds__(256) void head_decide_f32_kernel(const float* logit
     } else {
       s.z2 = fmaxf(s.z2, x);
     }
-  }
+  });
 #pragma unroll
   for (int x = 1; x < 64; x <<= 1) {
     const float ob = __shfl_xor(s.zmax, x), o2 = __shfl_xor(s.z2, x);
@@ -365,7 +375,7 @@ __global__ __launch_bounds__(256) void head_decide_f32_kernel(const float* logit
       s.idx = oi;
     }
   }
-  for (int v = threadIdx.x; v < vocab; v += 256) s.sum += stat_exp(a.scale * (z[v] - s.zmax));
+  each([&](int, float x) { s.sum += stat_exp(a.scale * (x - s.zmax)); });
 #pragma unroll
   for (int x = 1; x < 64; x <<= 1) s.sum += __shfl_xor(s.sum, x);
   __shared__ float4 red[4];
