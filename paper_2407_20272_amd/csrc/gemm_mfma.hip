@@ -980,20 +980,29 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
       return;
     }
   }
-  // Two tiles per workgroup where they fill the chip in one round: QKV of one batch tile as 2 * split_tiles whole tiles with a
-  // half each (7B, 256 workgroups, 32 rows: 24.2 -> 22.7 us), else pairs of tiles on 129 to 256 workgroups (13B: 45 -> 38 us at
-  // 64 rows, 39 -> 31 at 32; 7B at 64 rows: 34 -> 31).
-  if constexpr (!FILL) {
-    const bool one_half = m_tiles == 1 && g.split_tiles && 3 * g.split_tiles == g.n_tiles && g.split_tiles > 96 && g.split_tiles <= 128;
-    const bool pairs = ACC ? ap.kind == 3 : m_tiles <= 2 && g.n_tiles % 2 == 0 && g.n_tiles > 256 && g.n_tiles <= 512;
-    if (one_half || pairs) {
+  // Two tiles per workgroup where they fill the chip in one round.
+  // QKV, two batch tiles: pairs on 129 to 256 workgroups (264 tiles: 24.4 -> 22.6 us, 384: 34 -> 31, 480: 45 -> 38).  One batch tile:
+  // up to 384 tiles 2 * split_tiles whole tiles with a half each (294 tiles: 20.5 -> 19.0, 384: 24.2 -> 22.7), beyond pairs (480:
+  // 39 -> 31); at 288 tiles and fewer the idle compute units cost more than the shared operand saves (pairs of 288: 19.1 -> 20.3,
+  // of 264: 17.4 -> 19.6).
+  // Gate/up whose tiles do not divide by four: two batch tiles only (258 to 506 tiles: 16.1 -> 15.9, 17.5 -> 16.5, 18.1 -> 17.4,
+  // 19.7 -> 19.6; one: 12.5 -> 13.4, 13.9 -> 14.5, 14.4 -> 14.9, 15.8 -> 17.7).  The LM head gains at neither (16 rows: 12.7 to 15.4 ->
+  // 14.0 to 18.1, 64 rows: 16.8 to 19.9 -> 17.0 to 20.9): its statistics follow each tile.
+  if constexpr (!FILL && !std::is_same<Epi, LmEpi>::value) {
+    constexpr bool QKV = std::is_same<Epi, QkvEpi>::value, GATE = std::is_same<Epi, GateUpEpi>::value;
+    const bool one_half = QKV && m_tiles == 1 && 3 * g.split_tiles == g.n_tiles && g.split_tiles > 96 && g.split_tiles <= 128;
+    const bool pairs = m_tiles <= 2 && g.n_tiles % 2 == 0 && g.n_tiles > (m_tiles == 1 ? 384 : 256) && g.n_tiles <= 512;
+    if (ACC ? ap.kind == 3 : one_half || (pairs && (QKV || m_tiles == 2))) {
       GemmShape g2 = g;
       if (!one_half) g2.split_tiles = 0;
       const dim3 grid2((one_half ? 2 * g.split_tiles : g.n_tiles / 2) + cj.n_wg, ACC ? ap.ksplit : 1, nz);
-      if (m_tiles == 1)
-        hipLaunchKernelGGL((gemm_mfma_kernel<1, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
-      else
-        hipLaunchKernelGGL((gemm_mfma_kernel<2, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
+      if constexpr (!GATE) {
+        if (m_tiles == 1) {
+          hipLaunchKernelGGL((gemm_mfma_kernel<1, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
+          return;
+        }
+      }
+      hipLaunchKernelGGL((gemm_mfma_kernel<2, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
       return;
     }
   }

@@ -315,7 +315,8 @@ def test_bf16_row_counts_with_a_short_last_chunk(batch, heads):
 
 @pytest.mark.parametrize("heads,dh,batch", [
     (25, 128, 7),      # QKV as 200 whole tiles with half a V tile each: the last 8 past the groups that are rearranged
-    (44, 64, 31),      # 264 tiles as 132 pairs (88 halves would leave units idle), one batch tile
+    (44, 64, 31),      # 264 tiles, one batch tile: too few for two tiles a workgroup
+    (49, 64, 31),      # 294: 196 whole tiles with half a V tile each, the fewest
     (22, 128, 33),     # the same in two batch tiles, the second of one row
     (33, 128, 64),     # 396 tiles as 198 pairs; output projection of 132 tiles: pairs, three slices of 88 steps
     (33, 128, 2),      # ... in one batch tile
