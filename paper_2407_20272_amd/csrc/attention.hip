@@ -1032,17 +1032,21 @@ constexpr int ROWS_PER_GROUP = 4;
 
 template <class T, int DH>
 void launch_t(const AttnArgs& a, Pred pred, hipStream_t st) {
+  constexpr bool BF16 = std::is_same<T, bf16_t>::value;   // (only bf16 results leave in operand order)
   dim3 block(256);
   const size_t lds = (size_t)a.max_blocks * sizeof(int32_t);
   if (a.row_table) {   // rows share sequences: stream every sequence's K/V once per group of rows
-    if constexpr (std::is_same<T, bf16_t>::value) {
+    if constexpr (BF16) {
       if (a.out_xt ? launch_prompt<DH, true>(a, pred, st) : launch_prompt<DH, false>(a, pred, st)) return;
     }
     dim3 grid(a.n_heads, (a.B + ROWS_PER_GROUP - 1) / ROWS_PER_GROUP);
-    if (a.out_xt)
-      hipLaunchKernelGGL((attn_rows_kernel<T, DH, ROWS_PER_GROUP, true>), grid, block, lds, st, a, pred);
-    else
-      hipLaunchKernelGGL((attn_rows_kernel<T, DH, ROWS_PER_GROUP, false>), grid, block, lds, st, a, pred);
+    if constexpr (BF16) {
+      if (a.out_xt) {
+        hipLaunchKernelGGL((attn_rows_kernel<T, DH, ROWS_PER_GROUP, true>), grid, block, lds, st, a, pred);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((attn_rows_kernel<T, DH, ROWS_PER_GROUP, false>), grid, block, lds, st, a, pred);
     return;
   }
   if (a.split_ws && a.split_parts > 1) {
@@ -1057,10 +1061,13 @@ void launch_t(const AttnArgs& a, Pred pred, hipStream_t st) {
     return;
   }
   dim3 grid(a.n_heads, a.B);
-  if (a.out_xt)
-    hipLaunchKernelGGL((attn_decode_kernel<T, DH, true, false>), grid, block, lds, st, a, pred);
-  else
-    hipLaunchKernelGGL((attn_decode_kernel<T, DH, false, false>), grid, block, lds, st, a, pred);
+  if constexpr (BF16) {
+    if (a.out_xt) {
+      hipLaunchKernelGGL((attn_decode_kernel<T, DH, true, false>), grid, block, lds, st, a, pred);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((attn_decode_kernel<T, DH, false, false>), grid, block, lds, st, a, pred);
 }
 
 }  // namespace

@@ -673,14 +673,16 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pre
     }
     __syncthreads();
   };
-  if (active && MT == 4 && g.keep_chunks > 0 && M_eff > (g.keep_chunks - 1) * MT * 32) {
-    main_loop(std::true_type{}, std::integral_constant<bool, MT == 4>{});
-  } else if (active) {
-    main_loop(std::true_type{}, std::false_type{});
-  } else {
+  if (!active) {
     main_loop(std::false_type{}, std::false_type{});
     return;       // nothing to finish; the epilogues below take no workgroup barrier
   }
+  // (only these are ever launched with keep_chunks > 0)
+  constexpr bool MAY_KEEP = MT == 4 && NTW == 1 && !std::is_same<Epi, AccEpi>::value;
+  if (MAY_KEEP && g.keep_chunks > 0 && M_eff > (g.keep_chunks - 1) * MT * 32)
+    main_loop(std::true_type{}, std::integral_constant<bool, MAY_KEEP>{});
+  else
+    main_loop(std::true_type{}, std::false_type{});
 
   // every wavefront finishes its own tiles from registers
   if constexpr (std::is_same<Epi, LmEpi>::value) {
