@@ -42,7 +42,7 @@ __device__ inline bool decision_skip(const Pred& pred, const IterState& s, int l
 
 // Confidence and arg max of row m from its softmax statistics, then the status rule.  One thread.
 __device__ inline void decide_from_stat(const CombineArgs& a, int m, const HeadStat& s) {
-  if (a.argmax_out) a.argmax_out[m] = s.idx;
+  if (a.argmax_out) a.argmax_out[m] = s.idx == STAT_NO_INDEX ? 0 : s.idx;   // a row of NaN: any token, but one of the vocabulary
   if (a.layer == 0) return;
   float conf = 1.0f / s.sum;                                          // largest softmax probability
   if (a.conf_mode == 1) conf = (1.0f - expf(a.scale * (s.z2 - s.zmax))) / s.sum;  // top-1 minus top-2

@@ -147,13 +147,11 @@ struct HeadStat {
 // exp of a non-positive argument for the softmax sums: the hardware's base-2 exponential (relative error about 1e-7;
 // the library routine costs several times the instructions, and an exit head evaluates one per logit and row)
 __device__ inline float stat_exp(float x) { return __expf(x); }
-constexpr int STAT_NO_INDEX = 0x7fffffff;
+constexpr int STAT_NO_INDEX = 0x7fffffff;   // no logit yet, or none that equals the largest: all of them NaN
 __device__ inline HeadStat stat_empty() { return {-INFINITY, 0.0f, -INFINITY, STAT_NO_INDEX}; }
-// A record of logits beats an empty one whatever its maximum is: where every logit is NaN no comparison holds, and the index
-// has to stay inside the vocabulary all the same.
 __device__ inline HeadStat stat_merge(const HeadStat& a, const HeadStat& b, float scale) {
   HeadStat o;
-  if (b.idx == STAT_NO_INDEX || (a.idx != STAT_NO_INDEX && (a.zmax > b.zmax || (a.zmax == b.zmax && a.idx < b.idx)))) {
+  if (a.zmax > b.zmax || (a.zmax == b.zmax && a.idx < b.idx)) {
     o.zmax = a.zmax;
     o.idx = a.idx;
     o.z2 = fmaxf(a.z2, b.zmax);

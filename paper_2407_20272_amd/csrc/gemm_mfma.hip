@@ -429,9 +429,8 @@ __device__ inline void finish_lm(Get acc, int nt, int mtile, int M_eff, const Ge
   const float other = __shfl_xor(lane_best, 32);
   z2 = fmaxf(fminf(lane_best, other), fmaxf(z2, __shfl_xor(z2, 32)));
   const float best = fmaxf(lane_best, other);
-  // number of the lane's first logit (they are in vocabulary order) that is the row's largest; where all are NaN (nothing
-  // equals their maximum then) the first
-  int at = best == best ? N : 0;
+  // number of the lane's first logit (they are in vocabulary order) that is the row's largest
+  int at = N;
 #pragma unroll
   for (int i = N - 1; i >= 0; --i) at = acc(i >> 4, i & 15) == best ? i : at;
   int idx = at < N ? (nt + (at >> 4)) * 32 + ((at >> 3) & 1) * 16 + ((at >> 2) & 1) * 8 + half * 4 + (at & 3) : STAT_NO_INDEX;
