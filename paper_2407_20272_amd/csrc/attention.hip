@@ -863,8 +863,10 @@ __global__ __launch_bounds__(PW * 64) void attn_prompt_kernel(AttnArgs a, int R,
       for (int i = 0; i < 16; ++i) mx = fmaxf(mx, st[i]);
       mx = fmaxf(mx, __shfl_xor(mx, 32));
       // The sums are taken relative to m_run, which follows the maximum only when some row's has grown by a factor of sqrt(2)
-      // or more: probabilities a little above 1 lose nothing in float, and the output is hardly ever rescaled (a new maximum
-      // by any margin turns up in some row of 32 at most steps).  60.6 -> 57 us on the case above when it came in.
+      // or more: the output is rescaled less often (a new maximum by any margin turns up in some row of 32 at most steps).
+      // 512 rows of the case above, and relative error against float64 there: following every maximum 59.8 us, 2.83e-6; this
+      // margin 59.1, 2.83e-6; 2^2 57.0, 2.84e-6; 2^8 55.8, 2.86e-6 and single rows up to a fifth worse, in this order at every
+      // shape measured.  The margin is about the largest that costs no precision.
       if (__any(mx > m_run + 0.5f)) {
         const float alpha = __builtin_amdgcn_exp2f(m_run - mx);
         m_run = mx;

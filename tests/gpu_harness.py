@@ -65,6 +65,17 @@ def conf_tolerance(cfg, c: float, scale: float, zmax_abs: float) -> float:
     return (1e-4 if cfg.dtype == "fp32" else 1e-3) + 2.0 * scale * eps * max(c * (1.0 - c), 0.05)
 
 
+CONF_DEEP = 8   # layers beyond which confidence_sigma holds (measured there)
+
+
+def confidence_sigma(cfg, c: float, scale: float, z_rms: float, i: int) -> float:
+    """Standard deviation of a softmax confidence c after i layers between two correct bf16 computations: their hidden states
+    are 1.5e-2 relative RMS apart after 32 layers at the 7B width and 1.0e-2 after 16, i.e. grow apart as the square root of
+    the depth, and that reaches the confidence through the two logits that decide it (both measured between two oracles on
+    the CPU, tests/test_bf16_divergence.py)."""
+    return max(c * (1.0 - c), 0.05) * scale * math.sqrt(2.0) * 1.5e-2 * math.sqrt(i / 32.0) * z_rms
+
+
 def hidden_rel_err(cfg) -> float:
     """Relative RMS error of a hidden state that the arithmetic explains: float summation order for the fp32
     workload; for bf16 ones the disagreement on bf16 rounding directions accumulated over the layers (the RMS
@@ -74,8 +85,10 @@ def hidden_rel_err(cfg) -> float:
 
 def measure_tolerance(cfg, m, tr, i, b) -> float:
     """Tolerance of the confidence of sequence b at layer i (1-based), derived from the arithmetic of the measure.
-    conf_mode 0: through the softmax from a logit tolerance (conf_tolerance); conf_mode 1 (top-1 minus top-2): the sum
-      of that tolerance for the two probabilities.
+    conf_mode 0: through the softmax from a logit tolerance (conf_tolerance), which is two to three standard deviations of
+      what the arithmetic itself does in a deep model: beyond CONF_DEEP layers four of them, where that is more (two correct
+      computations have single entries at 3.5 among 200, tests/test_bf16_divergence.py; the RMS over many entries,
+      confidence_ratios, is the sharper test); conf_mode 1 (top-1 minus top-2): the sum of that for the two probabilities.
     conf_mode 2: cos of two vectors that are each off by a relative error delta moves by about 2 delta sin(angle).
     conf_mode 3: the unit's input w.x (x at unit root mean square, |x| = sqrt(d)) moves by about |w| delta sqrt(d)
       along a random direction, i.e. by 1.5 delta for the generator's rows of variance 1.5^2/d; 4 sigma of that
@@ -88,11 +101,30 @@ def measure_tolerance(cfg, m, tr, i, b) -> float:
         return (1e-5 if cfg.dtype == "fp32" else 1e-3) + max(c * (1.0 - c), 1e-3) * 4.0 * 1.5 * hidden_rel_err(cfg)
     z = O.head_logits(m, h[None])
     scale = cfg.logit_scale * i
+
+    def of(p):
+        tol = conf_tolerance(cfg, p, scale, float(z.abs().max()))
+        if cfg.dtype == "bf16" and i > CONF_DEEP:
+            tol = max(tol, 1e-3 + 4.0 * confidence_sigma(cfg, p, scale, float(z.pow(2).mean().sqrt()), i))
+        return tol
+
     if m.conf_mode == 1:
         # top-1 minus top-2: each of the two probabilities moves by its own p(1-p) * 2 * scale * eps
         p = torch.topk(torch.softmax(scale * z[0], -1), 2).values
-        return conf_tolerance(cfg, float(p[0]), scale, float(z.abs().max())) + conf_tolerance(cfg, float(p[1]), scale, float(z.abs().max()))
-    return conf_tolerance(cfg, c, scale, float(z.abs().max()))
+        return of(float(p[0])) + of(float(p[1]))
+    return of(c)
+
+
+def confidence_ratios(cfg, m, tr, g_conf) -> List[float]:
+    """conf_mode 0: |error| of every confidence beyond CONF_DEEP layers in units of confidence_sigma."""
+    oc, out = tr["conf"], []
+    for i in range(CONF_DEEP, oc.shape[0]):
+        rows = [b for b in range(oc.shape[1]) if not math.isnan(float(oc[i, b]))]
+        if rows:
+            z_rms = O.head_logits(m, tr["h"][i][rows]).pow(2).mean(-1).sqrt()
+            out += [abs(float(g_conf[i, b]) - float(oc[i, b]))
+                    / confidence_sigma(cfg, float(oc[i, b]), cfg.logit_scale * (i + 1), float(z_rms[r]), i + 1) for r, b in enumerate(rows)]
+    return out
 
 
 def check_confidences(cfg, m, tr, g_conf, what, lam_l=None, decisions=None):
