@@ -97,7 +97,7 @@ struct Workspace {
   float* hprev;       // bf16: [Mpad][d], fp32: [B][d]: hidden state before the current layer (similarity measure)
   RowMap rowmap;      // bf16: [Mpad] + [Mpad] + [1] row map of the sequences still active (per-sequence exit)
   // fp32 path
-  float *ao, *act, *logits;
+  float *ao, *act, *logits, *row_scale;   // (row_scale: see LmEpi)
   size_t bytes;
 };
 
@@ -144,6 +144,7 @@ Workspace carve(const ee_model_desc& D, int B, void* base) {
     w.ao = c.take<float>(Bp * d);
     w.act = c.take<float>(Bp * f);
     w.logits = c.take<float>(Bp * V);
+    w.row_scale = c.take<float>(Bp);
     w.hprev = c.take<float>(Bp * d);
   }
   w.bytes = (c.off + 255) & ~(size_t)255;
@@ -168,6 +169,7 @@ Workspace carve_exit_check(const ee_model_desc& D, int B, void* base) {
     w.xH = c.take<bf16_t>(d * Mpad);
   } else {
     w.logits = c.take<float>(Bp * V);
+    w.row_scale = c.take<float>(Bp);
   }
   w.bytes = (c.off + 255) & ~(size_t)255;
   return w;
@@ -284,7 +286,7 @@ void enqueue_head_bf16(const ee_model& M, const Workspace& w, int B, float scale
   const ee_model_desc& D = M.desc;
   GemmShape g{M.w_lm, w.xH, D.d_model, B, 0, D.vocab / 32, 16, 1};
   g.n_rows_dev = rm.n_active;   // compacted operand (prepared by the caller through the same map)
-  LmEpi e{w.partials, nullptr, D.vocab / 32, D.vocab, scale, rm.perm};
+  LmEpi e{w.partials, nullptr, nullptr, D.vocab / 32, D.vocab, scale, rm.perm};
   ProfScope ps(EE_K_HEAD, layer, st);
   launch_gemm_lm_bf16(g, e, pred, st);
 }
@@ -305,7 +307,7 @@ void enqueue_head_f32(const ee_model& M, const Workspace& w, const float* h, int
   const ee_model_desc& D = M.desc;
   ProfScope ps(EE_K_HEAD, layer, st);
   SimpleShape g{reinterpret_cast<const float*>(M.w_lm), h, reinterpret_cast<const float*>(M.g_final), D.rms_eps, D.d_model, B, 0, D.vocab, 1};
-  LmEpi e{nullptr, w.logits, 1, D.vocab, 0.0f, nullptr};
+  LmEpi e{nullptr, w.logits, w.row_scale, 1, D.vocab, 0.0f, nullptr};
   launch_simple_lm(g, e, pred, st);
 }
 
@@ -378,7 +380,7 @@ int enqueue_exit_check(const ee_model& M, int32_t layer, const float* hidden, in
     launch_combine(ca, always, st);
   } else {
     enqueue_head_f32(M, w, hidden, batch, layer, always, st);
-    launch_head_decide_f32(w.logits, D.vocab, ca, always, nullptr, nullptr, D.d_model, st);
+    launch_head_decide_f32(w.logits, w.row_scale, D.vocab, ca, always, nullptr, nullptr, D.d_model, st);
   }
   EE_HIP(hipGetLastError());
   return EE_OK;
@@ -739,7 +741,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       } else {
         ProfScope ps(EE_K_COMBINE, i, st);
         if (bf) launch_combine(ca, run_layers, st);
-        else launch_head_decide_f32(w.logits, D.vocab, ca, run_layers, nullptr, nullptr, d, st);
+        else launch_head_decide_f32(w.logits, w.row_scale, D.vocab, ca, run_layers, nullptr, nullptr, d, st);
       }
       if (compact) launch_compact(w.status, B, rmap, run_layers, st);
     }
@@ -774,7 +776,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
     CombineArgs ca{w.partials, D.vocab / 32, B, 0, 0.0f, 0.0f, 0, nullptr, s, out_tokens, nullptr};
     ProfScope ps(EE_K_COMBINE, n, st);
     if (bf) launch_combine_copy(ca, final_pred, w.h, out_hidden, d, st);
-    else launch_head_decide_f32(w.logits, D.vocab, ca, final_pred, w.h, out_hidden, d, st);
+    else launch_head_decide_f32(w.logits, w.row_scale, D.vocab, ca, final_pred, w.h, out_hidden, d, st);
   }
   EE_HIP(hipGetLastError());
   return EE_OK;

@@ -108,7 +108,8 @@ struct GateUpEpi {              // act = silu(gate) * up
 };
 struct LmEpi {                  // per-tile softmax statistics of the scaled logits
   float4* partials;             // [M][n_parts]: {max logit (unscaled), sum exp(scale*(z - max)), 2nd max, arg max as int bits}
-  float* logits;                // fp32 path: [M][vocab] raw logits; bf16 path: nullptr
+  float* logits;                // fp32 path: [M][vocab] logits of the row times the gains, short of
+  float* row_scale;             // [M] the row's 1 / sqrt(mean square + eps); bf16 path: nullptr, both
   int n_parts;
   int vocab;
   float scale;                  // logit_scale * layer
@@ -230,9 +231,9 @@ struct DecideArgs {
   float* conf_out;
 };
 void launch_decide(const DecideArgs& a, Pred pred, hipStream_t st);
-// fp32 path: the decision of every row from its own logits [B][vocab] (conf_mode 0, 1; layer 0: token selection), one
-// launch; dst as in launch_combine_copy.
-void launch_head_decide_f32(const float* logits, int vocab, const CombineArgs& a, Pred pred, const float* src, float* dst, int d,
+// fp32 path: the decision of every row from its own logits [B][vocab] and their scale [B] (LmEpi; conf_mode 0, 1; layer 0: token
+// selection), one launch; dst as in launch_combine_copy.
+void launch_head_decide_f32(const float* logits, const float* row_scale, int vocab, const CombineArgs& a, Pred pred, const float* src, float* dst, int d,
                             hipStream_t st);
 // fp32 path: the sums of a one-dot-product measure and the decision from them; other is the previous hidden state [B][d]
 // (per_row; it becomes h) or one row [d].

@@ -108,7 +108,16 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, 
   }
   static_assert(MC == 4, "eight sums, four squares");
   float r = wave_sums8(sum, lane);      // lane bits 5, 4: batch row, bit 3: lo / hi
-  if constexpr (NORM) r *= 1.0f / sqrtf(wave_sums4(sq, lane) / (float)g.K + g.eps);
+  if constexpr (NORM) {
+    const float rinv = 1.0f / sqrtf(wave_sums4(sq, lane) / (float)g.K + g.eps);
+    if constexpr (std::is_same<Epi, LmEpi>::value) {
+      // The logits stay as the sums they are and the decision scales their differences: one rounding of every logit less
+      // (confidences are off by 3.2e-7 as with a normalised operand, not 3.7e-7; 37 rows, width 256, logits times 12).
+      if (pair == 0 && (lane & 15) == 0 && m0 + (lane >> 4) < g.M) e.row_scale[m0 + (lane >> 4)] = rinv;
+    } else {
+      r *= rinv;
+    }
+  }
   const float lo = r, hi = __shfl_xor(r, 8);
   const int m = m0 + (lane >> 4);
   if ((lane & 15) != 0 || m >= g.M) return;

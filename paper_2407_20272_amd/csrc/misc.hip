@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256) void measure_decide_f32_kernel(const float* h,
 
 // fp32 path: softmax statistics of one row of materialised logits and the decision from them, one workgroup per row; src /
 // dst: the hidden states the caller asked for (last launch of an iteration), copied whatever the predicate says.
-__global__ __launch_bounds__(256) void head_decide_f32_kernel(const float* logits, int vocab, CombineArgs a, Pred pred, const float* src,
+__global__ __launch_bounds__(256) void head_decide_f32_kernel(const float* logits, const float* row_scale, int vocab, CombineArgs a, Pred pred, const float* src,
                                                               float* dst, int d) {
   const int m = blockIdx.x;
   copy_row(src, dst, m, d);
@@ -343,6 +343,7 @@ __global__ __launch_bounds__(256) void head_decide_f32_kernel(const float* logit
   if (a.left && ctl_load(a.left + m) != 0) return;   // left at an earlier layer: its token and exit layer stand
   // largest logit with its index and the runner-up first, the exponentials relative to the wavefront's largest after
   HeadStat s = stat_empty();
+  a.scale *= row_scale[m];
   const float* z = logits + (size_t)m * vocab;
   constexpr int AHEAD = 8;   // loads in flight: one at a time a row of 32000 took 53 us, now 24
   auto each = [&](auto take) {
@@ -489,9 +490,9 @@ void launch_fill_prep(const float* h, const GainTable& gains, int n_layers, bf16
 void launch_compact(const int32_t* status, int B, const RowMap& rm, Pred pred, hipStream_t st) {
   hipLaunchKernelGGL(compact_kernel, dim3(1), dim3(256), 0, st, status, B, rm, pred);
 }
-void launch_head_decide_f32(const float* logits, int vocab, const CombineArgs& a, Pred pred, const float* src, float* dst, int d,
+void launch_head_decide_f32(const float* logits, const float* row_scale, int vocab, const CombineArgs& a, Pred pred, const float* src, float* dst, int d,
                             hipStream_t st) {
-  hipLaunchKernelGGL(head_decide_f32_kernel, dim3(a.B), dim3(256), 0, st, logits, vocab, a, pred, src, dst, d);
+  hipLaunchKernelGGL(head_decide_f32_kernel, dim3(a.B), dim3(256), 0, st, logits, row_scale, vocab, a, pred, src, dst, d);
 }
 void launch_measure_decide_f32(const float* h, float* other, int per_row, const DecideArgs& a, Pred pred, hipStream_t st) {
   hipLaunchKernelGGL(measure_decide_f32_kernel, dim3(a.B), dim3(256), 0, st, h, other, per_row, a, pred);
