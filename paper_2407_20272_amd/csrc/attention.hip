@@ -1088,6 +1088,13 @@ int attn_split_parts(int B, int n_heads, int max_blocks) {
   return parts < 2 ? 1 : parts;
 }
 
+void attention_prepare() {
+  prompt_lds_allowed<64, false>();
+  prompt_lds_allowed<64, true>();
+  prompt_lds_allowed<128, false>();
+  prompt_lds_allowed<128, true>();
+}
+
 int launch_attention(const AttnArgs& a, int dtype, Pred pred, hipStream_t st) {
   if (a.B == 0) return EE_OK;
   if (a.split_parts > 1 && a.row_table) EE_FAIL(EE_ERR_UNSUPPORTED, "attention: split_parts does not go with row_table");

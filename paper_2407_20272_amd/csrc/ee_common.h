@@ -351,6 +351,8 @@ struct AttnArgs {
   int split_parts;
 };
 int launch_attention(const AttnArgs& a, int dtype, Pred pred, hipStream_t st);
+// Host-side set-up for the current device (function attributes) that the first launch over prompt rows would otherwise do.
+void attention_prepare();
 // How many workgroups should share one (sequence, head) pair for this batch, and the floats of split_ws that takes.
 int attn_split_parts(int B, int n_heads, int max_blocks);
 inline size_t attn_split_floats(int B, int n_heads, int head_dim, int parts) {

@@ -24,11 +24,13 @@ int hipGetDevice(int* d) { *d = 0; return 0; }
 int hipGetLastError(void) { int e = pending; pending = 0; return e; }
 int hipFuncSetAttribute(const void* f, int attr, int value) {
   (void)f; (void)attr;
+  printf("attribute %d\n", value);
   if (refuse && value > 65536) return pending = 1;   /* like the runtime: the error also waits for hipGetLastError */
   return 0;
 }
 int __hipPushCallConfiguration(dim g, dim b, size_t s, void* st) { (void)st; grid = g; block = b; lds = s; return 0; }
 int __hipPopCallConfiguration(dim* g, dim* b, size_t* s, void** st) { *g = grid; *b = block; *s = lds; *st = 0; return 0; }
+int hipGetSymbolAddress(void** p, const void* s) { (void)s; *p = (void*)0x20000; return 0; }
 int hipLaunchKernel(const void* f, dim g, dim b, void** args, size_t s, void* st) {
   (void)f; (void)args; (void)st;
   printf("launch %u %u %u %u %zu\n", g.x, g.y, g.z, b.x, s);
@@ -45,7 +47,9 @@ int main(int argc, char** argv) {
   ee_batch b = {B, p, p, p, 20, 300, p};
   const size_t n = ee_workspace_bytes(&m.desc, B, 300);
   int rc;
-  if (!strcmp(argv[1], "iteration"))
+  if (!strcmp(argv[1], "init"))
+    rc = ee_noalloc_init();
+  else if (!strcmp(argv[1], "iteration"))
     rc = ee_decode_iteration(&m, &c, &b, 0, 0, EE_EXIT_NONE, p, p, p, 0, 0, p, n, 0);
   else if (!strcmp(argv[1], "attention"))
     rc = ee_paged_attention_decode(&m.desc, &c, 1, p, &b, p, 0, 0, 0);
@@ -69,6 +73,7 @@ def program(tmp_path_factory):
 
     def run(*args):
         out = subprocess.run([str(exe), *map(str, args)], check=True, capture_output=True, text=True, timeout=60).stdout.split("\n")
+        run.attributes = [int(line.split()[1]) for line in out if line.startswith("attribute")]
         launches = [tuple(int(x) for x in line.split()[1:]) for line in out if line.startswith("launch")]
         return launches, [line for line in out if line.startswith("rc")][0]
 
@@ -98,3 +103,10 @@ def test_exit_check_without_the_lds_of_the_ring_kernel(program):
     got, rc = program("check", 1, 450)
     assert rc.strip() == "rc 0"
     assert got == [want[0], (8 * 4, 1, 1, 256, 0), want[2]]
+
+
+def test_set_up_before_a_graph_capture_asks_for_every_lds_size(program):
+    """ee_noalloc_init: two ring kernels, prompt attention with heads of 64 and 128 in both output orders."""
+    launches, rc = program("init", 0, 1)
+    assert rc.strip() == "rc 0" and not launches
+    assert sorted(program.attributes) == [65536, 65536, 131072, 131072, 131072, 131072]
