@@ -240,9 +240,9 @@ int ee_paged_attention_decode(const ee_model_desc* desc, const ee_kv_cache* cach
 #define EE_K_GATEUP 4   /* gate/up projection + SwiGLU                                          */
 #define EE_K_DOWN 5     /* down projection + residual                                           */
 #define EE_K_HEAD 6     /* exit head / LM head projection with softmax statistics               */
-#define EE_K_COMBINE 7  /* exit decision                                                        */
+#define EE_K_COMBINE 7  /* exit decision, token selection and copy of the hidden states         */
 #define EE_K_KVFILL 8   /* KV filling projection                                                */
-#define EE_K_OTHER 9    /* state reset, embedding, copies                                       */
+#define EE_K_OTHER 9    /* state reset, embedding, rotary table, first normalisation            */
 #define EE_K_CLASSES 10
 /* Plain device copy of n_floats floats (dev to dev) with the library's own copy kernel: a kernel of known traffic
  * (4 * n_floats bytes read, as many written) against which hardware byte counters are calibrated. */

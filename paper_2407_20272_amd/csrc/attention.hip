@@ -492,13 +492,14 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a, Pred pred) {
 //
 // What bounds it is the compute unit's intake of K and V (about 55 bytes a nanosecond, whatever cache they come from), so
 // the two groups share every tile: each of a slice's two wavefronts brings one of the step's two blocks, from memory to
-// LDS directly in whole kilobytes, into the slice's other buffer while this step is multiplied; one barrier per step.
+// LDS directly in whole kilobytes, into the slice's other buffer while this step is multiplied; the pair meets once per step.
 // The lanes of a load choose WHICH 16 bytes of a token they fetch, which permutes a token's channels in LDS so that
 // neither the fragment reads of K nor the transposing reads of V (ds_read_b64_tr_b16: four tokens x 16 channels per 16
 // lanes) meet in one bank.
 // 512 rows of four sequences at 0 to 3128 positions, 32 heads x 128: 129 us with 16 rows per workgroup, each streaming
-// the whole context, and V transposed through 2-byte LDS stores; 56 us now (a step costs a wavefront about 3200 cycles:
-// 1024 of multiplies, the rest softmax, LDS and the meeting).  16 rows of 12 sequences at up to 1000 positions: 141 us
+// the whole context, and V transposed through 2-byte LDS stores; 56 us now.  A step takes a slice 2.1 us (one prompt of 512
+// rows: 20.6 us at 4 steps a slice, 88.3 at 35): a wavefront's multiplies are 1024 cycles of that and two wavefronts share a
+// SIMD's matrix core, 40 % together; the rest is softmax, LDS and the meeting.  16 rows of 12 sequences at up to 1000 positions: 141 us
 // (runs one after the other, each through all four wavefronts) -> 28 us; 200 rows of four at up to 100: 16 -> 12 us.
 // ---------------------------------------------------------------------------------------------------------
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));

@@ -3,9 +3,8 @@
 // contraction, 16 bytes at a time where the operands allow it, and a halving exchange adds the 64 partial sums, so that
 // four lanes finish the four batch rows side by side.  A projection of a normalised operand takes the residual rows
 // themselves: every wavefront sums the squares of its rows beside the products (the rows are a few kilobytes in L1) and the
-// separate normalisation launches are gone.  What bounds this path is the number of dependent launches, about 3.3 us each:
-// one iteration of four layers of width 256 took 65 launches and 216 us,
-// 30 launches and 115 us in this form.
+// separate normalisation launches are gone.  What bounds this path at small widths is the number of dependent launches, 3 to 4
+// us each: one iteration of four layers of width 256 took 65 launches and 217 us, 30 launches and 110 us in this form.
 #include <type_traits>
 
 #include "ee_common.h"

@@ -175,8 +175,8 @@ __global__ __launch_bounds__(NORM_THREADS) void finish_norm_kernel(NormArgs a, P
 
 // Everything before the first projection of an iteration in one launch: workgroup m < Mpad resets the state of row m,
 // gathers its embedding (float residual row, sum of squares) and writes the first layer's operand with the arithmetic of
-// finish_norm_kernel; the workgroups from Mpad on tabulate the rotary angles.  (Four or five dependent launches before, about
-// 3.3 us each whatever they did; one now.)
+// finish_norm_kernel; the workgroups from Mpad on tabulate the rotary angles.  (Four or five dependent launches before, 3 to 4
+// us each whatever they did; one now.)
 __global__ __launch_bounds__(NORM_THREADS) void iter_begin_kernel(BeginArgs a) {
   __shared__ float red[NORM_THREADS / 64];
   const int m = blockIdx.x, d = a.d;

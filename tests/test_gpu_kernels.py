@@ -132,7 +132,7 @@ def test_attention_rows_sharing_one_block_table():
 
 @pytest.mark.parametrize("dh", [64, 128])
 def test_attention_rows_of_several_sequences_across_row_groups(dh):
-    """Rows of three sequences in one call (row_table), runs of 20, 5 and 17 rows: the 16-row groups of the
+    """Rows of three sequences in one call (row_table), runs of 20, 5 and 17 rows: the row groups of the
     matrix-core kernel straddle the runs, the last group is ragged, block counts are odd and even."""
     cfg = cfg_of("bf16", dh, 2).with_(batch=3, shuffled_blocks=True)
     lens = torch.tensor([69, 4, 199], dtype=torch.int32)        # last cached position of each sequence
