@@ -99,7 +99,8 @@ typedef struct ee_model {
  * k_pool and v_pool: dev [n_layers][num_blocks][n_heads][block_size][head_dim] in the model dtype.
  * block_size must be 16.  Position p of sequence b lives in block block_tables[b][p / 16] at offset p % 16.
  * Slots that hold no position of a sequence (the rest of its last block, blocks nobody owns) may contain
- * anything, NaN included: the attention kernels never let them reach a result. */
+ * anything, NaN included: the attention kernels never let them reach a result.  What one sequence has cached, Inf and
+ * NaN included, reaches no result of another. */
 typedef struct ee_kv_cache {
   void* k_pool;
   void* v_pool;
@@ -194,7 +195,7 @@ int ee_exit_check(const ee_model* model, int32_t layer, const float* hidden, int
  * EE_NOALLOC_SCRATCH_BYTES inside the library (each GPU the library runs on holds its own copy until the process
  * ends).  The call allocates and frees nothing.  A shape and batch that need more scratch than the array holds
  * (ee_exit_check_noalloc_bytes says how much: roughly batch * (vocab / 2 + 2 * d_model) bytes for EE_BF16, batch *
- * 4 * (vocab + d_model) for EE_FP32) are refused with EE_ERR_WORKSPACE before anything is enqueued.
+ * 4 * vocab for EE_FP32) are refused with EE_ERR_WORKSPACE before anything is enqueued.
  * Every call on one GPU uses that GPU's one array: calls that overlap on a GPU (two streams, two threads) race;
  * calls on one stream are ordered and each clears what it needs to start at zero.
  * ee_noalloc_init resolves the array's device address for the current device (one host-side query, no
