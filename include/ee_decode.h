@@ -100,7 +100,7 @@ typedef struct ee_model {
  * block_size must be 16.  Position p of sequence b lives in block block_tables[b][p / 16] at offset p % 16.
  * Slots that hold no position of a sequence (the rest of its last block, blocks nobody owns) may contain
  * anything, NaN included: the attention kernels never let them reach a result.  What one sequence has cached, Inf and
- * NaN included, reaches no result of another. */
+ * NaN included, reaches no other sequence's attention. */
 typedef struct ee_kv_cache {
   void* k_pool;
   void* v_pool;

@@ -13,7 +13,8 @@
 namespace ee {
 namespace {
 
-constexpr int MC = 4;  // batch rows per wavefront
+constexpr int MC = 4;            // batch rows per wavefront
+constexpr int ROW_BLOCKS = 64;   // row blocks side by side in grid.x; grid.y holds the rest (a grid dimension counts less than 2^32 threads)
 
 // Sums of v[0..7] over the wavefront: the lane of bits 5, 4, 3 = i gets sum i in every lane of its eight.
 __device__ inline float wave_sums8(float (&v)[8], int lane) {
@@ -58,8 +59,8 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, 
   // read of a weight row hit its L2.  With the row blocks outermost every block fetched the whole matrix from beyond the L2:
   // LM head of 32000 x 4096 and 32 rows 985 us (rows looped over in the wavefront, the form before: 665), now 570; gate/up
   // of 22016 x 4096 and 64 rows 1370 (1150), now 706.
-  const int row_blocks = (g.M + MC - 1) / MC, slot = (int)blockIdx.x >> 3;
-  const int m0 = slot % row_blocks * MC;
+  const int first = blockIdx.y * ROW_BLOCKS, row_blocks = min(ROW_BLOCKS, (g.M + MC - 1) / MC - first), slot = (int)blockIdx.x >> 3;
+  const int m0 = (first + slot % row_blocks) * MC;
   if constexpr (FILL) {   // one slice of the grid per layer; nothing to do where every row has been cached already
     const int layer = blockIdx.z + 1;
     bool need = false;
@@ -137,7 +138,9 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 
 template <class Epi, bool NORM, class Fill = NoFill>
 void launch(const SimpleShape& g, const Epi& e, Pred pred, hipStream_t st, const Fill& fill = Fill{}, int n_layers = 1) {
-  const dim3 grid(((g.n_rows / 2 + 3) / 4 + 7) / 8 * 8 * ((g.M + MC - 1) / MC), 1, n_layers);
+  const int row_blocks = (g.M + MC - 1) / MC;
+  const dim3 grid(((g.n_rows / 2 + 3) / 4 + 7) / 8 * 8 * (row_blocks < ROW_BLOCKS ? row_blocks : ROW_BLOCKS),
+                  (row_blocks + ROW_BLOCKS - 1) / ROW_BLOCKS, n_layers);
   // 16-byte loads need rows that keep the alignment and operands that start on it (the library asks no caller for that)
   bool vec = g.K % 4 == 0 && aligned16(g.w) && aligned16(g.x) && aligned16(g.gain);
   if constexpr (std::is_same<Fill, SimpleFill>::value)

@@ -45,6 +45,10 @@ int main(int argc, char** argv) {
   ee_model m = {{2, 256, 2, 128, 512, 1024, EE_BF16, 1e-5f, 1e4f, 1, 1.0f, 0}, p, p, p, w, 0, 0};
   ee_kv_cache c = {p, p, 64, 16};
   ee_batch b = {B, p, p, p, 20, 300, p};
+  if (!strcmp(argv[1], "check_fp32")) {
+    m.desc.dtype = EE_FP32;
+    m.desc.vocab = 32000;
+  }
   const size_t n = ee_workspace_bytes(&m.desc, B, 300);
   int rc;
   if (!strcmp(argv[1], "init"))
@@ -110,3 +114,15 @@ def test_set_up_before_a_graph_capture_asks_for_every_lds_size(program):
     launches, rc = program("init", 0, 1)
     assert rc.strip() == "rc 0" and not launches
     assert sorted(program.attributes) == [65536, 65536, 131072, 131072, 131072, 131072]
+
+
+@pytest.mark.parametrize("rows", [1, 4, 255, 257, 20000, 300000])
+def test_float_head_grid_covers_every_row_within_the_limits(program, rows):
+    """Eight weight rows a workgroup, padded to the eight XCDs, times up to 64 row blocks of four in x, the rest in y: a dimension
+    holds less than 2^32 threads and 65536 workgroups in y."""
+    launches, rc = program("check_fp32", 0, rows)
+    assert rc.strip() == "rc 0"
+    (x, y, z, threads, _), decide = launches
+    blocks = (rows + 3) // 4
+    assert (x, z, threads) == (4000 * min(blocks, 64), 1, 256) and (y - 1) * 64 < blocks <= y * 64
+    assert x * threads < 2 ** 32 and y < 65536 and decide[:4] == (rows, 1, 1, 256)
