@@ -10,6 +10,7 @@ import torch
 
 from oracle import ee_oracle as O
 from paper_2407_20272_amd import workloads as W
+from gpu_harness import confidence_sigma
 
 F64 = torch.float64
 
@@ -120,3 +121,24 @@ def test_what_the_drift_does_to_a_confidence(seed):
     r = torch.cat(ratios)
     print(f"seed {seed}: RMS {float(r.pow(2).mean().sqrt()):.2f}, largest {float(r.max()):.2f}")
     assert 0.3 < float(r.pow(2).mean().sqrt()) < 1.5 and float(r.max()) < 4.0
+
+
+@pytest.mark.parametrize("mistake", ["scores times 1.02", "last position left out"])
+def test_the_bound_on_many_confidences_notices_a_mistake(monkeypatch, mistake):
+    """The bound of the parity test (RMS of 1.5 in units of gpu_harness.confidence_sigma) against mistakes planted in the
+    attention of one oracle: 2 % on the scores moves single confidences by hardly more than four standard deviations, and the RMS
+    over all of them beyond the bound (1.7; 0.65 without a mistake)."""
+    cfg, m, (a, _), _ = two_computations(1024, 32, 8, vocab=4096)
+    right = O.attention_decode
+    wrong = {"scores times 1.02": lambda q, K, V: right(q * 1.02, K, V), "last position left out": lambda q, K, V: right(q, K[:-1], V[:-1])}
+    monkeypatch.setattr(O, "attention_decode", wrong[mistake])
+    _, _, _, (b, _) = two_computations(1024, 32, 8, vocab=4096)
+    ratios = []
+    for i in range(8, 32):
+        za, zb = O.head_logits(m, a["h"][i]), O.head_logits(m, b["h"][i])
+        scale = cfg.logit_scale * (i + 1)
+        top = za.argmax(-1, keepdim=True)
+        pa, pb = ((scale * z).softmax(-1).gather(1, top)[:, 0] for z in (za, zb))
+        ratios += [abs(float(y - x)) / confidence_sigma(cfg, float(x), scale, float(r), i + 1)
+                   for x, y, r in zip(pa, pb, za.pow(2).mean(-1).sqrt())]
+    assert (sum(r * r for r in ratios) / len(ratios)) ** 0.5 > 1.5
