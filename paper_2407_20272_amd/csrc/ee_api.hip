@@ -101,12 +101,6 @@ struct Workspace {
   size_t bytes;
 };
 
-// Contraction slices of the two accumulate projections of a layer (what the launches will write).
-int acc_slices_max(const ee_model_desc& D, int B) {
-  const int a = gemm_acc_slices(B, D.d_model / 32, D.d_model), b = gemm_acc_slices(B, D.d_model / 32, D.d_ffn);
-  return a > b ? a : b;
-}
-
 Workspace carve(const ee_model_desc& D, int B, void* base) {
   Workspace w{};
   Carver c{reinterpret_cast<char*>(base), 0};
@@ -127,7 +121,10 @@ Workspace carve(const ee_model_desc& D, int B, void* base) {
   if (D.dtype == EE_BF16) {
     w.partials = c.take<float4>((size_t)Mpad * (V / 32));
     w.h = c.take<float>(d * Mpad);
-    w.y = c.take<float>((size_t)acc_slices_max(D, Bp) * d * Mpad);
+    {
+      const size_t o = gemm_acc_rows(Bp, D.d_model), down = gemm_acc_rows(Bp, D.d_ffn);
+      w.y = c.take<float>((o > down ? o : down) * d);
+    }
     w.xH = c.take<bf16_t>(2 * d * Mpad);
     w.xT = w.xH ? w.xH + d * Mpad : nullptr;
     w.aoT = c.take<bf16_t>(d * Mpad);
@@ -241,8 +238,7 @@ int check_workspace(const ee_model_desc& D, int B, void* ws, size_t ws_bytes) {
 
 bool has_head(const ee_model_desc& D, int i) { return i < D.n_layers && i % D.exit_every == 0; }
 
-// Row compaction needs every projection that takes a compacted operand to run in the tiled kernel, and pays
-// from two 128-row chunks on (a chunk is what the kernel can skip).
+// Row compaction pays from two 128-row blocks on (a block is what the projections can skip).
 bool bf16_compactable(const ee_model_desc& D, int B) {
   return D.dtype == EE_BF16 && B > 128 && gemm_bf16_is_tiled(B, D.d_model / 32) && gemm_bf16_is_tiled(B, 2 * D.d_ffn / 32) &&
          gemm_bf16_is_tiled(B, D.vocab / 32);
@@ -518,7 +514,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // what it caches IS the KV filling of layer i for that sequence (Section 3.2) and only the layers above the
   // batch exit layer are left to the filling launch, as in Algorithm 1.
   const int32_t* left = use_exit_heads == EE_EXIT_PER_SEQUENCE ? w.status : nullptr;
-  // At batch sizes where the projections run in the tiled kernel (whose cost grows with the rows), the layers'
+  // At batch sizes where the projections' cost grows with the rows, the layers'
   // operands are compacted as well: attention writes the result of an active sequence to its position in the row
   // map, the output, FFN and exit-head projections run over the first n_active rows only and scatter into the
   // residual columns.  The QKV projection keeps all rows in place (it does the KV filling of those that left).

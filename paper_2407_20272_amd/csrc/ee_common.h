@@ -63,8 +63,8 @@ struct IterState {
   int32_t* batch_exit_layer;  // [1] output_layer of Algorithm 1
 };
 
-// Compaction of the rows that are still active (per-sequence exit at batch sizes the tiled projection kernel
-// serves): position p < *n_active of a compacted operand holds batch row perm[p]; cpos is the inverse map.
+// Compaction of the rows that are still active (per-sequence exit at more than 128 rows): position p < *n_active of a
+// compacted operand holds batch row perm[p]; cpos is the inverse map.
 // The map is rebuilt after every exit check and is constant inside a layer.
 struct RowMap {
   int32_t* perm;      // [Mpad]; nullptr = no compaction (every row, in place)
@@ -113,7 +113,7 @@ struct LmEpi {                  // per-tile softmax statistics of the scaled log
   int n_parts;
   int vocab;
   float scale;                  // logit_scale * layer
-  const int32_t* perm;          // nullptr, or [M]: operand row m is batch row perm[m] (compacted operand, tiled kernel only)
+  const int32_t* perm;          // nullptr, or [M]: operand row m is batch row perm[m] (compacted operand)
 };
 
 // ---------------------------------------------------------------------------------------------------
@@ -265,15 +265,15 @@ struct GemmShape {
   // QKV projection with one batch tile: the last split_tiles tiles (tiles without a rotation: V) are each computed
   // by two workgroups, 16 of the 32 output rows each, dispatched first; see gemm_mfma.hip.  0 = off.
   int split_tiles;
-  // Tiled kernel only: nullptr, or the device-side number of valid operand rows (<= M).  Row chunks beyond it
+  // Block kernel only: nullptr, or the device-side number of valid operand rows (<= M).  Row blocks beyond it
   // return at once, rows beyond it are not written.
   const int32_t* n_rows_dev;
   int grid_y;   // set by the launcher (tiled kernel): batch chunks x contraction slices per group of output tiles
-  int keep_chunks;  // set by the launcher (tiled kernel): > 0 = weights stay cached once this many 128-row chunks hold rows
+  int keep;     // set by the launcher (tiled kernel): weights stay cached
   int even_wgs; // set by the launcher (tiled kernel): > 0 = the tiles are dealt out evenly over this many workgroups
 };
-// Whether a projection of M rows onto n_tiles packed tiles runs in the tiled kernel (the one that takes
-// n_rows_dev and the epilogues' perm).
+// Whether a projection of M rows onto n_tiles packed tiles comes in whole groups of four tiles, three batch tiles at least: where
+// per-sequence exit may compact the operand (n_rows_dev and the epilogues' perm).
 bool gemm_bf16_is_tiled(int M, int n_tiles);
 // One-time host-side set-up of the projection kernels (function attributes) that the first launch would otherwise do.
 void gemm_bf16_prepare();
@@ -286,6 +286,8 @@ void launch_gemm_qkv_bf16(const GemmShape& g, const QkvEpi& e, Pred pred, hipStr
 bool gemm_qkv_carries_combine(int M);
 // Contraction slices the accumulate launch of this shape writes (the launch below uses exactly this many).
 int gemm_acc_slices(int M, int n_tiles, int K);
+// Rows of partial results (all slices) to set aside for accumulate launches of up to M rows over a contraction of K.
+size_t gemm_acc_rows(int M, int K);
 void launch_gemm_acc_bf16(const GemmShape& g, const AccEpi& e, Pred pred, hipStream_t st);
 void launch_gemm_gateup_bf16(const GemmShape& g, const GateUpEpi& e, Pred pred, hipStream_t st);
 void launch_gemm_lm_bf16(const GemmShape& g, const LmEpi& e, Pred pred, hipStream_t st);

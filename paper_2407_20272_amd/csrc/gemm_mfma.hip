@@ -1,14 +1,16 @@
-// bf16 projections of the decode step on the matrix cores (v_mfma_f32_32x32x16_bf16).  Three kernels, by batch size:
+// bf16 projections of the decode step on the matrix cores (v_mfma_f32_32x32x16_bf16).  Four kernels, by batch size:
 //
 //   gemm_mfma_kernel   one or two 32-row batch tiles, few output tiles (QKV, output projection): a weight streamer.
 //                      Every weight byte is fetched from HBM exactly once, straight into registers (1 KiB of
 //                      consecutive bytes per wavefront load thanks to the packed tile order), the small activation
 //                      operand comes out of L2.  A workgroup of four wavefronts owns one 32-row output tile and splits
 //                      the contraction four ways; the partial tiles meet in LDS.
-//   gemm_tiled_kernel  everything else up to 384 rows, and the projections with few output tiles beyond: the four
-//                      wavefronts own different output tiles over the same contraction range and share the activation
-//                      operand through LDS; 128-row chunks.
-//   gemm_ring_kernel   LM head and gate/up at 385-512 rows, where the matrix cores are what counts: 256 x 256 blocks.
+//   gemm_tiled_kernel  LM head, gate/up and down projection up to 128 rows, KV filling: the four wavefronts own different output
+//                      tiles over the same contraction range and share the activation operand through LDS; 128-row chunks.
+//   gemm_block_kernel  everything else: blocks of rows x columns, both operands through LDS, brought by wavefronts that do
+//                      nothing else.
+//   gemm_ring_kernel   LM head at 385-512 rows (gate/up where its blocks fit one round and others do not), where the matrix cores
+//                      are what counts: 256 x 256 blocks.
 //
 // The epilogues (rotary + paged cache write, partial results of the residual updates, SwiGLU, exit-head softmax
 // statistics) run on the finished sums, from LDS in the first kernel and from registers in the other two.
@@ -387,7 +389,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Main loop 2 (from three 32-row batch tiles on; LM head, gate/up and down projection always): the four
+// Main loop 2 (LM head, gate/up and down projection up to four 32-row batch tiles, KV filling): the four
 // wavefronts of a workgroup own four different 32-row
 // output tiles over the SAME contraction range, so the activation operand is fetched from L2 once per
 // workgroup, staged in LDS and read by all four; weights still go straight from HBM to registers, each byte
@@ -536,17 +538,7 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pre
   const int ny = g.grid_y;                      // chunks * contraction slices
   const int ksplit = ny / chunks;
   const int slot = (int)blockIdx.x >> 3;
-  int bx, by;
-  if (g.n_rows_dev) {
-    // compacted operand: most chunks may have nothing to do, and their workgroups return at once; chunk-major
-    // order keeps those behind the chunks that work instead of in between them
-    const int groups8 = (int)gridDim.x / (8 * ny);
-    by = slot / groups8;
-    bx = (slot % groups8) * 8 + ((int)blockIdx.x & 7);
-  } else {
-    bx = (slot / ny) * 8 + ((int)blockIdx.x & 7);
-    by = slot % ny;
-  }
+  const int bx = (slot / ny) * 8 + ((int)blockIdx.x & 7), by = slot % ny;
   // Which output tiles this workgroup owns.  Even split: four per workgroup.  Uneven split (g.even_wgs > 0, one
   // chunk, no contraction slices): the tiles are dealt out over exactly g.even_wgs workgroups, n_tiles / even_wgs
   // or one more each, and a wavefront beyond its workgroup's count owns none: it still stages its share of the
@@ -564,9 +556,6 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pre
   }
   const bool active = wave < my_tiles;
   const int chunk = by / ksplit, ksl = by % ksplit;
-  // compacted operand: only the first *n_rows_dev rows hold sequences that are still active
-  const int M_eff = g.n_rows_dev ? g.n_rows_dev[0] : g.M;
-  if (chunk * MT * 32 >= M_eff) return;
   // this wavefront's NTW consecutive output tiles (a wavefront without tiles points at the workgroup's first: never loaded)
   const int nt0 = g.tile_begin + tile0 + (active ? wave : 0) * NTW;
   const int k_steps = g.K >> 4;
@@ -676,10 +665,8 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pre
     main_loop(std::false_type{}, std::false_type{});
     return;       // nothing to finish; the epilogues below take no workgroup barrier
   }
-  // (only these are ever launched with keep_chunks > 0)
-  constexpr bool MAY_KEEP = MT == 4 && NTW == 1 && !std::is_same<Epi, AccEpi>::value;
-  if (MAY_KEEP && g.keep_chunks > 0 && M_eff > (g.keep_chunks - 1) * MT * 32)
-    main_loop(std::true_type{}, std::integral_constant<bool, MAY_KEEP>{});
+  if (FILL && g.keep)   // (nothing else is launched with it)
+    main_loop(std::true_type{}, std::integral_constant<bool, FILL>{});
   else
     main_loop(std::true_type{}, std::false_type{});
 
@@ -687,17 +674,17 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pre
   if constexpr (std::is_same<Epi, LmEpi>::value) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
-      finish_lm<NTW>([&](int t, int a) { return acc[t][mt][a]; }, nt0, chunk * MT + mt, M_eff, g, e, lane);
+      finish_lm<NTW>([&](int t, int a) { return acc[t][mt][a]; }, nt0, chunk * MT + mt, g.M, g, e, lane);
   } else {
 #pragma unroll
     for (int t = 0; t < NTW; ++t)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) finish_from_registers(acc[t][mt], nt0 + t, chunk * MT + mt, M_eff, ksl, g, e, lane);
+      for (int mt = 0; mt < MT; ++mt) finish_from_registers(acc[t][mt], nt0 + t, chunk * MT + mt, g.M, ksl, g, e, lane);
   }
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Main loop 3 (LM head and gate/up at 385 to 512 rows, where the matrix cores are what counts): one workgroup owns a
+// Main loop 3 (LM head, and now and then gate/up, at 385 to 512 rows, where the matrix cores are what counts): one workgroup owns a
 // 256-row x 256-column block of the result (eight batch tiles x eight weight tiles).  Wavefront w owns two weight
 // tiles (64 columns) against all eight batch tiles, 16 accumulator tiles = all 256 accumulation registers:
 //   * its weight fragments come straight from HBM into registers, RING_D contraction steps ahead (nobody else in
@@ -824,6 +811,280 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(GemmShape g, Epi e, Pred
   }
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// Main loop 4: one workgroup owns a block of MT batch tiles x NT weight tiles; both operands land in a ring of DS stages of U
+// contraction steps in LDS through direct-to-LDS loads, and every wavefront of WM x WN multiplies its part of the block.
+//   * What bounds it is how fast a compute unit takes its operands in: loads that miss L2 come at 31 GB/s a compute unit, shared
+//     or not, hits at 75 to 120, whatever is in flight beyond 32 KiB (so two or three stages are enough), and the order, the
+//     layout and the cache policy of the loads change little.  A block of 128 x 192 needs 10 KiB a step: 48 us over 256 steps
+//     with nothing but the loads; 256 x 192 14 KiB, 67 us.
+//   * A wavefront that issues such a load waits at it until the memory pipeline accepts it, and multiplies nothing meanwhile:
+//     with the loads in the multiplying wavefronts the same blocks took 77 and 115 us, loads and multiplies one after the
+//     other.  So NL wavefronts do nothing but load.  They are as fast as their address arithmetic: one bound register pair and a
+//     scalar offset (buffer loads), with 64-bit pointers and a select per load two of them reached 35 GB/s.
+//   * One barrier a stage: past it the next stage has landed (the loaders waited for it), and the fragments of this stage's last
+//     step are in registers, so its slot can be loaded again.
+// 512 rows of the 7B shape, before (tiled and ring kernels) and now: QKV 77 -> 59 us (128 x 192 blocks, 0.88 PFLOP/s), gate/up 107
+// to 123 -> 83 to 92 (256 x 192, 1.0 PFLOP/s), down 59 -> 48.  Tried: a wavefront that touches this workgroup's share of the shared
+// weight lines ahead of the loaders: 10 to 17 % faster without multiplies, 0 to 30 % slower with them; weights past the caches:
+// up to a third slower; four multiplying wavefronts of 128 x 96 instead of eight of 64 x 96: 92 -> 97 us.
+// ---------------------------------------------------------------------------------------------------------
+struct BlockGrid {
+  int row_blocks, col_blocks, ksplit;
+};
+
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef __amdgpu_buffer_rsrc_t buffer_t;
+__device__ inline buffer_t buffer_at(const char* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(p), 0, 0x7fffffff, 0x00020000); }
+__device__ inline void buffer_to_lds(buffer_t b, lds_void_ptr to, int lane_off, int off) {
+  // (cached, also weights that one workgroup reads: past the caches, as the other kernels load them, these loads are up to a third slower)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(b, to, 16, lane_off, off, 0, 0);
+}
+#else   // (the host pass knows neither the type nor the instruction)
+typedef int buffer_t;
+__device__ inline buffer_t buffer_at(const char*) { return 0; }
+__device__ inline void buffer_to_lds(buffer_t, lds_void_ptr, int, int) {}
+#endif
+
+// QKV epilogue of a block's wavefront: NTW neighbouring output tiles x MTW batch tiles.  Where a batch row's K and V go is
+// looked up while the first operands are on their way (slot: element of the layer's pool at head 0, channel 0; -1: nowhere),
+// and the rotary pairs of one batch tile are fetched while the one before is stored: looked up tile by tile, as the other
+// kernels do, each tile waits for a chain of dependent loads behind the stores of the last.
+__device__ inline long kv_slot(const QkvEpi& e, int m, int M) {
+  if (m >= M) return -1;
+  const int p = e.context_lens[m];
+  if ((unsigned)p >= (unsigned)(e.max_blocks * 16)) return -1;
+  const int blk = e.block_tables[(size_t)(e.row_table ? safe_row(e.row_table[m], e.table_rows) : m) * e.max_blocks + (p >> 4)];
+  if ((unsigned)blk >= (unsigned)e.num_blocks) return -1;   // never outside the pools
+  return ((long)blk * e.n_heads * 16 + (p & 15)) * e.head_dim;
+}
+template <int MTW, int NTW>
+__device__ inline void finish_qkv(const f32x16 (&acc)[NTW][MTW], int nt0, int n_tiles, int mtile0, const long (&slot)[MTW], const GemmShape& g,
+                                  const QkvEpi& e, int lane) {
+  const int d = e.d_model, dh = e.head_dim, hdim = dh >> 1, sub = (lane >> 5) * 4;
+  typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
+  float4 cs[2][NTW][2][2];
+  auto fetch = [&](int mt, float4 (&c)[NTW][2][2]) {
+    const int m = min((mtile0 + mt) * 32 + (lane & 31), g.M - 1);
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) {
+      const int f0 = packed_row_lo(nt0 + t, 0, g.pair_stride), j0 = f0 % dh;
+      if (nt0 + t < n_tiles && f0 < 2 * d && e.rope_theta > 0.0f) {
+        const float2* src = e.rope + (size_t)m * hdim + j0 + sub;
+#pragma unroll
+        for (int run = 0; run < 2; ++run) {
+          c[t][run][0] = *reinterpret_cast<const float4*>(src + run * 8);
+          c[t][run][1] = *reinterpret_cast<const float4*>(src + run * 8 + 2);
+        }
+      }
+    }
+  };
+  fetch(0, cs[0]);
+#pragma unroll
+  for (int mt = 0; mt < MTW; ++mt) {
+    if (mt + 1 < MTW) fetch(mt + 1, cs[(mt + 1) & 1]);
+    const int m = (mtile0 + mt) * 32 + (lane & 31);
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) {
+      if (nt0 + t >= n_tiles) break;
+      const int f0 = packed_row_lo(nt0 + t, 0, g.pair_stride);   // all of this is the same for the whole wavefront
+      const int which = f0 / d, within = f0 - which * d, head = within / dh, j = within - head * dh + sub;
+      const bool turn = which < 2 && e.rope_theta > 0.0f;
+#pragma unroll
+      for (int run = 0; run < 2; ++run) {
+        const float4 c01 = cs[mt & 1][t][run][0], c23 = cs[mt & 1][t][run][1];
+        const float co[4] = {c01.x, c01.z, c23.x, c23.z}, si[4] = {c01.y, c01.w, c23.y, c23.w};
+        float lo[4], hi[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float a = acc[t][mt][run * 4 + i], b = acc[t][mt][run * 4 + i + 8];
+          lo[i] = turn ? a * co[i] - b * si[i] : a;
+          hi[i] = turn ? b * co[i] + a * si[i] : b;
+        }
+        if (which == 0) {
+          if (m < g.M && e.q) {
+            float* q = e.q + (size_t)m * d + head * dh + j + run * 8;
+            *reinterpret_cast<float4*>(q) = make_float4(lo[0], lo[1], lo[2], lo[3]);
+            *reinterpret_cast<float4*>(q + hdim) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+          }
+        } else if (slot[mt] >= 0) {
+          bf16_t* at = reinterpret_cast<bf16_t*>(which == 1 ? e.k_pool : e.v_pool) + slot[mt] + (long)head * 16 * dh + j + run * 8;
+          *reinterpret_cast<bf16x4*>(at) = bf16x4{(bf16_t)lo[0], (bf16_t)lo[1], (bf16_t)lo[2], (bf16_t)lo[3]};
+          *reinterpret_cast<bf16x4*>(at + hdim) = bf16x4{(bf16_t)hi[0], (bf16_t)hi[1], (bf16_t)hi[2], (bf16_t)hi[3]};
+        }
+      }
+    }
+  }
+}
+
+template <int MT, int NT, int WM, int WN, int NL, int U, int DS, class Epi>
+__device__ __forceinline__ void block_body(u32x4* ring, const GemmShape& g, const Epi& e, int ksplit, int bm, int bn, int ksl, int M_eff) {
+  constexpr int P = MT + NT, CW = WM * WN, T = U * P / NL, MTW = MT / WM, NTW = NT / WN, G = U < 2 ? 2 : U;
+  static_assert(U * P % NL == 0 && MT % WM == 0 && NT % WN == 0 && DS > 2 && (DS - 1) * T < 64, "");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m_tiles = (g.M + 31) >> 5, k_steps = g.K >> 4;
+  const int ks0 = (int)((long)k_steps * ksl / ksplit), n = (int)((long)k_steps * (ksl + 1) / ksplit) - ks0;
+  const int stages = n / G * (G / U);   // whole groups of G steps; the rest follows one by one
+  const int rest = n % G;
+
+  if (wave >= CW) {   // a loader: its share of the pieces of every stage
+    const int lw = wave - CW;
+    const size_t tile_bytes = (size_t)k_steps * 1024;
+    const buffer_t wsrc = buffer_at(reinterpret_cast<const char*>(g.w) + (g.tile_begin + (size_t)bn * NT) * tile_bytes + (size_t)ks0 * 1024);
+    const buffer_t xsrc = buffer_at(reinterpret_cast<const char*>(g.x) + (size_t)bm * MT * tile_bytes + (size_t)ks0 * 1024);
+    int off[T];
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+      const int t = (i * NL + lw) % P;
+      off[i] = (int)((t < MT ? min(t, m_tiles - 1 - bm * MT) : min(t - MT, g.n_tiles - 1 - bn * NT)) * tile_bytes) + lane * 16;
+    }
+    auto issue = [&](int s, int slot) {
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        const int piece = i * NL + lw;
+        buffer_to_lds(piece % P < MT ? xsrc : wsrc, (lds_void_ptr)(ring + ((size_t)slot * U * P + piece) * 64), off[i],
+                      min(s * U + piece / P, n - 1) * 1024);
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < DS; ++s) {
+      issue(s, s);
+      asm volatile("" ::: "memory");
+    }
+    wait_loads_but<(DS - 1) * T>();
+    __builtin_amdgcn_s_barrier();
+    int slot = 0;
+    for (int s = 0; s < stages; ++s) {
+      wait_loads_but<(DS - 2) * T>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      issue(s + DS, slot);
+      slot = slot + 1 == DS ? 0 : slot + 1;
+    }
+    wait_loads_but<0>();   // (the loads past the end still target LDS)
+    return;
+  }
+  const int wm = wave % WM, wn = wave / WM;
+  u32x4 fx[2][MTW], fw[2][NTW];
+  auto read = [&](int slot, int u, int b) {
+    const u32x4* sp = ring + (size_t)(slot * U + u) * P * 64 + lane;
+#pragma unroll
+    for (int t = 0; t < MTW; ++t) fx[b][t] = sp[(wm * MTW + t) * 64];
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) fw[b][t] = sp[(MT + wn * NTW + t) * 64];
+  };
+  long kv_at[MTW];
+  if constexpr (std::is_same<Epi, QkvEpi>::value) {
+#pragma unroll
+    for (int mt = 0; mt < MTW; ++mt) kv_at[mt] = kv_slot(e, (bm * MT + wm * MTW + mt) * 32 + (lane & 31), g.M);
+  }
+  f32x16 acc[NTW][MTW];
+#pragma unroll
+  for (int t = 0; t < NTW; ++t)
+#pragma unroll
+    for (int mt = 0; mt < MTW; ++mt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[t][mt][i] = 0.0f;
+  auto multiply = [&](int b) {
+#pragma unroll
+    for (int t = 0; t < NTW; ++t)
+#pragma unroll
+      for (int mt = 0; mt < MTW; ++mt)
+        acc[t][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fw[b][t]),
+                                                             __builtin_bit_cast(bf16x8, fx[b][mt]), acc[t][mt], 0, 0, 0);
+  };
+  auto all_meet = [&]() {
+    // the loaders' pieces of the next stage have landed; this wavefront's fragments of the present one are in registers
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  read(0, 0, 0);
+  int slot = 0;
+  for (int s = 0; s < stages; s += G / U) {
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      constexpr int NM = MTW * NTW, RPM = MTW + NTW > 2 * NM ? 3 : 2;
+      __builtin_amdgcn_sched_barrier(0);
+      if (u % U == U - 1) {
+        all_meet();
+        slot = slot + 1 == DS ? 0 : slot + 1;
+        read(slot, 0, (u + 1) & 1);
+      } else {
+        read(slot, u % U + 1, (u + 1) & 1);
+      }
+      multiply(u & 1);
+      // fragment reads go out behind the first multiplies
+#pragma unroll
+      for (int i = 0; i < NM; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);
+      }
+    }
+  }
+  // fewer than G steps are left: the next stage (G > U: one step, its only one), which has landed
+  for (int u = 0; u < rest; ++u) {
+    read(slot, u, 0);
+    multiply(0);
+  }
+  if constexpr (std::is_same<Epi, QkvEpi>::value) {
+    finish_qkv<MTW, NTW>(acc, g.tile_begin + bn * NT + wn * NTW, g.tile_begin + g.n_tiles, bm * MT + wm * MTW, kv_at, g, e, lane);
+  } else {
+#pragma unroll
+    for (int mt = 0; mt < MTW; ++mt) {
+      const int mtile = bm * MT + wm * MTW + mt, nt0 = bn * NT + wn * NTW;
+      if (mtile >= m_tiles) continue;
+      if constexpr (std::is_same<Epi, LmEpi>::value) {
+        if (nt0 + NTW <= g.n_tiles) {
+          finish_lm<NTW>([&](int t, int a) { return acc[t][mt][a]; }, g.tile_begin + nt0, mtile, M_eff, g, e, lane);
+        } else {
+#pragma unroll
+          for (int t = 0; t < NTW; ++t)
+            if (nt0 + t < g.n_tiles) finish_lm<1>([&](int, int a) { return acc[t][mt][a]; }, g.tile_begin + nt0 + t, mtile, M_eff, g, e, lane);
+        }
+      } else {
+#pragma unroll
+        for (int t = 0; t < NTW; ++t)
+          if (nt0 + t < g.n_tiles) finish_from_registers(acc[t][mt], g.tile_begin + nt0 + t, mtile, M_eff, ksl, g, e, lane);
+      }
+    }
+  }
+}
+
+template <int MT, int NT, int WM, int WN, int NL, int U, int DS, bool HALVES, class Epi>
+__global__ __launch_bounds__((WM * WN + NL) * 64) void gemm_block_kernel(GemmShape g, Epi e, Pred pred, BlockGrid bg) {
+  __shared__ u32x4 ring[DS * U * (MT + NT) * 64];   // [stage][step][tile][lane]
+  if (pred_skip(pred)) return;
+  // Ids congruent modulo 8 share an XCD: the row blocks of a column block run on one, neighbouring column blocks too.
+  const int xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3, nq = bg.col_blocks * bg.ksplit, per = (nq + 7) >> 3;
+  int bm = HALVES ? j / per : j % bg.row_blocks;
+  const int q = nq * xcd / 8 + (HALVES ? j % per : j / bg.row_blocks);
+  if (q >= nq * (xcd + 1) / 8) return;
+  int bn = q / bg.ksplit;
+  const int ksl = q % bg.ksplit;
+  if constexpr (HALVES) {
+    // compacted operand: only the first *n_rows_dev rows hold sequences that are still active.  Where that leaves half of the
+    // row blocks without work, two workgroups share a column block (7B shape, 128 rows active of 256: gate/up 63 -> 48 us).
+    const int M_eff = g.n_rows_dev[0], active = (M_eff + MT * 32 - 1) / (MT * 32);
+    if (active * 2 <= bg.row_blocks) {
+      constexpr int HM = NT / 2 % WN ? WM * WN : WM, HN = WM * WN / HM;   // wavefronts, rows x columns
+      if (active == 0 || bm >= 2 * active) return;
+      bn = bn * 2 + bm / active;
+      if (bn * (NT / 2) >= g.n_tiles) return;
+      block_body<MT, NT / 2, HM, HN, NL, U, DS>(ring, g, e, bg.ksplit, bm % active, bn, ksl, M_eff);
+    } else if (bm < active) {
+      block_body<MT, NT, WM, WN, NL, U, DS>(ring, g, e, bg.ksplit, bm, bn, ksl, M_eff);
+    }
+  } else {
+    block_body<MT, NT, WM, WN, NL, U, DS>(ring, g, e, bg.ksplit, bm, bn, ksl, g.M);
+  }
+}
+
 // Which shapes the ring kernel serves: 385 to 512 rows (two row blocks, the second at least half full: below that the
 // tiled kernel's 128-row chunks waste less; above, the workgroups no longer fit the chip in one round), whole blocks
 // of eight weight tiles, a contraction of whole groups of sixteen steps.
@@ -831,41 +1092,90 @@ bool ring_serves(int M, int n_tiles, int K) {
   return M > 384 && M <= 512 && n_tiles % 8 == 0 && (K >> 4) % (RING_D + 1) == 0 && (K & 15) == 0;
 }
 
-// Batch tiles per pass of the streaming kernel / per chunk of the tiled kernel.
-int pick_mt(int M, int cap) {
-  const int m_tiles = (M + 31) / 32;
-  for (int mt = cap; mt > 1; mt >>= 1)
-    if (m_tiles % mt == 0) return mt;
-  return 1;
-}
-
 // From three batch tiles on, the tiled kernel (128-row chunks, the last one padded) beats re-streaming the weights
 // once per pass of the streaming kernel.
 bool tiled(int M, int n_tiles) { return (M + 31) / 32 >= 3 && n_tiles % NW == 0; }
+
+// Time of a projection in blocks of mt batch tiles x nt weight tiles over `steps` contraction steps, in ns: the blocks go round
+// by round over 256 compute units, and a step takes a compute unit what its operands take to come in (22 ns a KiB of weights,
+// 14 ns a KiB of activations: fitted to the kernel without multiplies, 128 x 192 blocks 48 us over 256 steps, 256 x 96 44,
+// 128 x 96 31) or what its multiplies take (7 ns a tile: 256 x 192 blocks 92 us).  Start, first loads and epilogue of a
+// round: 5 us.
+constexpr long block_cost(int m_tiles, int n_tiles, int steps, int mt, int nt) {
+  const long blocks = (long)((m_tiles + mt - 1) / mt) * ((n_tiles + nt - 1) / nt), in = 22 * nt + 14 * mt, mul = 7 * mt * nt;
+  return (blocks + 255) / 256 * (5000 + steps * (in > mul ? in : mul));
+}
+// The cheapest of a kernel's block shapes for a projection; of a compacted operand, of those that come in halves.
+struct BlockShape {
+  int mt, nt;
+};
+template <int N>
+BlockShape pick_block(const BlockShape (&shapes)[N], int m_tiles, int n_tiles, int steps, bool compacted = false) {
+  BlockShape best{0, 0};
+  long best_cost = 0;
+  for (const BlockShape& b : shapes) {
+    if (compacted && (b.mt != 4 || b.nt % 2)) continue;
+    const long c = block_cost(m_tiles, n_tiles, steps, b.mt, b.nt);
+    if (best.mt == 0 || c < best_cost) {
+      best = b;
+      best_cost = c;
+    }
+  }
+  return best;
+}
+constexpr BlockShape kQkvBlocks[] = {{2, 3}, {4, 2}, {4, 3}, {4, 4}, {4, 6}}, kGateUpBlocks[] = {{4, 3}, {4, 4}, {4, 6}, {8, 4}, {8, 6}},
+                     kLmBlocks[] = {{4, 4}, {4, 8}}, kAccBlocks[] = {{4, 2}, {4, 4}, {8, 4}};
 
 // Which kernel an accumulate projection (output or down projection) of M rows onto n_tiles packed tiles over a
 // contraction of K runs in, and how many contraction slices it writes.  Every slice is one more partial result for
 // the normalisation launch to read, so the count stays as small as filling the chip allows.
 struct AccPlan {
-  int kind;     // 0: streaming kernel, 1: tiled kernel with 128-row chunks, 2: tiled kernel, one chunk of one or two tiles,
+  int kind;     // 0: streaming kernel, 1: block kernel, 2: tiled kernel, one chunk of up to four tiles,
                 // 3: streaming kernel, two output tiles per workgroup
   int ksplit;
+  BlockShape block;
 };
-AccPlan acc_plan(int M, int n_tiles, int K) {
-  const int m_tiles = (M + 31) / 32, k_steps = K / 16;
-  AccPlan p{0, 1};
-  if (tiled(M, n_tiles)) {
-    const int chunks = (m_tiles + 3) / 4, groups = n_tiles / NW;
-    // one workgroup per compute unit (measured at 96-512 rows: better than two), slices of at least 64 steps
+// Slices hold at least 64 contraction steps; the normalisation launch adds at most eight, of 128 rows, four of 512.
+int acc_slices_most(int m_tiles, int K) {
+  const int by_k = K / 1024 < 1 ? 1 : K / 1024, by_m = m_tiles <= 4 ? 8 : m_tiles <= 16 ? 4 : 64 / m_tiles < 1 ? 1 : 64 / m_tiles;
+  return by_k < by_m ? by_k : by_m;
+}
+AccPlan acc_plan(int M, int n_tiles, int K, bool compacted = false) {
+  const int m_tiles = (M + 31) / 32, k_steps = K / 16, most = acc_slices_most(m_tiles, K);
+  AccPlan p{0, 1, {0, 0}};
+  // (One row chunk: more than 128 tiles or 512 steps stay with the tiled kernel, bound by the weight stream either way: 13B output
+  // projection at 128 rows 19.1 against 19.6 us in blocks, down projection 35.9 against 40.0.)
+  const bool one_chunk = m_tiles <= 4 && n_tiles % NW == 0 && (k_steps >= 512 || (m_tiles >= 3 && n_tiles > 128));
+  if (m_tiles >= 3 && !one_chunk) {
+    // A slice costs its partial result's way out and back in: 8 bytes an element at 5 TB/s.  (7B shape, 512 rows: down projection
+    // 59 -> 48 us in four slices of 256 x 128 blocks, output projection 26 -> 22 in two of 128 x 128; 128 rows: output projection
+    // 15.0 -> 11.7 in four of 128 x 64 instead of eight.)
     p.kind = 1;
-    p.ksplit = 256 / (groups * chunks);
-  } else if (m_tiles <= 2 && n_tiles % NW == 0 && k_steps >= 512) {
+    long best = 0;
+    for (int ks = 1; ks <= most; ++ks)
+      for (const BlockShape& b : kAccBlocks) {
+        const long c = block_cost(m_tiles, (n_tiles + b.nt - 1) / b.nt * b.nt * ks, (k_steps + ks - 1) / ks, b.mt, b.nt) + (long)ks * m_tiles * n_tiles * 1024 * 8 / 5000;
+        if (p.block.mt == 0 || c < best) {
+          best = c;
+          p.block = b;
+          p.ksplit = ks;
+        }
+      }
+    if (compacted) p.block = pick_block(kAccBlocks, m_tiles, n_tiles * p.ksplit, k_steps / p.ksplit, true);
+    return p;
+  }
+  if (one_chunk) {
     p.kind = 2;
     p.ksplit = 256 / (n_tiles / NW);
-  } else if (m_tiles <= 2 && n_tiles % 2 == 0 && n_tiles > 128 && n_tiles < 256 && k_steps / 64 >= 512 / n_tiles) {
+  } else if (m_tiles == 2 && n_tiles >= 128 && n_tiles <= 512) {
+    // 64 x 64 blocks: 7B output projection 11.6 -> 9.1 us at 64 rows (its four wavefronts no longer fetch an operand each)
+    p.kind = 1;
+    p.block = {2, 2};
+    p.ksplit = 512 / n_tiles;
+  } else if (m_tiles == 1 && n_tiles % 2 == 0 && n_tiles > 128 && n_tiles < 256 && k_steps / 64 >= 512 / n_tiles) {
     // One tile per workgroup would need two slices and a second round of workgroups for the remainder: two tiles and up to
-    // three slices fit one round (13B output projection, 160 tiles: 22.1 -> 16.7 us at 64 rows, 16.1 -> 13.8 at 32).  At 128 tiles
-    // two slices fill the chip exactly, and four of two tiles cost the normalisation more than they gain (12.6 against 13.0).
+    // three slices fit one round (13B output projection, 160 tiles: 16.1 -> 13.8 us at 32 rows).  At 128 tiles two slices fill the
+    // chip exactly, and four of two tiles cost the normalisation more than they gain (12.6 against 13.0).
     p.kind = 3;
     p.ksplit = 512 / n_tiles;
   } else {
@@ -873,8 +1183,7 @@ AccPlan acc_plan(int M, int n_tiles, int K) {
     // compute unit, no more
     p.ksplit = (256 + n_tiles - 1) / n_tiles;
   }
-  if (p.ksplit > k_steps / 64) p.ksplit = k_steps / 64;
-  if (p.ksplit > 8) p.ksplit = 8;   // the normalisation launch adds at most eight partial results
+  if (p.ksplit > most) p.ksplit = most;
   if (p.ksplit < 1) p.ksplit = 1;
   return p;
 }
@@ -892,67 +1201,114 @@ bool ring_allowed() {
   return ok > 0;
 }
 
+// Wavefronts (rows x columns of the block; two loaders), steps a stage and stages of each block shape: two workgroups fit a
+// compute unit but for the widest blocks.
+template <int MT, int NT, int WM, int WN, int U, int DS, class Epi>
+void launch_block(const GemmShape& g, const Epi& e, Pred pred, int ksplit, hipStream_t st) {
+  const BlockGrid bg{((g.M + 31) / 32 + MT - 1) / MT, (g.n_tiles + NT - 1) / NT, ksplit};
+  const dim3 grid((bg.col_blocks * ksplit + 7) / 8 * 8 * bg.row_blocks), block((WM * WN + 2) * 64);
+  if constexpr (MT == 4 && NT % 2 == 0 && !std::is_same<Epi, QkvEpi>::value) {
+    if (g.n_rows_dev) {
+      hipLaunchKernelGGL((gemm_block_kernel<MT, NT, WM, WN, 2, U, DS, true, Epi>), grid, block, 0, st, g, e, pred, bg);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((gemm_block_kernel<MT, NT, WM, WN, 2, U, DS, false, Epi>), grid, block, 0, st, g, e, pred, bg);
+}
+template <class Epi>
+void launch_blocks(BlockShape b, const GemmShape& g, const Epi& e, Pred pred, int ksplit, hipStream_t st) {
+  constexpr bool QKV = std::is_same<Epi, QkvEpi>::value, ACC = std::is_same<Epi, AccEpi>::value, GATE = std::is_same<Epi, GateUpEpi>::value,
+                 LM = std::is_same<Epi, LmEpi>::value;
+  switch (b.mt * 16 + b.nt) {
+    case 0x22: if constexpr (ACC) launch_block<2, 2, 2, 1, 2, 8>(g, e, pred, ksplit, st); break;
+    case 0x23: if constexpr (QKV) launch_block<2, 3, 2, 1, 2, 8>(g, e, pred, ksplit, st); break;
+    case 0x42: if constexpr (QKV || ACC) launch_block<4, 2, 4, 1, 2, 6>(g, e, pred, ksplit, st); break;
+    case 0x43: if constexpr (QKV || GATE) launch_block<4, 3, 4, 1, 2, 5>(g, e, pred, ksplit, st); break;
+    case 0x44: launch_block<4, 4, 2, 2, 2, 5>(g, e, pred, ksplit, st); break;
+    case 0x46: if constexpr (QKV || GATE) launch_block<4, 6, 2, 2, 2, 4>(g, e, pred, ksplit, st); break;
+    case 0x48: if constexpr (LM) launch_block<4, 8, 2, 2, 2, 5>(g, e, pred, ksplit, st); break;
+    case 0x84: if constexpr (GATE || ACC) launch_block<8, 4, 2, 2, 2, 5>(g, e, pred, ksplit, st); break;
+    case 0x86: if constexpr (GATE) launch_block<8, 6, 4, 2, 2, 5>(g, e, pred, ksplit, st); break;
+  }
+}
+
 template <class Epi, bool FILL>
 void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int nz, hipStream_t st,
             const CombineJob& cj = CombineJob{}) {
   dim3 block(256);
   const int m_tiles = (g.M + 31) / 32;
-  constexpr bool ACC = std::is_same<Epi, AccEpi>::value;
-  const AccPlan ap = ACC ? acc_plan(g.M, g.n_tiles, g.K) : AccPlan{0, 1};
-  // Batch chunks of 4 tiles (128 rows) measured faster than 8 at batch 256 and 512: twice the workgroups, each
-  // with half the accumulators, keeps more loads in flight; the second chunk's weight reads mostly hit the caches.
-  if (tiled(g.M, g.n_tiles)) {
-    // tiled kernel: the workgroup's output tiles share the activation operand through LDS
-    const int chunks = (m_tiles + 3) / 4;
-    // One output tile per wavefront, except for the LM head (below).
-    const int groups = g.n_tiles / NW;
-    const int ksplit = ap.ksplit;
-    if constexpr (std::is_same<Epi, QkvEpi>::value && !FILL) {
-      // Few output tiles and one 128-row chunk leave most compute units idle (QKV at 7B width: 96 workgroups):
-      // 64-row chunks double the workgroups as long as they all still start at once (measured at 128 rows:
-      // 61 -> 45 us; with more workgroups than compute units the second weight pass costs more than it gains).
-      const int chunks2 = (m_tiles + 1) / 2;
-      if (!g.n_rows_dev && groups * chunks < 128 && groups * chunks2 <= 256) {
-        GemmShape g2 = g;
-        g2.grid_y = chunks2;
-        dim3 grid2((groups + 7) / 8 * 8 * chunks2, 1, nz);
-        hipLaunchKernelGGL((gemm_tiled_kernel<2, 1, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc);
+  constexpr bool ACC = std::is_same<Epi, AccEpi>::value, LM = std::is_same<Epi, LmEpi>::value;
+  const AccPlan ap = ACC ? acc_plan(g.M, g.n_tiles, g.K, g.n_rows_dev != nullptr) : AccPlan{0, 1, {0, 0}};
+  const int k_steps = g.K >> 4;
+  if constexpr (!FILL) {
+    // Block kernel: QKV and output projection from two batch tiles on, the down projection from three, gate/up and the LM head from
+    // five.  (7B shape: QKV at 64 / 128 / 192 / 256 / 512 rows 28 -> 26, 37 -> 31, 45 -> 34, 47 -> 41, 77 -> 59 us, gate/up at 192 /
+    // 256 / 384 / 512 75 -> 52, 75 -> 59, 112 -> 88, 123 -> 92; at 128 rows and fewer gate/up and the LM head are bound by the weight
+    // stream either way: 44 against 43 to 46, 47 against 51.)
+    if constexpr (ACC) {
+      if (ap.kind == 1) {
+        launch_blocks(ap.block, g, e, pred, ap.ksplit, st);
         return;
       }
-    }
-    if constexpr (!FILL && (std::is_same<Epi, LmEpi>::value || std::is_same<Epi, GateUpEpi>::value)) {
-      // if the runtime refused the ring its 128 KiB of dynamic LDS, the tiled kernel below serves the shape
-      if (ring_allowed<Epi>() && !g.n_rows_dev && ring_serves(g.M, g.n_tiles, g.K)) {
+    } else if constexpr (std::is_same<Epi, QkvEpi>::value) {
+      if (m_tiles >= 3) {
+        launch_blocks(pick_block(kQkvBlocks, m_tiles, g.n_tiles, k_steps), g, e, pred, 1, st);
+        return;
+      }
+    } else {
+      // if the runtime refused the ring its 128 KiB of dynamic LDS, another kernel serves the shape
+      const bool ring = !g.n_rows_dev && ring_serves(g.M, g.n_tiles, g.K) && ring_allowed<Epi>();
+      // (three or four batch tiles: weight tiles that the tiled kernel does not take, unless a short contraction makes the start of
+      // a block most of its time: 50 tiles of 24 steps 6.3 us in the streaming kernel, 7.3 in blocks, 157 of 44 10.1 against 9.4)
+      const bool blocks = m_tiles >= 5 || (m_tiles >= 3 && g.n_tiles % NW && (m_tiles == 3 || k_steps > 44 || g.n_tiles > 128));
+      if constexpr (std::is_same<Epi, GateUpEpi>::value) {
+        const BlockShape b = pick_block(kGateUpBlocks, m_tiles, g.n_tiles, k_steps, g.n_rows_dev != nullptr);
+        const long ring_cost = block_cost(m_tiles, g.n_tiles, k_steps, 8, 8);
+        if (blocks && !(ring && ring_cost < block_cost(m_tiles, g.n_tiles, k_steps, b.mt, b.nt))) {
+          launch_blocks(b, g, e, pred, 1, st);
+          return;
+        }
+      } else if (blocks && (g.n_rows_dev || !ring_serves(g.M, g.n_tiles, g.K))) {
+        // 128 x 256 blocks are what the tiled kernel has with two tiles per wavefront: they pay from 192 steps on (140 to 192 rows, 1000
+        // tiles: 128 steps 39.4 -> 41.8 us, 256 steps 76 to 74 -> 66 to 70; 320 to 384 rows: 124 to 126 -> 114 to 118), not where that
+        // kernel's two 128-row chunks are nearly full (200 to 256 rows: 73 to 76 both ways).
+        const BlockShape b = pick_block(kLmBlocks, m_tiles, g.n_tiles, k_steps, g.n_rows_dev != nullptr);
+        if (g.n_rows_dev || b.nt < 8 || (k_steps >= 192 && (m_tiles < 7 || m_tiles > 8)) || g.n_tiles % (2 * NW)) {
+          launch_blocks(b, g, e, pred, 1, st);
+          return;
+        }
+      }
+      if (ring) {
         const int row_blocks = (m_tiles + 7) / 8, col_blocks = g.n_tiles / 8;
         dim3 gridr((col_blocks + 7) / 8 * 8 * row_blocks, 1, 1);
         hipLaunchKernelGGL((gemm_ring_kernel<Epi>), gridr, block, RING_LDS_BYTES, st, g, e, pred);
         return;
       }
     }
-    // From how many working row chunks on the weights are loaded to stay in the L2 that the chunks share, instead of past
-    // it: with one reader the plain load costs 10 % (LM head, 128 rows: 53 against 59 us), with two the second one's misses
-    // are worth more (gate/up of the 7B shape at 256 rows: 90 -> 77 us, at 384: 116 -> 95; LM head of 256 compacted rows:
-    // 105 -> 94).  QKV, one workgroup of the grid per unit and fewer, gains from three on (256 rows: 48.5 against 50.5 us,
-    // 384 rows: 80 -> 74).  The sliced projections and the LM head with two tiles per wavefront gain nothing.
-    GemmShape g4 = g;
-    g4.grid_y = chunks * ksplit;
-    g4.keep_chunks = ACC ? 0 : std::is_same<Epi, QkvEpi>::value ? 3 : 2;
-    if constexpr (!FILL && std::is_same<Epi, LmEpi>::value) {
-      // LM head: two output tiles per wavefront (each LDS operand read feeds two MFMAs, half the workgroups):
-      // 161 -> 153 us at 512 rows.  The same arrangement is slower for gate/up (119 -> 135 us) and is not used there.
-      // (from two 128-row chunks on: with one chunk it would halve the workgroups below the compute units; for the same
-      // reason not with a compacted operand, where often only the first chunk holds rows)
-      if (g.n_tiles % (2 * NW) == 0 && chunks >= 2 && !g.n_rows_dev) {
-        const int groups2 = g.n_tiles / (2 * NW);
-        g4.keep_chunks = 0;
-        dim3 grid2((groups2 + 7) / 8 * 8 * chunks * ksplit, 1, nz);
-        hipLaunchKernelGGL((gemm_tiled_kernel<4, 2, Epi, FILL>), grid2, block, 0, st, g4, e, pred, fc);
-        return;
+  }
+  // Tiled kernel: KV filling, gate/up and the LM head at three and four batch tiles, the LM head where block_cost leaves it.  Batch chunks of 4 tiles (128 rows) measured faster than 8 at batch 256 and 512: twice the
+  // workgroups, each with half the accumulators, keeps more loads in flight; the second chunk's weight reads mostly hit the caches.
+  if constexpr (FILL || LM || std::is_same<Epi, GateUpEpi>::value) {
+    if (tiled(g.M, g.n_tiles)) {
+      const int chunks = (m_tiles + 3) / 4, groups = g.n_tiles / NW;
+      // Weights that three row chunks and more read are loaded to stay in the L2 that the chunks share, instead of past it.
+      GemmShape g4 = g;
+      g4.grid_y = chunks;
+      g4.keep = FILL && chunks >= 3;
+      if constexpr (LM) {
+        // Two output tiles per wavefront (each LDS operand read feeds two MFMAs, half the workgroups): 161 -> 153 us at 512
+        // rows.
+        if (g.n_tiles % (2 * NW) == 0 && chunks >= 2) {
+          const int groups2 = g.n_tiles / (2 * NW);
+          dim3 grid2((groups2 + 7) / 8 * 8 * chunks, 1, nz);
+          hipLaunchKernelGGL((gemm_tiled_kernel<4, 2, Epi, FILL>), grid2, block, 0, st, g4, e, pred, fc);
+          return;
+        }
       }
+      dim3 grid((groups + 7) / 8 * 8 * chunks, 1, nz);
+      hipLaunchKernelGGL((gemm_tiled_kernel<4, 1, Epi, FILL>), grid, block, 0, st, g4, e, pred, fc);
+      return;
     }
-    dim3 grid((groups + 7) / 8 * 8 * chunks * ksplit, 1, nz);
-    hipLaunchKernelGGL((gemm_tiled_kernel<4, 1, Epi, FILL>), grid, block, 0, st, g4, e, pred, fc);
-    return;
   }
   // One or two batch tiles: the tiled kernel still wins where enough output tiles keep the chip busy with four
   // tiles per workgroup (its four wavefronts share every activation tile through LDS, a quarter of the L2 reads
@@ -976,47 +1332,53 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
       }
       if (m_tiles == 1)
         hipLaunchKernelGGL((gemm_tiled_kernel<1, 1, Epi, FILL>), grid1, block, 0, st, gs, e, pred, fc);
-      else
+      else if (!ACC || m_tiles == 2)
         hipLaunchKernelGGL((gemm_tiled_kernel<2, 1, Epi, FILL>), grid1, block, 0, st, gs, e, pred, fc);
+      else if constexpr (ACC)
+        hipLaunchKernelGGL((gemm_tiled_kernel<4, 1, Epi, FILL>), grid1, block, 0, st, gs, e, pred, fc);
       return;
     }
   }
-  // Two tiles per workgroup where they fill the chip in one round.
-  // QKV, two batch tiles: pairs on 129 to 256 workgroups (264 tiles: 24.4 -> 22.6 us, 384: 34 -> 31, 480: 45 -> 38).  One batch tile:
-  // up to 384 tiles 2 * split_tiles whole tiles with a half each (294 tiles: 20.5 -> 19.0, 384: 24.2 -> 22.7), beyond pairs (480:
+  // Streaming kernel.  Two tiles per workgroup where they fill the chip in one round.
+  // QKV, two batch tiles: pairs on 129 to 256 workgroups (264 tiles: 24.4 -> 22.6 us, 384: 34 -> 31, 480: 45 -> 38; 64 x 64 blocks: as fast, 38.3
+  // against 37.8).  One batch tile: up to 384 tiles 2 * split_tiles whole tiles with a half each (294 tiles: 20.5 -> 19.0, 384: 24.2 -> 22.7), beyond pairs (480:
   // 39 -> 31); at 288 tiles and fewer the idle compute units cost more than the shared operand saves (pairs of 288: 19.1 -> 20.3,
   // of 264: 17.4 -> 19.6).
   // Gate/up whose tiles do not divide by four: two batch tiles only (258 to 506 tiles: 16.1 -> 15.9, 17.5 -> 16.5, 18.1 -> 17.4,
   // 19.7 -> 19.6; one: 12.5 -> 13.4, 13.9 -> 14.5, 14.4 -> 14.9, 15.8 -> 17.7).  The LM head gains at neither (16 rows: 12.7 to 15.4 ->
   // 14.0 to 18.1, 64 rows: 16.8 to 19.9 -> 17.0 to 20.9): its statistics follow each tile.
-  if constexpr (!FILL && !std::is_same<Epi, LmEpi>::value) {
-    constexpr bool QKV = std::is_same<Epi, QkvEpi>::value, GATE = std::is_same<Epi, GateUpEpi>::value;
-    const bool one_half = QKV && m_tiles == 1 && 3 * g.split_tiles == g.n_tiles && g.split_tiles > 96 && g.split_tiles <= 128;
-    const bool pairs = m_tiles <= 2 && g.n_tiles % 2 == 0 && g.n_tiles > (m_tiles == 1 ? 384 : 256) && g.n_tiles <= 512;
-    if (ACC ? ap.kind == 3 : one_half || (pairs && (QKV || m_tiles == 2))) {
-      GemmShape g2 = g;
-      if (!one_half) g2.split_tiles = 0;
-      const dim3 grid2((one_half ? 2 * g.split_tiles : g.n_tiles / 2) + cj.n_wg, ACC ? ap.ksplit : 1, nz);
-      if constexpr (!GATE) {
-        if (m_tiles == 1) {
-          hipLaunchKernelGGL((gemm_mfma_kernel<1, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
+  if constexpr (!FILL) {   // (KV filling has whole groups of four tiles)
+    if constexpr (!LM) {
+      constexpr bool QKV = std::is_same<Epi, QkvEpi>::value, GATE = std::is_same<Epi, GateUpEpi>::value;
+      const bool one_half = QKV && m_tiles == 1 && 3 * g.split_tiles == g.n_tiles && g.split_tiles > 96 && g.split_tiles <= 128;
+      const bool pairs = m_tiles <= 2 && g.n_tiles % 2 == 0 && g.n_tiles > (m_tiles == 1 ? 384 : 256) && g.n_tiles <= 512;
+      if (ACC ? ap.kind == 3 : one_half || (pairs && (QKV || m_tiles == 2))) {
+        GemmShape g2 = g;
+        if (!one_half) g2.split_tiles = 0;
+        const dim3 grid2((one_half ? 2 * g.split_tiles : g.n_tiles / 2) + cj.n_wg, ACC ? ap.ksplit : 1, nz);
+        if constexpr (!GATE) {
+          if (m_tiles == 1) {
+            hipLaunchKernelGGL((gemm_mfma_kernel<1, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
+            return;
+          }
+        }
+        if constexpr (!ACC) {
+          hipLaunchKernelGGL((gemm_mfma_kernel<2, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
           return;
         }
       }
-      hipLaunchKernelGGL((gemm_mfma_kernel<2, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
-      return;
     }
-  }
-  // split tiles take two workgroups each (one batch tile only); the workgroups of a combine job come first
-  dim3 grid(g.n_tiles + g.split_tiles + cj.n_wg, ACC ? ap.ksplit : 1, nz);
-  switch (pick_mt(g.M, 4)) {
-    case 4:
-      hipLaunchKernelGGL((gemm_mfma_kernel<4, 1, 2, Epi, FILL>), grid, block, 0, st, g, e, pred, fc, cj);
-      break;
-    case 2:
+    // split tiles take two workgroups each (one batch tile only); the workgroups of a combine job come first
+    dim3 grid(g.n_tiles + g.split_tiles + cj.n_wg, ACC ? ap.ksplit : 1, nz);
+    if constexpr (LM || std::is_same<Epi, GateUpEpi>::value) {
+      if (m_tiles == 4) {
+        hipLaunchKernelGGL((gemm_mfma_kernel<4, 1, 2, Epi, FILL>), grid, block, 0, st, g, e, pred, fc, cj);
+        return;
+      }
+    }
+    if (m_tiles == 2)
       hipLaunchKernelGGL((gemm_mfma_kernel<2, 1, 4, Epi, FILL>), grid, block, 0, st, g, e, pred, fc, cj);
-      break;
-    default:
+    else
       hipLaunchKernelGGL((gemm_mfma_kernel<1, 1, 8, Epi, FILL>), grid, block, 0, st, g, e, pred, fc, cj);
   }
 }
@@ -1031,6 +1393,17 @@ void gemm_bf16_prepare() {
 }
 
 int gemm_acc_slices(int M, int n_tiles, int K) { return acc_plan(M, n_tiles, K).ksplit; }
+
+// (the most that the plan may write at M rows or, where fewer rows come in more slices, at fewer)
+size_t gemm_acc_rows(int M, int K) {
+  const int m = (M + 31) / 32, m4 = m < 4 ? m : 4, m16 = m < 16 ? m : 16;
+  int tiles = m;
+  if (tiles < m4 * acc_slices_most(m4, K)) tiles = m4 * acc_slices_most(m4, K);
+  if (tiles < m16 * acc_slices_most(m16, K)) tiles = m16 * acc_slices_most(m16, K);
+  const int wide = K / 1024 * m < 64 ? K / 1024 * m : 64;   // more than 512 rows: up to 64 tiles in all
+  if (m > 16 && tiles < wide) tiles = wide;
+  return (size_t)tiles * 32;
+}
 
 bool gemm_qkv_carries_combine(int M) { return (M + 31) / 32 <= 2; }   // the streaming kernel serves these batches
 

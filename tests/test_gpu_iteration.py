@@ -328,6 +328,26 @@ def test_bf16_two_output_tiles_per_workgroup(heads, dh, batch):
     assert stats["near_threshold"] + stats["near_tie"] <= max(2, stats["tokens"] // 20), stats
 
 
+@pytest.mark.parametrize("heads,dh,d_ffn,batch", [
+    (3, 64, 16, 65),        # QKV: 18 tiles in blocks of 3 (64 x 96), the last batch tile of one row; down: a contraction of one step
+    (5, 64, 112, 97),       # QKV: 30 tiles; gate/up of seven tiles, down of seven steps (one past the last pair)
+    (18, 64, 48, 497),      # QKV: 108 tiles as 128 x 64
+    (12, 128, 48, 481),     # 144 as 128 x 96; output projection: 48 tiles
+    (17, 128, 48, 512),     # 204 as 128 x 128; output projection: 68 tiles, two slices
+    (22, 128, 48, 385),     # 264 as 128 x 192
+    (2, 128, 16 * 385, 129),    # gate/up: 385 tiles as 128 x 128, a second row block of one row; down: four slices of 96 or 97 steps
+    (2, 128, 16 * 551, 160),    # 551 as 128 x 192, the last block one of five tiles
+    (2, 128, 16 * 802, 170),    # 802 as 256 x 128, the last of two tiles
+    (1, 128, 16 * 700, 290),    # 700 as 256 x 192, the last of four tiles, a second row block of two
+])
+def test_bf16_projections_in_blocks(heads, dh, d_ffn, batch):
+    """Every block shape of the projections from 65 rows on, at ragged edges of rows, tiles and contraction."""
+    cfg = small_bf16(n_layers=1, d_model=heads * dh, n_heads=heads, head_dim=dh, d_ffn=d_ffn, vocab=512, batch=batch, prompt_len=2,
+                     min_prompt_len=1, weight_std=0.02, shuffled_blocks=True, threshold=2.0)
+    stats = lockstep(cfg, seed=62, steps=1)
+    assert stats["near_threshold"] + stats["near_tie"] <= max(2, stats["tokens"] // 20), stats
+
+
 @pytest.mark.parametrize("exit_every", [1, 2])
 def test_per_sequence_compaction_across_chunk_boundaries(exit_every):
     """Forced exits that take the number of active rows through 129, 128, 127, 1 and 0 (the projections work on

@@ -432,6 +432,14 @@ def test_exit_check_385_to_512_rows(batch, heads):
     run_exit_check(cfg, seed=50 + heads, layer=2, threshold=0.3, hidden_scale=3.0)
 
 
+@pytest.mark.parametrize("batch,heads,vocab", [(129, 2, 32), (150, 6, 1312), (161, 48, 8544), (300, 48, 16416), (600, 2, 1280)])
+def test_exit_check_in_blocks(batch, heads, vocab):
+    """LM head in 128 x 128 and 128 x 256 blocks: one tile, tiles that leave a wavefront one, or none, of its own (statistics of
+    tiles that do not exist would land in the next row's records), more than 512 rows."""
+    cfg = cfg_of("bf16", 64, heads, n_layers=4, vocab=vocab, logit_scale=2.0, batch=batch)
+    run_exit_check(cfg, seed=70 + heads, layer=2, threshold=0.3, hidden_scale=3.0)
+
+
 @pytest.mark.parametrize("batch", [3, 40, 100, 200, 450])
 def test_exit_check_ties_go_to_the_lowest_index(batch):
     """Every LM-head row four times (16 rows on, in the next tile pair and half a vocabulary on): equal sums bit for bit, so the
