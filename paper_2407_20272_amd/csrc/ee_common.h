@@ -310,7 +310,15 @@ struct SimpleShape {
   int n_rows;       // output rows to compute (even)
   int pair_stride;  // rows (f, f + pair_stride) are computed together
 };
-void launch_simple_qkv(const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st);
+// An exit decision on materialised logits that rides along with a projection launch (one workgroup per row, in front).
+struct SimpleDecision {
+  CombineArgs a;
+  const float* logits;
+  const float* row_scale;
+  int vocab;
+  int n_wg;   // set by the launch
+};
+void launch_simple_qkv(const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st, const SimpleDecision* with = nullptr);
 void launch_simple_acc(const SimpleShape& g, const AccEpi& e, Pred pred, hipStream_t st);
 void launch_simple_gateup(const SimpleShape& g, const GateUpEpi& e, Pred pred, hipStream_t st);
 void launch_simple_lm(const SimpleShape& g, const LmEpi& e, Pred pred, hipStream_t st);

@@ -1,5 +1,5 @@
-// Exit decision of one layer (Section 3.1), shared by the stand-alone combine kernel and by the QKV projection
-// launch that carries the previous layer's decision along.
+// Exit decision of one layer (Section 3.1), shared by the stand-alone decision kernels and by the QKV projection
+// launches that carry the previous layer's decision along.
 #pragma once
 
 #include "ee_common.h"
@@ -64,6 +64,56 @@ __device__ inline void combine_row(const CombineArgs& a, int m, float4* red) {
     __syncthreads();
   }
   if (threadIdx.x == 0) decide_from_stat(a, m, stat_unpack(red[0]));
+}
+
+// fp32 path: softmax statistics of row m of materialised logits and the decision from them.  One workgroup of 256 threads; red:
+// four float4 of LDS.
+__device__ inline void decide_row_f32(const float* logits, const float* row_scale, int vocab, CombineArgs a, int m, float4* red) {
+  if (a.left && ctl_load(a.left + m) != 0) return;   // left at an earlier layer: its token and exit layer stand
+  // largest logit with its index and the runner-up first, the exponentials relative to the wavefront's largest after
+  HeadStat s = stat_empty();
+  a.scale *= row_scale[m];
+  const float* z = logits + (size_t)m * vocab;
+  constexpr int AHEAD = 8;   // loads in flight: one at a time a row of 32000 took 53 us, now 24
+  auto each = [&](auto take) {
+    for (int v0 = threadIdx.x; v0 < vocab; v0 += 256 * AHEAD) {
+      float x[AHEAD];
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) x[i] = z[min(v0 + 256 * i, vocab - 1)];
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i)
+        if (v0 + 256 * i < vocab) take(v0 + 256 * i, x[i]);
+    }
+  };
+  each([&](int v, float x) {
+    if (x > s.zmax || s.idx == STAT_NO_INDEX) {   // strict: the lowest index wins among equals
+      s.z2 = fmaxf(s.z2, s.zmax);
+      s.zmax = x;
+      s.idx = v;
+    } else {
+      s.z2 = fmaxf(s.z2, x);
+    }
+  });
+#pragma unroll
+  for (int x = 1; x < 64; x <<= 1) {
+    const float ob = __shfl_xor(s.zmax, x), o2 = __shfl_xor(s.z2, x);
+    const int oi = __shfl_xor(s.idx, x);
+    const bool take = ob > s.zmax || (ob == s.zmax && oi < s.idx);
+    s.z2 = fmaxf(fmaxf(s.z2, o2), take ? s.zmax : ob);
+    if (take) {
+      s.zmax = ob;
+      s.idx = oi;
+    }
+  }
+  each([&](int, float x) { s.sum += stat_exp(a.scale * (x - s.zmax)); });
+#pragma unroll
+  for (int x = 1; x < 64; x <<= 1) s.sum += __shfl_xor(s.sum, x);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = stat_pack(s);
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+#pragma unroll
+  for (int w = 1; w < 4; ++w) s = stat_merge(s, stat_unpack(red[w]), a.scale);
+  decide_from_stat(a, m, s);
 }
 
 // Confidence of row m from one dot product (hidden states similarity, dedicated classifier) and the status rule.

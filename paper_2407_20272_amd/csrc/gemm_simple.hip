@@ -4,11 +4,13 @@
 // four lanes finish the four batch rows side by side.  A projection of a normalised operand takes the residual rows
 // themselves: every wavefront sums the squares of its rows beside the products (the rows are a few kilobytes in L1) and the
 // separate normalisation launches are gone.  What bounds this path at small widths is the number of dependent launches, 3 to 4
-// us each: one iteration of four layers of width 256 took 65 launches and 217 us, 30 launches and 110 us in this form.
+// us each: one iteration of four layers of width 256 took 65 launches and 217 us, 30
+// launches and 110 us in this form, 27 and 100 us with the exit decisions inside the QKV launches.
 #include <type_traits>
 
 #include "ee_common.h"
 #include "ee_epilogue.h"
+#include "ee_decide.h"
 
 namespace ee {
 namespace {
@@ -50,16 +52,32 @@ __device__ inline float wave_sums4(float (&v)[4], int lane) {
 }
 
 struct NoFill {};   // (a launch that fills nothing does not carry a kilobyte of layer tables)
+struct NoJob {};
 
-template <class Epi, bool NORM, bool VEC, class Fill>
-__global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, Pred pred, Fill fill) {
+template <class Epi, bool NORM, bool VEC, class Fill, class Job>
+__global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, Pred pred, Fill fill, Job job) {
   constexpr bool FILL = std::is_same<Fill, SimpleFill>::value;
-  if (pred_skip(pred)) return;
+  int bx = blockIdx.x;
+  if constexpr (std::is_same<Job, SimpleDecision>::value) {
+    // Leading workgroups: the exit decision of the layer before, one row each.  The projection's own apply the same rule
+    // (layer_ran), not the live flag: the projection of the layer after the batch exit layer runs, and what it caches is what KV
+    // filling caches there.
+    const bool ran = layer_ran(job.a.s, job.a.layer);
+    if (bx < job.n_wg) {
+      __shared__ float4 red[4];
+      if (blockIdx.y == 0 && bx < job.a.B && ran) decide_row_f32(job.logits, job.row_scale, job.vocab, job.a, bx, red);
+      return;
+    }
+    if (!ran) return;
+    bx -= job.n_wg;
+  } else if (pred_skip(pred)) {
+    return;
+  }
   // The row blocks of one group of weight rows get ids 8 apart: they run on one XCD at the same time, and all but the first
   // read of a weight row hit its L2.  With the row blocks outermost every block fetched the whole matrix from beyond the L2:
   // LM head of 32000 x 4096 and 32 rows 985 us (rows looped over in the wavefront, the form before: 665), now 570; gate/up
   // of 22016 x 4096 and 64 rows 1370 (1150), now 706.
-  const int first = blockIdx.y * ROW_BLOCKS, row_blocks = min(ROW_BLOCKS, (g.M + MC - 1) / MC - first), slot = (int)blockIdx.x >> 3;
+  const int first = blockIdx.y * ROW_BLOCKS, row_blocks = min(ROW_BLOCKS, (g.M + MC - 1) / MC - first), slot = bx >> 3;
   const int m0 = (first + slot % row_blocks) * MC;
   if constexpr (FILL) {   // one slice of the grid per layer; nothing to do where every row has been cached already
     const int layer = blockIdx.z + 1;
@@ -73,7 +91,7 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, 
     e.v_pool = reinterpret_cast<char*>(e.v_pool) + (size_t)(layer - 1) * fill.pool_layer_bytes;
   }
   const int lane = threadIdx.x & 63;
-  const int pair = (slot / row_blocks * 8 + ((int)blockIdx.x & 7)) * 4 + (threadIdx.x >> 6);
+  const int pair = (slot / row_blocks * 8 + (bx & 7)) * 4 + (threadIdx.x >> 6);
   if (pair >= g.n_rows / 2) return;
   const int s = g.pair_stride;
   const int f_lo = g.row_begin + (pair / s) * 2 * s + pair % s;
@@ -136,24 +154,34 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, 
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-template <class Epi, bool NORM, class Fill = NoFill>
-void launch(const SimpleShape& g, const Epi& e, Pred pred, hipStream_t st, const Fill& fill = Fill{}, int n_layers = 1) {
+template <class Epi, bool NORM, class Fill = NoFill, class Job = NoJob>
+void launch(const SimpleShape& g, const Epi& e, Pred pred, hipStream_t st, const Fill& fill = Fill{}, int n_layers = 1, const Job& job = Job{}) {
   const int row_blocks = (g.M + MC - 1) / MC;
-  const dim3 grid(((g.n_rows / 2 + 3) / 4 + 7) / 8 * 8 * (row_blocks < ROW_BLOCKS ? row_blocks : ROW_BLOCKS),
+  int lead = 0;
+  if constexpr (std::is_same<Job, SimpleDecision>::value) lead = job.n_wg;
+  const dim3 grid(((g.n_rows / 2 + 3) / 4 + 7) / 8 * 8 * (row_blocks < ROW_BLOCKS ? row_blocks : ROW_BLOCKS) + lead,
                   (row_blocks + ROW_BLOCKS - 1) / ROW_BLOCKS, n_layers);
   // 16-byte loads need rows that keep the alignment and operands that start on it (the library asks no caller for that)
   bool vec = g.K % 4 == 0 && aligned16(g.w) && aligned16(g.x) && aligned16(g.gain);
   if constexpr (std::is_same<Fill, SimpleFill>::value)
     for (int i = 0; i < n_layers; ++i) vec = vec && aligned16(fill.layers.w_qkv[i]) && aligned16(fill.gains.g[i]);
   if (vec)
-    hipLaunchKernelGGL((gemm_simple_kernel<Epi, NORM, true, Fill>), grid, dim3(256), 0, st, g, e, pred, fill);
+    hipLaunchKernelGGL((gemm_simple_kernel<Epi, NORM, true, Fill, Job>), grid, dim3(256), 0, st, g, e, pred, fill, job);
   else
-    hipLaunchKernelGGL((gemm_simple_kernel<Epi, NORM, false, Fill>), grid, dim3(256), 0, st, g, e, pred, fill);
+    hipLaunchKernelGGL((gemm_simple_kernel<Epi, NORM, false, Fill, Job>), grid, dim3(256), 0, st, g, e, pred, fill, job);
 }
 
 }  // namespace
 
-void launch_simple_qkv(const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st) { launch<QkvEpi, true>(g, e, pred, st); }
+void launch_simple_qkv(const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st, const SimpleDecision* with) {
+  if (!with) {
+    launch<QkvEpi, true>(g, e, pred, st);
+    return;
+  }
+  SimpleDecision job = *with;
+  job.n_wg = (job.a.B + 7) / 8 * 8;   // a multiple of 8: the projection's workgroups keep their XCDs
+  launch<QkvEpi, true>(g, e, pred, st, NoFill{}, 1, job);
+}
 void launch_simple_acc(const SimpleShape& g, const AccEpi& e, Pred pred, hipStream_t st) { launch<AccEpi, false>(g, e, pred, st); }
 void launch_simple_gateup(const SimpleShape& g, const GateUpEpi& e, Pred pred, hipStream_t st) {
   launch<GateUpEpi, true>(g, e, pred, st);

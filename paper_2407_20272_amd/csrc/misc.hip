@@ -333,59 +333,15 @@ __global__ __launch_bounds__(256) void measure_decide_f32_kernel(const float* h,
                      red[2][0] + red[2][1] + red[2][2] + red[2][3]);
 }
 
-// fp32 path: softmax statistics of one row of materialised logits and the decision from them, one workgroup per row; src /
-// dst: the hidden states the caller asked for (last launch of an iteration), copied whatever the predicate says.
+// fp32 path: decide_row_f32 for every row; src / dst: the hidden states the caller asked for (last launch of an iteration),
+// copied whatever the predicate says.
 __global__ __launch_bounds__(256) void head_decide_f32_kernel(const float* logits, const float* row_scale, int vocab, CombineArgs a, Pred pred, const float* src,
                                                               float* dst, int d) {
   const int m = blockIdx.x;
   copy_row(src, dst, m, d);
   if (decision_skip(pred, a.s, a.layer)) return;
-  if (a.left && ctl_load(a.left + m) != 0) return;   // left at an earlier layer: its token and exit layer stand
-  // largest logit with its index and the runner-up first, the exponentials relative to the wavefront's largest after
-  HeadStat s = stat_empty();
-  a.scale *= row_scale[m];
-  const float* z = logits + (size_t)m * vocab;
-  constexpr int AHEAD = 8;   // loads in flight: one at a time a row of 32000 took 53 us, now 24
-  auto each = [&](auto take) {
-    for (int v0 = threadIdx.x; v0 < vocab; v0 += 256 * AHEAD) {
-      float x[AHEAD];
-#pragma unroll
-      for (int i = 0; i < AHEAD; ++i) x[i] = z[min(v0 + 256 * i, vocab - 1)];
-#pragma unroll
-      for (int i = 0; i < AHEAD; ++i)
-        if (v0 + 256 * i < vocab) take(v0 + 256 * i, x[i]);
-    }
-  };
-  each([&](int v, float x) {
-    if (x > s.zmax || s.idx == STAT_NO_INDEX) {   // strict: the lowest index wins among equals
-      s.z2 = fmaxf(s.z2, s.zmax);
-      s.zmax = x;
-      s.idx = v;
-    } else {
-      s.z2 = fmaxf(s.z2, x);
-    }
-  });
-#pragma unroll
-  for (int x = 1; x < 64; x <<= 1) {
-    const float ob = __shfl_xor(s.zmax, x), o2 = __shfl_xor(s.z2, x);
-    const int oi = __shfl_xor(s.idx, x);
-    const bool take = ob > s.zmax || (ob == s.zmax && oi < s.idx);
-    s.z2 = fmaxf(fmaxf(s.z2, o2), take ? s.zmax : ob);
-    if (take) {
-      s.zmax = ob;
-      s.idx = oi;
-    }
-  }
-  each([&](int, float x) { s.sum += stat_exp(a.scale * (x - s.zmax)); });
-#pragma unroll
-  for (int x = 1; x < 64; x <<= 1) s.sum += __shfl_xor(s.sum, x);
   __shared__ float4 red[4];
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = stat_pack(s);
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-#pragma unroll
-  for (int w = 1; w < 4; ++w) s = stat_merge(s, stat_unpack(red[w]), a.scale);
-  decide_from_stat(a, m, s);
+  decide_row_f32(logits, row_scale, vocab, a, m, red);
 }
 
 // ---------------------------------------------------------------------------------------------------

@@ -435,6 +435,16 @@ def test_prompt_chunk_beside_a_sequence_of_nan():
     assert ((got[1] - got[0]).norm(dim=1) <= 2e-2 * got[0].norm(dim=1)).all()
 
 
+@pytest.mark.parametrize("batch,d_model", [(1, 256), (64, 256), (65, 256), (9, 512), (9, 576)])
+@pytest.mark.parametrize("heads,exit_every", [(1, 1), (2, 2)])
+def test_float_exit_decision_inside_the_next_projection(batch, d_model, heads, exit_every):
+    """Float models: up to 64 rows of a width up to 512 the decision of a layer is taken by leading workgroups of the next layer's
+    QKV launch, beyond in a launch of its own; checks after every layer and after every other one, exits spread over the depth."""
+    cfg = TINY.with_(batch=batch, d_model=d_model, n_heads=d_model // 64, d_ffn=320, vocab=514, prompt_len=7, min_prompt_len=5, decode_steps=2,
+                     weight_std=0.05, logit_scale=1.0, threshold=0.3, exit_every=exit_every)
+    lockstep(cfg, seed=81 + batch, steps=2, heads=heads)
+
+
 @pytest.mark.parametrize("heads", [1, 2])
 def test_batch_of_one_and_prompts_ending_on_block_boundaries(heads):
     """Degenerate sizes: a single sequence, and prompts whose next position opens a new 16-token block."""
