@@ -191,6 +191,12 @@ __device__ inline void tile_finish(const f32x16& acc, int nt, int mt_global, con
   }
 }
 
+// Lane of an activation tile (row lane % 32) that this lane fetches for batch tile mt: the lanes of rows that no sequence has
+// fetch what row 0's lane does, the same bytes, instead of padding (their result columns are never written): a compute unit takes
+// in only so many bytes at a time, and a tile of 32 rows is as many as a weight tile.  7B shape, two layers at 1 / 33 / 47 rows
+// 241.5 -> 237.7, 311.8 -> 302.5, 334 -> 327 us; KV filling of two layers at 33 rows 48.7 -> 46.1.
+__device__ inline int x_lane(int lane, int mt, int M) { return mt * 32 + (lane & 31) < M ? lane : lane & 32; }
+
 // ---------------------------------------------------------------------------------------------------------
 // Main loop 1: bf16 operand tiles on both sides
 // ---------------------------------------------------------------------------------------------------------
@@ -201,8 +207,7 @@ struct Frag {
 };
 
 template <int MT, int NT, int U>
-__device__ inline void frag_load(Frag<MT, NT, U>& f, const u32x4* const (&wp)[NT], const u32x4* __restrict__ xp,
-                                 size_t x_tile_stride, int ks) {
+__device__ inline void frag_load(Frag<MT, NT, U>& f, const u32x4* const (&wp)[NT], const u32x4* const (&xp)[MT], int ks) {
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -210,13 +215,12 @@ __device__ inline void frag_load(Frag<MT, NT, U>& f, const u32x4* const (&wp)[NT
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int u = 0; u < U; ++u) f.x[mt][u] = xp[mt * x_tile_stride + (size_t)(ks + u) * 64];
+    for (int u = 0; u < U; ++u) f.x[mt][u] = xp[mt][(size_t)(ks + u) * 64];
 }
 
 // Last, partial group: steps past ks1 re-read the last valid weight tile against a zero activation tile.
 template <int MT, int NT, int U>
-__device__ inline void frag_load_tail(Frag<MT, NT, U>& f, const u32x4* const (&wp)[NT], const u32x4* __restrict__ xp,
-                                      size_t x_tile_stride, int ks, int ks1) {
+__device__ inline void frag_load_tail(Frag<MT, NT, U>& f, const u32x4* const (&wp)[NT], const u32x4* const (&xp)[MT], int ks, int ks1) {
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const bool ok = ks + u < ks1;
@@ -225,7 +229,7 @@ __device__ inline void frag_load_tail(Frag<MT, NT, U>& f, const u32x4* const (&w
     for (int t = 0; t < NT; ++t) f.w[t][u] = __builtin_nontemporal_load(wp[t] + (size_t)kk * 64);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      u32x4 v = xp[mt * x_tile_stride + (size_t)kk * 64];
+      u32x4 v = xp[mt][(size_t)kk * 64];
       f.x[mt][u] = ok ? v : u32x4{0, 0, 0, 0};
     }
   }
@@ -349,7 +353,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred
     wp[t] = reinterpret_cast<const u32x4*>(g.w) + (size_t)nt[t] * k_steps * 64 + (rhalf[t] >= 0 ? ((lane & ~16) | (rhalf[t] << 4)) : lane);
 
   for (int mt0 = 0; mt0 < m_tiles; mt0 += MT) {
-    const u32x4* xp = reinterpret_cast<const u32x4*>(g.x) + (size_t)mt0 * x_tile_stride + lane;
+    const u32x4* xp[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) xp[mt] = reinterpret_cast<const u32x4*>(g.x) + (size_t)(mt0 + mt) * x_tile_stride + x_lane(lane, mt0 + mt, g.M);
     f32x16 acc[NT][MT];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
@@ -362,14 +368,14 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred
     Frag<MT, NT, U> A, B;
     const int n = (ks1 - ks0) / U;
     int k = ks0;
-    if (n > 0) frag_load(A, wp, xp, x_tile_stride, k);
+    if (n > 0) frag_load(A, wp, xp, k);
     int i = 0;
     // (An unconditional steady-state loop with counted waits that keeps a whole group in flight behind the one
     // being multiplied was measured too: no faster in the decode step, so the simpler loop stays.)
     for (; i + 2 <= n; i += 2) {
-      frag_load(B, wp, xp, x_tile_stride, k + U);
+      frag_load(B, wp, xp, k + U);
       frag_mma(A, acc);
-      if (i + 2 < n) frag_load(A, wp, xp, x_tile_stride, k + 2 * U);
+      if (i + 2 < n) frag_load(A, wp, xp, k + 2 * U);
       frag_mma(B, acc);
       k += 2 * U;
     }
@@ -378,7 +384,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred
       k += U;
     }
     if (k < ks1) {
-      frag_load_tail(A, wp, xp, x_tile_stride, k, ks1);
+      frag_load_tail(A, wp, xp, k, ks1);
       frag_mma(A, acc);
     }
 #pragma unroll
@@ -566,6 +572,10 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pre
   const u32x4* wp = reinterpret_cast<const u32x4*>(g.w) + (size_t)nt0 * k_steps * 64 + lane;
   const u32x4* xp = reinterpret_cast<const u32x4*>(g.x) + (size_t)(chunk * MT) * x_tile_stride + lane;
   const int mt_last = min(MT, m_tiles - chunk * MT) - 1;   // last batch tile of this chunk that exists
+  // One or two batch tiles: every wavefront stages pieces of one of them, the rows that exist (x_lane).  (With four that form is
+  // slower, also where every row exists: 97 rows of the 13B shape, one layer, 317 -> 331 us; KV filling at 65 rows 51.8 -> 54.7.)
+  const int x_mt = MT <= 2 ? min(wave % MT, mt_last) : 0;
+  if constexpr (MT <= 2) xp += (size_t)x_mt * x_tile_stride + (x_lane(lane, chunk * MT + x_mt, g.M) - lane);
 
   f32x16 acc[NTW][MT];
 #pragma unroll
@@ -597,7 +607,7 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmShape g, Epi e, Pre
       }
 #pragma unroll
       for (int j = 0; j < XR; ++j) {
-        const int t = wave + NW * j, u = t / MT, mt = t % MT;
+        const int t = wave + NW * j, u = t / MT, mt = MT <= 2 ? 0 : t % MT;
         // past the end: a tile of zeros, chosen by address (a select on the loaded value would sit right behind
         // the load and make the wavefront wait for everything it has in flight)
         const bool ok = kbase + u < ks1;

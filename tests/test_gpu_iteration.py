@@ -445,6 +445,14 @@ def test_float_exit_decision_inside_the_next_projection(batch, d_model, heads, e
     lockstep(cfg, seed=81 + batch, steps=2, heads=heads)
 
 
+@pytest.mark.parametrize("batch", [2, 31, 32, 33, 63, 64, 65, 97])
+def test_rows_that_no_sequence_has(batch):
+    """Batches that leave a 32-row tile nearly empty or nearly full, one to four tiles: lanes of missing rows fetch another row's
+    operand, and what they compute reaches nothing."""
+    cfg = small_bf16(batch=batch, d_model=512, n_heads=4, d_ffn=1056, prompt_len=4, min_prompt_len=3, threshold=0.4)
+    lockstep(cfg, seed=90, steps=2, heads=2)
+
+
 @pytest.mark.parametrize("heads", [1, 2])
 def test_batch_of_one_and_prompts_ending_on_block_boundaries(heads):
     """Degenerate sizes: a single sequence, and prompts whose next position opens a new 16-token block."""
