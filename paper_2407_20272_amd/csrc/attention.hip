@@ -281,14 +281,30 @@ __global__ __launch_bounds__(DH) void attn_merge_kernel(AttnArgs a, Pred pred) {
   if (left != 0) return;
   const int out_row = a.out_pos ? a.out_pos[b] : b;
   const float* ws = a.split_ws + ((size_t)b * a.n_heads + head) * a.split_parts * (DH + 2);
+  // (everything is asked for at once: the maxima first and the rest behind them were two trips to memory; 7B shape, one sequence
+  // at 1000 positions, two layers 254 -> 250 us, 16384 positions 45.3 -> 44.2 us a call)
+  float m[kAttnMaxSplit], l[kAttnMaxSplit], o[kAttnMaxSplit];
+#pragma unroll
+  for (int s = 0; s < kAttnMaxSplit; ++s) {
+    m[s] = NEG_BIG;
+    l[s] = o[s] = 0.0f;
+    if (s < a.split_parts) {
+      const float* p = ws + (size_t)s * (DH + 2);
+      m[s] = p[0];
+      l[s] = p[1];
+      o[s] = p[2 + threadIdx.x];
+    }
+  }
   float M = NEG_BIG;
-  for (int s = 0; s < a.split_parts; ++s) M = fmaxf(M, ws[(size_t)s * (DH + 2)]);
+#pragma unroll
+  for (int s = 0; s < kAttnMaxSplit; ++s) M = fmaxf(M, m[s]);
   float L = 0.0f, acc = 0.0f;
-  for (int s = 0; s < a.split_parts; ++s) {
-    const float* p = ws + (size_t)s * (DH + 2);
-    const float wgt = __builtin_amdgcn_exp2f(p[0] - M);   // an empty part has the maximum -1e30: weight 0
-    L += p[1] * wgt;
-    acc += p[2 + threadIdx.x] * wgt;
+#pragma unroll
+  for (int s = 0; s < kAttnMaxSplit; ++s) {
+    if (s >= a.split_parts) break;
+    const float wgt = __builtin_amdgcn_exp2f(m[s] - M);   // an empty part has the maximum -1e30: weight 0
+    L += l[s] * wgt;
+    acc += o[s] * wgt;
   }
   const float r = acc / L;
   const int col = head * DH + threadIdx.x;
