@@ -19,6 +19,15 @@ __device__ inline float row_rinv(const float* rowsq, int m, int d, float eps) {
 __device__ inline void store_elem(float* p, float v) { *p = v; }
 __device__ inline void store_elem(bf16_t* p, float v) { *p = (bf16_t)v; }
 
+// Turns the rotary pair (lo, hi) by the angle with this cosine and sine.  Which of the two products is rounded on its own is
+// written out, the same for every epilogue: left to the compiler, the block kernel's q and K came out one rounding away from
+// what the other kernels and KV filling give (5 of 10 million cached elements differed).
+__device__ inline void rotate(float& lo, float& hi, float c, float s) {
+  const float a = __builtin_fmaf(lo, c, -(hi * s)), b = __builtin_fmaf(hi, c, lo * s);
+  lo = a;
+  hi = b;
+}
+
 // Rotary embedding (split-half pairing: channel j with j + dh/2, angle = pos * theta^(-2j/dh)) and the write of
 // this position's K/V into the paged cache; q goes to a dense buffer.  The (cos, sin) pairs come from a table
 // that rope_table_kernel fills once per call from angles formed in double (long contexts would lose the fraction
@@ -37,11 +46,7 @@ __device__ inline void epi_qkv(const QkvEpi& e, int m, int f_lo, float lo, float
   const int p = e.context_lens[m];
   if (which < 2 && e.rope_theta > 0.0f) {
     const float2 cs = e.rope[(size_t)m * half + j];   // (cos, sin) of pos * theta^(-2j/dh), tabulated once per iteration
-    const float c = cs.x, s = cs.y;
-    const float a = lo * c - hi * s;
-    const float b = hi * c + lo * s;
-    lo = a;
-    hi = b;
+    rotate(lo, hi, cs.x, cs.y);
   }
   if (which == 0) {
     if (e.q) {
@@ -80,12 +85,7 @@ __device__ inline void epi_qkv4(const QkvEpi& e, int m, int f_lo0, float (&lo)[4
     const float4 c23 = *reinterpret_cast<const float4*>(e.rope + (size_t)m * half + j + 2);
     const float cs[4] = {c01.x, c01.z, c23.x, c23.z}, sn[4] = {c01.y, c01.w, c23.y, c23.w};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float a = lo[i] * cs[i] - hi[i] * sn[i];
-      const float b = hi[i] * cs[i] + lo[i] * sn[i];
-      lo[i] = a;
-      hi[i] = b;
-    }
+    for (int i = 0; i < 4; ++i) rotate(lo[i], hi[i], cs[i], sn[i]);
   }
   if (which == 0) {
     if (e.q) {

@@ -143,10 +143,7 @@ __device__ inline void tile_finish(const f32x16& acc, int nt, int mt_global, con
           hi *= r;
           if (which < 2 && e.rope_theta > 0.0f) {
             const float2 cs = e.rope[(size_t)m * hdim + j0 + r16[ai]];
-            const float a = lo * cs.x - hi * cs.y;
-            const float b = hi * cs.x + lo * cs.y;
-            lo = a;
-            hi = b;
+            rotate(lo, hi, cs.x, cs.y);
           }
         }
         s.zt[r16[ai]][mcol] = lo;
@@ -908,8 +905,11 @@ __device__ inline void finish_qkv(const f32x16 (&acc)[NTW][MTW], int nt0, int n_
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float a = acc[t][mt][run * 4 + i], b = acc[t][mt][run * 4 + i + 8];
-          lo[i] = turn ? a * co[i] - b * si[i] : a;
-          hi[i] = turn ? b * co[i] + a * si[i] : b;
+          lo[i] = a;
+          hi[i] = b;
+          rotate(lo[i], hi[i], co[i], si[i]);
+          lo[i] = turn ? lo[i] : a;
+          hi[i] = turn ? hi[i] : b;
         }
         if (which == 0) {
           if (m < g.M && e.q) {
