@@ -1268,9 +1268,12 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
     } else {
       // if the runtime refused the ring its 128 KiB of dynamic LDS, another kernel serves the shape
       const bool ring = !g.n_rows_dev && ring_serves(g.M, g.n_tiles, g.K) && ring_allowed<Epi>();
-      // (three or four batch tiles: weight tiles that the tiled kernel does not take, unless a short contraction makes the start of
-      // a block most of its time: 50 tiles of 24 steps 6.3 us in the streaming kernel, 7.3 in blocks, 157 of 44 10.1 against 9.4)
-      const bool blocks = m_tiles >= 5 || (m_tiles >= 3 && g.n_tiles % NW && (m_tiles == 3 || k_steps > 44 || g.n_tiles > 128));
+      // Three or four batch tiles, weight tiles that the tiled kernel does not take: blocks where one workgroup a tile no longer
+      // fits one round (331 tiles, exit check: K of 704 / 2048 / 4096 2 to 6 / 7 to 13 / 16 to 32 us faster than in the streaming
+      // kernel).  Fewer tiles leave compute units idle in either, but the streaming kernel's wavefronts split the contraction four
+      // ways (128 rows, 50 tiles: K of 2048 / 4096 24.1 / 35.5 us a check in blocks, 22.3 / 26.9), unless three batch tiles, which it
+      // takes one after the other, cost it more: up to 48 steps (78 tiles of 44 steps 18.6 -> 17.4) or from 129 tiles on.
+      const bool blocks = m_tiles >= 5 || (m_tiles >= 3 && g.n_tiles % NW && (g.n_tiles > 256 || (m_tiles == 3 && (k_steps <= 48 || g.n_tiles > 128))));
       if constexpr (std::is_same<Epi, GateUpEpi>::value) {
         const BlockShape b = pick_block(kGateUpBlocks, m_tiles, g.n_tiles, k_steps, g.n_rows_dev != nullptr);
         const long ring_cost = block_cost(m_tiles, g.n_tiles, k_steps, 8, 8);

@@ -440,6 +440,14 @@ def test_exit_check_in_blocks(batch, heads, vocab):
     run_exit_check(cfg, seed=70 + heads, layer=2, threshold=0.3, hidden_scale=3.0)
 
 
+@pytest.mark.parametrize("batch,heads,vocab", [(65, 16, 32 * 18), (96, 13, 32 * 127), (97, 16, 32 * 50), (128, 14, 32 * 255)])
+def test_exit_check_of_tiles_that_do_not_come_in_fours(batch, heads, vocab):
+    """LM head of 65 to 128 rows in the streaming kernel: three batch tiles one after the other, four at once, the last one of one
+    row or full."""
+    cfg = cfg_of("bf16", 64, heads, n_layers=4, vocab=vocab, logit_scale=2.0, batch=batch)
+    run_exit_check(cfg, seed=74 + heads, layer=2, threshold=0.3, hidden_scale=3.0)
+
+
 @pytest.mark.parametrize("batch", [3, 40, 100, 200, 450])
 def test_exit_check_ties_go_to_the_lowest_index(batch):
     """Every LM-head row four times (16 rows on, in the next tile pair and half a vocabulary on): equal sums bit for bit, so the

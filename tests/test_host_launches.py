@@ -49,6 +49,12 @@ int main(int argc, char** argv) {
     m.desc.dtype = EE_FP32;
     m.desc.vocab = 32000;
   }
+  if (argc > 4) {                                    /* heads of 128, features, vocabulary */
+    m.desc.n_heads = atoi(argv[4]);
+    m.desc.d_model = m.desc.n_heads * 128;
+    m.desc.d_ffn = atoi(argv[5]);
+    m.desc.vocab = atoi(argv[6]);
+  }
   const size_t n = ee_workspace_bytes(&m.desc, B, 300);
   int rc;
   if (!strcmp(argv[1], "init"))
@@ -126,3 +132,20 @@ def test_float_head_grid_covers_every_row_within_the_limits(program, rows):
     blocks = (rows + 3) // 4
     assert (x, z, threads) == (4000 * min(blocks, 64), 1, 256) and (y - 1) * 64 < blocks <= y * 64
     assert x * threads < 2 ** 32 and y < 65536 and decide[:4] == (rows, 1, 1, 256)
+
+
+STREAMING, BLOCKS = 256, 384   # threads: four wavefronts a tile; four that multiply and two that load
+
+
+@pytest.mark.parametrize("rows,heads,tiles,threads", [
+    (128, 32, 50, STREAMING), (128, 16, 201, STREAMING), (97, 3, 255, STREAMING),   # four batch tiles: one round of tiles ...
+    (128, 16, 257, BLOCKS), (97, 3, 331, BLOCKS),                                   # ... or more
+    (96, 32, 50, STREAMING), (65, 8, 127, STREAMING),                               # three: a long contraction of few tiles ...
+    (96, 6, 50, BLOCKS), (65, 8, 129, BLOCKS),                                      # ... 48 steps, or more tiles
+])
+def test_lm_head_of_tiles_that_do_not_come_in_fours(program, rows, heads, tiles, threads):
+    """65 to 128 rows: the streaming kernel's four wavefronts split the contraction of a tile; a block's do not."""
+    launches, rc = program("check", 0, rows, heads, 512, 32 * tiles)
+    assert rc.strip() == "rc 0" and launches[1][3] == threads
+    if threads == STREAMING:
+        assert launches[1][:3] == (tiles, 1, 1)
