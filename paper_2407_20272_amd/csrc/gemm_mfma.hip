@@ -1177,16 +1177,19 @@ AccPlan acc_plan(int M, int n_tiles, int K, bool compacted = false) {
   if (one_chunk) {
     p.kind = 2;
     p.ksplit = 256 / (n_tiles / NW);
-  } else if (m_tiles == 2 && n_tiles >= 128 && n_tiles <= 512) {
-    // 64 x 64 blocks: 7B output projection 11.6 -> 9.1 us at 64 rows (its four wavefronts no longer fetch an operand each)
-    p.kind = 1;
-    p.block = {2, 2};
-    p.ksplit = 512 / n_tiles;
-  } else if (m_tiles == 1 && n_tiles % 2 == 0 && n_tiles > 128 && n_tiles < 256 && k_steps / 64 >= 512 / n_tiles) {
+  } else if ((m_tiles == 1 || (m_tiles == 2 && n_tiles > 212)) && n_tiles % 2 == 0 && n_tiles > 128 && n_tiles < 256 && k_steps / 64 >= 512 / n_tiles) {
     // One tile per workgroup would need two slices and a second round of workgroups for the remainder: two tiles and up to
     // three slices fit one round (13B output projection, 160 tiles: 16.1 -> 13.8 us at 32 rows).  At 128 tiles two slices fill the
     // chip exactly, and four of two tiles cost the normalisation more than they gain (12.6 against 13.0).
     p.kind = 3;
+    p.ksplit = 512 / n_tiles;
+  } else if (m_tiles == 2 && n_tiles >= 128) {
+    // 64 x 64 blocks: 7B output projection 11.6 -> 9.1 us at 64 rows (its four wavefronts no longer fetch an operand each).  A whole
+    // iteration against the form above or, at 128 and 256 tiles, below: 136 to 200 tiles 2.4 to 4.4 % faster at 64 rows, 2 to 3 % at
+    // 36 to 40, 212 tiles 1 and 0 %, 256 tiles 3 and 2.5 %; 216 to 248 tiles, where that form's pairs fill the chip as well, 1 to 1.5 %
+    // slower at 36 rows and no faster at 64: they keep it.
+    p.kind = 1;
+    p.block = {2, 2};
     p.ksplit = 512 / n_tiles;
   } else {
     // streaming kernel (its four wavefronts already split the slice four ways): enough workgroups for every
@@ -1375,10 +1378,8 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
             return;
           }
         }
-        if constexpr (!ACC) {
-          hipLaunchKernelGGL((gemm_mfma_kernel<2, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
-          return;
-        }
+        hipLaunchKernelGGL((gemm_mfma_kernel<2, 2, 4, Epi, FILL>), grid2, block, 0, st, g2, e, pred, fc, cj);
+        return;
       }
     }
     // split tiles take two workgroups each (one batch tile only); the workgroups of a combine job come first

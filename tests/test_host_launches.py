@@ -149,3 +149,14 @@ def test_lm_head_of_tiles_that_do_not_come_in_fours(program, rows, heads, tiles,
     assert rc.strip() == "rc 0" and launches[1][3] == threads
     if threads == STREAMING:
         assert launches[1][:3] == (tiles, 1, 1)
+
+
+@pytest.mark.parametrize("heads,rows,pairs", [(53, 64, False), (54, 64, True), (55, 33, True), (62, 64, True), (64, 64, False), (51, 32, True)])
+def test_output_projection_of_two_batch_tiles(program, heads, rows, pairs):
+    """33 to 64 rows: two tiles a workgroup in two slices where that fills the chip (214 to 254 tiles), else 64 x 64 blocks of two
+    wavefronts that multiply and two that load."""
+    launches, rc = program("iteration", 0, rows, heads, 512, 1024)
+    assert rc.strip() == "rc 0"
+    tiles = 4 * heads
+    assert ((tiles // 2, 2, 1, 256, 0) in launches) == pairs
+    assert ((tiles + 7) // 8 * 8, 1, 1, 256, 0) in launches or pairs   # (a workgroup for each XCD's last block)
