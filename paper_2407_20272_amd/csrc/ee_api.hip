@@ -122,7 +122,7 @@ Workspace carve(const ee_model_desc& D, int B, void* base) {
     w.partials = c.take<float4>((size_t)Mpad * (V / 32));
     w.h = c.take<float>(d * Mpad);
     {
-      const size_t o = gemm_acc_rows(Bp, D.d_model), down = gemm_acc_rows(Bp, D.d_ffn);
+      const size_t o = gemm_acc_rows(Bp, D.d_model / 32, D.d_model), down = gemm_acc_rows(Bp, D.d_model / 32, D.d_ffn);
       w.y = c.take<float>((o > down ? o : down) * d);
     }
     w.xH = c.take<bf16_t>(2 * d * Mpad);

@@ -286,8 +286,8 @@ void launch_gemm_qkv_bf16(const GemmShape& g, const QkvEpi& e, Pred pred, hipStr
 bool gemm_qkv_carries_combine(int M);
 // Contraction slices the accumulate launch of this shape writes (the launch below uses exactly this many).
 int gemm_acc_slices(int M, int n_tiles, int K);
-// Rows of partial results (all slices) to set aside for accumulate launches of up to M rows over a contraction of K.
-size_t gemm_acc_rows(int M, int K);
+// Rows of partial results (all slices) to set aside for accumulate launches of up to M rows onto n_tiles tiles over a contraction of K.
+size_t gemm_acc_rows(int M, int n_tiles, int K);
 void launch_gemm_acc_bf16(const GemmShape& g, const AccEpi& e, Pred pred, hipStream_t st);
 void launch_gemm_gateup_bf16(const GemmShape& g, const GateUpEpi& e, Pred pred, hipStream_t st);
 void launch_gemm_lm_bf16(const GemmShape& g, const LmEpi& e, Pred pred, hipStream_t st);

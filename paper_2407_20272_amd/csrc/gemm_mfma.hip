@@ -1145,13 +1145,15 @@ struct AccPlan {
   int ksplit;
   BlockShape block;
 };
-// Slices hold at least 64 contraction steps; the normalisation launch adds at most eight, of 128 rows, four of 512.
-int acc_slices_most(int m_tiles, int K) {
-  const int by_k = K / 1024 < 1 ? 1 : K / 1024, by_m = m_tiles <= 4 ? 8 : m_tiles <= 16 ? 4 : 64 / m_tiles < 1 ? 1 : 64 / m_tiles;
+// Slices hold at least 64 contraction steps; the normalisation launch adds at most eight, of 129 to 512 rows more than four only of a
+// long contraction that 128 x 64 blocks in as many slices sum in one round.
+int acc_slices_most(int m_tiles, int n_tiles, int K) {
+  const int by_k = K / 1024 < 1 ? 1 : K / 1024, round = 256 / ((m_tiles + 3) / 4 * ((n_tiles + 1) / 2));
+  const int by_m = m_tiles <= 4 ? 8 : m_tiles > 16 ? (64 / m_tiles < 1 ? 1 : 64 / m_tiles) : K < 8192 || round < 4 ? 4 : round > 8 ? 8 : round;
   return by_k < by_m ? by_k : by_m;
 }
 AccPlan acc_plan(int M, int n_tiles, int K, bool compacted = false) {
-  const int m_tiles = (M + 31) / 32, k_steps = K / 16, most = acc_slices_most(m_tiles, K);
+  const int m_tiles = (M + 31) / 32, k_steps = K / 16, most = acc_slices_most(m_tiles, n_tiles, K);
   AccPlan p{0, 1, {0, 0}};
   // (One row chunk: more than 128 tiles or 512 steps stay with the tiled kernel, bound by the weight stream either way: 13B output
   // projection at 128 rows 19.1 against 19.6 us in blocks, down projection 35.9 against 40.0.)
@@ -1409,11 +1411,11 @@ void gemm_bf16_prepare() {
 int gemm_acc_slices(int M, int n_tiles, int K) { return acc_plan(M, n_tiles, K).ksplit; }
 
 // (the most that the plan may write at M rows or, where fewer rows come in more slices, at fewer)
-size_t gemm_acc_rows(int M, int K) {
-  const int m = (M + 31) / 32, m4 = m < 4 ? m : 4, m16 = m < 16 ? m : 16;
+size_t gemm_acc_rows(int M, int n_tiles, int K) {
+  const int m = (M + 31) / 32;
   int tiles = m;
-  if (tiles < m4 * acc_slices_most(m4, K)) tiles = m4 * acc_slices_most(m4, K);
-  if (tiles < m16 * acc_slices_most(m16, K)) tiles = m16 * acc_slices_most(m16, K);
+  for (int i = 1; i <= 16 && i <= m; ++i)
+    if (tiles < i * acc_slices_most(i, n_tiles, K)) tiles = i * acc_slices_most(i, n_tiles, K);
   const int wide = K / 1024 * m < 64 ? K / 1024 * m : 64;   // more than 512 rows: up to 64 tiles in all
   if (m > 16 && tiles < wide) tiles = wide;
   return (size_t)tiles * 32;

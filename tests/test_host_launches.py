@@ -1,6 +1,7 @@
 """What the host side enqueues when the runtime refuses something, without a GPU: a small C program brings its own
 hipLaunchKernel, hipFuncSetAttribute, .. (a program's symbols come before those of the libraries it loads), calls the library with
 made-up device pointers, which the host never follows, and prints every launch."""
+import ctypes
 import os
 import subprocess
 
@@ -160,3 +161,32 @@ def test_output_projection_of_two_batch_tiles(program, heads, rows, pairs):
     tiles = 4 * heads
     assert ((tiles // 2, 2, 1, 256, 0) in launches) == pairs
     assert ((tiles + 7) // 8 * 8, 1, 1, 256, 0) in launches or pairs   # (a workgroup for each XCD's last block)
+
+
+@pytest.fixture(scope="module")
+def slices():
+    """(contraction slices of M rows onto n tiles over K, rows of partial results set aside for up to M rows)"""
+    f, g = B.lib()._ZN2ee15gemm_acc_slicesEiii, B.lib()._ZN2ee13gemm_acc_rowsEiii
+    f.restype, g.restype = ctypes.c_int, ctypes.c_size_t
+    return f, g
+
+
+@pytest.mark.parametrize("tiles,K", [(4, 16), (8, 16384), (20, 1008), (32, 5632), (32, 16384), (64, 28672), (96, 8192), (128, 4096), (128, 11008),
+                                     (160, 13824), (206, 6592), (256, 28672)])
+def test_workspace_covers_the_slices_of_every_smaller_batch(slices, tiles, K):
+    need = most = 0
+    for rows in list(range(1, 700)) + [1000, 1024, 2047, 2048, 2049, 5000]:
+        k = slices[0](rows, tiles, K)
+        assert 1 <= k <= 8 and k <= max(1, K // 1024)
+        need = max(need, k * ((rows + 31) // 32 * 32))
+        set_aside = slices[1](rows, tiles, K)
+        assert set_aside >= need and set_aside >= most
+        most = set_aside
+
+
+@pytest.mark.parametrize("rows,tiles,K,want", [(250, 32, 16384, 8), (300, 32, 16384, 5), (160, 8, 8192, 8), (512, 16, 11008, 8),
+                                                   (300, 48, 6080, 3), (250, 64, 11008, 4), (512, 128, 11008, 4)])
+def test_long_contractions_of_narrow_models_come_in_more_slices(slices, rows, tiles, K, want):
+    """More than 128 rows: as many slices as 128 x 64 blocks fill the chip with in one round, from four to eight, where the contraction
+    is long; the cheapest up to four where it is not."""
+    assert slices[0](rows, tiles, K) == want
