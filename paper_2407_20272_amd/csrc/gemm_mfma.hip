@@ -1078,10 +1078,17 @@ __global__ __launch_bounds__((WM * WN + NL) * 64) void gemm_block_kernel(GemmSha
   int bn = q / bg.ksplit;
   const int ksl = q % bg.ksplit;
   if constexpr (HALVES) {
-    // compacted operand: only the first *n_rows_dev rows hold sequences that are still active.  Where that leaves half of the
-    // row blocks without work, two workgroups share a column block (7B shape, 128 rows active of 256: gate/up 63 -> 48 us).
+    // compacted operand: only the first *n_rows_dev rows hold sequences that are still active
     const int M_eff = g.n_rows_dev[0], active = (M_eff + MT * 32 - 1) / (MT * 32);
-    if (active * 2 <= bg.row_blocks) {
+    if constexpr (MT == 8) {
+      // the only row block (the host sees to that): its upper half is left out once it is empty
+      if (M_eff > MT * 16)
+        block_body<MT, NT, WM, WN, NL, U, DS>(ring, g, e, bg.ksplit, 0, bn, ksl, M_eff);
+      else if (M_eff > 0)
+        block_body<MT / 2, NT, WM, WN, NL, U, DS>(ring, g, e, bg.ksplit, 0, bn, ksl, M_eff);
+    } else if (active * 2 <= bg.row_blocks) {
+      // half of the row blocks are without work: two workgroups share a column block (7B shape, 128 rows active of 256: gate/up
+      // 63 -> 48 us)
       constexpr int HM = NT / 2 % WN ? WM * WN : WM, HN = WM * WN / HM;   // wavefronts, rows x columns
       if (active == 0 || bm >= 2 * active) return;
       bn = bn * 2 + bm / active;
@@ -1115,16 +1122,15 @@ constexpr long block_cost(int m_tiles, int n_tiles, int steps, int mt, int nt) {
   const long blocks = (long)((m_tiles + mt - 1) / mt) * ((n_tiles + nt - 1) / nt), in = 22 * nt + 14 * mt, mul = 7 * mt * nt;
   return (blocks + 255) / 256 * (5000 + steps * (in > mul ? in : mul));
 }
-// The cheapest of a kernel's block shapes for a projection; of a compacted operand, of those that come in halves.
+// The cheapest of a kernel's block shapes for a projection.
 struct BlockShape {
   int mt, nt;
 };
 template <int N>
-BlockShape pick_block(const BlockShape (&shapes)[N], int m_tiles, int n_tiles, int steps, bool compacted = false) {
+BlockShape pick_block(const BlockShape (&shapes)[N], int m_tiles, int n_tiles, int steps) {
   BlockShape best{0, 0};
   long best_cost = 0;
   for (const BlockShape& b : shapes) {
-    if (compacted && (b.mt != 4 || b.nt % 2)) continue;
     const long c = block_cost(m_tiles, n_tiles, steps, b.mt, b.nt);
     if (best.mt == 0 || c < best_cost) {
       best = b;
@@ -1135,6 +1141,10 @@ BlockShape pick_block(const BlockShape (&shapes)[N], int m_tiles, int n_tiles, i
 }
 constexpr BlockShape kQkvBlocks[] = {{2, 3}, {4, 2}, {4, 3}, {4, 4}, {4, 6}}, kGateUpBlocks[] = {{4, 3}, {4, 4}, {4, 6}, {8, 4}, {8, 6}},
                      kLmBlocks[] = {{4, 4}, {4, 8}}, kAccBlocks[] = {{4, 2}, {4, 4}, {8, 4}};
+// Of a compacted operand, those that come in halves: 128-row blocks in halves of their columns; 256-row blocks in halves of their
+// rows, of gate/up up to 256 rows, where 128-row blocks may need a second round (13B shape, gate/up of 256 rows, all of them active: 98 us in the tiled kernel, 117
+// in 128 x 192 blocks, 91 in 256 x 128; three layers of 140 to 256 rows with exits of their own 2.5 to 7 % faster than without).
+constexpr BlockShape kAccHalves[] = {{4, 2}, {4, 4}}, kGateUpHalves[] = {{4, 4}, {4, 6}}, kGateUpHalves256[] = {{4, 4}, {4, 6}, {8, 4}, {8, 6}};
 
 // Which kernel an accumulate projection (output or down projection) of M rows onto n_tiles packed tiles over a
 // contraction of K runs in, and how many contraction slices it writes.  Every slice is one more partial result for
@@ -1173,7 +1183,7 @@ AccPlan acc_plan(int M, int n_tiles, int K, bool compacted = false) {
           p.ksplit = ks;
         }
       }
-    if (compacted) p.block = pick_block(kAccBlocks, m_tiles, n_tiles * p.ksplit, k_steps / p.ksplit, true);
+    if (compacted) p.block = pick_block(kAccHalves, m_tiles, n_tiles * p.ksplit, k_steps / p.ksplit);
     return p;
   }
   if (one_chunk) {
@@ -1222,7 +1232,7 @@ template <int MT, int NT, int WM, int WN, int U, int DS, class Epi>
 void launch_block(const GemmShape& g, const Epi& e, Pred pred, int ksplit, hipStream_t st) {
   const BlockGrid bg{((g.M + 31) / 32 + MT - 1) / MT, (g.n_tiles + NT - 1) / NT, ksplit};
   const dim3 grid((bg.col_blocks * ksplit + 7) / 8 * 8 * bg.row_blocks), block((WM * WN + 2) * 64);
-  if constexpr (MT == 4 && NT % 2 == 0 && !std::is_same<Epi, QkvEpi>::value) {
+  if constexpr ((MT == 4 && NT % 2 == 0 && !std::is_same<Epi, QkvEpi>::value) || (MT == 8 && std::is_same<Epi, GateUpEpi>::value)) {
     if (g.n_rows_dev) {
       hipLaunchKernelGGL((gemm_block_kernel<MT, NT, WM, WN, 2, U, DS, true, Epi>), grid, block, 0, st, g, e, pred, bg);
       return;
@@ -1280,7 +1290,9 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
       // takes one after the other, cost it more: up to 48 steps (78 tiles of 44 steps 18.6 -> 17.4) or from 129 tiles on.
       const bool blocks = m_tiles >= 5 || (m_tiles >= 3 && g.n_tiles % NW && (g.n_tiles > 256 || (m_tiles == 3 && (k_steps <= 48 || g.n_tiles > 128))));
       if constexpr (std::is_same<Epi, GateUpEpi>::value) {
-        const BlockShape b = pick_block(kGateUpBlocks, m_tiles, g.n_tiles, k_steps, g.n_rows_dev != nullptr);
+        const BlockShape b = !g.n_rows_dev   ? pick_block(kGateUpBlocks, m_tiles, g.n_tiles, k_steps)
+                             : m_tiles <= 8 ? pick_block(kGateUpHalves256, m_tiles, g.n_tiles, k_steps)
+                                            : pick_block(kGateUpHalves, m_tiles, g.n_tiles, k_steps);
         const long ring_cost = block_cost(m_tiles, g.n_tiles, k_steps, 8, 8);
         if (blocks && !(ring && ring_cost < block_cost(m_tiles, g.n_tiles, k_steps, b.mt, b.nt))) {
           launch_blocks(b, g, e, pred, 1, st);
@@ -1290,7 +1302,7 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
         // 128 x 256 blocks are what the tiled kernel has with two tiles per wavefront: they pay from 192 steps on (140 to 192 rows, 1000
         // tiles: 128 steps 39.4 -> 41.8 us, 256 steps 76 to 74 -> 66 to 70; 320 to 384 rows: 124 to 126 -> 114 to 118), not where that
         // kernel's two 128-row chunks are nearly full (200 to 256 rows: 73 to 76 both ways).
-        const BlockShape b = pick_block(kLmBlocks, m_tiles, g.n_tiles, k_steps, g.n_rows_dev != nullptr);
+        const BlockShape b = pick_block(kLmBlocks, m_tiles, g.n_tiles, k_steps);
         if (g.n_rows_dev || b.nt < 8 || (k_steps >= 192 && (m_tiles < 7 || m_tiles > 8)) || g.n_tiles % (2 * NW)) {
           launch_blocks(b, g, e, pred, 1, st);
           return;

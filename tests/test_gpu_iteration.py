@@ -402,6 +402,21 @@ def test_per_sequence_compaction_across_chunk_boundaries(exit_every):
         assert stats["L"] == want
 
 
+@pytest.mark.parametrize("tiles,batch", [(772, 256), (776, 130), (1036, 200), (1028, 161)])   # 256 x 128 blocks; 256 x 192, the last one of four or two tiles
+def test_compacted_gate_up_in_blocks_of_256_rows(tiles, batch):
+    """Gate/up of up to 256 rows with exits of their own in one row block: more than 128 rows active, exactly 128 and fewer (the upper
+    half is left out), one, none.  (Weights of the usual 0.05: with 0.03 the three largest logits of one prompt lay within 4e-4 of each
+    other, where the arithmetic allows 4e-3, and the comparison knows ties of two only.)"""
+    cfg = small_bf16(n_layers=6, d_model=128, n_heads=1, d_ffn=16 * tiles, prompt_len=2, min_prompt_len=1, shuffled_blocks=True, batch=batch)
+    forced = torch.full((2, batch), 3, dtype=torch.int32)
+    forced[:, torch.randperm(batch, generator=torch.Generator().manual_seed(6))[:batch - 128]] = 2
+    forced[:, 0] = 1
+    forced[0, batch - 1] = 6      # one sequence runs every layer, or leaves before the last
+    forced[1, batch - 1] = 5
+    stats = lockstep(cfg, seed=51, steps=2, forced_seq=forced, heads=2)
+    assert stats["L"] == [6, 5]
+
+
 @pytest.mark.parametrize("heads", [0, 2])
 def test_token_of_a_sequence_of_nan_among_compacted_rows(heads):
     """A sequence whose embedding is NaN among 200 (two row chunks; with exits of their own the rows are compacted): its

@@ -62,7 +62,11 @@ int main(int argc, char** argv) {
     rc = ee_noalloc_init();
   else if (!strcmp(argv[1], "iteration"))
     rc = ee_decode_iteration(&m, &c, &b, 0, 0, EE_EXIT_NONE, p, p, p, 0, 0, p, n, 0);
-  else if (!strcmp(argv[1], "attention"))
+  else if (!strcmp(argv[1], "per_sequence")) {
+    const float never[2] = {2, 2};
+    b.row_table = 0;
+    rc = ee_decode_iteration(&m, &c, &b, never, 0, EE_EXIT_PER_SEQUENCE, p, p, p, 0, 0, p, n, 0);
+  } else if (!strcmp(argv[1], "attention"))
     rc = ee_paged_attention_decode(&m.desc, &c, 1, p, &b, p, 0, 0, 0);
   else
     rc = ee_exit_check(&m, 1, p, B, 0.5f, 0, p, p, p, p, p, 0, 0, p, n, 0);
@@ -190,3 +194,14 @@ def test_long_contractions_of_narrow_models_come_in_more_slices(slices, rows, ti
     """More than 128 rows: as many slices as 128 x 64 blocks fill the chip with in one round, from four to eight, where the contraction
     is long; the cheapest up to four where it is not."""
     assert slices[0](rows, tiles, K) == want
+
+
+@pytest.mark.parametrize("rows,tiles,blocks,threads", [
+    (256, 768, 2 * 128, 384), (256, 772, 200, 384), (200, 864, 216, 384), (129, 1024, 256, 384),   # 128 x 192 as long as they fit one round; 256 x 128
+    (256, 1036, 176, 640), (129, 1536, 256, 640),                                                  # 256 x 192
+    (257, 864, 3 * 144, 384),                                                                      # more rows: 128-row blocks
+])
+def test_gate_up_of_a_compacted_operand(program, rows, tiles, blocks, threads):
+    launches, rc = program("per_sequence", 0, rows, 1, 16 * tiles, 4096)
+    assert rc.strip() == "rc 0"
+    assert launches.count((blocks, 1, 1, threads, 0)) == 2
