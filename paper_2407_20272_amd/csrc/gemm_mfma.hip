@@ -1293,6 +1293,10 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
         const BlockShape b = !g.n_rows_dev   ? pick_block(kGateUpBlocks, m_tiles, g.n_tiles, k_steps)
                              : m_tiles <= 8 ? pick_block(kGateUpHalves256, m_tiles, g.n_tiles, k_steps)
                                             : pick_block(kGateUpHalves, m_tiles, g.n_tiles, k_steps);
+        // The ring kernel where its 256 x 256 blocks fit one round and 256 x 192 ones do not (776 to 1024 tiles; 1544 to 2048 in two
+        // rounds against three).  A whole iteration of 400 to 512 rows, 776 to 1024 tiles, in blocks and in the ring: K of 1024 480 to
+        // 568 -> 454 to 526 us, 2048 408 to 469 -> 382 to 451, 4096 722 to 833 -> 707 to 814, 5120 (13B shape, 864 tiles, 512 rows) 1020
+        // -> 995; K of 256 299 to 335 -> 302 to 331.  1544 to 2048 tiles: K of 1024 396 to 463 -> 369 to 419, 4096 1054 to 1226 -> 1025 to 1198.
         const long ring_cost = block_cost(m_tiles, g.n_tiles, k_steps, 8, 8);
         if (blocks && !(ring && ring_cost < block_cost(m_tiles, g.n_tiles, k_steps, b.mt, b.nt))) {
           launch_blocks(b, g, e, pred, 1, st);

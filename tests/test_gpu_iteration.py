@@ -277,8 +277,8 @@ def test_per_sequence_forced_exits(cfg):
 
 
 def compactable_bf16(**kw):
-    """Widths at which every projection runs in the tiled kernel once the batch is a multiple of 128 rows: the
-    per-sequence rule then compacts the rows that are still active."""
+    """Widths whose weight tiles come in whole groups of four: from 129 rows on the per-sequence rule compacts the rows that are
+    still active."""
     return small_bf16(n_layers=6, d_ffn=384, prompt_len=10, min_prompt_len=3, shuffled_blocks=True, **kw)
 
 
@@ -294,10 +294,21 @@ def test_bf16_per_sequence_exit_compacted_rows_lockstep(conf_mode, threshold, ba
 @pytest.mark.parametrize("batch", [385, 400, 481, 512])
 @pytest.mark.parametrize("heads", [1, 2])
 def test_bf16_385_to_512_rows_lockstep(batch, heads):
-    """385 to 512 rows: LM head and gate/up run in the 256 x 256 ring kernel under Algorithm 1 (a second row block
-    from one row to full), and stay in the tiled kernel with compacted rows under the per-sequence rule."""
+    """385 to 512 rows: the LM head runs in the 256 x 256 ring kernel under Algorithm 1 (a second row block that ends in one row or
+    is full), with compacted rows in blocks under the per-sequence rule; everything else runs in blocks."""
     cfg = compactable_bf16(batch=batch)
     stats = lockstep(cfg, seed=46, steps=2, heads=heads)
+    total = stats["decisions"] + stats["tokens"]
+    assert stats["near_threshold"] + stats["near_tie"] <= max(2, total // 20), stats
+
+
+@pytest.mark.parametrize("heads,tiles,batch", [(2, 776, 385), (2, 1024, 512), (4, 1544, 400)])
+def test_bf16_gate_up_in_the_ring_kernel(heads, tiles, batch):
+    """385 to 512 rows and 776 gate/up tiles or more: 256 x 256 blocks in one round (the second row block ends in one row, or is
+    full), or in two; one and two turns of the ring."""
+    cfg = small_bf16(n_layers=2, d_model=128 * heads, n_heads=heads, d_ffn=16 * tiles, vocab=512, batch=batch, prompt_len=2, min_prompt_len=1,
+                     shuffled_blocks=True)
+    stats = lockstep(cfg, seed=47, steps=1)
     total = stats["decisions"] + stats["tokens"]
     assert stats["near_threshold"] + stats["near_tie"] <= max(2, total // 20), stats
 
@@ -305,8 +316,8 @@ def test_bf16_385_to_512_rows_lockstep(batch, heads):
 @pytest.mark.parametrize("batch", [96, 150, 200])
 @pytest.mark.parametrize("heads", [1, 2])
 def test_bf16_row_counts_with_a_short_last_chunk(batch, heads):
-    """Three, five and seven 32-row tiles: the tiled projection kernel pads its last 128-row chunk (and, under
-    the per-sequence rule above 128 rows, compacts the active rows as well)."""
+    """Three, five and seven 32-row tiles: a last block of fewer tiles than the others, in the tiled and in the block kernel (under
+    the per-sequence rule above 128 rows with the active rows compacted)."""
     cfg = compactable_bf16(batch=batch)
     stats = lockstep(cfg, seed=45, steps=3, heads=heads)
     total = stats["decisions"] + stats["tokens"]

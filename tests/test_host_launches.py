@@ -205,3 +205,15 @@ def test_gate_up_of_a_compacted_operand(program, rows, tiles, blocks, threads):
     launches, rc = program("per_sequence", 0, rows, 1, 16 * tiles, 4096)
     assert rc.strip() == "rc 0"
     assert launches.count((blocks, 1, 1, threads, 0)) == 2
+
+
+@pytest.mark.parametrize("rows,heads,tiles,ring", [(385, 2, 776, True), (512, 2, 1024, True), (400, 4, 1544, True), (512, 2, 768, False), (384, 2, 776, False),
+                                                   (513, 2, 776, False), (450, 2, 778, False)])
+def test_gate_up_in_the_ring_kernel(program, rows, heads, tiles, ring):
+    """385 to 512 rows, weight tiles in whole blocks of eight whose blocks take fewer rounds than others; without its 128 KiB the
+    block kernel takes the shape."""
+    want = ((tiles // 8 + 7) // 8 * 8 * 2, 1, 1, 256, 131072)
+    launches, rc = program("iteration", 0, rows, heads, 16 * tiles, 1024)
+    assert rc.strip() == "rc 0" and launches.count(want) == (2 if ring else 0)
+    launches, rc = program("iteration", 1, rows, heads, 16 * tiles, 1024)
+    assert rc.strip() == "rc 0" and want not in launches
