@@ -498,10 +498,28 @@ def test_prompt_chunk_beside_a_sequence_of_nan():
 @pytest.mark.parametrize("heads,exit_every", [(1, 1), (2, 2)])
 def test_float_exit_decision_inside_the_next_projection(batch, d_model, heads, exit_every):
     """Float models: up to 64 rows of a width up to 512 the decision of a layer is taken by leading workgroups of the next layer's
-    QKV launch, beyond in a launch of its own; checks after every layer and after every other one, exits spread over the depth."""
+    QKV launch, beyond in a launch of its own; checks after every layer and after every other one, decided by the confidences (the
+    batch as a whole stays to the last layer)."""
     cfg = TINY.with_(batch=batch, d_model=d_model, n_heads=d_model // 64, d_ffn=320, vocab=514, prompt_len=7, min_prompt_len=5, decode_steps=2,
                      weight_std=0.05, logit_scale=1.0, threshold=0.3, exit_every=exit_every)
     lockstep(cfg, seed=81 + batch, steps=2, heads=heads)
+
+
+@pytest.mark.parametrize("batch,d_model", [(1, 256), (64, 256), (65, 256), (17, 512), (9, 576)])
+@pytest.mark.parametrize("heads", [1, 2])
+def test_float_batch_that_leaves_inside_the_next_projection(batch, d_model, heads):
+    """The same launch when the decision in it ends the iteration: the whole batch leaves at layer 1, in the middle, before the last
+    layer, or one by one, the last row early.  The projection behind the decision still runs and caches what KV filling then finds
+    cached; everything after it is empty."""
+    cfg = TINY.with_(batch=batch, n_layers=5, d_model=d_model, n_heads=d_model // 64, d_ffn=320, vocab=514, prompt_len=7, min_prompt_len=5,
+                     decode_steps=4, weight_std=0.05, logit_scale=1.0)
+    forced = torch.empty(4, batch, dtype=torch.int32)
+    forced[0], forced[1], forced[2] = 1, 3, cfg.n_layers - 1
+    forced[3] = torch.arange(batch, 0, -1) % (cfg.n_layers - 1) + 1
+    forced[3, 0] = 4
+    forced[3, batch - 1] = 2 if batch > 1 else 4
+    stats = lockstep(cfg, seed=84 + batch, steps=4, forced_seq=forced, heads=heads)
+    assert stats["L"] == [1, 3, 4, 4]
 
 
 @pytest.mark.parametrize("batch", [2, 31, 32, 33, 63, 64, 65, 97])
