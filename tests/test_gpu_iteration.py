@@ -349,7 +349,7 @@ def test_bf16_output_projection_in_pairs_of_two_batch_tiles(heads, dh, batch):
 
 @pytest.mark.parametrize("heads,dh,d_ffn,batch", [
     (3, 64, 16, 65),        # QKV: 18 tiles in blocks of 3 (64 x 96), the last batch tile of one row; down: a contraction of one step
-    (5, 64, 112, 97),       # QKV: 30 tiles; gate/up of seven tiles, down of seven steps (one past the last pair)
+    (5, 64, 112, 97),       # QKV: 30 tiles; down of seven steps (one past the last pair); gate/up of seven tiles: streaming kernel
     (18, 64, 48, 497),      # QKV: 108 tiles as 128 x 64
     (12, 128, 48, 481),     # 144 as 128 x 96; output projection: 48 tiles
     (17, 128, 48, 512),     # 204 as 128 x 128; output projection: 68 tiles, two slices
@@ -358,9 +358,11 @@ def test_bf16_output_projection_in_pairs_of_two_batch_tiles(heads, dh, batch):
     (2, 128, 16 * 551, 160),    # 551 as 128 x 192, the last block one of five tiles
     (2, 128, 16 * 802, 170),    # 802 as 256 x 128, the last of two tiles
     (1, 128, 16 * 700, 290),    # 700 as 256 x 192, the last of four tiles, a second row block of two
+    (43, 64, 4096, 385),        # down: 86 tiles as 256 x 128 in four slices, the last block of two tiles, a second row block that ends in one row
 ])
 def test_bf16_projections_in_blocks(heads, dh, d_ffn, batch):
-    """Every block shape of the projections from 65 rows on, at ragged edges of rows, tiles and contraction."""
+    """The block shapes of QKV, gate/up, output and down projection from 65 rows on, at ragged edges of rows, tiles and contraction.
+    (64 x 64 blocks: test_bf16_two_output_tiles_per_workgroup; the LM head's: test_exit_check_in_blocks; compacted rows: below.)"""
     cfg = small_bf16(n_layers=1, d_model=heads * dh, n_heads=heads, head_dim=dh, d_ffn=d_ffn, vocab=512, batch=batch, prompt_len=2,
                      min_prompt_len=1, weight_std=0.02, shuffled_blocks=True, threshold=2.0)
     stats = lockstep(cfg, seed=62, steps=1)
@@ -411,6 +413,20 @@ def test_per_sequence_compaction_across_chunk_boundaries(exit_every):
     want = [n, n - 1 if exit_every == 1 else n, int(forced[2].max())]
     if exit_every == 1:
         assert stats["L"] == want
+
+
+@pytest.mark.parametrize("batch", [256, 300])
+def test_compacted_rows_in_halves_of_blocks(batch):
+    """At most half of the row blocks active: two workgroups share a column block of gate/up (524 tiles in blocks of six, the last one
+    of two: its second half has none) and of the LM head (516 in blocks of eight, the last one of four)."""
+    cfg = small_bf16(n_layers=5, d_model=128, n_heads=1, d_ffn=16 * 524, vocab=32 * 516, prompt_len=2, min_prompt_len=1, shuffled_blocks=True,
+                     batch=batch)
+    forced = torch.ones(1, batch, dtype=torch.int32)
+    forced[0, torch.randperm(batch, generator=torch.Generator().manual_seed(7))[:128]] = 2   # 128 rows after layer 1
+    forced[0, 5] = 3
+    forced[0, batch - 1] = 4
+    stats = lockstep(cfg, seed=53, steps=1, forced_seq=forced, heads=2)
+    assert stats["L"] == [4]
 
 
 @pytest.mark.parametrize("tiles,batch", [(772, 256), (776, 130), (1036, 200), (1028, 161)])   # 256 x 128 blocks; 256 x 192, the last one of four or two tiles
