@@ -725,7 +725,6 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(GemmShape g, Epi e, Pred
   const int xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
   const int bm = j % row_blocks, bn = (j / row_blocks) * 8 + xcd;
   if (bn >= col_blocks) return;
-  const int M_eff = g.M;            // (compacted operands stay with the tiled kernel, which skips empty 128-row chunks)
   const int k_steps = g.K >> 4;     // a multiple of RING_D + 1 (the host checks)
   const int nt0 = g.tile_begin + bn * 8 + wave * 2;
   const u32x4* wsrc[2];
@@ -810,16 +809,16 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(GemmShape g, Epi e, Pred
   for (int b = 0; b < 8; ++b) {
     if (bm * 8 + b >= m_tiles) continue;
     if constexpr (std::is_same<Epi, LmEpi>::value) {
-      finish_lm<2>([&](int t, int a) { return acc[t][b][a]; }, nt0, bm * 8 + b, M_eff, g, e, lane);
+      finish_lm<2>([&](int t, int a) { return acc[t][b][a]; }, nt0, bm * 8 + b, g.M, g, e, lane);
     } else {
 #pragma unroll
-      for (int a = 0; a < 2; ++a) finish_from_registers(acc[a][b], nt0 + a, bm * 8 + b, M_eff, 0, g, e, lane);
+      for (int a = 0; a < 2; ++a) finish_from_registers(acc[a][b], nt0 + a, bm * 8 + b, g.M, 0, g, e, lane);
     }
   }
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Main loop 4: one workgroup owns a block of MT batch tiles x NT weight tiles; both operands land in a ring of DS stages of U
+// Main loop 4: one workgroup owns a block of MT batch tiles x NT weight tiles; both operands land in a ring of DS stages of two
 // contraction steps in LDS through direct-to-LDS loads, and every wavefront of WM x WN multiplies its part of the block.
 //   * What bounds it is how fast a compute unit takes its operands in: loads that miss L2 come at 31 GB/s a compute unit, shared
 //     or not, hits at 75 to 120, whatever is in flight beyond 32 KiB (so two or three stages are enough), and the order, the
@@ -827,7 +826,7 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(GemmShape g, Epi e, Pred
 //     with nothing but the loads; 256 x 192 14 KiB, 67 us.
 //   * A wavefront that issues such a load waits at it until the memory pipeline accepts it, and multiplies nothing meanwhile:
 //     with the loads in the multiplying wavefronts the same blocks took 77 and 115 us, loads and multiplies one after the
-//     other.  So NL wavefronts do nothing but load.  They are as fast as their address arithmetic: one bound register pair and a
+//     other.  So two wavefronts do nothing but load.  They are as fast as their address arithmetic: one bound register pair and a
 //     scalar offset (buffer loads), with 64-bit pointers and a select per load two of them reached 35 GB/s.
 //   * One barrier a stage: past it the next stage has landed (the loaders waited for it), and the fragments of this stage's last
 //     step are in registers, so its slot can be loaded again.
@@ -836,6 +835,7 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(GemmShape g, Epi e, Pred
 // weight lines ahead of the loaders: 10 to 17 % faster without multiplies, 0 to 30 % slower with them; weights past the caches:
 // up to a third slower; four multiplying wavefronts of 128 x 96 instead of eight of 64 x 96: 92 -> 97 us.
 // ---------------------------------------------------------------------------------------------------------
+constexpr int BLOCK_U = 2, BLOCK_NL = 2;   // contraction steps a stage, loaders
 struct BlockGrid {
   int row_blocks, col_blocks, ksplit;
 };
@@ -927,16 +927,15 @@ __device__ inline void finish_qkv(const f32x16 (&acc)[NTW][MTW], int nt0, int n_
   }
 }
 
-template <int MT, int NT, int WM, int WN, int NL, int U, int DS, class Epi>
+template <int MT, int NT, int WM, int WN, int DS, class Epi>
 __device__ __forceinline__ void block_body(u32x4* ring, const GemmShape& g, const Epi& e, int ksplit, int bm, int bn, int ksl, int M_eff) {
-  constexpr int P = MT + NT, CW = WM * WN, T = U * P / NL, MTW = MT / WM, NTW = NT / WN, G = U < 2 ? 2 : U;
-  static_assert(U * P % NL == 0 && MT % WM == 0 && NT % WN == 0 && DS > 2 && (DS - 1) * T < 64, "");
+  constexpr int U = BLOCK_U, NL = BLOCK_NL, P = MT + NT, CW = WM * WN, T = U * P / NL, MTW = MT / WM, NTW = NT / WN;
+  static_assert(U == 2 && U * P % NL == 0 && MT % WM == 0 && NT % WN == 0 && DS > 2 && (DS - 1) * T < 64, "");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m_tiles = (g.M + 31) >> 5, k_steps = g.K >> 4;
   const int ks0 = (int)((long)k_steps * ksl / ksplit), n = (int)((long)k_steps * (ksl + 1) / ksplit) - ks0;
-  const int stages = n / G * (G / U);   // whole groups of G steps; the rest follows one by one
-  const int rest = n % G;
+  const int stages = n / U;   // whole ones; the step that an odd contraction leaves over follows
 
   if (wave >= CW) {   // a loader: its share of the pieces of every stage
     const int lw = wave - CW;
@@ -1016,17 +1015,17 @@ __device__ __forceinline__ void block_body(u32x4* ring, const GemmShape& g, cons
   asm volatile("" ::: "memory");
   read(0, 0, 0);
   int slot = 0;
-  for (int s = 0; s < stages; s += G / U) {
+  for (int s = 0; s < stages; ++s) {
 #pragma unroll
-    for (int u = 0; u < G; ++u) {
+    for (int u = 0; u < U; ++u) {
       constexpr int NM = MTW * NTW, RPM = MTW + NTW > 2 * NM ? 3 : 2;
       __builtin_amdgcn_sched_barrier(0);
-      if (u % U == U - 1) {
+      if (u == U - 1) {
         all_meet();
         slot = slot + 1 == DS ? 0 : slot + 1;
         read(slot, 0, (u + 1) & 1);
       } else {
-        read(slot, u % U + 1, (u + 1) & 1);
+        read(slot, u + 1, (u + 1) & 1);
       }
       multiply(u & 1);
       // fragment reads go out behind the first multiplies
@@ -1037,11 +1036,7 @@ __device__ __forceinline__ void block_body(u32x4* ring, const GemmShape& g, cons
       }
     }
   }
-  // fewer than G steps are left: the next stage (G > U: one step, its only one), which has landed
-  for (int u = 0; u < rest; ++u) {
-    read(slot, u, 0);
-    multiply(0);
-  }
+  if (n % U) multiply(0);   // the first step of the next stage, which has landed and been read
   if constexpr (std::is_same<Epi, QkvEpi>::value) {
     finish_qkv<MTW, NTW>(acc, g.tile_begin + bn * NT + wn * NTW, g.tile_begin + g.n_tiles, bm * MT + wm * MTW, kv_at, g, e, lane);
   } else {
@@ -1066,9 +1061,9 @@ __device__ __forceinline__ void block_body(u32x4* ring, const GemmShape& g, cons
   }
 }
 
-template <int MT, int NT, int WM, int WN, int NL, int U, int DS, bool HALVES, class Epi>
-__global__ __launch_bounds__((WM * WN + NL) * 64) void gemm_block_kernel(GemmShape g, Epi e, Pred pred, BlockGrid bg) {
-  __shared__ u32x4 ring[DS * U * (MT + NT) * 64];   // [stage][step][tile][lane]
+template <int MT, int NT, int WM, int WN, int DS, bool HALVES, class Epi>
+__global__ __launch_bounds__((WM * WN + BLOCK_NL) * 64) void gemm_block_kernel(GemmShape g, Epi e, Pred pred, BlockGrid bg) {
+  __shared__ u32x4 ring[DS * BLOCK_U * (MT + NT) * 64];   // [stage][step][tile][lane]
   if (pred_skip(pred)) return;
   // Ids congruent modulo 8 share an XCD: the row blocks of a column block run on one, neighbouring column blocks too.
   const int xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3, nq = bg.col_blocks * bg.ksplit, per = (nq + 7) >> 3;
@@ -1083,9 +1078,9 @@ __global__ __launch_bounds__((WM * WN + NL) * 64) void gemm_block_kernel(GemmSha
     if constexpr (MT == 8) {
       // the only row block (the host sees to that): its upper half is left out once it is empty
       if (M_eff > MT * 16)
-        block_body<MT, NT, WM, WN, NL, U, DS>(ring, g, e, bg.ksplit, 0, bn, ksl, M_eff);
+        block_body<MT, NT, WM, WN, DS>(ring, g, e, bg.ksplit, 0, bn, ksl, M_eff);
       else if (M_eff > 0)
-        block_body<MT / 2, NT, WM, WN, NL, U, DS>(ring, g, e, bg.ksplit, 0, bn, ksl, M_eff);
+        block_body<MT / 2, NT, WM, WN, DS>(ring, g, e, bg.ksplit, 0, bn, ksl, M_eff);
     } else if (active * 2 <= bg.row_blocks) {
       // half of the row blocks are without work: two workgroups share a column block (7B shape, 128 rows active of 256: gate/up
       // 63 -> 48 us)
@@ -1093,12 +1088,12 @@ __global__ __launch_bounds__((WM * WN + NL) * 64) void gemm_block_kernel(GemmSha
       if (active == 0 || bm >= 2 * active) return;
       bn = bn * 2 + bm / active;
       if (bn * (NT / 2) >= g.n_tiles) return;
-      block_body<MT, NT / 2, HM, HN, NL, U, DS>(ring, g, e, bg.ksplit, bm % active, bn, ksl, M_eff);
+      block_body<MT, NT / 2, HM, HN, DS>(ring, g, e, bg.ksplit, bm % active, bn, ksl, M_eff);
     } else if (bm < active) {
-      block_body<MT, NT, WM, WN, NL, U, DS>(ring, g, e, bg.ksplit, bm, bn, ksl, M_eff);
+      block_body<MT, NT, WM, WN, DS>(ring, g, e, bg.ksplit, bm, bn, ksl, M_eff);
     }
   } else {
-    block_body<MT, NT, WM, WN, NL, U, DS>(ring, g, e, bg.ksplit, bm, bn, ksl, g.M);
+    block_body<MT, NT, WM, WN, DS>(ring, g, e, bg.ksplit, bm, bn, ksl, g.M);
   }
 }
 
@@ -1226,34 +1221,35 @@ bool ring_allowed() {
   return ok > 0;
 }
 
-// Wavefronts (rows x columns of the block; two loaders), steps a stage and stages of each block shape: two workgroups fit a
-// compute unit but for the widest blocks.
-template <int MT, int NT, int WM, int WN, int U, int DS, class Epi>
+// Wavefronts that multiply (rows x columns of the block) and stages of each block shape.  Two workgroups share a compute unit where
+// LDS (2 * DS * (MT + NT) KiB of 160) and registers allow: not with eight batch or weight tiles, nor in 128 x 192 blocks of QKV (206
+// registers).
+template <int MT, int NT, int WM, int WN, int DS, class Epi>
 void launch_block(const GemmShape& g, const Epi& e, Pred pred, int ksplit, hipStream_t st) {
   const BlockGrid bg{((g.M + 31) / 32 + MT - 1) / MT, (g.n_tiles + NT - 1) / NT, ksplit};
-  const dim3 grid((bg.col_blocks * ksplit + 7) / 8 * 8 * bg.row_blocks), block((WM * WN + 2) * 64);
+  const dim3 grid((bg.col_blocks * ksplit + 7) / 8 * 8 * bg.row_blocks), block((WM * WN + BLOCK_NL) * 64);
   if constexpr ((MT == 4 && NT % 2 == 0 && !std::is_same<Epi, QkvEpi>::value) || (MT == 8 && std::is_same<Epi, GateUpEpi>::value)) {
     if (g.n_rows_dev) {
-      hipLaunchKernelGGL((gemm_block_kernel<MT, NT, WM, WN, 2, U, DS, true, Epi>), grid, block, 0, st, g, e, pred, bg);
+      hipLaunchKernelGGL((gemm_block_kernel<MT, NT, WM, WN, DS, true, Epi>), grid, block, 0, st, g, e, pred, bg);
       return;
     }
   }
-  hipLaunchKernelGGL((gemm_block_kernel<MT, NT, WM, WN, 2, U, DS, false, Epi>), grid, block, 0, st, g, e, pred, bg);
+  hipLaunchKernelGGL((gemm_block_kernel<MT, NT, WM, WN, DS, false, Epi>), grid, block, 0, st, g, e, pred, bg);
 }
 template <class Epi>
 void launch_blocks(BlockShape b, const GemmShape& g, const Epi& e, Pred pred, int ksplit, hipStream_t st) {
   constexpr bool QKV = std::is_same<Epi, QkvEpi>::value, ACC = std::is_same<Epi, AccEpi>::value, GATE = std::is_same<Epi, GateUpEpi>::value,
                  LM = std::is_same<Epi, LmEpi>::value;
   switch (b.mt * 16 + b.nt) {
-    case 0x22: if constexpr (ACC) launch_block<2, 2, 2, 1, 2, 8>(g, e, pred, ksplit, st); break;
-    case 0x23: if constexpr (QKV) launch_block<2, 3, 2, 1, 2, 8>(g, e, pred, ksplit, st); break;
-    case 0x42: if constexpr (QKV || ACC) launch_block<4, 2, 4, 1, 2, 6>(g, e, pred, ksplit, st); break;
-    case 0x43: if constexpr (QKV || GATE) launch_block<4, 3, 4, 1, 2, 5>(g, e, pred, ksplit, st); break;
-    case 0x44: launch_block<4, 4, 2, 2, 2, 5>(g, e, pred, ksplit, st); break;
-    case 0x46: if constexpr (QKV || GATE) launch_block<4, 6, 2, 2, 2, 4>(g, e, pred, ksplit, st); break;
-    case 0x48: if constexpr (LM) launch_block<4, 8, 2, 2, 2, 5>(g, e, pred, ksplit, st); break;
-    case 0x84: if constexpr (GATE || ACC) launch_block<8, 4, 2, 2, 2, 5>(g, e, pred, ksplit, st); break;
-    case 0x86: if constexpr (GATE) launch_block<8, 6, 4, 2, 2, 5>(g, e, pred, ksplit, st); break;
+    case 0x22: if constexpr (ACC) launch_block<2, 2, 2, 1, 8>(g, e, pred, ksplit, st); break;
+    case 0x23: if constexpr (QKV) launch_block<2, 3, 2, 1, 8>(g, e, pred, ksplit, st); break;
+    case 0x42: if constexpr (QKV || ACC) launch_block<4, 2, 4, 1, 6>(g, e, pred, ksplit, st); break;
+    case 0x43: if constexpr (QKV || GATE) launch_block<4, 3, 4, 1, 5>(g, e, pred, ksplit, st); break;
+    case 0x44: launch_block<4, 4, 2, 2, 5>(g, e, pred, ksplit, st); break;
+    case 0x46: if constexpr (QKV || GATE) launch_block<4, 6, 2, 2, 4>(g, e, pred, ksplit, st); break;
+    case 0x48: if constexpr (LM) launch_block<4, 8, 2, 2, 5>(g, e, pred, ksplit, st); break;
+    case 0x84: if constexpr (GATE || ACC) launch_block<8, 4, 2, 2, 5>(g, e, pred, ksplit, st); break;
+    case 0x86: if constexpr (GATE) launch_block<8, 6, 4, 2, 5>(g, e, pred, ksplit, st); break;
   }
 }
 
