@@ -268,8 +268,6 @@ QkvEpi make_qkv_epi(const ee_model_desc& D, const ee_kv_cache& C, const ee_batch
   e.head_dim = D.head_dim;
   e.d_model = D.d_model;
   e.rope_theta = D.rope_theta;
-  e.rowsq = nullptr;
-  e.eps = D.rms_eps;
   e.num_blocks = C.num_blocks;
   e.table_rows = Bt.batch;
   return e;
@@ -640,7 +638,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
         ProfScope ps(EE_K_GATEUP, i, st);
         GemmShape gg{L.w_gate_up, w.xT, d, B, 0, 2 * f / 32, f, 1};
         gg.n_rows_dev = rmap.n_active;
-        launch_gemm_gateup_bf16(gg, GateUpEpi{w.actT, f, nullptr, D.rms_eps, d}, run_layers, st);
+        launch_gemm_gateup_bf16(gg, GateUpEpi{w.actT, f}, run_layers, st);
       }
       {
         ProfScope ps(EE_K_DOWN, i, st);
@@ -698,7 +696,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       {
         ProfScope ps(EE_K_GATEUP, i, st);
         SimpleShape gg{reinterpret_cast<const float*>(L.w_gate_up), w.h, reinterpret_cast<const float*>(L.g_ffn), D.rms_eps, d, B, 0, 2 * f, f};
-        launch_simple_gateup(gg, GateUpEpi{w.act, f, nullptr, D.rms_eps, d}, run_layers, st);
+        launch_simple_gateup(gg, GateUpEpi{w.act, f}, run_layers, st);
       }
       {
         ProfScope ps(EE_K_DOWN, i, st);

@@ -80,14 +80,12 @@ struct QkvEpi {                 // rotary embedding + paged cache write (+ q out
   const int32_t* context_lens;  // [M]
   const int32_t* block_tables;  // [M][max_blocks]
   const int32_t* row_table;     // nullptr, or [M]: row m uses row row_table[m] of block_tables
-  const int32_t* fill_from;     // nullptr, or [M]: only rows with fill_from[m] < layer are written (KV filling)
+  const int32_t* fill_from;     // nullptr, or [M]: only rows with fill_from[m] < layer are written (KV filling, which has no q)
   int fill_from_stride;         // 1 = per row, 0 = one value for the whole batch
   int layer;
   int max_blocks, n_heads, head_dim, d_model;
   float rope_theta;
   const float2* rope;           // [M][dh/2] (cos, sin) of the rotary angles at context_lens[m] (rope_theta > 0)
-  const float* rowsq;           // nullptr, or [M] sum of squares of the hidden row: value *= rsqrt(rowsq/d + eps)
-  float eps;
   int num_blocks;               // blocks per layer of the pools: a slot whose block id or position is out of range is not written
   int table_rows;               // rows of block_tables (the batch size): a row_table entry outside 0..table_rows-1 is read as 0
 };
@@ -102,9 +100,6 @@ struct AccEpi {                 // residual update
 struct GateUpEpi {              // act = silu(gate) * up
   void* act;                    // XT bf16 [Mpad][f] (bf16 path) or plain float [M][f]
   int d_ffn;
-  const float* rowsq;
-  float eps;
-  int d_model;
 };
 struct LmEpi {                  // per-tile softmax statistics of the scaled logits
   float4* partials;             // [M][n_parts]: {max logit (unscaled), sum exp(scale*(z - max)), 2nd max, arg max as int bits}

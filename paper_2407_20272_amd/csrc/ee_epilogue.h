@@ -12,10 +12,6 @@ namespace ee {
 __device__ inline int32_t ctl_load(const int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void ctl_store(int32_t* p, int32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-__device__ inline float row_rinv(const float* rowsq, int m, int d, float eps) {
-  return rowsq ? rsqrtf(rowsq[m] / (float)d + eps) : 1.0f;
-}
-
 __device__ inline void store_elem(float* p, float v) { *p = v; }
 __device__ inline void store_elem(bf16_t* p, float v) { *p = (bf16_t)v; }
 
@@ -35,9 +31,6 @@ __device__ inline void rotate(float& lo, float& hi, float c, float s) {
 template <class T>
 __device__ inline void epi_qkv(const QkvEpi& e, int m, int f_lo, float lo, float hi) {
   if (e.fill_from && !(e.fill_from[(size_t)m * e.fill_from_stride] < e.layer)) return;
-  const float r = row_rinv(e.rowsq, m, e.d_model, e.eps);
-  lo *= r;
-  hi *= r;
   const int d = e.d_model, dh = e.head_dim, half = dh >> 1;
   const int which = f_lo / d;  // 0 q, 1 k, 2 v
   const int within = f_lo - which * d;
@@ -69,17 +62,11 @@ __device__ inline void epi_qkv(const QkvEpi& e, int m, int f_lo, float lo, float
 // rotary partners, bf16 cache: one look-up of the slot, 8-byte stores into the cache, 16-byte stores into q.
 __device__ inline void epi_qkv4(const QkvEpi& e, int m, int f_lo0, float (&lo)[4], float (&hi)[4]) {
   if (e.fill_from && !(e.fill_from[(size_t)m * e.fill_from_stride] < e.layer)) return;
-  const float r = row_rinv(e.rowsq, m, e.d_model, e.eps);
   const int d = e.d_model, dh = e.head_dim, half = dh >> 1;
   const int which = f_lo0 / d;  // 0 q, 1 k, 2 v
   const int within = f_lo0 - which * d;
   const int head = within / dh;
   const int j = within - head * dh;  // < dh/2, a multiple of 4
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    lo[i] *= r;
-    hi[i] *= r;
-  }
   if (which < 2 && e.rope_theta > 0.0f) {
     const float4 c01 = *reinterpret_cast<const float4*>(e.rope + (size_t)m * half + j);       // (cos, sin) x 2
     const float4 c23 = *reinterpret_cast<const float4*>(e.rope + (size_t)m * half + j + 2);
@@ -114,9 +101,6 @@ __device__ inline void epi_acc(const AccEpi& e, int m, int f, float v) {
 // SwiGLU product; f_lo is the gate row f, f_hi the up row f + d_ffn.
 template <class T>
 __device__ inline void epi_gateup(const GateUpEpi& e, int m, int f, float gate, float up) {
-  const float r = row_rinv(e.rowsq, m, e.d_model, e.eps);
-  gate *= r;
-  up *= r;
   const float a = gate / (1.0f + expf(-gate)) * up;
   if constexpr (sizeof(T) == 2) {
     reinterpret_cast<bf16_t*>(e.act)[xt_index(m, f, e.d_ffn)] = (bf16_t)a;
@@ -127,14 +111,10 @@ __device__ inline void epi_gateup(const GateUpEpi& e, int m, int f, float gate, 
 
 // SwiGLU products of four consecutive features f0..f0+3 (f0 a multiple of 4), bf16 operand-tile order: one 8-byte store.
 __device__ inline void epi_gateup4(const GateUpEpi& e, int m, int f0, const float (&gate)[4], const float (&up)[4]) {
-  const float r = row_rinv(e.rowsq, m, e.d_model, e.eps);
   typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
   bf16x4 out;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float g = gate[i] * r, u = up[i] * r;
-    out[i] = (bf16_t)(g / (1.0f + expf(-g)) * u);
-  }
+  for (int i = 0; i < 4; ++i) out[i] = (bf16_t)(gate[i] / (1.0f + expf(-gate[i])) * up[i]);
   *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16_t*>(e.act) + xt_index(m, f0, e.d_ffn)) = out;
 }
 

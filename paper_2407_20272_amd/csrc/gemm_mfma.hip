@@ -137,14 +137,9 @@ __device__ inline void tile_finish(const f32x16& acc, int nt, int mt_global, con
 #pragma unroll
       for (int ai = 0; ai < 2; ++ai) {
         float lo = vlo[ai], hi = vhi[ai];
-        if (m < g.M) {
-          const float r = row_rinv(e.rowsq, m, e.d_model, e.eps);
-          lo *= r;
-          hi *= r;
-          if (which < 2 && e.rope_theta > 0.0f) {
-            const float2 cs = e.rope[(size_t)m * hdim + j0 + r16[ai]];
-            rotate(lo, hi, cs.x, cs.y);
-          }
+        if (m < g.M && which < 2 && e.rope_theta > 0.0f) {
+          const float2 cs = e.rope[(size_t)m * hdim + j0 + r16[ai]];
+          rotate(lo, hi, cs.x, cs.y);
         }
         s.zt[r16[ai]][mcol] = lo;
         s.zt[16 + r16[ai]][mcol] = hi;
@@ -858,7 +853,7 @@ __device__ inline void buffer_to_lds(buffer_t, lds_void_ptr, int, int) {}
 // and the rotary pairs of one batch tile are fetched while the one before is stored: looked up tile by tile, as the other
 // kernels do, each tile waits for a chain of dependent loads behind the stores of the last.
 __device__ inline long kv_slot(const QkvEpi& e, int m, int M) {
-  if (m >= M) return -1;
+  if (m >= M || (e.fill_from && !(e.fill_from[(size_t)m * e.fill_from_stride] < e.layer))) return -1;
   const int p = e.context_lens[m];
   if ((unsigned)p >= (unsigned)(e.max_blocks * 16)) return -1;
   const int blk = e.block_tables[(size_t)(e.row_table ? safe_row(e.row_table[m], e.table_rows) : m) * e.max_blocks + (p >> 4)];
