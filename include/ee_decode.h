@@ -30,6 +30,10 @@
  *     dtype EE_BF16: weights, embedding, gains and KV cache are bfloat16; matrices
  *     are in the MFMA tile order written by ee_pack_weight.  The residual stream,
  *     q, softmax statistics, logits and confidences are float in both cases.
+ *   - Projections of more than 32 rows (EE_BF16) take up to 140 KiB of LDS per workgroup, of the 160 KiB that
+ *     every compute unit of gfx950 has.  It is part of their code objects and not asked for, so no call checks
+ *     for it.  (Two kernels ask for 128 KiB, the LM head's and gate/up's from 385 rows on and prompt attention's;
+ *     where the runtime refuses that, others take their place.)
  */
 #ifndef EE_DECODE_H
 #define EE_DECODE_H

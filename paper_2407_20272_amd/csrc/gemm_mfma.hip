@@ -1211,7 +1211,7 @@ bool ring_allowed() {
   if (ok < 0) {
     ok = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_kernel<Epi>), hipFuncAttributeMaxDynamicSharedMemorySize,
                              RING_LDS_BYTES) == hipSuccess;
-    if (!ok) (void)hipGetLastError();   // not the call's error: the tiled kernel takes the shape
+    if (!ok) (void)hipGetLastError();   // not the call's error: another kernel takes the shape
   }
   return ok > 0;
 }
@@ -1272,7 +1272,8 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
         return;
       }
     } else {
-      // if the runtime refused the ring its 128 KiB of dynamic LDS, another kernel serves the shape
+      // If the runtime refused the ring its 128 KiB of dynamic LDS, another kernel serves the shape.  (Only what is asked for can be
+      // refused: the blocks' LDS, up to 140 KiB, is static.)
       const bool ring = !g.n_rows_dev && ring_serves(g.M, g.n_tiles, g.K) && ring_allowed<Epi>();
       // Three or four batch tiles, weight tiles that the tiled kernel does not take: blocks where one workgroup a tile no longer
       // fits one round (331 tiles, exit check: K of 704 / 2048 / 4096 2 to 6 / 7 to 13 / 16 to 32 us faster than in the streaming
