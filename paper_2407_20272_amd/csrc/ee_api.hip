@@ -240,8 +240,8 @@ bool has_head(const ee_model_desc& D, int i) { return i < D.n_layers && i % D.ex
 
 // Row compaction pays from two 128-row blocks on (a block is what the projections can skip).
 bool bf16_compactable(const ee_model_desc& D, int B) {
-  return D.dtype == EE_BF16 && B > 128 && gemm_bf16_is_tiled(B, D.d_model / 32) && gemm_bf16_is_tiled(B, 2 * D.d_ffn / 32) &&
-         gemm_bf16_is_tiled(B, D.vocab / 32);
+  return D.dtype == EE_BF16 && B > 128 && gemm_bf16_takes_compacted(D.d_model / 32) && gemm_bf16_takes_compacted(2 * D.d_ffn / 32) &&
+         gemm_bf16_takes_compacted(D.vocab / 32);
 }
 
 size_t pool_layer_elems(const ee_model_desc& D, const ee_kv_cache& C) {

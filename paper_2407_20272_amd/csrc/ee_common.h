@@ -267,9 +267,9 @@ struct GemmShape {
   int keep;     // set by the launcher (tiled kernel): weights stay cached
   int even_wgs; // set by the launcher (tiled kernel): > 0 = the tiles are dealt out evenly over this many workgroups
 };
-// Whether a projection of M rows onto n_tiles packed tiles comes in whole groups of four tiles, three batch tiles at least: where
-// per-sequence exit may compact the operand (n_rows_dev and the epilogues' perm).
-bool gemm_bf16_is_tiled(int M, int n_tiles);
+// Whether a projection of more than 128 rows onto n_tiles packed tiles takes a compacted operand (n_rows_dev and the epilogues' perm):
+// whole groups of four tiles.
+bool gemm_bf16_takes_compacted(int n_tiles);
 // One-time host-side set-up of the projection kernels (function attributes) that the first launch would otherwise do.
 void gemm_bf16_prepare();
 // with_combine != nullptr (only where gemm_qkv_carries_combine(M) holds): the launch also takes the exit decision

@@ -1,19 +1,22 @@
 // bf16 projections of the decode step on the matrix cores (v_mfma_f32_32x32x16_bf16).  Four kernels, by batch size:
 //
-//   gemm_mfma_kernel   one or two 32-row batch tiles, few output tiles (QKV, output projection): a weight streamer.
+//   gemm_mfma_kernel   QKV of one or two 32-row batch tiles, output projection of one (of two where blocks gain nothing), weight
+//                      tiles that do not come in fours up to 128 rows where blocks gain nothing: a weight streamer.
 //                      Every weight byte is fetched from HBM exactly once, straight into registers (1 KiB of
 //                      consecutive bytes per wavefront load thanks to the packed tile order), the small activation
 //                      operand comes out of L2.  A workgroup of four wavefronts owns one 32-row output tile and splits
 //                      the contraction four ways; the partial tiles meet in LDS.
-//   gemm_tiled_kernel  LM head, gate/up and down projection up to 128 rows, KV filling: the four wavefronts own different output
-//                      tiles over the same contraction range and share the activation operand through LDS; 128-row chunks.
+//   gemm_tiled_kernel  LM head and gate/up up to 128 rows, accumulate projections up to 128 rows of a long contraction (8192 on) or,
+//                      from 65 rows, onto more than 128 tiles, KV filling, LM heads of more rows where blocks gain nothing: the
+//                      four wavefronts own different output tiles over the same contraction range and share the activation
+//                      operand through LDS; 128-row chunks.
 //   gemm_block_kernel  everything else: blocks of rows x columns, both operands through LDS, brought by wavefronts that do
 //                      nothing else.
 //   gemm_ring_kernel   LM head at 385-512 rows (gate/up where its blocks fit one round and others do not), where the matrix cores
 //                      are what counts: 256 x 256 blocks.
 //
 // The epilogues (rotary + paged cache write, partial results of the residual updates, SwiGLU, exit-head softmax
-// statistics) run on the finished sums, from LDS in the first kernel and from registers in the other two.
+// statistics) run on the finished sums, from LDS in the first kernel and from registers in the others.
 //
 // The second operand is bf16 in operand-tile order: the attention output, the SwiGLU product, or the normalised
 // hidden state written by finish_norm_kernel.  (Building the normalised operand on the fly from the float residual
@@ -387,9 +390,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Main loop 2 (LM head, gate/up and down projection up to four 32-row batch tiles, KV filling): the four
-// wavefronts of a workgroup own four different 32-row
-// output tiles over the SAME contraction range, so the activation operand is fetched from L2 once per
+// Main loop 2 (LM head, gate/up and long accumulate projections up to four 32-row batch tiles, KV filling): the four
+// wavefronts of a workgroup own four different 32-row output tiles over the SAME contraction range, so the activation operand is fetched from L2 once per
 // workgroup, staged in LDS and read by all four; weights still go straight from HBM to registers, each byte
 // once per batch chunk of MT*32 rows.  Groups of UT contraction steps: while group g is multiplied, the loads
 // of groups g+1 and g+2 are in flight (three rotating weight register sets, two activation register sets that
@@ -449,7 +451,7 @@ __device__ inline void finish_lm(Get acc, int nt, int mtile, int M_eff, const Ge
   }
 }
 
-// Epilogue of one finished 32 x 32 result tile held in a wavefront's registers (tiled and ring kernels): accumulator a
+// Epilogue of one finished 32 x 32 result tile held in a wavefront's registers (tiled, block and ring kernels): accumulator a
 // (< 8) of a lane is result row r16 = (a/4)*8 + (lane/32)*4 + a%4 of column lane%32, accumulator a+8 is row r16+16 (its
 // partner row in the packed order).  nt: packed weight tile, mtile: 32-row batch tile, M_eff: valid rows, ksl: the
 // contraction slice this workgroup summed (accumulate projections).
@@ -825,10 +827,11 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(GemmShape g, Epi e, Pred
 //     scalar offset (buffer loads), with 64-bit pointers and a select per load two of them reached 35 GB/s.
 //   * One barrier a stage: past it the next stage has landed (the loaders waited for it), and the fragments of this stage's last
 //     step are in registers, so its slot can be loaded again.
-// 512 rows of the 7B shape, before (tiled and ring kernels) and now: QKV 77 -> 59 us (128 x 192 blocks, 0.88 PFLOP/s), gate/up 107
-// to 123 -> 83 to 92 (256 x 192, 1.0 PFLOP/s), down 59 -> 48.  Tried: a wavefront that touches this workgroup's share of the shared
-// weight lines ahead of the loaders: 10 to 17 % faster without multiplies, 0 to 30 % slower with them; weights past the caches:
-// up to a third slower; four multiplying wavefronts of 128 x 96 instead of eight of 64 x 96: 92 -> 97 us.
+// 512 rows of the 7B shape, before (tiled and ring kernels) and now: QKV 73 -> 58 us (128 x 192 blocks, 0.89 PFLOP/s, matrix
+// cores busy 35 % of the time), gate/up 101 -> 80 (256 x 192, 1.15, 51 %), down 57 -> 48 (256 x 128, 0.97, 37 %).  Tried: a wavefront
+// that touches this workgroup's share of the shared weight lines ahead of the loaders: 10 to 17 % faster without multiplies, 0 to
+// 30 % slower with them; weights past the caches: up to a third slower; four multiplying wavefronts of 128 x 96 instead of eight
+// of 64 x 96: 92 -> 97 us.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int BLOCK_U = 2, BLOCK_NL = 2;   // contraction steps a stage, loaders
 struct BlockGrid {
@@ -1092,9 +1095,9 @@ __global__ __launch_bounds__((WM * WN + BLOCK_NL) * 64) void gemm_block_kernel(G
   }
 }
 
-// Which shapes the ring kernel serves: 385 to 512 rows (two row blocks, the second at least half full: below that the
-// tiled kernel's 128-row chunks waste less; above, the workgroups no longer fit the chip in one round), whole blocks
-// of eight weight tiles, a contraction of whole groups of sixteen steps.
+// Which shapes the ring kernel serves: 385 to 512 rows (two row blocks, the second at least half full: below that blocks of
+// 128 rows waste less; above, the workgroups no longer fit the chip in one round), whole blocks of eight weight tiles, a
+// contraction of whole groups of sixteen steps.
 bool ring_serves(int M, int n_tiles, int K) {
   return M > 384 && M <= 512 && n_tiles % 8 == 0 && (K >> 4) % (RING_D + 1) == 0 && (K & 15) == 0;
 }
@@ -1106,7 +1109,7 @@ bool tiled(int M, int n_tiles) { return (M + 31) / 32 >= 3 && n_tiles % NW == 0;
 // Time of a projection in blocks of mt batch tiles x nt weight tiles over `steps` contraction steps, in ns: the blocks go round
 // by round over 256 compute units, and a step takes a compute unit what its operands take to come in (22 ns a KiB of weights,
 // 14 ns a KiB of activations: fitted to the kernel without multiplies, 128 x 192 blocks 48 us over 256 steps, 256 x 96 44,
-// 128 x 96 31) or what its multiplies take (7 ns a tile: 256 x 192 blocks 92 us).  Start, first loads and epilogue of a
+// 128 x 96 31) or what its multiplies take (7 ns a tile: 256 x 192 blocks 80 to 92 us, from card to card).  Start, first loads and epilogue of a
 // round: 5 us.
 constexpr long block_cost(int m_tiles, int n_tiles, int steps, int mt, int nt) {
   const long blocks = (long)((m_tiles + mt - 1) / mt) * ((n_tiles + nt - 1) / nt), in = 22 * nt + 14 * mt, mul = 7 * mt * nt;
@@ -1160,8 +1163,8 @@ AccPlan acc_plan(int M, int n_tiles, int K, bool compacted = false) {
   const bool one_chunk = m_tiles <= 4 && n_tiles % NW == 0 && (k_steps >= 512 || (m_tiles >= 3 && n_tiles > 128));
   if (m_tiles >= 3 && !one_chunk) {
     // A slice costs its partial result's way out and back in: 8 bytes an element at 5 TB/s.  (7B shape, 512 rows: down projection
-    // 59 -> 48 us in four slices of 256 x 128 blocks, output projection 26 -> 22 in two of 128 x 128; 128 rows: output projection
-    // 15.0 -> 11.7 in four of 128 x 64 instead of eight.)
+    // 57 -> 48 us in four slices of 256 x 128 blocks, output projection 25.9 -> 25.0 in two of 128 x 128; 128 rows: output projection
+    // 15.7 -> 13.8 in four of 128 x 64.)
     p.kind = 1;
     long best = 0;
     for (int ks = 1; ks <= most; ++ks)
@@ -1186,7 +1189,7 @@ AccPlan acc_plan(int M, int n_tiles, int K, bool compacted = false) {
     p.kind = 3;
     p.ksplit = 512 / n_tiles;
   } else if (m_tiles == 2 && n_tiles >= 128) {
-    // 64 x 64 blocks: 7B output projection 11.6 -> 9.1 us at 64 rows (its four wavefronts no longer fetch an operand each).  A whole
+    // 64 x 64 blocks: 7B output projection 12.8 -> 8.8 us at 64 rows (its four wavefronts no longer fetch an operand each).  A whole
     // iteration against the form above or, at 128 and 256 tiles, below: 136 to 200 tiles 2.4 to 4.4 % faster at 64 rows, 2 to 3 % at
     // 36 to 40, 212 tiles 1 and 0 %, 256 tiles 3 and 2.5 %; 216 to 248 tiles, where that form's pairs fill the chip as well, 1 to 1.5 %
     // slower at 36 rows and no faster at 64: they keep it.
@@ -1257,10 +1260,11 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
   const AccPlan ap = ACC ? acc_plan(g.M, g.n_tiles, g.K, g.n_rows_dev != nullptr) : AccPlan{0, 1, {0, 0}};
   const int k_steps = g.K >> 4;
   if constexpr (!FILL) {
-    // Block kernel: QKV and output projection from two batch tiles on, the down projection from three, gate/up and the LM head from
-    // five.  (7B shape: QKV at 64 / 128 / 192 / 256 / 512 rows 28 -> 26, 37 -> 31, 45 -> 34, 47 -> 41, 77 -> 59 us, gate/up at 192 /
-    // 256 / 384 / 512 75 -> 52, 75 -> 59, 112 -> 88, 123 -> 92; at 128 rows and fewer gate/up and the LM head are bound by the weight
-    // stream either way: 44 against 43 to 46, 47 against 51.)
+    // Block kernel: QKV from three batch tiles on (at two the streaming kernel, which carries the exit decision), accumulate
+    // projections by acc_plan, gate/up and the LM head from five (three where the tiled kernel does not take their tiles, below).
+    // (7B shape, us: QKV at 128 / 192 / 256 / 384 / 512 rows 38 -> 34, 46 -> 37, 48 -> 41, 72 -> 57, 73 -> 58; gate/up at 192 / 256 / 384 /
+    // 512 72 -> 57, 75 -> 61, 91 -> 78, 101 -> 80; LM head at 192 / 350 / 384 77 -> 75, 123 -> 111, 123 -> 115; at 128 rows and fewer gate/up and the LM head are bound by the weight stream either way: 44 against 43 to
+    // 46 us, 47 against 51.)
     if constexpr (ACC) {
       if (ap.kind == 1) {
         launch_blocks(ap.block, g, e, pred, ap.ksplit, st);
@@ -1312,8 +1316,9 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
       }
     }
   }
-  // Tiled kernel: KV filling, gate/up and the LM head at three and four batch tiles, the LM head where block_cost leaves it.  Batch chunks of 4 tiles (128 rows) measured faster than 8 at batch 256 and 512: twice the
-  // workgroups, each with half the accumulators, keeps more loads in flight; the second chunk's weight reads mostly hit the caches.
+  // Tiled kernel: KV filling, gate/up and the LM head at three and four batch tiles, the LM head where block_cost leaves it.  Batch
+  // chunks of 4 tiles (128 rows) measured faster than 8 at batch 256 and 512: twice the workgroups, each with half the accumulators,
+  // keeps more loads in flight; the second chunk's weight reads mostly hit the caches.
   if constexpr (FILL || LM || std::is_same<Epi, GateUpEpi>::value) {
     if (tiled(g.M, g.n_tiles)) {
       const int chunks = (m_tiles + 3) / 4, groups = g.n_tiles / NW;
@@ -1366,10 +1371,10 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
     }
   }
   // Streaming kernel.  Two tiles per workgroup where they fill the chip in one round.
-  // QKV, two batch tiles: pairs on 129 to 256 workgroups (264 tiles: 24.4 -> 22.6 us, 384: 34 -> 31, 480: 45 -> 38; 64 x 64 blocks: as fast, 38.3
-  // against 37.8).  One batch tile: up to 384 tiles 2 * split_tiles whole tiles with a half each (294 tiles: 20.5 -> 19.0, 384: 24.2 -> 22.7), beyond pairs (480:
-  // 39 -> 31); at 288 tiles and fewer the idle compute units cost more than the shared operand saves (pairs of 288: 19.1 -> 20.3,
-  // of 264: 17.4 -> 19.6).
+  // QKV, two batch tiles: pairs on 129 to 256 workgroups (264 tiles: 24.4 -> 22.6 us, 384: 34 -> 31, 480: 45 -> 38; 64 x 64 blocks:
+  // as fast, 38.3 against 37.8).  One batch tile: up to 384 tiles 2 * split_tiles whole tiles with a half each (294 tiles: 20.5 -> 19.0,
+  // 384: 24.2 -> 22.7), beyond pairs (480: 39 -> 31); at 288 tiles and fewer the idle compute units cost more than the shared operand
+  // saves (pairs of 288: 19.1 -> 20.3, of 264: 17.4 -> 19.6).
   // Gate/up whose tiles do not divide by four: two batch tiles only (258 to 506 tiles: 16.1 -> 15.9, 17.5 -> 16.5, 18.1 -> 17.4,
   // 19.7 -> 19.6; one: 12.5 -> 13.4, 13.9 -> 14.5, 14.4 -> 14.9, 15.8 -> 17.7).  The LM head gains at neither (16 rows: 12.7 to 15.4 ->
   // 14.0 to 18.1, 64 rows: 16.8 to 19.9 -> 17.0 to 20.9): its statistics follow each tile.
@@ -1409,7 +1414,7 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
 
 }  // namespace
 
-bool gemm_bf16_is_tiled(int M, int n_tiles) { return tiled(M, n_tiles); }
+bool gemm_bf16_takes_compacted(int n_tiles) { return n_tiles % NW == 0; }
 
 void gemm_bf16_prepare() {
   ring_allowed<LmEpi>();
