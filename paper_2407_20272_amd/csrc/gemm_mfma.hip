@@ -391,8 +391,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmShape g, Epi e, Pred
 
 // ---------------------------------------------------------------------------------------------------------
 // Main loop 2 (LM head, gate/up and long accumulate projections up to four 32-row batch tiles, KV filling): the four
-// wavefronts of a workgroup own four different 32-row output tiles over the SAME contraction range, so the activation operand is fetched from L2 once per
-// workgroup, staged in LDS and read by all four; weights still go straight from HBM to registers, each byte
+// wavefronts of a workgroup own four different 32-row output tiles over the SAME contraction range, so the activation
+// operand is fetched from L2 once per workgroup, staged in LDS and read by all four; weights still go straight from HBM to registers, each byte
 // once per batch chunk of MT*32 rows.  Groups of UT contraction steps: while group g is multiplied, the loads
 // of groups g+1 and g+2 are in flight (three rotating weight register sets, two activation register sets that
 // drain into two LDS stages).  Every wavefront finishes its own tiles, so the epilogue runs from registers.
@@ -1135,8 +1135,9 @@ BlockShape pick_block(const BlockShape (&shapes)[N], int m_tiles, int n_tiles, i
 constexpr BlockShape kQkvBlocks[] = {{2, 3}, {4, 2}, {4, 3}, {4, 4}, {4, 6}}, kGateUpBlocks[] = {{4, 3}, {4, 4}, {4, 6}, {8, 4}, {8, 6}},
                      kLmBlocks[] = {{4, 4}, {4, 8}}, kAccBlocks[] = {{4, 2}, {4, 4}, {8, 4}};
 // Of a compacted operand, those that come in halves: 128-row blocks in halves of their columns; 256-row blocks in halves of their
-// rows, of gate/up up to 256 rows, where 128-row blocks may need a second round (13B shape, gate/up of 256 rows, all of them active: 98 us in the tiled kernel, 117
-// in 128 x 192 blocks, 91 in 256 x 128; three layers of 140 to 256 rows with exits of their own 2.5 to 7 % faster than without).
+// rows, of gate/up up to 256 rows, where 128-row blocks may need a second round (13B shape, gate/up of 256 rows, all of them active:
+// 98 us in the tiled kernel, 117 in 128 x 192 blocks, 91 in 256 x 128; three layers of 140 to 256 rows with exits of their own 2.5 to
+// 10 % faster than without).
 constexpr BlockShape kAccHalves[] = {{4, 2}, {4, 4}}, kGateUpHalves[] = {{4, 4}, {4, 6}}, kGateUpHalves256[] = {{4, 4}, {4, 6}, {8, 4}, {8, 6}};
 
 // Which kernel an accumulate projection (output or down projection) of M rows onto n_tiles packed tiles over a
@@ -1263,8 +1264,8 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
     // Block kernel: QKV from three batch tiles on (at two the streaming kernel, which carries the exit decision), accumulate
     // projections by acc_plan, gate/up and the LM head from five (three where the tiled kernel does not take their tiles, below).
     // (7B shape, us: QKV at 128 / 192 / 256 / 384 / 512 rows 38 -> 34, 46 -> 37, 48 -> 41, 72 -> 57, 73 -> 58; gate/up at 192 / 256 / 384 /
-    // 512 72 -> 57, 75 -> 61, 91 -> 78, 101 -> 80; LM head at 192 / 350 / 384 77 -> 75, 123 -> 111, 123 -> 115; at 128 rows and fewer gate/up and the LM head are bound by the weight stream either way: 44 against 43 to
-    // 46 us, 47 against 51.)
+    // 512 72 -> 57, 75 -> 61, 91 -> 78, 101 -> 80; LM head at 192 / 350 / 384 77 -> 75, 123 -> 111, 123 -> 115; at 128 rows and fewer
+    // gate/up and the LM head are bound by the weight stream either way: 44 against 43 to 46 us, 47 against 51.)
     if constexpr (ACC) {
       if (ap.kind == 1) {
         launch_blocks(ap.block, g, e, pred, ap.ksplit, st);
