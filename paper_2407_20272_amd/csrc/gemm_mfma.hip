@@ -993,6 +993,24 @@ __device__ __forceinline__ void block_body(u32x4* ring, const GemmShape& g, cons
     for (int mt = 0; mt < MTW; ++mt)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[t][mt][i] = 0.0f;
+  // 64 x 64 blocks stand in for the streaming kernel and add as it does: a slice in four parts, the parts' sums one after the other.
+  constexpr bool PARTS = MT == 2 && NT == 2;
+  f32x16 sum[PARTS ? NTW : 1][PARTS ? MTW : 1] = {};
+  const int per = 4 * ksplit;   // (a slice has four steps at least: no part is empty)
+  int end = k_steps * (4 * ksl + 1) / per - ks0;
+  const int end2 = k_steps * (4 * ksl + 2) / per - ks0, end3 = k_steps * (4 * ksl + 3) / per - ks0;
+  auto add_part = [&]() {
+#pragma unroll
+    for (int t = 0; t < NTW; ++t)
+#pragma unroll
+      for (int mt = 0; mt < MTW; ++mt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          sum[t][mt][i] += acc[t][mt][i];
+          acc[t][mt][i] = 0.0f;
+        }
+    end = end < end2 ? end2 : end < end3 ? end3 : -1;
+  };
   auto multiply = [&](int b) {
 #pragma unroll
     for (int t = 0; t < NTW; ++t)
@@ -1017,6 +1035,8 @@ __device__ __forceinline__ void block_body(u32x4* ring, const GemmShape& g, cons
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       constexpr int NM = MTW * NTW, RPM = MTW + NTW > 2 * NM ? 3 : 2;
+      if constexpr (PARTS)
+        if (s * U + u == end) add_part();
       __builtin_amdgcn_sched_barrier(0);
       if (u == U - 1) {
         all_meet();
@@ -1034,7 +1054,17 @@ __device__ __forceinline__ void block_body(u32x4* ring, const GemmShape& g, cons
       }
     }
   }
+  if constexpr (PARTS)
+    if (n % U)
+      if (n - 1 == end) add_part();
   if (n % U) multiply(0);   // the first step of the next stage, which has landed and been read
+  if constexpr (PARTS) {
+    add_part();
+#pragma unroll
+    for (int t = 0; t < NTW; ++t)
+#pragma unroll
+      for (int mt = 0; mt < MTW; ++mt) acc[t][mt] = sum[t][mt];
+  }
   if constexpr (std::is_same<Epi, QkvEpi>::value) {
     finish_qkv<MTW, NTW>(acc, g.tile_begin + bn * NT + wn * NTW, g.tile_begin + g.n_tiles, bm * MT + wm * MTW, kv_at, g, e, lane);
   } else {
@@ -1189,11 +1219,11 @@ AccPlan acc_plan(int M, int n_tiles, int K, bool compacted = false) {
     // chip exactly, and four of two tiles cost the normalisation more than they gain (12.6 against 13.0).
     p.kind = 3;
     p.ksplit = 512 / n_tiles;
-  } else if (m_tiles == 2 && n_tiles >= 128) {
+  } else if (m_tiles == 2 && n_tiles >= 128 && k_steps >= 4) {
     // 64 x 64 blocks: 7B output projection 12.8 -> 8.8 us at 64 rows (its four wavefronts no longer fetch an operand each).  A whole
     // iteration against the form above or, at 128 and 256 tiles, below: 136 to 200 tiles 2.4 to 4.4 % faster at 64 rows, 2 to 3 % at
     // 36 to 40, 212 tiles 1 and 0 %, 256 tiles 3 and 2.5 %; 216 to 248 tiles, where that form's pairs fill the chip as well, 1 to 1.5 %
-    // slower at 36 rows and no faster at 64: they keep it.
+    // slower at 36 rows and no faster at 64: they keep it.  (Adding a slice in four parts, as that kernel does, costs nothing.)
     p.kind = 1;
     p.block = {2, 2};
     p.ksplit = 512 / n_tiles;

@@ -339,6 +339,34 @@ def test_bf16_two_output_tiles_per_workgroup(heads, dh, batch):
     assert stats["near_threshold"] + stats["near_tie"] <= max(2, stats["tokens"] // 20), stats
 
 
+@pytest.mark.parametrize("d_ffn", [16, 48, 80])
+def test_bf16_short_contractions_onto_many_tiles(d_ffn):
+    """Two batch tiles, 128 weight tiles and a down projection of one, three or five steps: too short for 64 x 64 blocks, which add a
+    slice in four parts, or just long enough."""
+    cfg = small_bf16(n_layers=1, d_model=4096, n_heads=32, head_dim=128, d_ffn=d_ffn, vocab=512, batch=34, prompt_len=1, min_prompt_len=1,
+                     weight_std=0.02, shuffled_blocks=True, threshold=2.0)
+    stats = lockstep(cfg, seed=64, steps=1)
+    assert stats["near_threshold"] + stats["near_tie"] <= max(2, stats["tokens"] // 20), stats
+
+
+@pytest.mark.parametrize("heads,d_ffn,layers", [(33, 1104, 2), (40, 2064, 1), (53, 96, 1)])
+def test_bf16_rows_do_not_hang_on_the_other_batch_tile(heads, d_ffn, layers):
+    """Output and down projection onto 132, 160 and 212 tiles: one batch tile in pairs of tiles in the streaming kernel, two in 64 x 64
+    blocks, which add the same parts in the same order.  64 sequences end with the hidden states that they have 32 at a time, bit for
+    bit (slices of odd lengths, parts that end inside a stage)."""
+    cfg = small_bf16(n_layers=layers, d_model=heads * 128, n_heads=heads, head_dim=128, d_ffn=d_ffn, vocab=512, batch=64, prompt_len=1,
+                     min_prompt_len=1, weight_std=0.02)
+    lens = torch.full((64,), 3, dtype=torch.int32)
+    run = HipRun(cfg, W.make_weights(cfg, seed=65, gain_jitter=0.1), lens, 1, seed=65)
+    tokens = torch.randint(0, cfg.vocab, (64,), generator=torch.Generator().manual_seed(65), dtype=torch.int32)
+    run.cache.k.normal_()
+    run.cache.v.normal_()
+    want = run.step(tokens, lens.long(), 2.0, heads=False)[4]
+    for half in (list(range(32)), list(range(32, 64))):
+        got = run.step(tokens[half], lens[half].long(), 2.0, heads=False, rows=half)[4]
+        assert torch.equal(got, want[half])
+
+
 @pytest.mark.parametrize("heads,dh,batch", [(107, 64, 33), (54, 128, 64)])   # 214 and 216 tiles, the second batch tile of one row or full
 def test_bf16_output_projection_in_pairs_of_two_batch_tiles(heads, dh, batch):
     cfg = small_bf16(n_layers=1, d_model=heads * dh, n_heads=heads, head_dim=dh, d_ffn=96, vocab=512, batch=batch, prompt_len=1,
