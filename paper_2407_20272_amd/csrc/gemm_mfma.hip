@@ -1141,8 +1141,8 @@ bool tiled(int M, int n_tiles) { return (M + 31) / 32 >= 3 && n_tiles % NW == 0;
 // 14 ns a KiB of activations: fitted to the kernel without multiplies, 128 x 192 blocks 48 us over 256 steps, 256 x 96 44,
 // 128 x 96 31) or what its multiplies take (7 ns a tile: 256 x 192 blocks 80 to 92 us, from card to card).  Start, first loads and epilogue of a
 // round: 5 us.
-constexpr long block_cost(int m_tiles, int n_tiles, int steps, int mt, int nt) {
-  const long blocks = (long)((m_tiles + mt - 1) / mt) * ((n_tiles + nt - 1) / nt), in = 22 * nt + 14 * mt, mul = 7 * mt * nt;
+constexpr long block_cost(int m_tiles, int n_tiles, int steps, int mt, int nt, int slices = 1) {
+  const long blocks = (long)((m_tiles + mt - 1) / mt) * ((n_tiles + nt - 1) / nt) * slices, in = 22 * nt + 14 * mt, mul = 7 * mt * nt;
   return (blocks + 255) / 256 * (5000 + steps * (in > mul ? in : mul));
 }
 // The cheapest of a kernel's block shapes for a projection.
@@ -1150,11 +1150,11 @@ struct BlockShape {
   int mt, nt;
 };
 template <int N>
-BlockShape pick_block(const BlockShape (&shapes)[N], int m_tiles, int n_tiles, int steps) {
+BlockShape pick_block(const BlockShape (&shapes)[N], int m_tiles, int n_tiles, int steps, int slices = 1) {
   BlockShape best{0, 0};
   long best_cost = 0;
   for (const BlockShape& b : shapes) {
-    const long c = block_cost(m_tiles, n_tiles, steps, b.mt, b.nt);
+    const long c = block_cost(m_tiles, n_tiles, steps, b.mt, b.nt, slices);
     if (best.mt == 0 || c < best_cost) {
       best = b;
       best_cost = c;
@@ -1178,6 +1178,7 @@ struct AccPlan {
                 // 3: streaming kernel, two output tiles per workgroup
   int ksplit;
   BlockShape block;
+  long cost;    // of a plan for the block kernel
 };
 // Slices hold at least 64 contraction steps; the normalisation launch adds at most eight, of 129 to 512 rows more than four only of a
 // long contraction that 128 x 64 blocks in as many slices sum in one round.
@@ -1188,7 +1189,7 @@ int acc_slices_most(int m_tiles, int n_tiles, int K) {
 }
 AccPlan acc_plan(int M, int n_tiles, int K, bool compacted = false) {
   const int m_tiles = (M + 31) / 32, k_steps = K / 16, most = acc_slices_most(m_tiles, n_tiles, K);
-  AccPlan p{0, 1, {0, 0}};
+  AccPlan p{0, 1, {0, 0}, 0};
   // (One row chunk: more than 128 tiles or 512 steps stay with the tiled kernel, bound by the weight stream either way: 13B output
   // projection at 128 rows 19.1 against 19.6 us in blocks, down projection 35.9 against 40.0.)
   const bool one_chunk = m_tiles <= 4 && n_tiles % NW == 0 && (k_steps >= 512 || (m_tiles >= 3 && n_tiles > 128));
@@ -1196,18 +1197,24 @@ AccPlan acc_plan(int M, int n_tiles, int K, bool compacted = false) {
     // A slice costs its partial result's way out and back in: 8 bytes an element at 5 TB/s.  (7B shape, 512 rows: down projection
     // 57 -> 48 us in four slices of 256 x 128 blocks, output projection 25.9 -> 25.0 in two of 128 x 128; 128 rows: output projection
     // 15.7 -> 13.8 in four of 128 x 64.)
-    p.kind = 1;
-    long best = 0;
-    for (int ks = 1; ks <= most; ++ks)
-      for (const BlockShape& b : kAccBlocks) {
-        const long c = block_cost(m_tiles, (n_tiles + b.nt - 1) / b.nt * b.nt * ks, (k_steps + ks - 1) / ks, b.mt, b.nt) + (long)ks * m_tiles * n_tiles * 1024 * 8 / 5000;
-        if (p.block.mt == 0 || c < best) {
-          best = c;
-          p.block = b;
-          p.ksplit = ks;
-        }
-      }
-    if (compacted) p.block = pick_block(kAccHalves, m_tiles, n_tiles * p.ksplit, k_steps / p.ksplit);
+    const auto in_slices = [&](int ks) {   // the cheapest blocks of that many slices, and their cost
+      AccPlan q{1, ks, pick_block(kAccBlocks, m_tiles, n_tiles, (k_steps + ks - 1) / ks, ks)};
+      q.cost = block_cost(m_tiles, n_tiles, (k_steps + ks - 1) / ks, q.block.mt, q.block.nt, ks) + (long)ks * m_tiles * n_tiles * 1024 * 8 / 5000;
+      return q;
+    };
+    for (int ks = 1; ks <= most; ++ks) {
+      const AccPlan q = in_slices(ks);
+      if (ks == 1 || q.cost < p.cost) p = q;
+    }
+    // No more than 128 x 128 blocks fill the chip with, unless more are a tenth cheaper: the rule is no finer than that (7B shape, down
+    // projection: it finds four slices 7 % cheaper than two; a whole call is 1.7 / 1.2 / 0.9 % faster with two at 288 / 416 / 448 rows,
+    // as fast at 480, 0.7 % slower at 512), and the sums stay those of the tiled kernel, which sliced like this.
+    const int fill = 256 / ((m_tiles + 3) / 4 * ((n_tiles + 3) / 4));
+    if (p.ksplit > fill) {
+      const AccPlan q = in_slices(fill < 1 ? 1 : fill);
+      if (p.cost * 10 >= q.cost * 9) p = q;
+    }
+    if (compacted) p.block = pick_block(kAccHalves, m_tiles, n_tiles, k_steps / p.ksplit, p.ksplit);
     return p;
   }
   if (one_chunk) {
@@ -1288,7 +1295,7 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
   dim3 block(256);
   const int m_tiles = (g.M + 31) / 32;
   constexpr bool ACC = std::is_same<Epi, AccEpi>::value, LM = std::is_same<Epi, LmEpi>::value;
-  const AccPlan ap = ACC ? acc_plan(g.M, g.n_tiles, g.K, g.n_rows_dev != nullptr) : AccPlan{0, 1, {0, 0}};
+  const AccPlan ap = ACC ? acc_plan(g.M, g.n_tiles, g.K, g.n_rows_dev != nullptr) : AccPlan{0, 1, {0, 0}, 0};
   const int k_steps = g.K >> 4;
   if constexpr (!FILL) {
     // Block kernel: QKV from three batch tiles on (at two the streaming kernel, which carries the exit decision), accumulate

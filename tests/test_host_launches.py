@@ -189,7 +189,7 @@ def test_workspace_covers_the_slices_of_every_smaller_batch(slices, tiles, K):
 
 
 @pytest.mark.parametrize("rows,tiles,K,want", [(250, 32, 16384, 8), (300, 32, 16384, 5), (160, 8, 8192, 8), (512, 16, 11008, 8),
-                                                   (300, 48, 6080, 3), (250, 64, 11008, 4), (512, 128, 11008, 4)])
+                                                   (300, 48, 6080, 3), (250, 64, 11008, 4), (512, 128, 11008, 2), (384, 128, 11008, 4), (512, 160, 13824, 3)])
 def test_long_contractions_of_narrow_models_come_in_more_slices(slices, rows, tiles, K, want):
     """More than 128 rows: as many slices as 128 x 64 blocks fill the chip with in one round, from four to eight, where the contraction
     is long; the cheapest up to four where it is not."""
