@@ -925,7 +925,7 @@ __device__ inline void finish_qkv(const f32x16 (&acc)[NTW][MTW], int nt0, int n_
   }
 }
 
-template <int MT, int NT, int WM, int WN, int DS, class Epi>
+template <int MT, int NT, int WM, int WN, int DS, bool COMPACTED, class Epi>
 __device__ __forceinline__ void block_body(u32x4* ring, const GemmShape& g, const Epi& e, int ksplit, int bm, int bn, int ksl, int M_eff) {
   constexpr int U = BLOCK_U, NL = BLOCK_NL, P = MT + NT, CW = WM * WN, T = U * P / NL, MTW = MT / WM, NTW = NT / WN;
   static_assert(U == 2 && U * P % NL == 0 && MT % WM == 0 && NT % WN == 0 && DS > 2 && (DS - 1) * T < 64, "");
@@ -1073,7 +1073,8 @@ __device__ __forceinline__ void block_body(u32x4* ring, const GemmShape& g, cons
       const int mtile = bm * MT + wm * MTW + mt, nt0 = bn * NT + wn * NTW;
       if (mtile >= m_tiles) continue;
       if constexpr (std::is_same<Epi, LmEpi>::value) {
-        if (nt0 + NTW <= g.n_tiles) {
+        // (compacted rows: a record a tile, so that a confidence does not hang on whether the block or half of it is worked on)
+        if (!COMPACTED && nt0 + NTW <= g.n_tiles) {
           finish_lm<NTW>([&](int t, int a) { return acc[t][mt][a]; }, g.tile_begin + nt0, mtile, M_eff, g, e, lane);
         } else {
 #pragma unroll
@@ -1106,9 +1107,9 @@ __global__ __launch_bounds__((WM * WN + BLOCK_NL) * 64) void gemm_block_kernel(G
     if constexpr (MT == 8) {
       // the only row block (the host sees to that): its upper half is left out once it is empty
       if (M_eff > MT * 16)
-        block_body<MT, NT, WM, WN, DS>(ring, g, e, bg.ksplit, 0, bn, ksl, M_eff);
+        block_body<MT, NT, WM, WN, DS, HALVES>(ring, g, e, bg.ksplit, 0, bn, ksl, M_eff);
       else if (M_eff > 0)
-        block_body<MT / 2, NT, WM, WN, DS>(ring, g, e, bg.ksplit, 0, bn, ksl, M_eff);
+        block_body<MT / 2, NT, WM, WN, DS, HALVES>(ring, g, e, bg.ksplit, 0, bn, ksl, M_eff);
     } else if (active * 2 <= bg.row_blocks) {
       // half of the row blocks are without work: two workgroups share a column block (7B shape, 128 rows active of 256: gate/up
       // 63 -> 48 us)
@@ -1116,12 +1117,12 @@ __global__ __launch_bounds__((WM * WN + BLOCK_NL) * 64) void gemm_block_kernel(G
       if (active == 0 || bm >= 2 * active) return;
       bn = bn * 2 + bm / active;
       if (bn * (NT / 2) >= g.n_tiles) return;
-      block_body<MT, NT / 2, HM, HN, DS>(ring, g, e, bg.ksplit, bm % active, bn, ksl, M_eff);
+      block_body<MT, NT / 2, HM, HN, DS, HALVES>(ring, g, e, bg.ksplit, bm % active, bn, ksl, M_eff);
     } else if (bm < active) {
-      block_body<MT, NT, WM, WN, DS>(ring, g, e, bg.ksplit, bm, bn, ksl, M_eff);
+      block_body<MT, NT, WM, WN, DS, HALVES>(ring, g, e, bg.ksplit, bm, bn, ksl, M_eff);
     }
   } else {
-    block_body<MT, NT, WM, WN, DS>(ring, g, e, bg.ksplit, bm, bn, ksl, g.M);
+    block_body<MT, NT, WM, WN, DS, HALVES>(ring, g, e, bg.ksplit, bm, bn, ksl, g.M);
   }
 }
 

@@ -457,6 +457,28 @@ def test_compacted_rows_in_halves_of_blocks(batch):
     assert stats["L"] == [4]
 
 
+@pytest.mark.parametrize("batch,vocab", [(256, 32 * 516), (300, 32 * 64)])
+def test_confidences_do_not_hang_on_how_many_rows_are_active(batch, vocab):
+    """The sequences that stay have the confidences and hidden states, bit for bit, that they have when the others stay too (whole
+    blocks of the projections against halves of them)."""
+    cfg = small_bf16(n_layers=3, d_model=256, n_heads=2, d_ffn=16 * 532, vocab=vocab, batch=batch)
+    lens = torch.full((batch,), 3, dtype=torch.int32)
+    run = HipRun(cfg, W.make_weights(cfg, seed=54, gain_jitter=0.1), lens, 1, seed=54)
+    tokens = torch.randint(0, vocab, (batch,), generator=torch.Generator().manual_seed(54), dtype=torch.int32)
+    run.cache.k.normal_()
+    run.cache.v.normal_()
+    forced = torch.full((batch,), cfg.n_layers, dtype=torch.int32)
+    _, _, _, want_conf, want = run.step(tokens, lens.long(), 2.0, forced=forced, heads=2)
+    stay = torch.zeros(batch, dtype=torch.bool)
+    stay[torch.randperm(batch, generator=torch.Generator().manual_seed(55))[:100]] = True
+    forced[~stay] = 1
+    _, exits, L, conf, hidden = run.step(tokens, lens.long(), 2.0, forced=forced, heads=2)
+    assert L == cfg.n_layers and torch.equal(exits, forced)
+    assert not want_conf[:2].isnan().any()
+    assert torch.equal(conf[0], want_conf[0]) and torch.equal(conf[1, stay], want_conf[1, stay])
+    assert torch.equal(hidden[stay], want[stay])
+
+
 @pytest.mark.parametrize("tiles,batch", [(772, 256), (776, 130), (1036, 200), (1028, 161)])   # 256 x 128 blocks; 256 x 192, the last one of four or two tiles
 def test_compacted_gate_up_in_blocks_of_256_rows(tiles, batch):
     """Gate/up of up to 256 rows with exits of their own in one row block: more than 128 rows active, exactly 128 and fewer (the upper
