@@ -827,8 +827,8 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(GemmShape g, Epi e, Pred
 //     scalar offset (buffer loads), with 64-bit pointers and a select per load two of them reached 35 GB/s.
 //   * One barrier a stage: past it the next stage has landed (the loaders waited for it), and the fragments of this stage's last
 //     step are in registers, so its slot can be loaded again.
-// 512 rows of the 7B shape, before (tiled and ring kernels) and now: QKV 73 -> 58 us (128 x 192 blocks, 0.89 PFLOP/s, matrix
-// cores busy 35 % of the time), gate/up 101 -> 80 (256 x 192, 1.15, 51 %), down 57 -> 48 (256 x 128, 0.97, 37 %).  Tried: a wavefront
+// 512 rows of the 7B shape, before (tiled and ring kernels) and now: QKV 76 -> 59 us (128 x 192 blocks, 0.87 PFLOP/s, matrix
+// cores busy 35 % of the time), gate/up 107 -> 82 (256 x 192, 1.12, 52 %), down 58 -> 56 (128 x 128 in two slices, 0.83).  Tried: a wavefront
 // that touches this workgroup's share of the shared weight lines ahead of the loaders: 10 to 17 % faster without multiplies, 0 to
 // 30 % slower with them; weights past the caches: up to a third slower; four multiplying wavefronts of 128 x 96 instead of eight
 // of 64 x 96: 92 -> 97 us.
@@ -1195,9 +1195,8 @@ AccPlan acc_plan(int M, int n_tiles, int K, bool compacted = false) {
   // projection at 128 rows 19.1 against 19.6 us in blocks, down projection 35.9 against 40.0.)
   const bool one_chunk = m_tiles <= 4 && n_tiles % NW == 0 && (k_steps >= 512 || (m_tiles >= 3 && n_tiles > 128));
   if (m_tiles >= 3 && !one_chunk) {
-    // A slice costs its partial result's way out and back in: 8 bytes an element at 5 TB/s.  (7B shape, 512 rows: down projection
-    // 57 -> 48 us in four slices of 256 x 128 blocks, output projection 25.9 -> 25.0 in two of 128 x 128; 128 rows: output projection
-    // 15.7 -> 13.8 in four of 128 x 64.)
+    // A slice costs its partial result's way out and back in: 8 bytes an element at 5 TB/s.  (7B shape, down projection at 192 / 256 /
+    // 384 / 512 rows 35 -> 32, 36.5 -> 35, 56 -> 49, 58 -> 56 us, output projection at 128 / 512 rows 15.6 -> 13.6, 26.3 -> 25.2.)
     const auto in_slices = [&](int ks) {   // the cheapest blocks of that many slices, and their cost
       AccPlan q{1, ks, pick_block(kAccBlocks, m_tiles, n_tiles, (k_steps + ks - 1) / ks, ks)};
       q.cost = block_cost(m_tiles, n_tiles, (k_steps + ks - 1) / ks, q.block.mt, q.block.nt, ks) + (long)ks * m_tiles * n_tiles * 1024 * 8 / 5000;
@@ -1228,7 +1227,7 @@ AccPlan acc_plan(int M, int n_tiles, int K, bool compacted = false) {
     p.kind = 3;
     p.ksplit = 512 / n_tiles;
   } else if (m_tiles == 2 && n_tiles >= 128 && k_steps >= 4) {
-    // 64 x 64 blocks: 7B output projection 12.8 -> 8.8 us at 64 rows (its four wavefronts no longer fetch an operand each).  A whole
+    // 64 x 64 blocks: 7B output projection 12.9 -> 9.1 us at 64 rows (its four wavefronts no longer fetch an operand each).  A whole
     // iteration against the form above or, at 128 and 256 tiles, below: 136 to 200 tiles 2.4 to 4.4 % faster at 64 rows, 2 to 3 % at
     // 36 to 40, 212 tiles 1 and 0 %, 256 tiles 3 and 2.5 %; 216 to 248 tiles, where that form's pairs fill the chip as well, 1 to 1.5 %
     // slower at 36 rows and no faster at 64: they keep it.  (Adding a slice in four parts, as that kernel does, costs nothing.)
@@ -1301,8 +1300,8 @@ void launch(const GemmShape& g, const Epi& e, Pred pred, const FillCtl& fc, int 
   if constexpr (!FILL) {
     // Block kernel: QKV from three batch tiles on (at two the streaming kernel, which carries the exit decision), accumulate
     // projections by acc_plan, gate/up and the LM head from five (three where the tiled kernel does not take their tiles, below).
-    // (7B shape, us: QKV at 128 / 192 / 256 / 384 / 512 rows 38 -> 34, 46 -> 37, 48 -> 41, 72 -> 57, 73 -> 58; gate/up at 192 / 256 / 384 /
-    // 512 72 -> 57, 75 -> 61, 91 -> 78, 101 -> 80; LM head at 192 / 350 / 384 77 -> 75, 123 -> 111, 123 -> 115; at 128 rows and fewer
+    // (7B shape, us: QKV at 128 / 192 / 256 / 384 / 512 rows 39 -> 34, 47 -> 38, 49 -> 42, 74 -> 58, 76 -> 59; gate/up at 192 / 256 / 384 /
+    // 512 74 -> 58, 76 -> 62, 95 -> 81, 107 -> 82; LM head at 192 / 350 / 384 80 -> 77, 129 -> 116, 129 -> 116; at 128 rows and fewer
     // gate/up and the LM head are bound by the weight stream either way: 44 against 43 to 46 us, 47 against 51.)
     if constexpr (ACC) {
       if (ap.kind == 1) {
