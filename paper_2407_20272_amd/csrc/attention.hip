@@ -13,6 +13,7 @@
 
 #include "ee_common.h"
 #include "ee_epilogue.h"
+#include "ee_decide.h"
 
 namespace ee {
 namespace {
@@ -78,15 +79,24 @@ __device__ uint4 k_zero16;
 
 constexpr int TABLE_LDS_MAX = kAttnMaxBlocks;   // block-table entries staged in LDS
 
-template <class T, int DH, bool OUT_XT, bool SPLIT>
-__global__ __launch_bounds__(256) void attn_decode_kernel(AttnArgs a, Pred pred) {
+// What attention of the float path may do besides (launch_attention_f32).
+struct NoOproj {};
+struct Oproj {
+  const float* w;
+  float* parts;
+  SimpleDecision job;   // n_wg: rows of leading workgroups (0: no decision)
+};
+
+template <class T, int DH, bool OUT_XT, bool SPLIT, class Op, class Skip>
+__device__ __forceinline__ void attn_decode(const AttnArgs& a, const Op& op, int b, Skip skip) {
+  constexpr bool OPROJ = std::is_same<Op, Oproj>::value;
   constexpr int EPL = Elems<T>::N;         // values per 16-byte lane load
   constexpr int LPT = DH / EPL;            // lanes per token
   constexpr int TPL = 64 / LPT;            // tokens per wavefront load
   constexpr int LPB = 16 / TPL;            // loads per 16-token block
   static_assert(LPT >= 8 && LPT <= 32, "unsupported head_dim for this element type");
 
-  const int head = blockIdx.x, b = blockIdx.y;
+  const int head = blockIdx.x;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int sub = lane % LPT;              // which EPL-wide slice of the head this lane holds
@@ -94,7 +104,8 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnArgs a, Pred pred)
   const int32_t* table = a.block_tables + (size_t)(a.row_table ? safe_row(a.row_table[b], a.B) : b) * a.max_blocks;
 
   extern __shared__ int32_t tbl[];
-  if (pred_skip(pred)) return;
+  if constexpr (!OPROJ)
+    if (skip()) return;
   // Everything the first K/V load needs is requested before any of it is waited for: the context length, the
   // start of the block-table row (its width is known without the length) and q: one memory round trip, not
   // three in a row.
@@ -107,6 +118,10 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnArgs a, Pred pred)
     const float* qp = a.q + ((size_t)b * a.n_heads + head) * DH + sub * EPL;
 #pragma unroll
     for (int i = 0; i < EPL; ++i) q[i] = qp[i];
+  }
+  if constexpr (OPROJ) {   // (the float path's launches are short enough for this to be a part of them)
+    asm volatile("" ::: "memory");   // the loads above stay above
+    if (skip()) return;
   }
   if (left != 0) return;   // the sequence has left at an earlier layer: nothing to attend, nothing read
   // positions 0..p inclusive, never beyond the block table's width
@@ -195,6 +210,21 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnArgs a, Pred pred)
   int lb = lb_begin + wave;
   if (lb < lb_end) fetch(A, lb);
   if (lb + NW < lb_end) fetch(B, lb + NW);
+  // The head's columns of this workgroup's rows of the output projection, LPT lanes a row, are on their way while the keys are
+  // looked at.
+  constexpr int AHEAD = OPROJ ? 8 : 1, RPI = NW * TPL;
+  float4 wo[AHEAD];
+  [[maybe_unused]] const float* wrow = nullptr;
+  [[maybe_unused]] int d_out = 0, rows = 0;
+  if constexpr (OPROJ) {
+    d_out = a.n_heads * DH;
+    rows = d_out / (int)gridDim.z;   // (whole iterations of RPI rows: d_out is a multiple of 64)
+    if (op.w) {
+      wrow = op.w + (size_t)(blockIdx.z * rows + wave * TPL + grp) * d_out + head * DH + sub * EPL;
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) wo[i] = *reinterpret_cast<const float4*>(wrow + (size_t)min(i * RPI, rows - RPI) * d_out);
+    }
+  }
   for (; lb + 3 * NW < lb_end; lb += 2 * NW) {
     consume(A, lb);
     __builtin_amdgcn_sched_barrier(0);
@@ -231,7 +261,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnArgs a, Pred pred)
   }
 
   // merge the wavefronts
-  __shared__ float sm[NW], sl[NW], so[NW][DH];
+  __shared__ __align__(16) float sm[NW], sl[NW], so[NW][DH];
   if (grp == 0) {
 #pragma unroll
     for (int e = 0; e < EPL; ++e) so[wave][sub * EPL + e] = o[e];
@@ -263,13 +293,50 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnArgs a, Pred pred)
     } else {
       const float r = acc / L;
       const int col = head * DH + threadIdx.x;
-      if constexpr (OUT_XT) {
+      if (OPROJ && wrow) {
+        so[0][threadIdx.x] = r;   // (this thread was the last to read it)
+      } else if constexpr (OUT_XT) {
         reinterpret_cast<bf16_t*>(a.out)[xt_index(out_row, col, a.n_heads * DH)] = (bf16_t)r;
       } else {
         reinterpret_cast<float*>(a.out)[(size_t)out_row * a.n_heads * DH + col] = r;
       }
     }
   }
+  if constexpr (OPROJ) {
+    if (!wrow) return;
+    __syncthreads();
+    const float4 x = *reinterpret_cast<const float4*>(&so[0][sub * EPL]);
+    float* part = op.parts + ((size_t)head * a.B + b) * d_out + blockIdx.z * rows + wave * TPL + grp;
+    auto row = [&](const float4& w, int i) {
+      const float v = group_sum<LPT>(fmaf(w.w, x.w, fmaf(w.z, x.z, fmaf(w.y, x.y, w.x * x.x))));
+      if (sub == 0) part[i * RPI] = v;
+    };
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i)
+      if (i * RPI < rows) row(wo[i], i);
+    for (int i = AHEAD; i * RPI < rows; ++i) row(*reinterpret_cast<const float4*>(wrow + (size_t)i * RPI * d_out), i);
+  }
+}
+
+template <class T, int DH, bool OUT_XT, bool SPLIT>
+__global__ __launch_bounds__(256) void attn_decode_kernel(AttnArgs a, Pred pred) {
+  attn_decode<T, DH, OUT_XT, SPLIT>(a, NoOproj{}, blockIdx.y, [&] { return pred_skip(pred); });
+}
+
+// fp32 path: attention and output projection in one launch, with the exit decision of the layer before in leading workgroups.  All of
+// them apply the decision's own rule (layer_ran), not the live flag: the attention of the layer after the batch exit layer may
+// run, and nobody reads its result.
+template <int DH>
+__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, Pred pred, Oproj op) {
+  if ((int)blockIdx.y < op.job.n_wg) {
+    if (blockIdx.z || !layer_ran(op.job.a.s, op.job.a.layer)) return;
+    __shared__ float4 red[4];
+    const int m = blockIdx.y * gridDim.x + blockIdx.x;
+    if (m < op.job.a.B) decide_row_f32(op.job.logits, op.job.row_scale, op.job.vocab, op.job.a, m, red);
+    return;
+  }
+  attn_decode<float, DH, false, false>(a, op, (int)blockIdx.y - op.job.n_wg,
+                                       [&] { return op.job.n_wg ? !layer_ran(op.job.a.s, op.job.a.layer) : pred_skip(pred); });
 }
 
 // Second launch of the split form: one workgroup of DH threads per (sequence, head) adds the parts in part order.
@@ -1110,6 +1177,16 @@ void attention_prepare() {
   prompt_lds_allowed<64, true>();
   prompt_lds_allowed<128, false>();
   prompt_lds_allowed<128, true>();
+}
+
+void launch_attention_f32(const AttnArgs& a, const float* w_o, float* parts, Pred pred, hipStream_t st, const SimpleDecision* with) {
+  Oproj op{w_o, parts, with ? *with : SimpleDecision{}};
+  op.job.n_wg = with ? (with->a.B + a.n_heads - 1) / a.n_heads : 0;
+  // Four workgroups share a head's columns, each with the attention to itself: 64 KB of weights are 2 us for one compute unit.
+  const dim3 grid(a.n_heads, a.B + op.job.n_wg, w_o ? 4 : 1), block(256);
+  const size_t lds = (size_t)a.max_blocks * sizeof(int32_t);
+  if (a.head_dim == 64) hipLaunchKernelGGL((attn_f32_kernel<64>), grid, block, lds, st, a, pred, op);
+  else hipLaunchKernelGGL((attn_f32_kernel<128>), grid, block, lds, st, a, pred, op);
 }
 
 int launch_attention(const AttnArgs& a, int dtype, Pred pred, hipStream_t st) {

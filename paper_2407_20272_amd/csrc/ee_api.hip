@@ -98,8 +98,12 @@ struct Workspace {
   RowMap rowmap;      // bf16: [Mpad] + [Mpad] + [1] row map of the sequences still active (per-sequence exit)
   // fp32 path
   float *ao, *act, *logits, *row_scale;   // (row_scale: see LmEpi)
+  float *h2, *parts;  // [B][d], [H][B][d]: hidden states between the layer's halves, attention times the output projection head by head (parts_f32)
   size_t bytes;
 };
+
+// Small float models: a layer in four launches instead of six (see ee_decode_iteration).
+constexpr int kF32FewRows = 64, kF32FewWidth = 512;
 
 Workspace carve(const ee_model_desc& D, int B, void* base) {
   Workspace w{};
@@ -143,6 +147,8 @@ Workspace carve(const ee_model_desc& D, int B, void* base) {
     w.logits = c.take<float>(Bp * V);
     w.row_scale = c.take<float>(Bp);
     w.hprev = c.take<float>(Bp * d);
+    w.h2 = c.take<float>(Bp * d);
+    w.parts = c.take<float>((Bp * D.n_heads < 64 ? Bp * D.n_heads : 64) * d);
   }
   w.bytes = (c.off + 255) & ~(size_t)255;
   return w;
@@ -297,12 +303,13 @@ NormArgs plain_norm(const ee_model_desc& D, const float* h, const void* gain, bf
   return a;
 }
 // Logits of RMSNorm(h; g_final); the decision (launch_head_decide_f32) reads them.
+SimpleShape head_shape_f32(const ee_model& M, const float* h, int B) {
+  return SimpleShape{reinterpret_cast<const float*>(M.w_lm), h, reinterpret_cast<const float*>(M.g_final), M.desc.rms_eps, M.desc.d_model, B, 0, M.desc.vocab, 1};
+}
+LmEpi head_epi_f32(const ee_model& M, const Workspace& w) { return LmEpi{nullptr, w.logits, w.row_scale, 1, M.desc.vocab, 0.0f, nullptr}; }
 void enqueue_head_f32(const ee_model& M, const Workspace& w, const float* h, int B, int layer, Pred pred, hipStream_t st) {
-  const ee_model_desc& D = M.desc;
   ProfScope ps(EE_K_HEAD, layer, st);
-  SimpleShape g{reinterpret_cast<const float*>(M.w_lm), h, reinterpret_cast<const float*>(M.g_final), D.rms_eps, D.d_model, B, 0, D.vocab, 1};
-  LmEpi e{nullptr, w.logits, w.row_scale, 1, D.vocab, 0.0f, nullptr};
-  launch_simple_lm(g, e, pred, st);
+  launch_simple_lm(head_shape_f32(M, h, B), head_epi_f32(M, w), pred, st);
 }
 
 // --- KV filling for layers above fill_from ----------------------------------------------------------------
@@ -324,8 +331,9 @@ void enqueue_fill_bf16(const ee_model& M, const ee_kv_cache& C, const ee_batch& 
   e.fill_from_stride = stride;
   launch_gemm_kvfill_bf16(fl, D.n_layers, w.fill_x, (size_t)Mpad * D.d_model, pool_layer_elems(D, C), g, e, pred, st);
 }
+// head: also the LM head over h, in the same launch, where its own predicate holds.
 void enqueue_fill_f32(const ee_model& M, const ee_kv_cache& C, const ee_batch& Bt, const Workspace& w, const float* h,
-                      const int32_t* fill_from, int stride, Pred pred, hipStream_t st) {
+                      const int32_t* fill_from, int stride, Pred pred, hipStream_t st, const Pred* head = nullptr) {
   const ee_model_desc& D = M.desc;
   ProfScope ps(EE_K_KVFILL, 0, st);
   SimpleFill fill{};
@@ -338,7 +346,10 @@ void enqueue_fill_f32(const ee_model& M, const ee_kv_cache& C, const ee_batch& B
   QkvEpi e = make_qkv_epi(D, C, Bt, w, 1, nullptr);
   e.fill_from = fill_from;
   e.fill_from_stride = stride;
-  launch_simple_kvfill(fill, D.n_layers, g, e, pred, st);
+  if (head)
+    launch_simple_head_kvfill(head_shape_f32(M, h, Bt.batch), head_epi_f32(M, w), *head, fill, D.n_layers, g, e, pred, st);
+  else
+    launch_simple_kvfill(fill, D.n_layers, g, e, pred, st);
 }
 
 // --- stand-alone exit check: validation and launch sequence shared by the two entry points -----------------
@@ -583,13 +594,24 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // The exit decision of layer i (softmax-response measures, bf16, batches the streaming projection kernel serves)
   // rides along with the QKV projection launch of layer i + 1: one launch less per checked layer.
   const bool carry_combine = bf && !dotmode && !compact && gemm_qkv_carries_combine(B);
-  // The float path does the same where the projection is no more than its launch (the one behind the batch exit layer runs in
-  // vain) and the rows' decisions find room beside it: four layers of width 256 and four sequences 111 -> 100 us, 64 sequences 214 -> 201.
-  const bool carry_f32 = !bf && !dotmode && B <= 64 && d <= 512;
+  // Float path, where a launch costs more than what it does: a layer in four launches instead of six.  The LM head of layer i shares
+  // the launch of layer i + 1's QKV projection (both read the same hidden states), the decision from it that of layer i + 1's
+  // attention (behind the batch exit layer both run in vain), KV filling and the last LM head one more.  And attention multiplies by
+  // the head's columns of the output projection, so that what is left of the latter is a sum of as many parts as there are heads, which
+  // gate/up takes while it loads its operand.  Every gate/up workgroup reads all parts and four attention workgroups repeat a pair's
+  // keys, so that goes up to 64 pairs.  Iterations of the four-layer model of width 256 (six launches a layer -> four, us): 4 sequences
+  // 98 -> 83; attention with the output projection at 128 pairs 104 against 92 without, at 256 152 against 114; the shared launches
+  // alone 119 -> 114 with 33 sequences, 64 rows even.
+  bool few_f32 = !bf && !batch->row_table && B <= kF32FewRows && d <= kF32FewWidth && attn_split_parts(B, D.n_heads, batch->max_blocks) == 1;
+  bool parts_f32 = few_f32 && B * D.n_heads <= 64;
+  for (int i = 0; i < n; ++i) parts_f32 = parts_f32 && (reinterpret_cast<uintptr_t>(model->layers[i].w_o) & 15) == 0;   // (16-byte loads)
+  // Contexts that several workgroups share: the decision alone, inside the QKV launch.
+  const bool carry_f32 = !bf && !dotmode && B <= 64 && d <= kF32FewWidth && !few_f32;
   const bool carry_decide = bf && dotmode && !compact && gemm_qkv_carries_combine(B);
   CombineArgs pending{};
   DecideArgs pending_dot{};
   bool have_pending = false, have_pending_dot = false;
+  Pred pending_pred = always;   // (few_f32) of the layer whose LM head is still to run
   // Algorithm 1, batch inference loop.  Everything is enqueued; the done flag turns later layers into no-ops.
   for (int i = 1; i <= n; ++i) {
     const Pred run_layers = i <= first_check ? always : after_check;
@@ -673,22 +695,30 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
         launch_finish_norm(na, run_layers, st);
       }
     } else {
+      const SimpleDecision job{pending, w.logits, w.row_scale, D.vocab, 0};
       {
         ProfScope ps(EE_K_QKV, i, st);
         SimpleShape gq{reinterpret_cast<const float*>(L.w_qkv), w.h, reinterpret_cast<const float*>(L.g_attn), D.rms_eps, d, B, 0, 3 * d,
                        D.head_dim / 2};
         QkvEpi qe = make_qkv_epi(D, *cache, *batch, w, i, w.q);
-        const SimpleDecision job{pending, w.logits, w.row_scale, D.vocab, 0};
-        launch_simple_qkv(gq, qe, run_layers, st, have_pending ? &job : nullptr);
-        have_pending = false;
+        if (have_pending && few_f32)
+          launch_simple_head_qkv(head_shape_f32(*model, w.h, B), head_epi_f32(*model, w), gq, qe, pending_pred, st);
+        else
+          launch_simple_qkv(gq, qe, run_layers, st, have_pending ? &job : nullptr);
+        have_pending = have_pending && few_f32;
       }
-      {
+      if (few_f32) {
+        ProfScope ps(EE_K_ATTN, i, st);
+        at.out = w.ao;
+        launch_attention_f32(at, parts_f32 ? reinterpret_cast<const float*>(L.w_o) : nullptr, w.parts, run_layers, st, have_pending ? &job : nullptr);
+        have_pending = false;
+      } else {
         ProfScope ps(EE_K_ATTN, i, st);
         at.out = w.ao;
         at.out_xt = 0;
         if ((rc = launch_attention(at, D.dtype, run_layers, st))) return rc;
       }
-      {
+      if (!parts_f32) {
         ProfScope ps(EE_K_OPROJ, i, st);
         SimpleShape go{reinterpret_cast<const float*>(L.w_o), w.ao, nullptr, 0.0f, d, B, 0, d, 1};
         launch_simple_acc(go, AccEpi{w.h, 0, d, left}, run_layers, st);
@@ -696,12 +726,18 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       {
         ProfScope ps(EE_K_GATEUP, i, st);
         SimpleShape gg{reinterpret_cast<const float*>(L.w_gate_up), w.h, reinterpret_cast<const float*>(L.g_ffn), D.rms_eps, d, B, 0, 2 * f, f};
+        if (parts_f32) {
+          gg.parts = w.parts;
+          gg.n_parts = D.n_heads;
+          gg.x_out = w.h2;
+          gg.left = left;
+        }
         launch_simple_gateup(gg, GateUpEpi{w.act, f}, run_layers, st);
       }
       {
         ProfScope ps(EE_K_DOWN, i, st);
         SimpleShape gd{reinterpret_cast<const float*>(L.w_down), w.act, nullptr, 0.0f, f, B, 0, d, 1};
-        launch_simple_acc(gd, AccEpi{w.h, 0, d, left}, run_layers, st);
+        launch_simple_acc(gd, AccEpi{w.h, 0, d, left, parts_f32 ? w.h2 : nullptr}, run_layers, st);
       }
     }
     if (!bf && simmode && !head_here && i < n) launch_copy_f32(w.h, w.hprev, (size_t)B * d, st);
@@ -739,9 +775,10 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       CombineArgs ca{w.partials, D.vocab / 32, B, i, scale, thresholds[i - 1], D.conf_mode, forced_exit_layer, s, out_tokens,
                      out_conf ? out_conf + (size_t)(i - 1) * B : nullptr, left};
       if (bf) enqueue_head_bf16(*model, w, B, scale, i, rmap, run_layers, st);
-      else enqueue_head_f32(*model, w, w.h, B, i, run_layers, st);
-      if (carry_combine || carry_f32) {   // decided inside the next layer's QKV projection launch (i < n: there is one)
+      else if (!few_f32) enqueue_head_f32(*model, w, w.h, B, i, run_layers, st);
+      if (carry_combine || few_f32 || carry_f32) {   // decided inside a launch of the next layer (i < n: there is one)
         pending = ca;
+        pending_pred = run_layers;
         have_pending = true;
       } else {
         ProfScope ps(EE_K_COMBINE, i, st);
@@ -755,18 +792,18 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // Algorithm 1, KV cache filling for layers output_layer+1..n (runs only if the batch left early).  With
   // per-sequence exit the layers between a sequence's own exit layer and output_layer were filled by those
   // layers' own QKV projections (see above); every column of the residual stream is that sequence's exit state.
+  const Pred final_pred = dotmode ? always : after_check;
   if (use_exit_heads) {
     if (bf)
       enqueue_fill_bf16(*model, *cache, *batch, w, w.h, Mpad, out_batch_exit_layer, 0, run_fill, RopeJob{}, st);
     else
-      enqueue_fill_f32(*model, *cache, *batch, w, w.h, out_batch_exit_layer, 0, run_fill, st);
+      enqueue_fill_f32(*model, *cache, *batch, w, w.h, out_batch_exit_layer, 0, run_fill, st, few_f32 ? &final_pred : nullptr);
   }
 
   // With a head-less confidence measure no exit head has produced a token: the LM head then always runs, on the
   // hidden state at output_layer (still in place: later layers were skipped).  Otherwise it runs only when the loop
   // reached the last layer, whose normalisation launch has left the head's operand in place.
   {
-    const Pred final_pred = dotmode ? always : after_check;
     if (bf && dotmode) {
       {
         ProfScope ps(EE_K_NORM, n, st);
@@ -775,7 +812,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       enqueue_head_bf16(*model, w, B, 0.0f, n, RowMap{}, always, st);
     } else if (bf) {
       enqueue_head_bf16(*model, w, B, 0.0f, n, RowMap{}, final_pred, st);
-    } else {
+    } else if (!few_f32 || !use_exit_heads) {   // (otherwise it ran in the launch above)
       enqueue_head_f32(*model, w, w.h, B, n, final_pred, st);
     }
     CombineArgs ca{w.partials, D.vocab / 32, B, 0, 0.0f, 0.0f, 0, nullptr, s, out_tokens, nullptr};

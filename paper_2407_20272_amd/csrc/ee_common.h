@@ -96,6 +96,7 @@ struct AccEpi {                 // residual update
   int Mpad;                     // row count of a slice (bf16 path) or 0 (fp32 path)
   int n_out;
   const int32_t* skip;          // fp32 path: nullptr, or [M]: rows with skip[m] != 0 keep their hidden state
+  const float* h_in;            // fp32 path: nullptr (added in place), or what is added to, with h the result
 };
 struct GateUpEpi {              // act = silu(gate) * up
   void* act;                    // XT bf16 [Mpad][f] (bf16 path) or plain float [M][f]
@@ -304,6 +305,12 @@ struct SimpleShape {
   int row_begin;    // first output row
   int n_rows;       // output rows to compute (even)
   int pair_stride;  // rows (f, f + pair_stride) are computed together
+  // gate/up behind attention that has multiplied by the output projection's columns, head by head: the operand is x + parts[0] + parts[1] +
+  // .. ([n_parts][M][K]; rows with left[m] != 0: x alone), and is left in x_out [M][K].  parts == nullptr: x.
+  const float* parts;
+  int n_parts;
+  float* x_out;
+  const int32_t* left;
 };
 // An exit decision on materialised logits that rides along with a projection launch (one workgroup per row, in front).
 struct SimpleDecision {
@@ -314,6 +321,9 @@ struct SimpleDecision {
   int n_wg;   // set by the launch
 };
 void launch_simple_qkv(const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st, const SimpleDecision* with = nullptr);
+// The LM head in the launch of the next layer's QKV projection, or of KV filling (which runs where the head, by its predicate ph, does not).  Up to
+// 256 rows.
+void launch_simple_head_qkv(const SimpleShape& gh, const LmEpi& eh, const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st);
 void launch_simple_acc(const SimpleShape& g, const AccEpi& e, Pred pred, hipStream_t st);
 void launch_simple_gateup(const SimpleShape& g, const GateUpEpi& e, Pred pred, hipStream_t st);
 void launch_simple_lm(const SimpleShape& g, const LmEpi& e, Pred pred, hipStream_t st);
@@ -324,6 +334,8 @@ struct SimpleFill {
   size_t pool_layer_bytes;
 };
 void launch_simple_kvfill(const SimpleFill& fill, int n_layers, const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st);
+void launch_simple_head_kvfill(const SimpleShape& gh, const LmEpi& eh, Pred ph, const SimpleFill& fill, int n_layers, const SimpleShape& g, const QkvEpi& e,
+                               Pred pred, hipStream_t st);
 
 // attention.hip
 // Block ids and positions come from device memory the caller filled in; the kernels never let them reach outside
@@ -356,6 +368,9 @@ struct AttnArgs {
   int split_parts;
 };
 int launch_attention(const AttnArgs& a, int dtype, Pred pred, hipStream_t st);
+// fp32 path: attention of one workgroup per (sequence, head) that multiplies its result by the head's columns of the output projection w_o
+// [d][d] (parts [H][B][d], see SimpleShape), and takes the exit decision `with` of the layer before, if there is one, in leading workgroups.
+void launch_attention_f32(const AttnArgs& a, const float* w_o, float* parts, Pred pred, hipStream_t st, const SimpleDecision* with);
 // Host-side set-up for the current device (function attributes) that the first launch over prompt rows would otherwise do.
 void attention_prepare();
 // How many workgroups should share one (sequence, head) pair for this batch, and the floats of split_ws that takes.

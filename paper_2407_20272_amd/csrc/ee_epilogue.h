@@ -12,9 +12,6 @@ namespace ee {
 __device__ inline int32_t ctl_load(const int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void ctl_store(int32_t* p, int32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-__device__ inline void store_elem(float* p, float v) { *p = v; }
-__device__ inline void store_elem(bf16_t* p, float v) { *p = (bf16_t)v; }
-
 // Turns the rotary pair (lo, hi) by the angle with this cosine and sine.  Which of the two products is rounded on its own is
 // written out, the same for every epilogue: left to the compiler, the block kernel's q and K came out one rounding away from
 // what the other kernels and KV filling give (5 of 10 million cached elements differed).
@@ -24,42 +21,11 @@ __device__ inline void rotate(float& lo, float& hi, float c, float s) {
   hi = b;
 }
 
-// Rotary embedding (split-half pairing: channel j with j + dh/2, angle = pos * theta^(-2j/dh)) and the write of
-// this position's K/V into the paged cache; q goes to a dense buffer.  The (cos, sin) pairs come from a table
-// that rope_table_kernel fills once per call from angles formed in double (long contexts would lose the fraction
-// of the angle to float rounding of the frequency).
-template <class T>
-__device__ inline void epi_qkv(const QkvEpi& e, int m, int f_lo, float lo, float hi) {
-  if (e.fill_from && !(e.fill_from[(size_t)m * e.fill_from_stride] < e.layer)) return;
-  const int d = e.d_model, dh = e.head_dim, half = dh >> 1;
-  const int which = f_lo / d;  // 0 q, 1 k, 2 v
-  const int within = f_lo - which * d;
-  const int head = within / dh;
-  const int j = within - head * dh;  // < dh/2
-  const int p = e.context_lens[m];
-  if (which < 2 && e.rope_theta > 0.0f) {
-    const float2 cs = e.rope[(size_t)m * half + j];   // (cos, sin) of pos * theta^(-2j/dh), tabulated once per iteration
-    rotate(lo, hi, cs.x, cs.y);
-  }
-  if (which == 0) {
-    if (e.q) {
-      float* q = e.q + (size_t)m * d + head * dh + j;
-      q[0] = lo;
-      q[half] = hi;
-    }
-    return;
-  }
-  const bool p_ok = (unsigned)p < (unsigned)(e.max_blocks * 16);
-  const int blk = e.block_tables[(size_t)(e.row_table ? safe_row(e.row_table[m], e.table_rows) : m) * e.max_blocks + (p_ok ? p >> 4 : 0)];
-  if (!p_ok || (unsigned)blk >= (unsigned)e.num_blocks) return;   // never outside the pools
-  const size_t at = (((size_t)blk * e.n_heads + head) * 16 + (p & 15)) * dh + j;
-  T* pool = reinterpret_cast<T*>(which == 1 ? e.k_pool : e.v_pool);
-  store_elem(pool + at, lo);
-  store_elem(pool + at + half, hi);
-}
-
-// The same for four consecutive channels f_lo0..f_lo0+3 (f_lo0 a multiple of 4) of batch row m and their four
-// rotary partners, bf16 cache: one look-up of the slot, 8-byte stores into the cache, 16-byte stores into q.
+// Rotary embedding (split-half pairing: channel j with j + dh/2, angle = pos * theta^(-2j/dh)) of four consecutive channels
+// f_lo0..f_lo0+3 (f_lo0 a multiple of 4) of batch row m and their four rotary partners, and the write of this position's K/V into the paged
+// bf16 cache; q goes to a dense buffer.  One look-up of the slot, 8-byte stores into the cache, 16-byte stores into q.  The (cos, sin)
+// pairs come from a table that is filled once per call from angles formed in double (long contexts would lose the fraction of the
+// angle to float rounding of the frequency).
 __device__ inline void epi_qkv4(const QkvEpi& e, int m, int f_lo0, float (&lo)[4], float (&hi)[4]) {
   if (e.fill_from && !(e.fill_from[(size_t)m * e.fill_from_stride] < e.layer)) return;
   const int d = e.d_model, dh = e.head_dim, half = dh >> 1;
@@ -91,11 +57,6 @@ __device__ inline void epi_qkv4(const QkvEpi& e, int m, int f_lo0, float (&lo)[4
   typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
   *reinterpret_cast<bf16x4*>(pool + at) = bf16x4{(bf16_t)lo[0], (bf16_t)lo[1], (bf16_t)lo[2], (bf16_t)lo[3]};
   *reinterpret_cast<bf16x4*>(pool + at + half) = bf16x4{(bf16_t)hi[0], (bf16_t)hi[1], (bf16_t)hi[2], (bf16_t)hi[3]};
-}
-
-__device__ inline void epi_acc(const AccEpi& e, int m, int f, float v) {
-  if (e.skip && ctl_load(e.skip + m) != 0) return;
-  e.h[(size_t)m * e.n_out + f] += v;   // fp32 path: every element of the residual stream has one contributor per launch
 }
 
 // SwiGLU product; f_lo is the gate row f, f_hi the up row f + d_ffn.

@@ -77,6 +77,27 @@ def test_fp32_odd_widths(batch, d_ffn, vocab, conf_mode):
     assert stats["near_threshold"] + stats["near_tie"] <= 1
 
 
+@pytest.mark.parametrize("batch,heads,dh,d_ffn,layers,head_mode", [
+    (1, 1, 64, 62, 1, True),       # no layer behind the first: the only LM head runs beside KV filling
+    (32, 2, 64, 130, 3, 2),        # 64 (sequence, head) pairs: attention multiplies by the output projection; contraction of 130, no 16-byte loads
+    (33, 2, 64, 256, 3, True),     # 66: a launch of its own again
+    (12, 5, 64, 1028, 3, 2),       # 320 channels: a last iteration of 64 of them; five parts, four of them loaded ahead; past 1024 in a loop
+    (16, 4, 128, 1024, 3, True),   # 512 channels, 64 pairs, 1024 of a contraction ahead
+    (64, 2, 128, 320, 2, 2),       # the last row count of the four-launch form ..
+    (65, 2, 128, 320, 2, True),    # .. past it
+    (5, 9, 64, 576, 2, True),      # .. and past its width
+])
+def test_fp32_layers_in_four_launches(batch, heads, dh, d_ffn, layers, head_mode):
+    """Float layers of up to 64 rows and 512 channels, at the edges of the forms: the LM head beside the next QKV projection or KV filling,
+    the decision in front of attention, the output projection inside it; sequences leave together or one by one."""
+    cfg = TINY.with_(batch=batch, n_heads=heads, head_dim=dh, d_model=heads * dh, d_ffn=d_ffn, vocab=130, n_layers=layers, prompt_len=20,
+                     min_prompt_len=3, weight_std=0.05, logit_scale=1.0, threshold=0.3, shuffled_blocks=True, tied_head=False)
+    forced = torch.randint(1, layers + 1, (3, batch), generator=torch.Generator().manual_seed(batch), dtype=torch.int32)
+    if head_mode is True:
+        forced = None
+    lockstep(cfg, seed=13, steps=3, heads=head_mode, forced_seq=forced)
+
+
 def test_fp32_ragged_prompts_shuffled_blocks_conf_mode1():
     cfg = TINY.with_(batch=6, prompt_len=21, min_prompt_len=3, shuffled_blocks=True, conf_mode=1, weight_std=0.05,
                      logit_scale=2.0, threshold=0.2, n_layers=5, exit_every=2)
