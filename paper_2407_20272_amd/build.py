@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libee_decode.so")
-SOURCES = ["ee_api.hip", "gemm_mfma.hip", "gemm_simple.hip", "attention.hip", "misc.hip", "pack.hip", "calib.hip"]
+SOURCES = ["ee_api.hip", "gemm_mfma.hip", "gemm_small.hip", "gemm_simple.hip", "attention.hip", "misc.hip", "pack.hip", "calib.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]

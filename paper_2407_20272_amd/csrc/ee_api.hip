@@ -290,6 +290,14 @@ void enqueue_head_bf16(const ee_model& M, const Workspace& w, int B, float scale
   ProfScope ps(EE_K_HEAD, layer, st);
   launch_gemm_lm_bf16(g, e, pred, st);
 }
+// The same from the residual rows themselves (gemm_small_takes).
+void enqueue_head_small(const ee_model& M, const Workspace& w, int B, float scale, int layer, Pred pred, hipStream_t st) {
+  const ee_model_desc& D = M.desc;
+  SmallShape g{M.w_lm, w.h, reinterpret_cast<const bf16_t*>(M.g_final), D.rms_eps, D.d_model, B, 16, D.vocab / 32, 0, 0};
+  LmEpi e{w.partials, nullptr, nullptr, D.vocab / 32, D.vocab, scale, nullptr};
+  ProfScope ps(EE_K_HEAD, layer, st);
+  launch_small_lm(g, e, pred, st);
+}
 // RMSNorm of hidden rows h [B][d] (nothing added) with one gain into x.
 NormArgs plain_norm(const ee_model_desc& D, const float* h, const void* gain, bf16_t* x, int B) {
   NormArgs a{};
@@ -594,6 +602,8 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // The exit decision of layer i (softmax-response measures, bf16, batches the streaming projection kernel serves)
   // rides along with the QKV projection launch of layer i + 1: one launch less per checked layer.
   const bool carry_combine = bf && !dotmode && !compact && gemm_qkv_carries_combine(B);
+  // Up to eight sequences: projections that build their operand from the residual rows and add to these, no launch between them.
+  const bool small = bf && !dotmode && !batch->row_table && gemm_small_takes(B, d);
   // Float path, where a launch costs more than what it does: a layer in four launches instead of six.  The LM head of layer i shares
   // the launch of layer i + 1's QKV projection (both read the same hidden states), the decision from it that of layer i + 1's
   // attention (behind the batch exit layer both run in vain), KV filling and the last LM head one more.  And attention multiplies by
@@ -625,7 +635,35 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       at.split_ws = at.split_parts > 1 ? w.attn_split : nullptr;
     }
     const bool head_here = use_exit_heads && has_head(D, i);
-    if (bf) {
+    if (small) {
+      auto shape = [&](const void* weights, const void* x, const void* gain, int K, int pair_stride, int whole, int halves) {
+        return SmallShape{weights, x, reinterpret_cast<const bf16_t*>(gain), D.rms_eps, K, B, pair_stride, whole, halves, 0};
+      };
+      const AccEpi add{w.h, 0, d, left, nullptr};
+      {
+        ProfScope ps(EE_K_QKV, i, st);   // (V has no rotation: its tiles go by halves)
+        launch_small_qkv(shape(L.w_qkv, w.h, L.g_attn, d, D.head_dim / 2, 2 * d / 32, d / 16), make_qkv_epi(D, *cache, *batch, w, i, w.q), run_layers,
+                         st, have_pending ? &pending : nullptr);
+        have_pending = false;
+      }
+      {
+        ProfScope ps(EE_K_ATTN, i, st);
+        at.out = w.y;
+        if ((rc = launch_attention(at, D.dtype, run_layers, st))) return rc;
+      }
+      {
+        ProfScope ps(EE_K_OPROJ, i, st);
+        launch_small_oproj(shape(L.w_o, w.y, nullptr, d, 16, 0, 0), add, run_layers, st);
+      }
+      {
+        ProfScope ps(EE_K_GATEUP, i, st);
+        launch_small_gateup(shape(L.w_gate_up, w.h, L.g_ffn, d, f, 2 * f / 32, 0), GateUpEpi{w.actT, f}, run_layers, st);
+      }
+      {
+        ProfScope ps(EE_K_DOWN, i, st);
+        launch_small_down(shape(L.w_down, w.actT, nullptr, f, 16, 0, 0), add, run_layers, st);
+      }
+    } else if (bf) {
       {
         ProfScope ps(EE_K_QKV, i, st);
         GemmShape gq{L.w_qkv, w.xT, d, B, 0, 3 * d / 32, D.head_dim / 2, 1};
@@ -774,7 +812,8 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       const float scale = D.logit_scale * (float)i;
       CombineArgs ca{w.partials, D.vocab / 32, B, i, scale, thresholds[i - 1], D.conf_mode, forced_exit_layer, s, out_tokens,
                      out_conf ? out_conf + (size_t)(i - 1) * B : nullptr, left};
-      if (bf) enqueue_head_bf16(*model, w, B, scale, i, rmap, run_layers, st);
+      if (small) enqueue_head_small(*model, w, B, scale, i, run_layers, st);
+      else if (bf) enqueue_head_bf16(*model, w, B, scale, i, rmap, run_layers, st);
       else if (!few_f32) enqueue_head_f32(*model, w, w.h, B, i, run_layers, st);
       if (carry_combine || few_f32 || carry_f32) {   // decided inside a launch of the next layer (i < n: there is one)
         pending = ca;
@@ -810,6 +849,8 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
         launch_finish_norm(plain_norm(D, w.h, model->g_final, w.xH, B), always, st);
       }
       enqueue_head_bf16(*model, w, B, 0.0f, n, RowMap{}, always, st);
+    } else if (small) {
+      enqueue_head_small(*model, w, B, 0.0f, n, final_pred, st);
     } else if (bf) {
       enqueue_head_bf16(*model, w, B, 0.0f, n, RowMap{}, final_pred, st);
     } else if (!few_f32 || !use_exit_heads) {   // (otherwise it ran in the launch above)

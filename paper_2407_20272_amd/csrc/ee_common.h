@@ -294,6 +294,26 @@ struct FillLayers {
 void launch_gemm_kvfill_bf16(const FillLayers& fl, int n_layers, const bf16_t* x_slabs, size_t x_slab_elems,
                              size_t pool_layer_elems, const GemmShape& g, const QkvEpi& e, Pred pred, hipStream_t st);
 
+// gemm_small.hip (bf16 path, up to eight rows).  w: packed.  QKV, gate/up and the LM head take the residual rows [M][K] and multiply
+// RMSNorm(x; gain); the output projection takes float rows, the down projection bf16 rows [M][K], and both add to the residual rows in place
+// (AccEpi as on the fp32 path).  gate/up leaves plain rows [M][d_ffn].
+struct SmallShape {
+  const void* w;
+  const void* x;
+  const bf16_t* gain;
+  float eps;
+  int K, M;
+  int pair_stride;
+  int whole, halves;   // output tiles that are finished whole, and 16-row halves of the tiles behind them
+  int wgs;             // set by the launcher
+};
+bool gemm_small_takes(int B, int d);
+void launch_small_qkv(const SmallShape& g, const QkvEpi& e, Pred pred, hipStream_t st, const CombineArgs* with_combine);
+void launch_small_oproj(const SmallShape& g, const AccEpi& e, Pred pred, hipStream_t st);
+void launch_small_gateup(const SmallShape& g, const GateUpEpi& e, Pred pred, hipStream_t st);
+void launch_small_down(const SmallShape& g, const AccEpi& e, Pred pred, hipStream_t st);
+void launch_small_lm(const SmallShape& g, const LmEpi& e, Pred pred, hipStream_t st);
+
 // gemm_simple.hip (fp32 path).  w: plain [n_out][K]; x: plain [M][K]; QKV, gate/up and the LM head take the residual rows
 // as x and multiply RMSNorm(x; gain), the accumulate projections take x as it is (gain unused).
 struct SimpleShape {

@@ -115,6 +115,29 @@ def test_small_bf16_lockstep(batch):
     assert len(set(stats["L"])) >= 1
 
 
+@pytest.mark.parametrize("batch,heads,dh,d_ffn,vocab,layers,head_mode", [
+    (1, 1, 64, 16, 32, 2, True),       # one tile everywhere, a contraction of one step, wavefronts without a load
+    (2, 3, 64, 48, 96, 3, 2),          # three steps: a last load that is not full
+    (3, 5, 64, 496, 1344, 3, 2),       # three rows of four, 31 steps
+    (4, 2, 128, 80, 64, 2, True),
+    (5, 6, 64, 1040, 160, 3, 2),       # the narrowest of five to eight rows ..
+    (8, 6, 64, 336, 160, 3, True),
+    (8, 5, 64, 336, 160, 3, 2),        # .. and one narrower, in the other kernels
+    (8, 24, 128, 32, 64, 1, True),     # the widest of eight rows: 24576 channels; 8-row units
+    (7, 25, 128, 32, 64, 1, True),     # .. and wider
+    (1, 32, 128, 80, 64, 2, True),     # 16-row units, one a workgroup
+    (3, 33, 128, 32, 64, 1, True),     # past 4096 channels: operand rows in four groups
+])
+def test_bf16_up_to_eight_sequences(batch, heads, dh, d_ffn, vocab, layers, head_mode):
+    """Projections that build their own operand and add to the residual rows, at the edges of their units, loads and rule; sequences leave
+    together or one by one."""
+    cfg = small_bf16(batch=batch, n_heads=heads, head_dim=dh, d_model=heads * dh, d_ffn=d_ffn, vocab=vocab, n_layers=layers, prompt_len=19,
+                     min_prompt_len=5, shuffled_blocks=True, weight_std=0.05 if heads * dh < 1024 else 0.02)
+    forced = torch.randint(1, layers + 1, (3, batch), generator=torch.Generator().manual_seed(batch), dtype=torch.int32)
+    stats = lockstep(cfg, seed=17, steps=3, heads=head_mode, forced_seq=forced if head_mode == 2 else None)
+    assert stats["near_threshold"] + stats["near_tie"] <= max(2, (stats["decisions"] + stats["tokens"]) // 20), stats
+
+
 def test_bf16_width_1280_partly_rearranged_tile_order():
     """d_model 1280 (10 heads x 128): the QKV projection has 80 whole and 40 halved tiles, so the XCD-aware tile
     order of the streaming kernel rearranges 64 of each and leaves the rest in place; KV filling runs too."""
