@@ -268,6 +268,7 @@ QkvEpi make_qkv_epi(const ee_model_desc& D, const ee_kv_cache& C, const ee_batch
   e.row_table = Bt.row_table;
   e.fill_from = nullptr;
   e.fill_from_stride = 0;
+  e.fill_lead = 0;
   e.layer = layer;
   e.max_blocks = Bt.max_blocks;
   e.n_heads = D.n_heads;
@@ -323,7 +324,7 @@ void enqueue_head_f32(const ee_model& M, const Workspace& w, const float* h, int
 // --- KV filling for layers above fill_from ----------------------------------------------------------------
 // h: hidden rows [B][d] (inside an iteration: the residual stream, final at the batch exit layer).
 void enqueue_fill_bf16(const ee_model& M, const ee_kv_cache& C, const ee_batch& Bt, const Workspace& w, const float* h,
-                       int Mpad, const int32_t* fill_from, int stride, Pred pred, const RopeJob& rope, hipStream_t st) {
+                       int Mpad, const int32_t* fill_from, int stride, int lead, Pred pred, const RopeJob& rope, hipStream_t st) {
   const ee_model_desc& D = M.desc;
   GainTable gt{};
   FillLayers fl{};
@@ -332,16 +333,17 @@ void enqueue_fill_bf16(const ee_model& M, const ee_kv_cache& C, const ee_batch& 
     fl.w_qkv[i] = M.layers[i].w_qkv;
   }
   ProfScope ps(EE_K_KVFILL, 0, st);
-  launch_fill_prep(h, gt, D.n_layers, w.fill_x, D.rms_eps, fill_from, stride, Bt.batch, Mpad, D.d_model, pred, rope, st);
+  launch_fill_prep(h, gt, D.n_layers, w.fill_x, D.rms_eps, fill_from, stride, lead, Bt.batch, Mpad, D.d_model, pred, rope, st);
   GemmShape g{nullptr, nullptr, D.d_model, Bt.batch, D.d_model / 32, 2 * D.d_model / 32, D.head_dim / 2, 1};
   QkvEpi e = make_qkv_epi(D, C, Bt, w, 1, nullptr);
   e.fill_from = fill_from;
   e.fill_from_stride = stride;
+  e.fill_lead = lead;
   launch_gemm_kvfill_bf16(fl, D.n_layers, w.fill_x, (size_t)Mpad * D.d_model, pool_layer_elems(D, C), g, e, pred, st);
 }
 // head: also the LM head over h, in the same launch, where its own predicate holds.
 void enqueue_fill_f32(const ee_model& M, const ee_kv_cache& C, const ee_batch& Bt, const Workspace& w, const float* h,
-                      const int32_t* fill_from, int stride, Pred pred, hipStream_t st, const Pred* head = nullptr) {
+                      const int32_t* fill_from, int stride, int lead, Pred pred, hipStream_t st, const Pred* head = nullptr) {
   const ee_model_desc& D = M.desc;
   ProfScope ps(EE_K_KVFILL, 0, st);
   SimpleFill fill{};
@@ -354,6 +356,7 @@ void enqueue_fill_f32(const ee_model& M, const ee_kv_cache& C, const ee_batch& B
   QkvEpi e = make_qkv_epi(D, C, Bt, w, 1, nullptr);
   e.fill_from = fill_from;
   e.fill_from_stride = stride;
+  e.fill_lead = lead;
   if (head)
     launch_simple_head_kvfill(head_shape_f32(M, h, Bt.batch), head_epi_f32(M, w), *head, fill, D.n_layers, g, e, pred, st);
   else
@@ -832,11 +835,14 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // per-sequence exit the layers between a sequence's own exit layer and output_layer were filled by those
   // layers' own QKV projections (see above); every column of the residual stream is that sequence's exit state.
   const Pred final_pred = dotmode ? always : after_check;
+  // Where the decision shared a launch with or behind the next layer's QKV projection, that layer has been cached (from the same operand):
+  // filling it again read a layer's weights for nothing (7B shape, 32 sequences that leave after 3 of 4 layers: 642 -> 613 us).
+  const int lead = carry_combine || carry_decide || carry_f32 || (few_f32 && !dotmode) ? 1 : 0;
   if (use_exit_heads) {
     if (bf)
-      enqueue_fill_bf16(*model, *cache, *batch, w, w.h, Mpad, out_batch_exit_layer, 0, run_fill, RopeJob{}, st);
+      enqueue_fill_bf16(*model, *cache, *batch, w, w.h, Mpad, out_batch_exit_layer, 0, lead, run_fill, RopeJob{}, st);
     else
-      enqueue_fill_f32(*model, *cache, *batch, w, w.h, out_batch_exit_layer, 0, run_fill, st, few_f32 ? &final_pred : nullptr);
+      enqueue_fill_f32(*model, *cache, *batch, w, w.h, out_batch_exit_layer, 0, lead, run_fill, st, few_f32 ? &final_pred : nullptr);
   }
 
   // With a head-less confidence measure no exit head has produced a token: the LM head then always runs, on the
@@ -923,11 +929,11 @@ int ee_kv_fill(const ee_model* model, const ee_kv_cache* cache, const ee_batch* 
   const int Mpad = round_up(B, 32);
   const Pred always{nullptr, 0};
   if (D.dtype == EE_BF16) {
-    enqueue_fill_bf16(*model, *cache, *batch, w, hidden, Mpad, fill_from_layer, 1, always,
+    enqueue_fill_bf16(*model, *cache, *batch, w, hidden, Mpad, fill_from_layer, 1, 0, always,
                       RopeJob{batch->context_lens, w.rope, D.head_dim, D.rope_theta}, st);
   } else {
     launch_rope_table(batch->context_lens, w.rope, B, D.head_dim, D.rope_theta, st);
-    enqueue_fill_f32(*model, *cache, *batch, w, hidden, fill_from_layer, 1, always, st);
+    enqueue_fill_f32(*model, *cache, *batch, w, hidden, fill_from_layer, 1, 0, always, st);
   }
   EE_HIP(hipGetLastError());
   return EE_OK;

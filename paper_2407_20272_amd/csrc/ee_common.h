@@ -80,8 +80,9 @@ struct QkvEpi {                 // rotary embedding + paged cache write (+ q out
   const int32_t* context_lens;  // [M]
   const int32_t* block_tables;  // [M][max_blocks]
   const int32_t* row_table;     // nullptr, or [M]: row m uses row row_table[m] of block_tables
-  const int32_t* fill_from;     // nullptr, or [M]: only rows with fill_from[m] < layer are written (KV filling, which has no q)
+  const int32_t* fill_from;     // nullptr, or [M]: only rows with fill_from[m] + fill_lead < layer are written (KV filling, which has no q)
   int fill_from_stride;         // 1 = per row, 0 = one value for the whole batch
+  int fill_lead;                // layers behind fill_from that have been cached as well
   int layer;
   int max_blocks, n_heads, head_dim, d_model;
   float rope_theta;
@@ -89,6 +90,10 @@ struct QkvEpi {                 // rotary embedding + paged cache write (+ q out
   int num_blocks;               // blocks per layer of the pools: a slot whose block id or position is out of range is not written
   int table_rows;               // rows of block_tables (the batch size): a row_table entry outside 0..table_rows-1 is read as 0
 };
+// Whether KV filling has nothing to do for row m (no row of other projections).
+__device__ inline bool kv_filled(const QkvEpi& e, int m) {
+  return e.fill_from && !(e.fill_from[(size_t)m * e.fill_from_stride] + e.fill_lead < e.layer);
+}
 struct AccEpi {                 // residual update
   float* h;                     // fp32 path: the residual stream [M][n_out], added to in place (one contributor per element).
                                 // bf16 path: partial results [slices][Mpad][n_out]; slice s receives the sum over the
@@ -180,7 +185,7 @@ struct BeginArgs {
 };
 void launch_iter_begin(const BeginArgs& a, hipStream_t st);
 void launch_iter_begin_f32(const BeginArgs& a, hipStream_t st);
-// KV filling: x slab of layer l = bf16(RMSNorm(h; gains.g[l-1])) for every layer some row needs (fill_from < l).
+// KV filling: x slab of layer l = bf16(RMSNorm(h; gains.g[l-1])) for every layer some row needs (fill_from + fill_lead < l).
 // rope.table != nullptr: the same launch also tabulates the rotary angles.
 struct RopeJob {
   const int32_t* context_lens;
@@ -189,7 +194,7 @@ struct RopeJob {
   float theta;
 };
 void launch_fill_prep(const float* h, const GainTable& gains, int n_layers, bf16_t* x_slabs, float eps,
-                      const int32_t* fill_from, int fill_from_stride, int B, int Mpad, int d, Pred pred, const RopeJob& rope,
+                      const int32_t* fill_from, int fill_from_stride, int fill_lead, int B, int Mpad, int d, Pred pred, const RopeJob& rope,
                       hipStream_t st);
 struct CombineArgs {
   const float4* partials;
@@ -276,7 +281,7 @@ void gemm_bf16_prepare();
 // with_combine != nullptr (only where gemm_qkv_carries_combine(M) holds): the launch also takes the exit decision
 // of the previous layer.  The projection then runs SPECULATIVELY when that decision ends the iteration (its
 // predicate word may or may not show the new value yet): what it caches for its layer is what KV filling
-// (Section 3.2) caches there anyway, and KV filling runs afterwards over every layer above the batch exit layer.
+// (Section 3.2) caches there, and KV filling starts one layer further on.
 void launch_gemm_qkv_bf16(const GemmShape& g, const QkvEpi& e, Pred pred, hipStream_t st,
                           const CombineArgs* with_combine = nullptr, const DecideArgs* with_decide = nullptr);
 bool gemm_qkv_carries_combine(int M);

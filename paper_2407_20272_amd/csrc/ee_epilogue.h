@@ -27,7 +27,7 @@ __device__ inline void rotate(float& lo, float& hi, float c, float s) {
 // pairs come from a table that is filled once per call from angles formed in double (long contexts would lose the fraction of the
 // angle to float rounding of the frequency).
 __device__ inline void epi_qkv4(const QkvEpi& e, int m, int f_lo0, float (&lo)[4], float (&hi)[4]) {
-  if (e.fill_from && !(e.fill_from[(size_t)m * e.fill_from_stride] < e.layer)) return;
+  if (kv_filled(e, m)) return;
   const int d = e.d_model, dh = e.head_dim, half = dh >> 1;
   const int which = f_lo0 / d;  // 0 q, 1 k, 2 v
   const int within = f_lo0 - which * d;

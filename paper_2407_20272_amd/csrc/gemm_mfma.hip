@@ -56,13 +56,13 @@ __device__ inline bool fill_skip(const Pred& pred, const QkvEpi& e, int M, int l
     const int32_t from = ctl_load(e.fill_from);
     const int32_t flag = pred.flag ? ctl_load(pred.flag) : 0;
     if (pred.flag && ((flag != 0) != (pred.run_when != 0))) return true;
-    return !(from < layer);
+    return !(from + e.fill_lead < layer);
   }
   if (pred_skip(pred)) return true;
   if (threadIdx.x == 0) lds_flag = 0;
   __syncthreads();
   int need = 0;
-  for (int m = threadIdx.x; m < M; m += blockDim.x) need |= e.fill_from[m] < layer;
+  for (int m = threadIdx.x; m < M; m += blockDim.x) need |= e.fill_from[m] + e.fill_lead < layer;
   if (need) lds_flag = 1;
   __syncthreads();
   const bool any = lds_flag != 0;
@@ -152,7 +152,7 @@ __device__ inline void tile_finish(const f32x16& acc, int nt, int mt_global, con
         if (e.q) {   // thread -> (row, run, quarter of the run): four floats
           const int mr = threadIdx.x >> 3, part = threadIdx.x & 7, run = part >> 2, c0 = run * 16 + (part & 3) * 4;
           const int mm = mt_global * 32 + mr;
-          if (mm < g.M && !(e.fill_from && !(e.fill_from[(size_t)mm * e.fill_from_stride] < e.layer))) {
+          if (mm < g.M && !kv_filled(e, mm)) {
             float4 v = make_float4(s.zt[c0][mr], s.zt[c0 + 1][mr], s.zt[c0 + 2][mr], s.zt[c0 + 3][mr]);
             *reinterpret_cast<float4*>(e.q + (size_t)mm * d + head * dh + j0 + run * hdim + (part & 3) * 4) = v;
           }
@@ -161,8 +161,7 @@ __device__ inline void tile_finish(const f32x16& acc, int nt, int mt_global, con
         const int mr = threadIdx.x >> 2, part = threadIdx.x & 3, run = part >> 1, c0 = run * 16 + (part & 1) * 8;
         const int mm = mt_global * 32 + mr;
         // a workgroup that computed one half of the tile's rows (row_half) holds one of the two runs only
-        if (mm < g.M && (row_half < 0 || run == row_half) &&
-            !(e.fill_from && !(e.fill_from[(size_t)mm * e.fill_from_stride] < e.layer))) {
+        if (mm < g.M && (row_half < 0 || run == row_half) && !kv_filled(e, mm)) {
           const int p = e.context_lens[mm];
           const bool p_ok = (unsigned)p < (unsigned)(e.max_blocks * 16);
           const int blk = e.block_tables[(size_t)(e.row_table ? safe_row(e.row_table[mm], e.table_rows) : mm) * e.max_blocks + (p_ok ? p >> 4 : 0)];
@@ -856,7 +855,7 @@ __device__ inline void buffer_to_lds(buffer_t, lds_void_ptr, int, int) {}
 // and the rotary pairs of one batch tile are fetched while the one before is stored: looked up tile by tile, as the other
 // kernels do, each tile waits for a chain of dependent loads behind the stores of the last.
 __device__ inline long kv_slot(const QkvEpi& e, int m, int M) {
-  if (m >= M || (e.fill_from && !(e.fill_from[(size_t)m * e.fill_from_stride] < e.layer))) return -1;
+  if (m >= M || kv_filled(e, m)) return -1;
   const int p = e.context_lens[m];
   if ((unsigned)p >= (unsigned)(e.max_blocks * 16)) return -1;
   const int blk = e.block_tables[(size_t)(e.row_table ? safe_row(e.row_table[m], e.table_rows) : m) * e.max_blocks + (p >> 4)];

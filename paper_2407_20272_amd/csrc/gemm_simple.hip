@@ -70,7 +70,7 @@ __device__ inline RowOf row_of(const Epi& e, int m, int f_lo, int f_hi) {
   r.write = true;
   if constexpr (std::is_same<Epi, QkvEpi>::value) {
     const int d = e.d_model, dh = e.head_dim, half = dh >> 1, which = f_lo / d, j = (f_lo - which * d) % dh;
-    if (e.fill_from) r.write = e.fill_from[(size_t)m * e.fill_from_stride] < e.layer;
+    r.write = !kv_filled(e, m);
     if (which < 2 && e.rope_theta > 0.0f) r.turn = e.rope[(size_t)m * half + j];
     if (which > 0) {
       r.pos = e.context_lens[m];
@@ -122,7 +122,7 @@ __device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fi
   if constexpr (FILL) {   // one slice of the grid per layer; nothing to do where every row has been cached already
     const int layer = blockIdx.z + 1;
     bool need = false;
-    for (int m = m0; m < min(m0 + MC, g.M); ++m) need |= ctl_load(e.fill_from + (size_t)m * e.fill_from_stride) < layer;
+    for (int m = m0; m < min(m0 + MC, g.M); ++m) need |= ctl_load(e.fill_from + (size_t)m * e.fill_from_stride) + e.fill_lead < layer;
     if (!need) return;
     g.w = reinterpret_cast<const float*>(fill.layers.w_qkv[layer - 1]);
     g.gain = reinterpret_cast<const float*>(fill.gains.g[layer - 1]);

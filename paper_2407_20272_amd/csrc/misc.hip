@@ -233,7 +233,7 @@ __global__ __launch_bounds__(NORM_THREADS) void iter_begin_kernel(BeginArgs a) {
 // for bit the operand that layer's own pass would have built from the same hidden state.
 __global__ __launch_bounds__(NORM_THREADS) void fill_prep_kernel(const float* h, GainTable gains, bf16_t* x_slabs,
                                                                  size_t slab_elems, float eps, const int32_t* fill_from,
-                                                                 int fill_from_stride, int B, int Mpad, int d, Pred pred,
+                                                                 int fill_from_stride, int fill_lead, int B, int Mpad, int d, Pred pred,
                                                                  RopeJob rope) {
   if (pred_skip(pred)) return;
   __shared__ float red[NORM_THREADS / 64];
@@ -244,8 +244,8 @@ __global__ __launch_bounds__(NORM_THREADS) void fill_prep_kernel(const float* h,
   }
   bf16_t* x = x_slabs + (size_t)blockIdx.y * slab_elems;
   if (fill_from_stride == 0) {
-    if (!(ctl_load(fill_from) < layer)) return;     // Algorithm 1: one batch exit layer for everybody
-  } else if (m < B && !(fill_from[m] < layer)) {
+    if (!(ctl_load(fill_from) + fill_lead < layer)) return;     // Algorithm 1: one batch exit layer for everybody
+  } else if (m < B && !(fill_from[m] + fill_lead < layer)) {
     return;                                          // this row's K/V of this layer exist already: its operand row is never used
   }
   if (m >= B) {
@@ -437,11 +437,11 @@ void launch_finish_norm(const NormArgs& a, Pred pred, hipStream_t st) {
   }
 }
 void launch_fill_prep(const float* h, const GainTable& gains, int n_layers, bf16_t* x_slabs, float eps,
-                      const int32_t* fill_from, int fill_from_stride, int B, int Mpad, int d, Pred pred, const RopeJob& rope,
+                      const int32_t* fill_from, int fill_from_stride, int fill_lead, int B, int Mpad, int d, Pred pred, const RopeJob& rope,
                       hipStream_t st) {
   const int rope_wgs = rope.table && rope.theta > 0.0f ? (B * (rope.head_dim / 2) + NORM_THREADS - 1) / NORM_THREADS : 0;
   hipLaunchKernelGGL(fill_prep_kernel, dim3(Mpad + rope_wgs, n_layers), dim3(NORM_THREADS), 0, st, h, gains, x_slabs, (size_t)Mpad * d,
-                     eps, fill_from, fill_from_stride, B, Mpad, d, pred, rope);
+                     eps, fill_from, fill_from_stride, fill_lead, B, Mpad, d, pred, rope);
 }
 void launch_compact(const int32_t* status, int B, const RowMap& rm, Pred pred, hipStream_t st) {
   hipLaunchKernelGGL(compact_kernel, dim3(1), dim3(256), 0, st, status, B, rm, pred);

@@ -238,6 +238,18 @@ def test_saturated_model_forced_exit_cache_equals_full_pass(dtype):
             assert float((a != b).float().mean()) < 0.02, "more than 2 % of the filled values differ in the last bit"
 
 
+@pytest.mark.parametrize("dtype,batch,conf_mode", [("bf16", 3, 0), ("bf16", 33, 1), ("bf16", 64, 2), ("bf16", 65, 0), ("bf16", 40, 3),
+                                                   ("fp32", 5, 0), ("fp32", 5, 2), ("fp32", 65, 1)])
+def test_kv_filling_behind_the_last_layer_that_ran_or_was_cached(dtype, batch, conf_mode):
+    """The batch leaves at the first, a middle and the last checked layer: every layer above it is cached once, by the projection that shares a
+    launch with the decision or by KV filling, whichever the batch and the measure take."""
+    base = dict(batch=batch, n_layers=4, conf_mode=conf_mode, prompt_len=12, min_prompt_len=4, shuffled_blocks=True)
+    cfg = TINY.with_(**base) if dtype == "fp32" else small_bf16(**base)
+    forced = torch.tensor([1, 2, 3], dtype=torch.int32)[:, None].expand(3, batch).contiguous()
+    stats = lockstep(cfg, seed=23, steps=3, forced_seq=forced)
+    assert stats["L"] == [1, 2, 3]
+
+
 def test_empty_batch_is_a_noop():
     cfg = TINY
     w = W.make_weights(cfg, seed=0)
