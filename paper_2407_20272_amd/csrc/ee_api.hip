@@ -544,6 +544,10 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // residual columns.  The QKV projection keeps all rows in place (it does the KV filling of those that left).
   const bool compact = left && bf16_compactable(D, B);
   const RowMap rmap = compact ? w.rowmap : RowMap{};
+  // So does the last LM head, whose rows that have left have their tokens (a head-less measure has produced none).  7B shape, 256 rows of four
+  // layers with exits of their own 1791 -> 1770 us, 200 of three 895 -> 878, nobody leaving equal; at 300 to 500 rows 2 to 4 % faster with
+  // exits spread over the layers, but 2 % slower where nobody leaves: compacted rows do not go in blocks of as many.
+  const bool compact_last = compact && !dotmode && B <= 256;
   // Kernels of the layer loop run only while the batch has not left.  It cannot have before the first check has been decided:
   // what is launched up to then takes no predicate (a kernel
   // that has one waits for it before its first load, about 0.2 us a launch: 7B shape, one sequence, two layers 259.4 -> 256.6 us).
@@ -736,6 +740,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
         } else {
           na.gain[0] = reinterpret_cast<const bf16_t*>(model->g_final);
           na.x[0] = w.xH;
+          na.compacted[0] = compact_last;
         }
         launch_finish_norm(na, run_layers, st);
       }
@@ -862,11 +867,11 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
     } else if (small) {
       enqueue_head_small(*model, w, w.h, B, 0.0f, n, final_pred, st);
     } else if (bf) {
-      enqueue_head_bf16(*model, w, B, 0.0f, n, RowMap{}, final_pred, st);
+      enqueue_head_bf16(*model, w, B, 0.0f, n, compact_last ? rmap : RowMap{}, final_pred, st);
     } else if (!few_f32 || !use_exit_heads) {   // (otherwise it ran in the launch above)
       enqueue_head_f32(*model, w, w.h, B, n, final_pred, st);
     }
-    CombineArgs ca{w.partials, D.vocab / 32, B, 0, 0.0f, 0.0f, 0, nullptr, s, out_tokens, nullptr};
+    CombineArgs ca{w.partials, D.vocab / 32, B, 0, 0.0f, 0.0f, 0, nullptr, s, out_tokens, nullptr, compact_last ? left : nullptr};
     ProfScope ps(EE_K_COMBINE, n, st);
     if (bf) launch_combine_copy(ca, final_pred, w.h, out_hidden, d, st);
     else launch_head_decide_f32(w.logits, w.row_scale, D.vocab, ca, final_pred, w.h, out_hidden, d, st);

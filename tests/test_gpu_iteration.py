@@ -513,6 +513,17 @@ def test_compacted_rows_in_halves_of_blocks(batch):
     assert stats["L"] == [4]
 
 
+@pytest.mark.parametrize("batch,exit_every", [(129, 1), (256, 1), (257, 1), (200, 6)])   # compacted up to 256 rows; no check ahead of the last layer
+def test_last_lm_head_of_the_rows_that_stay(batch, exit_every):
+    """Nobody, half of the rows, all but one leave ahead of the last layer: who stays gets a token there, the others keep theirs."""
+    cfg = compactable_bf16(batch=batch, exit_every=exit_every)
+    forced = torch.full((3, batch), cfg.n_layers, dtype=torch.int32)
+    forced[1, ::2] = 2
+    forced[2, 1:] = cfg.n_layers - 1
+    stats = lockstep(cfg, seed=45, steps=3, forced_seq=forced, heads=2)
+    assert stats["L"] == [cfg.n_layers] * 3
+
+
 @pytest.mark.parametrize("batch,vocab", [(256, 32 * 516), (300, 32 * 64)])
 def test_confidences_do_not_hang_on_how_many_rows_are_active(batch, vocab):
     """The sequences that stay have the confidences and hidden states, bit for bit, that they have when the others stay too (whole
