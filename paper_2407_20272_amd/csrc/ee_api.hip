@@ -560,9 +560,11 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // Algorithm 1, initialisation.  rowsq slot 0: after the embedding; slot 2i-1: after layer i's attention
   // update; slot 2i: after layer i.
   auto rs = [&](int slot) { return w.rowsq + (size_t)slot * Mpad; };
+  // (Small float models: in the launch of the first projection, which reads the embedding rows and forms the angles itself: four sequences 72.8 -> 70.6 us.)
+  const bool begin_f32 = !bf && B <= kF32FewRows && d <= kF32FewWidth;
+  BeginArgs ba{};
   {
     ProfScope ps(EE_K_OTHER, 0, st);
-    BeginArgs ba{};
     ba.s = s;
     ba.conf_out = out_conf;
     ba.context_lens = batch->context_lens;
@@ -587,7 +589,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       launch_iter_begin(ba, st);
     } else {
       ba.embed_f32 = reinterpret_cast<const float*>(model->embed);
-      launch_iter_begin_f32(ba, st);
+      if (!begin_f32) launch_iter_begin_f32(ba, st);
     }
   }
   // bf16 path: the residual update of a projection and the RMSNorm that follows it are one launch (NormArgs):
@@ -751,7 +753,10 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
         SimpleShape gq{reinterpret_cast<const float*>(L.w_qkv), w.h, reinterpret_cast<const float*>(L.g_attn), D.rms_eps, d, B, 0, 3 * d,
                        D.head_dim / 2};
         QkvEpi qe = make_qkv_epi(D, *cache, *batch, w, i, w.q);
-        if (have_pending && few_f32)
+        if (i == 1 && begin_f32) {
+          gq.x = ba.embed_f32;
+          launch_simple_begin_qkv(ba, gq, qe, st);
+        } else if (have_pending && few_f32)
           launch_simple_head_qkv(head_shape_f32(*model, w.h, B), head_epi_f32(*model, w), gq, qe, pending_pred, st);
         else
           launch_simple_qkv(gq, qe, run_layers, st, have_pending ? &job : nullptr);

@@ -346,6 +346,8 @@ struct SimpleDecision {
   int n_wg;   // set by the launch
 };
 void launch_simple_qkv(const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st, const SimpleDecision* with = nullptr);
+// The first layer's, which begins the iteration (launch_iter_begin_f32) as well: g.x is the embedding table.
+void launch_simple_begin_qkv(const BeginArgs& begin, const SimpleShape& g, const QkvEpi& e, hipStream_t st);
 // The LM head in the launch of the next layer's QKV projection, or of KV filling (which runs where the head, by its predicate ph, does not).  Up to
 // 256 rows.
 void launch_simple_head_qkv(const SimpleShape& gh, const LmEpi& eh, const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st);

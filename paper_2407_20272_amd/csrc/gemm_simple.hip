@@ -7,12 +7,14 @@
 // them the chain of dependent loads (predicate, operands, what the epilogue looks up): a launch took 4 to 5 us for work of well under
 // one.  So the launches are few (ee_decode_iteration) and everything whose address is known at the start is asked for at the start.
 // One iteration of four sequences and four layers of width 256, leaving at layer 3: 65 launches and 217 us with a launch a step, 27
-// and 98 us with norms and decisions inside the projections, 19 and 83 us as sequenced now, 75 us with the loads in front.
+// and 98 us with norms and decisions inside the projections, 19 and 83 us with four launches a layer, 75 us with the loads in front, 73 with
+// no second layer-4 projection in KV filling, 18 and 71 us with the start in the first projection's launch.
 #include <type_traits>
 
 #include "ee_common.h"
 #include "ee_epilogue.h"
 #include "ee_decide.h"
+#include "ee_begin.h"
 
 namespace ee {
 namespace {
@@ -55,6 +57,10 @@ __device__ inline float wave_sums4(float (&v)[4], int lane) {
 
 struct NoFill {};   // (a launch that fills nothing does not carry a kilobyte of layer tables)
 struct NoJob {};
+struct BeginJob {   // the first projection of an iteration: leading workgroups begin it, the others read the embedding rows themselves
+  BeginArgs a;
+  int n_wg;
+};
 
 // What an epilogue reads of batch row m besides the sums.  It is asked for with the first operands: behind the sums it would be a
 // chain of dependent loads at the end of a launch that takes a few microseconds.
@@ -64,14 +70,15 @@ struct RowOf {
   float2 turn;        // (cos, sin)
   float lo, hi;       // residual update: what is added to
 };
-template <class Epi>
-__device__ inline RowOf row_of(const Epi& e, int m, int f_lo, int f_hi) {
+// at: position of the row where the rotary table is not there yet (BEGIN).
+template <class Epi, bool BEGIN>
+__device__ inline RowOf row_of(const Epi& e, int m, int f_lo, int f_hi, int at) {
   RowOf r{};
   r.write = true;
   if constexpr (std::is_same<Epi, QkvEpi>::value) {
     const int d = e.d_model, dh = e.head_dim, half = dh >> 1, which = f_lo / d, j = (f_lo - which * d) % dh;
     r.write = !kv_filled(e, m);
-    if (which < 2 && e.rope_theta > 0.0f) r.turn = e.rope[(size_t)m * half + j];
+    if (which < 2 && e.rope_theta > 0.0f) r.turn = BEGIN ? rope_turn(at, j, dh, e.rope_theta) : e.rope[(size_t)m * half + j];
     if (which > 0) {
       r.pos = e.context_lens[m];
       const bool ok = (unsigned)r.pos < (unsigned)(e.max_blocks * 16);
@@ -108,9 +115,9 @@ __device__ inline void put_qkv(const QkvEpi& e, const RowOf& r, int m, int f_lo,
 // One workgroup (bx of those of a projection) of four wavefronts, a pair of output rows each.  PARTS: the operand comes in parts
 // (SimpleShape::parts).  PIECES > 0: the contraction is at most that many times 256, and all of a wavefront's operands are asked for at
 // once, before it looks (skip) whether the launch has anything to do.
-template <class Epi, bool NORM, bool VEC, bool PARTS, int PIECES, class Fill, class Skip>
-__device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fill, int bx, Skip skip) {
-  constexpr bool FILL = std::is_same<Fill, SimpleFill>::value;
+template <class Epi, bool NORM, bool VEC, bool PARTS, int PIECES, class Fill, class Skip, class Job = NoJob>
+__device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fill, int bx, Skip skip, const Job& job = Job{}) {
+  constexpr bool FILL = std::is_same<Fill, SimpleFill>::value, BEGIN = std::is_same<Job, BeginJob>::value;
   if constexpr (PIECES == 0 || FILL)
     if (skip()) return;
   // The row blocks of one group of weight rows get ids 8 apart: they run on one XCD at the same time, and all but the first
@@ -140,7 +147,13 @@ __device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fi
   const float* w_hi = g.w + (size_t)f_hi * g.K;
   const float* x[MC];
 #pragma unroll
-  for (int i = 0; i < MC; ++i) x[i] = g.x + (size_t)min(m0 + i, g.M - 1) * g.K;   // rows past the last repeat it, never written
+  for (int i = 0; i < MC; ++i) {   // rows past the last repeat it, never written
+    const int mi = min(m0 + i, g.M - 1);
+    if constexpr (BEGIN) x[i] = embed_row_f32(g.x, job.a.tokens[mi], job.a.vocab, g.K);
+    else x[i] = g.x + (size_t)mi * g.K;
+  }
+  int at = 0;
+  if constexpr (BEGIN) at = job.a.context_lens[min(m0 + (lane >> 4), g.M - 1)];   // (ahead of the operands: loads return in order)
   float sum[2 * MC], sq[MC];   // sum[2 i + hi]
 #pragma unroll
   for (int i = 0; i < MC; ++i) sum[2 * i] = sum[2 * i + 1] = sq[i] = 0.0f;
@@ -194,7 +207,7 @@ __device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fi
     Piece v[PIECES];
 #pragma unroll
     for (int c = 0; c < PIECES; ++c) load(v[c], min(c * 64 * N + lane * N, g.K - N));
-    row = row_of(e, min(m, g.M - 1), f_lo, f_hi);
+    row = row_of<Epi, BEGIN>(e, min(m, g.M - 1), f_lo, f_hi, at);
     asm volatile("" ::: "memory");   // the loads above stay above
     if constexpr (!FILL)
       if (skip()) return;
@@ -208,7 +221,7 @@ __device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fi
       load(v, k);
       multiply(v, k);
     }
-    row = row_of(e, min(m, g.M - 1), f_lo, f_hi);
+    row = row_of<Epi, BEGIN>(e, min(m, g.M - 1), f_lo, f_hi, at);
   }
   float r = wave_sums8(sum, lane);      // lane bits 5, 4: batch row, bit 3: lo / hi
   if constexpr (NORM) {
@@ -254,6 +267,12 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, 
     if (!ran) return;
     bx -= job.n_wg;
     simple_body<Epi, NORM, VEC, PARTS, PIECES>(g, e, fill, bx, [] { return false; });
+  } else if constexpr (std::is_same<Job, BeginJob>::value) {
+    if (bx < job.n_wg) {
+      if (blockIdx.y == 0) begin_row_f32(job.a, bx);
+      return;
+    }
+    simple_body<Epi, NORM, VEC, PARTS, PIECES>(g, e, fill, bx - job.n_wg, [] { return false; }, job);
   } else {
     simple_body<Epi, NORM, VEC, PARTS, PIECES>(g, e, fill, bx, [&] { return pred_skip(pred); });
   }
@@ -299,7 +318,7 @@ template <class Epi, bool NORM, bool PARTS = false, class Fill = NoFill, class J
 void launch(const SimpleShape& g, const Epi& e, Pred pred, hipStream_t st, const Fill& fill = Fill{}, int n_layers = 1, const Job& job = Job{}) {
   const int row_blocks = (g.M + MC - 1) / MC;
   int lead = 0;
-  if constexpr (std::is_same<Job, SimpleDecision>::value) lead = job.n_wg;
+  if constexpr (!std::is_same<Job, NoJob>::value) lead = job.n_wg;
   const dim3 grid(workgroups(g) + lead, (row_blocks + ROW_BLOCKS - 1) / ROW_BLOCKS, n_layers);
   bool vec = vectors(g);
   if constexpr (std::is_same<Fill, SimpleFill>::value) vec = vec && vectors(fill, n_layers);
@@ -331,6 +350,10 @@ void launch_simple_qkv(const SimpleShape& g, const QkvEpi& e, Pred pred, hipStre
   SimpleDecision job = *with;
   job.n_wg = (job.a.B + 7) / 8 * 8;   // a multiple of 8: the projection's workgroups keep their XCDs
   launch<QkvEpi, true>(g, e, pred, st, NoFill{}, 1, job);
+}
+void launch_simple_begin_qkv(const BeginArgs& begin, const SimpleShape& g, const QkvEpi& e, hipStream_t st) {
+  const int rope_wgs = begin.theta > 0.0f ? (begin.B * (begin.head_dim / 2) + 255) / 256 : 0;
+  launch<QkvEpi, true>(g, e, Pred{nullptr, 0}, st, NoFill{}, 1, BeginJob{begin, (begin.B + rope_wgs + 7) / 8 * 8});
 }
 void launch_simple_head_qkv(const SimpleShape& gh, const LmEpi& eh, const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st) {
   launch_with_head(gh, eh, pred, g, e, pred, NoFill{}, 1, vectors(g), st);

@@ -2,36 +2,11 @@
 #include "ee_common.h"
 #include "ee_epilogue.h"
 #include "ee_decide.h"
+#include "ee_begin.h"
 
 namespace ee {
 namespace {
 
-// ---------------------------------------------------------------------------------------------------
-// Status <- False for sequence m (Algorithm 1, initialisation), no confidence yet; row 0: the counters.  One workgroup a row.
-// ---------------------------------------------------------------------------------------------------
-__device__ inline void init_row(const IterState& s, int m, int B, int n_layers, float* conf_out) {
-  if (threadIdx.x == 0) {
-    s.status[m] = 0;
-    s.exit_layer[m] = n_layers;
-    if (m == 0) {
-      *s.n_exited = 0;
-      *s.done = 0;
-      *s.batch_exit_layer = n_layers;
-    }
-  }
-  if (conf_out && (int)threadIdx.x < n_layers) conf_out[(size_t)threadIdx.x * B + m] = __builtin_nanf("");
-}
-
-// (cos, sin) of pos_m * theta^(-2j/dh) for every sequence m and channel pair j, angles formed in double.
-__device__ inline void rope_entry(const int32_t* context_lens, float2* table, int idx, int B, int head_dim, float theta) {
-  const int half = head_dim >> 1;
-  if (idx >= B * half) return;
-  const int m = idx / half, j = idx - m * half;
-  const double ang = (double)context_lens[m] * exp2(-2.0 * (double)j / (double)head_dim * log2((double)theta));
-  double sn, cs;
-  sincos(ang, &sn, &cs);
-  table[idx] = make_float2((float)cs, (float)sn);
-}
 __global__ void rope_table_kernel(const int32_t* context_lens, float2* table, int B, int head_dim, float theta) {
   rope_entry(context_lens, table, blockIdx.x * blockDim.x + threadIdx.x, B, head_dim, theta);
 }
@@ -273,21 +248,7 @@ __global__ __launch_bounds__(NORM_THREADS) void fill_prep_kernel(const float* h,
 }
 
 // fp32 path: the same, without the operand (the projections normalise for themselves).
-__global__ __launch_bounds__(256) void iter_begin_f32_kernel(BeginArgs a) {
-  const int m = blockIdx.x, d = a.d;
-  if (m >= a.B) {
-    rope_entry(a.context_lens, a.rope, (m - a.B) * 256 + threadIdx.x, a.B, a.head_dim, a.theta);
-    return;
-  }
-  init_row(a.s, m, a.B, a.n_layers, a.conf_out);
-  const int tok = a.tokens[m];
-  const float* row = a.embed_f32 + (size_t)((unsigned)tok < (unsigned)a.vocab ? tok : 0) * d;   // never outside the table
-  for (int k = threadIdx.x; k < d; k += 256) {
-    const float v = row[k];
-    a.h[(size_t)m * d + k] = v;
-    if (a.snapshot) a.snapshot[(size_t)m * d + k] = v;
-  }
-}
+__global__ __launch_bounds__(256) void iter_begin_f32_kernel(BeginArgs a) { begin_row_f32(a, blockIdx.x); }
 
 // Copies row m of src to dst (either alignment), all threads of a 256-thread workgroup.
 __device__ inline void copy_row(const float* src, float* dst, int m, int d) {
