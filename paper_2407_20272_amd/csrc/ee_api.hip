@@ -560,6 +560,9 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // Algorithm 1, initialisation.  rowsq slot 0: after the embedding; slot 2i-1: after layer i's attention
   // update; slot 2i: after layer i.
   auto rs = [&](int slot) { return w.rowsq + (size_t)slot * Mpad; };
+  // Up to eight sequences: projections that build their operand from the residual rows and add to these, no launch between them.
+  const bool small = bf && !dotmode && !batch->row_table && gemm_small_takes(B, d);
+  const bool begin_small = small && (reinterpret_cast<uintptr_t>(model->embed) & 15) == 0;   // (in the first projection's launch: 7B shape, one sequence 219.9 -> 216.6 us)
   // (Small float models: in the launch of the first projection, which reads the embedding rows and forms the angles itself: four sequences 72.8 -> 70.6 us.)
   const bool begin_f32 = !bf && B <= kF32FewRows && d <= kF32FewWidth;
   BeginArgs ba{};
@@ -586,7 +589,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       ba.x = w.xT;
       ba.rowsq_out = rs(0);
       ba.rm = rmap;
-      launch_iter_begin(ba, st);
+      if (!begin_small) launch_iter_begin(ba, st);
     } else {
       ba.embed_f32 = reinterpret_cast<const float*>(model->embed);
       if (!begin_f32) launch_iter_begin_f32(ba, st);
@@ -615,8 +618,6 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // The exit decision of layer i (softmax-response measures, bf16, batches the streaming projection kernel serves)
   // rides along with the QKV projection launch of layer i + 1: one launch less per checked layer.
   const bool carry_combine = bf && !dotmode && !compact && gemm_qkv_carries_combine(B);
-  // Up to eight sequences: projections that build their operand from the residual rows and add to these, no launch between them.
-  const bool small = bf && !dotmode && !batch->row_table && gemm_small_takes(B, d);
   // Float path, where a launch costs more than what it does: a layer in four launches instead of six.  The LM head of layer i shares
   // the launch of layer i + 1's QKV projection (both read the same hidden states), the decision from it that of layer i + 1's
   // attention (behind the batch exit layer both run in vain), KV filling and the last LM head one more.  And attention multiplies by
@@ -655,8 +656,10 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
       const AccEpi add{w.h, 0, d, left, nullptr};
       {
         ProfScope ps(EE_K_QKV, i, st);   // (V has no rotation: its tiles go by halves)
-        launch_small_qkv(shape(L.w_qkv, w.h, L.g_attn, d, D.head_dim / 2, 2 * d / 32, d / 16), make_qkv_epi(D, *cache, *batch, w, i, w.q), run_layers,
-                         st, have_pending ? &pending : nullptr);
+        const SmallShape gq = shape(L.w_qkv, w.h, L.g_attn, d, D.head_dim / 2, 2 * d / 32, d / 16);
+        const QkvEpi qe = make_qkv_epi(D, *cache, *batch, w, i, w.q);
+        if (i == 1 && begin_small) launch_small_begin_qkv(ba, gq, qe, st);
+        else launch_small_qkv(gq, qe, run_layers, st, have_pending ? &pending : nullptr);
         have_pending = false;
       }
       {

@@ -53,5 +53,22 @@ __device__ inline void begin_row_f32(const BeginArgs& a, int wg) {
     if (a.snapshot) a.snapshot[(size_t)m * d + k] = v;
   }
 }
+// bf16 path, rows that are normalised by whoever multiplies them (gemm_small.hip), workgroup wg of 256 threads: as above, from rows of whole 16-byte loads.
+__device__ inline void begin_row_small(const BeginArgs& a, int wg) {
+  const int m = wg, d = a.d;
+  if (m >= a.B) {
+    if (a.theta > 0.0f) rope_entry(a.context_lens, a.rope, (m - a.B) * 256 + threadIdx.x, a.B, a.head_dim, a.theta);
+    return;
+  }
+  init_row(a.s, m, a.B, a.n_layers, a.conf_out);
+  const int tok = a.tokens[m];
+  const bf16_t* row = a.embed + (size_t)((unsigned)tok < (unsigned)a.vocab ? tok : 0) * d;   // never outside the table
+  for (int k = threadIdx.x * 8; k < d; k += 256 * 8) {
+    const bf16x8 e = *reinterpret_cast<const bf16x8*>(row + k);
+    float* h = a.h + (size_t)m * d + k;
+    *reinterpret_cast<float4*>(h) = make_float4((float)e[0], (float)e[1], (float)e[2], (float)e[3]);
+    *reinterpret_cast<float4*>(h + 4) = make_float4((float)e[4], (float)e[5], (float)e[6], (float)e[7]);
+  }
+}
 
 }  // namespace ee

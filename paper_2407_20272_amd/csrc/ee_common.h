@@ -314,6 +314,8 @@ struct SmallShape {
 };
 bool gemm_small_takes(int B, int d);
 void launch_small_qkv(const SmallShape& g, const QkvEpi& e, Pred pred, hipStream_t st, const CombineArgs* with_combine);
+// The first layer's, which begins the iteration as well (x unused; the embedding table starts on 16 bytes).
+void launch_small_begin_qkv(const BeginArgs& begin, const SmallShape& g, const QkvEpi& e, hipStream_t st);
 void launch_small_oproj(const SmallShape& g, const AccEpi& e, Pred pred, hipStream_t st);
 void launch_small_gateup(const SmallShape& g, const GateUpEpi& e, Pred pred, hipStream_t st);
 void launch_small_down(const SmallShape& g, const AccEpi& e, Pred pred, hipStream_t st);

@@ -13,6 +13,7 @@
 #include "ee_common.h"
 #include "ee_epilogue.h"
 #include "ee_decide.h"
+#include "ee_begin.h"
 
 namespace ee {
 namespace {
@@ -25,9 +26,11 @@ constexpr int SM_OPERAND = 24576;   // channels of all rows
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Operand: RMSNorm of float rows, float rows (both in LDS), bf16 rows (fetched with the weights: where a workgroup has one 16-row unit,
+// Operand: RMSNorm of float rows, of embedding rows, float rows (all in LDS), bf16 rows (fetched with the weights: where a workgroup has one 16-row unit,
 // as in the down projection of the 7B shape, nothing would be read twice).
-enum { X_NORM, X_F32, X_ROWS };
+enum { X_NORM, X_EMBED, X_F32, X_ROWS };
+
+struct NoJob {};
 
 __host__ __device__ constexpr int x_row_bytes(int K) { return 2 * K + 64; }   // (64: rows start 16 banks apart)
 constexpr int lds_bytes(int K, int R, int XM) {
@@ -58,20 +61,28 @@ __device__ inline float wave_sum(float v) {
 // R: batch rows (columns of the product); NG: groups of 2048 channels that a row has at most; RU: output rows of a unit.  RU = 8: a
 // wavefront load is 8 rows x 64 of the contraction, the second 32 as rows 8 to 15 of the first operand against columns 8 to 15 of the
 // second, so that both sets of sums come out of one instruction (and two that nobody needs).
-template <class Epi, int R, int XM, int NG, int RU>
-__global__ __launch_bounds__(256) void gemm_small_kernel(SmallShape g, Epi e, Pred pred, CombineJob cj) {
+template <class Epi, int R, int XM, int NG, int RU, class Job>
+__global__ __launch_bounds__(256) void gemm_small_kernel(SmallShape g, Epi e, Pred pred, Job job) {
   extern __shared__ __align__(16) unsigned char sm[];
   constexpr bool QKV = std::is_same<Epi, QkvEpi>::value, ACC = std::is_same<Epi, AccEpi>::value, LM = std::is_same<Epi, LmEpi>::value;
+  constexpr bool NORM = XM == X_NORM || XM == X_EMBED;
   int bx = blockIdx.x;
   bool skip = false;
-  if (QKV && cj.n_wg) {   // leading workgroups: the exit decision of the layer before (see gemm_mfma_kernel)
-    const bool ran = layer_ran(cj.a.s, cj.a.layer);
-    if (bx < cj.n_wg) {
-      if (bx < cj.a.B && ran) combine_row(cj.a, bx, reinterpret_cast<float4*>(sm));
+  if constexpr (std::is_same<Job, CombineJob>::value) {   // leading workgroups: the exit decision of the layer before (see gemm_mfma_kernel)
+    const bool ran = layer_ran(job.a.s, job.a.layer);
+    if (bx < job.n_wg) {
+      if (bx < job.a.B && ran) combine_row(job.a, bx, reinterpret_cast<float4*>(sm));
       return;
     }
     skip = !ran;
-    bx -= cj.n_wg;
+    bx -= job.n_wg;
+  } else if constexpr (XM == X_EMBED) {   // .. or the start of the iteration
+    const int lead = gridDim.x - g.wgs;
+    if (bx < lead) {
+      begin_row_small(job, bx);
+      return;
+    }
+    bx -= lead;
   } else {
     skip = pred_skip(pred);
   }
@@ -111,6 +122,14 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallShape g, Epi e, Pr
     for (int r = 0; r < RP; ++r)
 #pragma unroll
       for (int i = 0; i < NG; ++i) {
+        if constexpr (XM == X_EMBED) {
+          const int tok = job.tokens[min(r0 + r, g.M - 1)];
+          const bf16x8 e8 = *reinterpret_cast<const bf16x8*>(job.embed + (size_t)((unsigned)tok < (unsigned)job.vocab ? tok : 0) * K +
+                                                             min((i * 256 + (int)threadIdx.x) * 8, K - 8));
+#pragma unroll
+          for (int x = 0; x < 8; ++x) v[r][i][x] = (float)e8[x];
+          continue;
+        }
         const float* p = reinterpret_cast<const float*>(g.x) + (size_t)min(r0 + r, g.M - 1) * K + min((i * 256 + (int)threadIdx.x) * 8, K - 8);
         const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
         v[r][i][0] = a.x; v[r][i][1] = a.y; v[r][i][2] = a.z; v[r][i][3] = a.w;
@@ -118,7 +137,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallShape g, Epi e, Pr
       }
   };
   if constexpr (XM != X_ROWS) load_rows(0);
-  if constexpr (XM == X_NORM) {
+  if constexpr (NORM) {
 #pragma unroll
     for (int i = 0; i < NG; ++i) gv[i] = *reinterpret_cast<const bf16x8*>(g.gain + min((i * 256 + (int)threadIdx.x) * 8, K - 8));
   }
@@ -144,12 +163,13 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallShape g, Epi e, Pr
       const int mm = min(m0 + 4 * q, g.M - 1);
       if constexpr (QKV) {
         const int f0 = packed_row_lo(tile, 0, g.pair_stride);
-        if (f0 < 2 * e.d_model && e.rope_theta > 0.0f) turn[q] = e.rope[(size_t)mm * (e.head_dim >> 1) + f0 % e.head_dim + r16];
+        if (f0 < 2 * e.d_model && e.rope_theta > 0.0f) turn[q] = XM == X_EMBED ? rope_turn(pos[q], f0 % e.head_dim + r16, e.head_dim, e.rope_theta)
+                                : e.rope[(size_t)mm * (e.head_dim >> 1) + f0 % e.head_dim + r16];
       }
       if constexpr (ACC) h_in[q] = e.h[(size_t)mm * e.n_out + tile * 32 + half * RU + row];
     }
   };
-  look(0);
+  if constexpr (XM != X_EMBED) look(0);
   asm volatile("" ::: "memory");   // all of this is asked for ahead of the weights
   if (skip) return;
 
@@ -188,6 +208,8 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallShape g, Epi e, Pr
   for (int s = 0; s < SM_SETS - 1; ++s) issue(W[s], set_x(s));
   asm volatile("" ::: "memory");
 
+  if constexpr (XM == X_EMBED) look(0);   // (angles: behind the first weights)
+
   // ---- operand to LDS ------------------------------------------------------------------------------------
   unsigned char* zero16 = sm + (XM == X_ROWS ? 0 : R * row_bytes);
   float* red = reinterpret_cast<float*>(zero16 + 64);              // [2][NW][2][R][16]
@@ -206,7 +228,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallShape g, Epi e, Pr
     for (int r0 = 0; r0 < R; r0 += RP) {
       if (r0) load_rows(r0);
       float rinv[RP];
-      if constexpr (XM == X_NORM) {
+      if constexpr (NORM) {
         // the order of finish_norm_kernel: its thread t = (i % 2) * 256 + threadIdx.x owns what v[..][i] and v[..][i + 2] hold
 #pragma unroll
         for (int r = 0; r < RP; ++r)
@@ -240,7 +262,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallShape g, Epi e, Pr
           for (int r = 0; r < RP; ++r) {
             bf16x8 o;
 #pragma unroll
-            for (int x = 0; x < 8; ++x) o[x] = XM == X_NORM ? (bf16_t)(v[r][i][x] * rinv[r] * (float)gv[i][x]) : (bf16_t)v[r][i][x];
+            for (int x = 0; x < 8; ++x) o[x] = NORM ? (bf16_t)(v[r][i][x] * rinv[r] * (float)gv[i][x]) : (bf16_t)v[r][i][x];
             *reinterpret_cast<bf16x8*>(sm + (r0 + r) * row_bytes + k0 * 2) = o;
           }
         }
@@ -362,13 +384,13 @@ auto for_shape(int M, int K, Go go) {
   return rows(std::integral_constant<int, 4>{});
 }
 
-template <class Epi, int XM, int RU>
-void launch(SmallShape g, const Epi& e, Pred pred, const CombineJob& cj, hipStream_t st) {
+template <class Epi, int XM, int RU, class Job = NoJob>
+void launch(SmallShape g, const Epi& e, Pred pred, hipStream_t st, int lead = 0, const Job& job = Job{}) {
   const int units = g.whole + g.halves;
   g.wgs = units < SM_WGS ? units : SM_WGS;
   for_shape(g.M, g.K, [&](auto r, auto ng) {
     constexpr int R = decltype(r)::value, NG = XM == X_ROWS ? 1 : decltype(ng)::value;   // (that operand passes through no registers)
-    hipLaunchKernelGGL((gemm_small_kernel<Epi, R, XM, NG, RU>), dim3(g.wgs + cj.n_wg), dim3(256), lds_bytes(g.K, R, XM), st, g, e, pred, cj);
+    hipLaunchKernelGGL((gemm_small_kernel<Epi, R, XM, NG, RU, Job>), dim3(g.wgs + lead), dim3(256), lds_bytes(g.K, R, XM), st, g, e, pred, job);
   });
 }
 // Accumulate projections: units of 8 rows where fewer rows then fall to the busiest compute unit (d = 5120: 24 instead of 32).
@@ -377,8 +399,8 @@ void launch_acc(SmallShape g, const AccEpi& e, Pred pred, hipStream_t st) {
   const int d = e.n_out, by16 = (d / 16 + SM_WGS - 1) / SM_WGS * 16, by8 = (d / 8 + SM_WGS - 1) / SM_WGS * 8;
   g.whole = 0;
   g.halves = by8 < by16 ? d / 8 : d / 16;
-  if (by8 < by16) launch<AccEpi, XM, 8>(g, e, pred, CombineJob{}, st);
-  else launch<AccEpi, XM, 16>(g, e, pred, CombineJob{}, st);
+  if (by8 < by16) launch<AccEpi, XM, 8>(g, e, pred, st);
+  else launch<AccEpi, XM, 16>(g, e, pred, st);
 }
 
 }  // namespace
@@ -392,17 +414,23 @@ bool gemm_small_takes(int B, int d) {
   return B <= 8 && R * d <= SM_OPERAND && (R < 8 || d >= 384);   // (no more than 64 KiB of LDS)
 }
 void launch_small_qkv(const SmallShape& g, const QkvEpi& e, Pred pred, hipStream_t st, const CombineArgs* with_combine) {
-  CombineJob cj{};
-  if (with_combine) {
-    cj.a = *with_combine;
-    cj.kind = 1;
-    cj.n_wg = (cj.a.B + 7) / 8 * 8;
+  if (!with_combine) {
+    launch<QkvEpi, X_NORM, 16>(g, e, pred, st);
+    return;
   }
-  launch<QkvEpi, X_NORM, 16>(g, e, pred, cj, st);
+  CombineJob cj{};
+  cj.a = *with_combine;
+  cj.kind = 1;
+  cj.n_wg = (cj.a.B + 7) / 8 * 8;
+  launch<QkvEpi, X_NORM, 16>(g, e, pred, st, cj.n_wg, cj);
+}
+void launch_small_begin_qkv(const BeginArgs& begin, const SmallShape& g, const QkvEpi& e, hipStream_t st) {
+  const int rope_wgs = begin.theta > 0.0f ? (begin.B * (begin.head_dim / 2) + 255) / 256 : 0;
+  launch<QkvEpi, X_EMBED, 16>(g, e, Pred{nullptr, 0}, st, (begin.B + rope_wgs + 7) / 8 * 8, begin);
 }
 void launch_small_oproj(const SmallShape& g, const AccEpi& e, Pred pred, hipStream_t st) { launch_acc<X_F32>(g, e, pred, st); }
-void launch_small_gateup(const SmallShape& g, const GateUpEpi& e, Pred pred, hipStream_t st) { launch<GateUpEpi, X_NORM, 16>(g, e, pred, CombineJob{}, st); }
+void launch_small_gateup(const SmallShape& g, const GateUpEpi& e, Pred pred, hipStream_t st) { launch<GateUpEpi, X_NORM, 16>(g, e, pred, st); }
 void launch_small_down(const SmallShape& g, const AccEpi& e, Pred pred, hipStream_t st) { launch_acc<X_ROWS>(g, e, pred, st); }
-void launch_small_lm(const SmallShape& g, const LmEpi& e, Pred pred, hipStream_t st) { launch<LmEpi, X_NORM, 16>(g, e, pred, CombineJob{}, st); }
+void launch_small_lm(const SmallShape& g, const LmEpi& e, Pred pred, hipStream_t st) { launch<LmEpi, X_NORM, 16>(g, e, pred, st); }
 
 }  // namespace ee
