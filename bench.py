@@ -361,18 +361,20 @@ def main():
             E_cpu, C_cpu = E_steps.cpu(), C_steps.cpu()
             per_iter = len(recs) // P
             agg = collections.defaultdict(lambda: [0, 0.0, 0.0])     # launches, milliseconds, algorithmic bytes
+            # up to 64 rows the projection that shares a launch with the decision has cached the first skipped layer
+            cached_ahead = 1 if cfg.dtype == "bf16" and Bsz <= 64 else 0
             for it in range(P):
                 for cls, layer, ms in recs[it * per_iter:(it + 1) * per_iter]:
                     # kernels of layers above the batch exit layer return at once; KV filling only runs after an
                     # early exit; the final LM pass (recorded at layer n) only when the loop reached layer n
-                    executed = (Lp[it] < n) if cls == "kv_fill" else (layer == 0 or layer <= Lp[it])
+                    executed = (Lp[it] + cached_ahead < n) if cls == "kv_fill" else (layer == 0 or layer <= Lp[it])
                     # measures without an exit head: the one LM-head pass for the tokens (recorded at layer n) always runs
                     if base_mode in ("sim", "cls") and layer == n and cls in ("head", "norm", "combine"):
                         executed = True
                     if not executed:
                         continue
-                    if cls == "kv_fill":      # K and V weight rows of every skipped layer
-                        ab = (n - Lp[it]) * 2.0 * cfg.d_model * cfg.d_model * 2
+                    if cls == "kv_fill":      # K and V weight rows of every layer it fills
+                        ab = (n - Lp[it] - cached_ahead) * 2.0 * cfg.d_model * cfg.d_model * 2
                     elif cls == "attention":  # cached K/V of the sequences that still attend in this layer
                         attends = (E_cpu[it] >= layer) if per_seq_mode else torch.ones(Bsz, dtype=torch.bool)
                         ab = float((C_cpu[it][attends] + 1).sum()) * kv_bytes_per_position(cfg)
