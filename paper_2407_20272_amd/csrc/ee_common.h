@@ -104,7 +104,7 @@ struct AccEpi {                 // residual update
   const float* h_in;            // fp32 path: nullptr (added in place), or what is added to, with h the result
 };
 struct GateUpEpi {              // act = silu(gate) * up
-  void* act;                    // XT bf16 [Mpad][f] (bf16 path) or plain float [M][f]
+  void* act;                    // XT bf16 [Mpad][f] (bf16 path), plain bf16 [M][f] (gemm_small.hip) or plain float [M][f]
   int d_ffn;
 };
 struct LmEpi {                  // per-tile softmax statistics of the scaled logits
