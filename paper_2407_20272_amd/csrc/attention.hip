@@ -111,7 +111,12 @@ __device__ __forceinline__ void attn_decode(const AttnArgs& a, const Op& op, int
   // three in a row.
   const int t0 = (int)threadIdx.x < a.max_blocks ? safe_block(table[threadIdx.x], a.num_blocks) : 0;
   const int len = a.context_lens[b];
-  const int left = a.skip ? __hip_atomic_load(a.skip + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  int left = 0;
+  if constexpr (OPROJ) {
+    if (a.skip) left = op.job.n_wg ? left_before(op.job.a.s, b, op.job.a.layer) : ctl_load(a.skip + b);
+  } else {
+    left = a.skip ? ctl_load(a.skip + b) : 0;
+  }
   const int out_row = a.out_pos ? a.out_pos[b] : b;
   float q[EPL];
   {
@@ -324,8 +329,8 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnArgs a, Pred pred)
 }
 
 // fp32 path: attention and output projection in one launch, with the exit decision of the layer before in leading workgroups.  All of
-// them apply the decision's own rule (layer_ran), not the live flag: the attention of the layer after the batch exit layer may
-// run, and nobody reads its result.
+// them apply the decision's own rule (layer_ran, and left_before for a sequence), not the live words: the attention of the layer after the
+// batch exit layer, or of a sequence that leaves by this decision, runs, and nobody reads its result.
 template <int DH>
 __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, Pred pred, Oproj op) {
   if ((int)blockIdx.y < op.job.n_wg) {

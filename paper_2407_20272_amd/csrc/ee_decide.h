@@ -35,6 +35,11 @@ __device__ inline void decide_row(const IterState& s, int m, int B, int layer, f
 __device__ inline bool layer_ran(const IterState& s, int layer) {
   return ctl_load(s.done) == 0 || ctl_load(s.batch_exit_layer) >= layer;
 }
+// Had sequence m left at an earlier layer than `layer`?  For a launch that takes layer `layer`'s decision and skips the sequences that have left:
+// their status words change under its readers, and wavefronts of one workgroup that disagree do half of its work (half of a block table in LDS,
+// say).  The exit layer changes as well, but only from n_layers to `layer`, neither of which is less than it, so that every reader gets the same
+// answer here too.
+__device__ inline bool left_before(const IterState& s, int m, int layer) { return ctl_load(s.exit_layer + m) < layer; }
 // Whether a launch that takes layer `layer`'s decision has nothing to do (layer 0, the final token selection, raises nothing).
 __device__ inline bool decision_skip(const Pred& pred, const IterState& s, int layer) {
   return layer > 0 && pred.flag ? !layer_ran(s, layer) : pred_skip(pred);
