@@ -104,8 +104,9 @@ __device__ __forceinline__ void attn_decode(const AttnArgs& a, const Op& op, int
   const int32_t* table = a.block_tables + (size_t)(a.row_table ? safe_row(a.row_table[b], a.B) : b) * a.max_blocks;
 
   extern __shared__ int32_t tbl[];
-  if constexpr (!OPROJ)
-    if (skip()) return;
+  if constexpr (OPROJ)   // (what the launch was given is fetched ahead of the predicate, not in a second trip behind it)
+    asm volatile("" ::"s"(a.q), "s"(a.k_pool), "s"(a.v_pool), "s"(a.context_lens), "s"(a.block_tables), "s"(a.max_blocks), "s"(a.num_blocks), "s"(op.w));
+  if (skip()) return;
   // Everything the first K/V load needs is requested before any of it is waited for: the context length, the
   // start of the block-table row (its width is known without the length) and q: one memory round trip, not
   // three in a row.
@@ -123,10 +124,6 @@ __device__ __forceinline__ void attn_decode(const AttnArgs& a, const Op& op, int
     const float* qp = a.q + ((size_t)b * a.n_heads + head) * DH + sub * EPL;
 #pragma unroll
     for (int i = 0; i < EPL; ++i) q[i] = qp[i];
-  }
-  if constexpr (OPROJ) {   // (the float path's launches are short enough for this to be a part of them)
-    asm volatile("" ::: "memory");   // the loads above stay above
-    if (skip()) return;
   }
   if (left != 0) return;   // the sequence has left at an earlier layer: nothing to attend, nothing read
   // positions 0..p inclusive, never beyond the block table's width

@@ -33,7 +33,8 @@ __device__ inline void decide_row(const IterState& s, int m, int B, int layer, f
 // batch_exit_layer == layer or, not yet visible, its initial n_layers; one raised at an earlier layer with that layer's
 // number, both visible since an earlier launch.  So every reader of the launch gets the same answer, whenever it reads.
 __device__ inline bool layer_ran(const IterState& s, int layer) {
-  return ctl_load(s.done) == 0 || ctl_load(s.batch_exit_layer) >= layer;
+  const int32_t done = ctl_load(s.done), at = ctl_load(s.batch_exit_layer);   // (side by side: behind the exit both are needed)
+  return done == 0 || at >= layer;
 }
 // Had sequence m left at an earlier layer than `layer`?  For a launch that takes layer `layer`'s decision and skips the sequences that have left:
 // their status words change under its readers, and wavefronts of one workgroup that disagree do half of its work (half of a block table in LDS,

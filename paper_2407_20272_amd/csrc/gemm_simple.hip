@@ -5,10 +5,10 @@
 // themselves: every wavefront sums the squares of its rows beside the products (the rows are a few kilobytes in L1) and the
 // separate normalisation launches are gone.  What bounds this path at small widths is the chain of dependent launches, and in each of
 // them the chain of dependent loads (predicate, operands, what the epilogue looks up): a launch took 4 to 5 us for work of well under
-// one.  So the launches are few (ee_decode_iteration) and everything whose address is known at the start is asked for at the start.
+// one.  So the launches are few (ee_decode_iteration) and what a launch reads is asked for at once, behind its predicate.
 // One iteration of four sequences and four layers of width 256, leaving at layer 3: 65 launches and 217 us with a launch a step, 27
-// and 98 us with norms and decisions inside the projections, 19 and 83 us with four launches a layer, 75 us with the loads in front, 73 with
-// no second layer-4 projection in KV filling, 18 and 71 us with the start in the first projection's launch.
+// and 98 us with norms and decisions inside the projections, 19 and 83 us with four launches a layer, 75 us with the operands asked for at once,
+// 73 with no second layer-4 projection in KV filling, 18 and 71 us with the start in the first projection's launch.
 #include <type_traits>
 
 #include "ee_common.h"
@@ -114,12 +114,10 @@ __device__ inline void put_qkv(const QkvEpi& e, const RowOf& r, int m, int f_lo,
 
 // One workgroup (bx of those of a projection) of four wavefronts, a pair of output rows each.  PARTS: the operand comes in parts
 // (SimpleShape::parts).  PIECES > 0: the contraction is at most that many times 256, and all of a wavefront's operands are asked for at
-// once, before it looks (skip) whether the launch has anything to do.
-template <class Epi, bool NORM, bool VEC, bool PARTS, int PIECES, class Fill, class Skip, class Job = NoJob>
-__device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fill, int bx, Skip skip, const Job& job = Job{}) {
+// once.  layer: of KV filling.
+template <class Epi, bool NORM, bool VEC, bool PARTS, int PIECES, class Fill, class Job = NoJob>
+__device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fill, int bx, int layer, const Job& job = Job{}) {
   constexpr bool FILL = std::is_same<Fill, SimpleFill>::value, BEGIN = std::is_same<Job, BeginJob>::value;
-  if constexpr (PIECES == 0 || FILL)
-    if (skip()) return;
   // The row blocks of one group of weight rows get ids 8 apart: they run on one XCD at the same time, and all but the first
   // read of a weight row hit its L2.  With the row blocks outermost every block fetched the whole matrix from beyond the L2:
   // LM head of 32000 x 4096 and 32 rows 985 us (rows looped over in the wavefront, the form before: 665), now 570; gate/up
@@ -127,7 +125,6 @@ __device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fi
   const int first = blockIdx.y * ROW_BLOCKS, row_blocks = min(ROW_BLOCKS, (g.M + MC - 1) / MC - first), slot = bx >> 3;
   const int m0 = (first + slot % row_blocks) * MC;
   if constexpr (FILL) {   // one slice of the grid per layer; nothing to do where every row has been cached already
-    const int layer = blockIdx.z + 1;
     bool need = false;
     for (int m = m0; m < min(m0 + MC, g.M); ++m) need |= ctl_load(e.fill_from + (size_t)m * e.fill_from_stride) + e.fill_lead < layer;
     if (!need) return;
@@ -209,8 +206,6 @@ __device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fi
     for (int c = 0; c < PIECES; ++c) load(v[c], min(c * 64 * N + lane * N, g.K - N));
     row = row_of<Epi, BEGIN>(e, min(m, g.M - 1), f_lo, f_hi, at);
     asm volatile("" ::: "memory");   // the loads above stay above
-    if constexpr (!FILL)
-      if (skip()) return;
 #pragma unroll
     for (int c = 0; c < PIECES; ++c)
       if (c * 64 * N + lane * N < g.K) multiply(v[c], c * 64 * N + lane * N);
@@ -251,9 +246,20 @@ __device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fi
   }
 }
 
+// Every launch looks at its predicate first, and asks for its operands behind it: behind the exit there are four launches a layer with nothing
+// to do, and one that had asked for its operands took 3 us instead of 1.7 (a wavefront stays until its loads are back, also where the
+// predicate was asked for ahead of them).  Width 256, 24 layers, 4 / 64 sequences that leave at layer 2: 267 / 489 us with the operands first,
+// 181 / 319 with the predicate first.
+// What the launch was given is fetched ahead of that: behind the branch the compiler would fetch it in a second trip (0.15 us a launch:
+// 24 layers that all run, 4 sequences, 404 -> 392 us).
+__device__ __forceinline__ void args_first(const SimpleShape& g) {
+  asm volatile("" ::"s"(g.w), "s"(g.x), "s"(g.gain), "s"(g.K), "s"(g.M), "s"(g.n_rows), "s"(g.pair_stride));
+}
+
 template <class Epi, bool NORM, bool VEC, bool PARTS, int PIECES, class Fill, class Job>
 __global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, Pred pred, Fill fill, Job job) {
   int bx = blockIdx.x;
+  const int layer = blockIdx.z + 1;
   if constexpr (std::is_same<Job, SimpleDecision>::value) {
     // Leading workgroups: the exit decision of the layer before, one row each.  The projection's own apply the same rule
     // (layer_ran), not the live flag: the projection of the layer after the batch exit layer runs, and what it caches is what KV
@@ -266,27 +272,33 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, 
     }
     if (!ran) return;
     bx -= job.n_wg;
-    simple_body<Epi, NORM, VEC, PARTS, PIECES>(g, e, fill, bx, [] { return false; });
+    simple_body<Epi, NORM, VEC, PARTS, PIECES>(g, e, fill, bx, layer);
   } else if constexpr (std::is_same<Job, BeginJob>::value) {
     if (bx < job.n_wg) {
       if (blockIdx.y == 0) begin_row_f32(job.a, bx);
       return;
     }
-    simple_body<Epi, NORM, VEC, PARTS, PIECES>(g, e, fill, bx - job.n_wg, [] { return false; }, job);
+    simple_body<Epi, NORM, VEC, PARTS, PIECES>(g, e, fill, bx - job.n_wg, layer, job);
   } else {
-    simple_body<Epi, NORM, VEC, PARTS, PIECES>(g, e, fill, bx, [&] { return pred_skip(pred); });
+    args_first(g);
+    if (pred_skip(pred)) return;
+    simple_body<Epi, NORM, VEC, PARTS, PIECES>(g, e, fill, bx, layer);
   }
 }
 
 // Two launches in one: the LM head (its workgroups in front) and a projection of the same hidden states that needs no result of it:
-// the next layer's QKV, or KV filling (whose predicate is the opposite one).
+// the next layer's QKV, or KV filling.
 template <bool VEC, int PIECES, class Fill>
 __global__ __launch_bounds__(256) void gemm_simple_head_kernel(SimpleShape gh, LmEpi eh, Pred ph, SimpleShape g, QkvEpi e, Pred pred, Fill fill, int head_wgs) {
+  args_first(gh);
+  args_first(g);
   if ((int)blockIdx.x < head_wgs) {
-    if (blockIdx.z == 0) simple_body<LmEpi, true, VEC, false, PIECES>(gh, eh, NoFill{}, blockIdx.x, [&] { return pred_skip(ph); });
+    if (blockIdx.z != 0 || pred_skip(ph)) return;
+    simple_body<LmEpi, true, VEC, false, PIECES>(gh, eh, NoFill{}, blockIdx.x, 0);
     return;
   }
-  simple_body<QkvEpi, true, VEC, false, PIECES>(g, e, fill, (int)blockIdx.x - head_wgs, [&] { return pred_skip(pred); });
+  if (pred_skip(pred)) return;
+  simple_body<QkvEpi, true, VEC, false, PIECES>(g, e, fill, (int)blockIdx.x - head_wgs, blockIdx.z + 1);
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -308,10 +320,10 @@ bool vectors(const SimpleFill& fill, int n_layers) {
 // 83 with four sequences, 113 instead of 153 with 64 (whose row blocks each ran the chain of dependent loads).
 template <class Go>
 void for_pieces(bool vec, int K, Go go) {
-  if (vec && K <= 256) go(std::true_type{}, std::integral_constant<int, 1>{});
-  else if (vec && K <= 1024) go(std::true_type{}, std::integral_constant<int, 4>{});
-  else if (vec) go(std::true_type{}, std::integral_constant<int, 0>{});
-  else go(std::false_type{}, std::integral_constant<int, 0>{});
+  if (vec && K <= 256) return go(std::true_type{}, std::integral_constant<int, 1>{});
+  if (vec && K <= 1024) return go(std::true_type{}, std::integral_constant<int, 4>{});
+  if (vec) return go(std::true_type{}, std::integral_constant<int, 0>{});
+  go(std::false_type{}, std::integral_constant<int, 0>{});
 }
 
 template <class Epi, bool NORM, bool PARTS = false, class Fill = NoFill, class Job = NoJob>
