@@ -1,6 +1,6 @@
 """What the host side enqueues when the runtime refuses something, without a GPU: a small C program brings its own
 hipLaunchKernel, hipFuncSetAttribute, .. (a program's symbols come before those of the libraries it loads), calls the library with
-made-up device pointers, which the host never follows, and prints every launch."""
+made-up device pointers, which the host never follows, and prints every launch, with the kernel's name."""
 import ctypes
 import os
 import subprocess
@@ -32,9 +32,20 @@ int hipFuncSetAttribute(const void* f, int attr, int value) {
 int __hipPushCallConfiguration(dim g, dim b, size_t s, void* st) { (void)st; grid = g; block = b; lds = s; return 0; }
 int __hipPopCallConfiguration(dim* g, dim* b, size_t* s, void** st) { *g = grid; *b = block; *s = lds; *st = 0; return 0; }
 int hipGetSymbolAddress(void** p, const void* s) { (void)s; *p = (void*)0x20000; return 0; }
+static struct { const void* f; const char* name; } kernels[4096];
+static int n_kernels;
+void __hipRegisterFunction(void** modules, const void* f, char* device, const char* name, unsigned limit, void* tid, void* bid, void* bd, void* gd,
+                           int* size) {
+  (void)modules; (void)device; (void)limit; (void)tid; (void)bid; (void)bd; (void)gd; (void)size;
+  kernels[n_kernels].f = f;
+  kernels[n_kernels++].name = name;
+}
 int hipLaunchKernel(const void* f, dim g, dim b, void** args, size_t s, void* st) {
-  (void)f; (void)args; (void)st;
-  printf("launch %u %u %u %u %zu\n", g.x, g.y, g.z, b.x, s);
+  (void)args; (void)st;
+  printf("launch %u %u %u %u %zu", g.x, g.y, g.z, b.x, s);
+  for (int i = 0; i < n_kernels; ++i)
+    if (kernels[i].f == f) printf(" %s", kernels[i].name);
+  printf("\n");
   return 0;
 }
 
@@ -56,14 +67,22 @@ int main(int argc, char** argv) {
     m.desc.d_ffn = atoi(argv[5]);
     m.desc.vocab = atoi(argv[6]);
   }
+  if (!strcmp(argv[1], "float")) {                   /* heads of 64, 15 blocks a sequence */
+    m.desc.dtype = EE_FP32;
+    m.desc.head_dim = 64;
+    m.desc.d_model = m.desc.n_heads * 64;
+    b = (ee_batch){B, p, p, p, 15, 200, 0};
+  }
   const size_t n = ee_workspace_bytes(&m.desc, B, 300);
+  const float never[2] = {2, 2};
   int rc;
   if (!strcmp(argv[1], "init"))
     rc = ee_noalloc_init();
   else if (!strcmp(argv[1], "iteration"))
     rc = ee_decode_iteration(&m, &c, &b, 0, 0, EE_EXIT_NONE, p, p, p, 0, 0, p, n, 0);
+  else if (!strcmp(argv[1], "float"))
+    rc = ee_decode_iteration(&m, &c, &b, never, 0, EE_EXIT_BATCH, p, p, p, 0, 0, p, n, 0);
   else if (!strcmp(argv[1], "per_sequence")) {
-    const float never[2] = {2, 2};
     b.row_table = 0;
     rc = ee_decode_iteration(&m, &c, &b, never, 0, EE_EXIT_PER_SEQUENCE, p, p, p, 0, 0, p, n, 0);
   } else if (!strcmp(argv[1], "attention"))
@@ -89,7 +108,8 @@ def program(tmp_path_factory):
     def run(*args):
         out = subprocess.run([str(exe), *map(str, args)], check=True, capture_output=True, text=True, timeout=60).stdout.split("\n")
         run.attributes = [int(line.split()[1]) for line in out if line.startswith("attribute")]
-        launches = [tuple(int(x) for x in line.split()[1:]) for line in out if line.startswith("launch")]
+        launches = [tuple(int(x) for x in line.split()[1:6]) for line in out if line.startswith("launch")]
+        run.names = [line.split()[6] for line in out if line.startswith("launch")]
         return launches, [line for line in out if line.startswith("rc")][0]
 
     return run
@@ -217,3 +237,16 @@ def test_gate_up_in_the_ring_kernel(program, rows, heads, tiles, ring):
     assert rc.strip() == "rc 0" and launches.count(want) == (2 if ring else 0)
     launches, rc = program("iteration", 1, rows, heads, 16 * tiles, 1024)
     assert rc.strip() == "rc 0" and want not in launches
+
+
+FOUR_PIECES = "ELi4E"   # gemm_simple_kernel<.., PIECES = 4, ..>
+
+
+@pytest.mark.parametrize("rows,heads,ffn,vocab", [(4, 5, 1280, 512), (16, 8, 2048, 512), (4, 8, 1024, 32000), (64, 4, 1024, 512), (500, 16, 4096, 8000)])
+def test_float_contractions_of_four_pieces_where_a_launch_leaves_the_chip_idle(program, rows, heads, ffn, vocab):
+    """All operands of a contraction of 257 to 1024 at once only where there are no more workgroups than compute units."""
+    launches, rc = program("float", 0, rows, heads, ffn, vocab)
+    assert rc.strip() == "rc 0"
+    for (x, y, z, _, _), name in zip(launches, program.names):
+        if FOUR_PIECES in name:
+            assert x * y * z <= 256, name
