@@ -103,7 +103,7 @@ struct Workspace {
 };
 
 // Small float models: a layer in four launches instead of six (see ee_decode_iteration).
-constexpr int kF32FewRows = 64, kF32FewWidth = 512;
+constexpr int kF32FewRows = 64, kF32FewWidth = 256;
 
 Workspace carve(const ee_model_desc& D, int B, void* base) {
   Workspace w{};
@@ -625,12 +625,14 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // gate/up takes while it loads its operand.  Every gate/up workgroup reads all parts and four attention workgroups repeat a pair's
   // keys, so that goes up to 64 pairs.  Iterations of the four-layer model of width 256 (six launches a layer -> four, us): 4 sequences
   // 98 -> 83; attention with the output projection at 128 pairs 104 against 92 without, at 256 152 against 114; the shared launches
-  // alone 119 -> 114 with 33 sequences, 64 rows even.
+  // alone 119 -> 114 with 33 sequences, 64 rows even.  Wider than 256, gate/up holds a long operand in parts: 512 channels gain with some
+  // batches (32 rows 143 -> 137) and lose with others (8 rows 104 -> 141, 16 rows with heads of 128 118 -> 152).  The width that counts
+  // for the split is that of the block table, not the contexts: up to 64 pairs, a table of 16 blocks (256 positions) or more keeps the six launches.
   bool few_f32 = !bf && !batch->row_table && B <= kF32FewRows && d <= kF32FewWidth && attn_split_parts(B, D.n_heads, batch->max_blocks) == 1;
   bool parts_f32 = few_f32 && B * D.n_heads <= 64;
   for (int i = 0; i < n; ++i) parts_f32 = parts_f32 && (reinterpret_cast<uintptr_t>(model->layers[i].w_o) & 15) == 0;   // (16-byte loads)
   // Contexts that several workgroups share: the decision alone, inside the QKV launch.
-  const bool carry_f32 = !bf && !dotmode && B <= 64 && d <= kF32FewWidth && !few_f32;
+  const bool carry_f32 = !bf && !dotmode && B <= 64 && d <= 512 && !few_f32;
   const bool carry_decide = bf && dotmode && !compact && gemm_qkv_carries_combine(B);
   CombineArgs pending{};
   DecideArgs pending_dot{};

@@ -242,6 +242,16 @@ def test_gate_up_in_the_ring_kernel(program, rows, heads, tiles, ring):
 FOUR_PIECES = "ELi4E"   # gemm_simple_kernel<.., PIECES = 4, ..>
 
 
+@pytest.mark.parametrize("heads,rows,launches", [(1, 1, 10), (4, 16, 10), (4, 17, 12), (4, 64, 12), (4, 65, 16), (5, 1, 15), (5, 16, 15), (8, 4, 15)])
+def test_float_layers_in_four_launches_up_to_width_256(program, heads, rows, launches):
+    """Two layers of four launches and two behind them; five a layer above 64 (sequence, head) pairs; wider models and more rows keep the
+    launches that are faster there."""
+    _, rc = program("float", 0, rows, heads, 256 * heads, 512)
+    assert rc.strip() == "rc 0"
+    assert len(program.names) == launches
+    assert any("attn_f32_kernel" in n for n in program.names) == (launches <= 12)
+
+
 @pytest.mark.parametrize("rows,heads,ffn,vocab", [(4, 5, 1280, 512), (16, 8, 2048, 512), (4, 8, 1024, 32000), (64, 4, 1024, 512), (500, 16, 4096, 8000)])
 def test_float_contractions_of_four_pieces_where_a_launch_leaves_the_chip_idle(program, rows, heads, ffn, vocab):
     """All operands of a contraction of 257 to 1024 at once only where there are no more workgroups than compute units."""
