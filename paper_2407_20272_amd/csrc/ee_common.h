@@ -332,8 +332,8 @@ struct SimpleShape {
   int row_begin;    // first output row
   int n_rows;       // output rows to compute (even)
   int pair_stride;  // rows (f, f + pair_stride) are computed together
-  // gate/up behind attention that has multiplied by the output projection's columns, head by head: the operand is x + parts[0] + parts[1] +
-  // .. ([n_parts][M][K]; rows with left[m] != 0: x alone), and is left in x_out [M][K].  parts == nullptr: x.
+  // gate/up (of up to 256 channels) behind attention that has multiplied by the columns of the output projection, head by head: the operand is
+  // x + parts[0] + parts[1] + .. ([n_parts][M][K]; rows with left[m] != 0: x alone), and is left in x_out [M][K].  parts == nullptr: x.
   const float* parts;
   int n_parts;
   float* x_out;
@@ -349,9 +349,10 @@ struct SimpleDecision {
 };
 void launch_simple_qkv(const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st, const SimpleDecision* with = nullptr);
 // The first layer's, which begins the iteration (launch_iter_begin_f32) as well: g.x is the embedding table.
+// Up to 256 channels.
 void launch_simple_begin_qkv(const BeginArgs& begin, const SimpleShape& g, const QkvEpi& e, hipStream_t st);
-// The LM head in the launch of the next layer's QKV projection, or of KV filling (which runs where the head, by its predicate ph, does not).  Up to
-// 256 rows.
+// The LM head in the launch of the next layer's QKV projection, or of KV filling (each by its own predicate: with a measure that has no head both
+// run).  Up to 256 rows and 256 channels.
 void launch_simple_head_qkv(const SimpleShape& gh, const LmEpi& eh, const SimpleShape& g, const QkvEpi& e, Pred pred, hipStream_t st);
 void launch_simple_acc(const SimpleShape& g, const AccEpi& e, Pred pred, hipStream_t st);
 void launch_simple_gateup(const SimpleShape& g, const GateUpEpi& e, Pred pred, hipStream_t st);

@@ -287,18 +287,21 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(SimpleShape g, Epi e, 
 }
 
 // Two launches in one: the LM head (its workgroups in front) and a projection of the same hidden states that needs no result of it:
-// the next layer's QKV, or KV filling.
+// the next layer's QKV, or KV filling of every layer (wgs workgroups each).  In one dimension: as a grid of layers the head's workgroups
+// were there once a layer, and all but one of them empty.
 template <bool VEC, int PIECES, class Fill>
-__global__ __launch_bounds__(256) void gemm_simple_head_kernel(SimpleShape gh, LmEpi eh, Pred ph, SimpleShape g, QkvEpi e, Pred pred, Fill fill, int head_wgs) {
+__global__ __launch_bounds__(256) void gemm_simple_head_kernel(SimpleShape gh, LmEpi eh, Pred ph, SimpleShape g, QkvEpi e, Pred pred, Fill fill, int head_wgs,
+                                                               int wgs) {
   args_first(gh);
   args_first(g);
   if ((int)blockIdx.x < head_wgs) {
-    if (blockIdx.z != 0 || pred_skip(ph)) return;
+    if (pred_skip(ph)) return;
     simple_body<LmEpi, true, VEC, false, PIECES>(gh, eh, NoFill{}, blockIdx.x, 0);
     return;
   }
   if (pred_skip(pred)) return;
-  simple_body<QkvEpi, true, VEC, false, PIECES>(g, e, fill, (int)blockIdx.x - head_wgs, blockIdx.z + 1);
+  const int at = (int)blockIdx.x - head_wgs, layer = at / wgs;
+  simple_body<QkvEpi, true, VEC, false, PIECES>(g, e, fill, at - layer * wgs, layer + 1);
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -345,13 +348,13 @@ void launch(const SimpleShape& g, const Epi& e, Pred pred, hipStream_t st, const
 template <class Fill>
 void launch_with_head(const SimpleShape& gh, const LmEpi& eh, Pred ph, const SimpleShape& g, const QkvEpi& e, Pred pred, const Fill& fill, int n_layers,
                       bool vec, hipStream_t st) {
-  const int lead = workgroups(gh);
-  const dim3 grid(lead + workgroups(g), 1, n_layers);   // (both of one group of row blocks: the host sees to that)
+  const int lead = workgroups(gh), wgs = workgroups(g);
+  const dim3 grid(lead + wgs * n_layers);   // (both of one group of row blocks: the host sees to that)
   auto go = [&](auto vec_c, auto pieces_c) {
     hipLaunchKernelGGL((gemm_simple_head_kernel<decltype(vec_c)::value, decltype(pieces_c)::value, Fill>), grid, dim3(256), 0, st, gh, eh, ph, g, e, pred,
-                       fill, lead);
+                       fill, lead, wgs);
   };
-  for_pieces(vec && vectors(gh), g.K, (long)grid.x * grid.z, go);
+  for_pieces(vec && vectors(gh), g.K, grid.x, go);
 }
 
 }  // namespace

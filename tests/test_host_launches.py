@@ -260,3 +260,14 @@ def test_float_contractions_of_four_pieces_where_a_launch_leaves_the_chip_idle(p
     for (x, y, z, _, _), name in zip(launches, program.names):
         if FOUR_PIECES in name:
             assert x * y * z <= 256, name
+
+
+@pytest.mark.parametrize("rows,vocab", [(1, 512), (64, 32000)])
+def test_float_head_beside_kv_filling_is_there_once(program, rows, vocab):
+    """Not once a layer: the head's workgroups, then those of each of the two layers."""
+    launches, rc = program("float", 0, rows, 4, 1024, vocab)
+    assert rc.strip() == "rc 0"
+    blocks = (rows + 3) // 4
+    head, fill = -(-vocab // 8 // 8) * 8 * blocks, 64 * blocks
+    assert launches[-2][:3] == (head + 2 * fill, 1, 1)
+
