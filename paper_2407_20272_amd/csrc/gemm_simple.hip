@@ -319,15 +319,17 @@ bool vectors(const SimpleFill& fill, int n_layers) {
   return true;
 }
 
-// Contractions of up to 256 have their operands in registers at once.  So do those of up to 1024 where the launch
+// Contractions of up to 256 have their operands in registers at once (SHORT: there are no others).  So do those of up to 1024 where the launch
 // has no more workgroups than compute units (four layers, four sequences: width 320 87 us in a loop, 81 so; width 640 108 and 103): from there
 // on the other wavefronts of a compute unit hide the chain of dependent loads, and 146 registers a lane leave too few of them (four layers,
 // 16 / 500 rows of width 512: 266 / 2623 us so, 118 / 1370 in a loop; 64 rows of width 1024 925 and 642).
-template <class Go>
+template <bool SHORT, class Go>
 void for_pieces(bool vec, int K, long wgs, Go go) {
   if (vec && K <= 256) return go(std::true_type{}, std::integral_constant<int, 1>{});
-  if (vec && K <= 1024 && wgs <= 256) return go(std::true_type{}, std::integral_constant<int, 4>{});
-  if (vec) return go(std::true_type{}, std::integral_constant<int, 0>{});
+  if constexpr (!SHORT) {
+    if (vec && K <= 1024 && wgs <= 256) return go(std::true_type{}, std::integral_constant<int, 4>{});
+    if (vec) return go(std::true_type{}, std::integral_constant<int, 0>{});
+  }
   go(std::false_type{}, std::integral_constant<int, 0>{});
 }
 
@@ -343,7 +345,7 @@ void launch(const SimpleShape& g, const Epi& e, Pred pred, hipStream_t st, const
     hipLaunchKernelGGL((gemm_simple_kernel<Epi, NORM, decltype(vec_c)::value, PARTS, decltype(pieces_c)::value, Fill, Job>), grid, dim3(256), 0, st, g, e,
                        pred, fill, job);
   };
-  for_pieces(vec, g.K, (long)grid.x * grid.y * grid.z, go);
+  for_pieces<PARTS || std::is_same<Job, BeginJob>::value>(vec, g.K, (long)grid.x * grid.y * grid.z, go);
 }
 template <class Fill>
 void launch_with_head(const SimpleShape& gh, const LmEpi& eh, Pred ph, const SimpleShape& g, const QkvEpi& e, Pred pred, const Fill& fill, int n_layers,
@@ -354,7 +356,7 @@ void launch_with_head(const SimpleShape& gh, const LmEpi& eh, Pred ph, const Sim
     hipLaunchKernelGGL((gemm_simple_head_kernel<decltype(vec_c)::value, decltype(pieces_c)::value, Fill>), grid, dim3(256), 0, st, gh, eh, ph, g, e, pred,
                        fill, lead, wgs);
   };
-  for_pieces(vec && vectors(gh), g.K, grid.x, go);
+  for_pieces<true>(vec && vectors(gh), g.K, grid.x, go);
 }
 
 }  // namespace

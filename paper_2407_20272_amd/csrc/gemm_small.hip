@@ -114,29 +114,29 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallShape g, Epi e, Pr
   const int P = (k_steps + SPL - 1) / SPL, p0 = P * wave / NW, p1 = P * (wave + 1) / NW, nc = max(1, (p1 - p0 + SM_U - 1) / SM_U);
 
   // ---- operand loads -------------------------------------------------------------------------------------
-  constexpr int RP = R < 16 / NG ? R : 16 / NG;   // rows in registers at a time
-  float v[RP][NG][8];
+  static_assert(XM == X_ROWS || R * NG <= 16, "all rows in registers");
+  float v[R][NG][8];
   bf16x8 gv[NG];
-  auto load_rows = [&](int r0) {
+  auto load_rows = [&] {
 #pragma unroll
-    for (int r = 0; r < RP; ++r)
+    for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int i = 0; i < NG; ++i) {
         if constexpr (XM == X_EMBED) {
-          const int tok = job.tokens[min(r0 + r, g.M - 1)];
+          const int tok = job.tokens[min(r, g.M - 1)];
           const bf16x8 e8 = *reinterpret_cast<const bf16x8*>(job.embed + (size_t)((unsigned)tok < (unsigned)job.vocab ? tok : 0) * K +
                                                              min((i * 256 + (int)threadIdx.x) * 8, K - 8));
 #pragma unroll
           for (int x = 0; x < 8; ++x) v[r][i][x] = (float)e8[x];
           continue;
         }
-        const float* p = reinterpret_cast<const float*>(g.x) + (size_t)min(r0 + r, g.M - 1) * K + min((i * 256 + (int)threadIdx.x) * 8, K - 8);
+        const float* p = reinterpret_cast<const float*>(g.x) + (size_t)min(r, g.M - 1) * K + min((i * 256 + (int)threadIdx.x) * 8, K - 8);
         const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
         v[r][i][0] = a.x; v[r][i][1] = a.y; v[r][i][2] = a.z; v[r][i][3] = a.w;
         v[r][i][4] = b.x; v[r][i][5] = b.y; v[r][i][6] = b.z; v[r][i][7] = b.w;
       }
   };
-  if constexpr (XM != X_ROWS) load_rows(0);
+  if constexpr (XM != X_ROWS) load_rows();
   if constexpr (NORM) {
 #pragma unroll
     for (int i = 0; i < NG; ++i) gv[i] = *reinterpret_cast<const bf16x8*>(g.gain + min((i * 256 + (int)threadIdx.x) * 8, K - 8));
@@ -224,47 +224,43 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallShape g, Epi e, Pr
     }
   }
   if constexpr (XM != X_ROWS) {
+    float rinv[R];
+    if constexpr (NORM) {
+      // the order of finish_norm_kernel: its thread t = (i % 2) * 256 + threadIdx.x owns what v[..][i] and v[..][i + 2] hold
 #pragma unroll
-    for (int r0 = 0; r0 < R; r0 += RP) {
-      if (r0) load_rows(r0);
-      float rinv[RP];
-      if constexpr (NORM) {
-        // the order of finish_norm_kernel: its thread t = (i % 2) * 256 + threadIdx.x owns what v[..][i] and v[..][i + 2] hold
+      for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int r = 0; r < RP; ++r)
+        for (int i = 0; i < (NG < 2 ? NG : 2); ++i) {
+          float ss = 0.0f;
 #pragma unroll
-          for (int i = 0; i < (NG < 2 ? NG : 2); ++i) {
-            float ss = 0.0f;
+          for (int c = i; c < NG; c += 2) {
+            float t = ss;
 #pragma unroll
-            for (int c = i; c < NG; c += 2) {
-              float t = ss;
-#pragma unroll
-              for (int x = 0; x < 8; ++x) t = fmaf(v[r][c][x], v[r][c][x], t);
-              if ((c * 256 + (int)threadIdx.x) * 8 < K) ss = t;
-            }
-            ss = wave_sum(ss);
-            if (lane == 0) sums[(r0 + r) * 8 + i * NW + wave] = ss;
+            for (int x = 0; x < 8; ++x) t = fmaf(v[r][c][x], v[r][c][x], t);
+            if ((c * 256 + (int)threadIdx.x) * 8 < K) ss = t;
           }
-        meet();
-#pragma unroll
-        for (int r = 0; r < RP; ++r) {
-          float t = 0.0f;
-#pragma unroll
-          for (int w = 0; w < (NG < 2 ? 4 : 8); ++w) t += sums[(r0 + r) * 8 + w];
-          rinv[r] = rsqrtf(t / (float)K + g.eps);
+          ss = wave_sum(ss);
+          if (lane == 0) sums[r * 8 + i * NW + wave] = ss;
         }
+      meet();
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < (NG < 2 ? 4 : 8); ++w) t += sums[r * 8 + w];
+        rinv[r] = rsqrtf(t / (float)K + g.eps);
       }
+    }
 #pragma unroll
-      for (int i = 0; i < NG; ++i) {
-        const int k0 = (i * 256 + (int)threadIdx.x) * 8;
-        if (k0 < K) {
+    for (int i = 0; i < NG; ++i) {
+      const int k0 = (i * 256 + (int)threadIdx.x) * 8;
+      if (k0 < K) {
 #pragma unroll
-          for (int r = 0; r < RP; ++r) {
-            bf16x8 o;
+        for (int r = 0; r < R; ++r) {
+          bf16x8 o;
 #pragma unroll
-            for (int x = 0; x < 8; ++x) o[x] = NORM ? (bf16_t)(v[r][i][x] * rinv[r] * (float)gv[i][x]) : (bf16_t)v[r][i][x];
-            *reinterpret_cast<bf16x8*>(sm + (r0 + r) * row_bytes + k0 * 2) = o;
-          }
+          for (int x = 0; x < 8; ++x) o[x] = NORM ? (bf16_t)(v[r][i][x] * rinv[r] * (float)gv[i][x]) : (bf16_t)v[r][i][x];
+          *reinterpret_cast<bf16x8*>(sm + r * row_bytes + k0 * 2) = o;
         }
       }
     }
@@ -370,14 +366,14 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallShape g, Epi e, Pr
   }
 }
 
-// go(rows, groups of 2048 channels of a row) as constants.
+// go(rows, groups of 2048 channels of a row) as constants (gemm_small_takes: eight rows are no wider than 3072).
 template <class Go>
-auto for_shape(int M, int K, Go go) {
+void for_shape(int M, int K, Go go) {
   const auto rows = [&](auto ng) {
     if (M == 1) return go(std::integral_constant<int, 1>{}, ng);
     if (M == 2) return go(std::integral_constant<int, 2>{}, ng);
-    if (M <= 4) return go(std::integral_constant<int, 4>{}, ng);
-    return go(std::integral_constant<int, 8>{}, ng);
+    if constexpr (decltype(ng)::value == 4) return go(std::integral_constant<int, 4>{}, ng);
+    else return M <= 4 ? go(std::integral_constant<int, 4>{}, ng) : go(std::integral_constant<int, 8>{}, ng);
   };
   if (K <= 2048) return rows(std::integral_constant<int, 1>{});
   if (K <= 4096) return rows(std::integral_constant<int, 2>{});
@@ -388,9 +384,11 @@ template <class Epi, int XM, int RU, class Job = NoJob>
 void launch(SmallShape g, const Epi& e, Pred pred, hipStream_t st, int lead = 0, const Job& job = Job{}) {
   const int units = g.whole + g.halves;
   g.wgs = units < SM_WGS ? units : SM_WGS;
-  for_shape(g.M, g.K, [&](auto r, auto ng) {
+  for_shape(g.M, XM == X_ROWS ? 0 : g.K, [&](auto r, auto ng) {
     constexpr int R = decltype(r)::value, NG = XM == X_ROWS ? 1 : decltype(ng)::value;   // (that operand passes through no registers)
-    hipLaunchKernelGGL((gemm_small_kernel<Epi, R, XM, NG, RU, Job>), dim3(g.wgs + lead), dim3(256), lds_bytes(g.K, R, XM), st, g, e, pred, job);
+    // (launch_acc's rule: the output projection takes units of 8 rows up to 2048 channels, never from there to 4096)
+    if constexpr (XM != X_F32 || NG != (RU == 8 ? 2 : 1))
+      hipLaunchKernelGGL((gemm_small_kernel<Epi, R, XM, NG, RU, Job>), dim3(g.wgs + lead), dim3(256), lds_bytes(g.K, R, XM), st, g, e, pred, job);
   });
 }
 // Accumulate projections: units of 8 rows where fewer rows then fall to the busiest compute unit (d = 5120: 24 instead of 32).
