@@ -123,10 +123,14 @@ def test_small_bf16_lockstep(batch):
     (5, 6, 64, 1040, 160, 3, 2),       # the narrowest of five to eight rows ..
     (8, 6, 64, 336, 160, 3, True),
     (8, 5, 64, 336, 160, 3, 2),        # .. and one narrower, in the other kernels
-    (8, 24, 128, 32, 64, 1, True),     # the widest of eight rows: 24576 channels; 8-row units
+    (8, 24, 128, 32, 64, 1, True),     # the widest of eight rows: 24576 channels; residual updates in 16-row units (8-row ones up to 2048)
     (7, 25, 128, 32, 64, 1, True),     # .. and wider
     (1, 32, 128, 80, 64, 2, True),     # 16-row units, one a workgroup
-    (3, 33, 128, 32, 64, 1, True),     # past 4096 channels: operand rows in four groups
+    (3, 33, 128, 32, 64, 1, True),     # past 4096 channels: operand rows in three groups, 8-row units, three a workgroup
+    (2, 52, 128, 32, 64, 1, True),     # past 6144: in four; 16-row units, two a workgroup
+    (1, 8, 128, 8240, 16480, 2, True), # 515 tiles of gate/up and of the LM head: two or three a workgroup
+    (3, 10, 64, 8240, 24608, 2, 2),    # .. 769: three or four
+    (8, 10, 64, 12304, 16480, 2, 2),   # .. of eight rows
 ])
 def test_bf16_up_to_eight_sequences(batch, heads, dh, d_ffn, vocab, layers, head_mode):
     """Projections that build their own operand and add to the residual rows, at the edges of their units, loads and rule; sequences leave

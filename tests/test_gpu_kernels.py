@@ -432,6 +432,14 @@ def test_exit_check_385_to_512_rows(batch, heads):
     run_exit_check(cfg, seed=50 + heads, layer=2, threshold=0.3, hidden_scale=3.0)
 
 
+@pytest.mark.parametrize("batch,heads,vocab", [(1, 16, 32000), (2, 64, 16416), (3, 8, 24608), (4, 16, 32000), (8, 16, 16416)])
+def test_exit_check_of_up_to_eight_rows(batch, heads, vocab):
+    """The LM head that normalises its own rows: 513 to 1000 tiles on 256 workgroups, rows of up to 8192 channels."""
+    cfg = W.reduced(TINY, dtype="bf16", d_model=heads * 128, n_heads=heads, head_dim=128, n_layers=2, vocab=vocab, batch=batch, logit_scale=0.5,
+                    weight_std=0.02)
+    run_exit_check(cfg, seed=batch + heads, layer=1, threshold=0.02)
+
+
 @pytest.mark.parametrize("batch,heads,vocab", [(129, 2, 32), (150, 6, 1312), (161, 48, 8544), (300, 48, 16416), (600, 2, 1280)])
 def test_exit_check_in_blocks(batch, heads, vocab):
     """LM head in 128 x 128 and 128 x 256 blocks: one tile, tiles that leave a wavefront one, or none, of its own (statistics of
