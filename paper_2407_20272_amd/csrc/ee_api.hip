@@ -391,7 +391,7 @@ int enqueue_exit_check(const ee_model& M, int32_t layer, const float* hidden, in
   IterState s{status, exit_layer, n_exited, done_flag, batch_exit_layer};
   CombineArgs ca{w.partials, D.vocab / 32, batch, layer, scale, threshold, D.conf_mode, forced_exit_layer, s, argmax, conf};
   if (D.dtype == EE_BF16) {
-    if (gemm_small_takes(batch, D.d_model)) {   // no launch for the operand: 7B shape, one row 50.6 -> 45.4 us, eight rows of width 2048 32.6 -> 29.1
+    if (gemm_small_takes_check(batch, D.d_model, D.vocab / 32)) {   // no launch for the operand: 7B shape, one row 50.6 -> 45.4 us, eight rows of width 2048 32.6 -> 29.1
       enqueue_head_small(M, w, hidden, batch, scale, layer, always, st);
     } else {
       launch_finish_norm(plain_norm(D, hidden, M.g_final, w.xH, batch), always, st);
@@ -561,7 +561,7 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // update; slot 2i: after layer i.
   auto rs = [&](int slot) { return w.rowsq + (size_t)slot * Mpad; };
   // Up to eight sequences: projections that build their operand from the residual rows and add to these, no launch between them.
-  const bool small = bf && !dotmode && !batch->row_table && gemm_small_takes(B, d);
+  const bool small = bf && !dotmode && !batch->row_table && gemm_small_takes(B, d, first_check < n ? D.vocab / 32 : 0);
   const bool begin_small = small && (reinterpret_cast<uintptr_t>(model->embed) & 15) == 0;   // (in the first projection's launch: 7B shape, one sequence 219.9 -> 216.6 us)
   // (Small float models: in the launch of the first projection, which reads the embedding rows and forms the angles itself: four sequences 72.8 -> 70.6 us.)
   const bool begin_f32 = !bf && B <= kF32FewRows && d <= kF32FewWidth;

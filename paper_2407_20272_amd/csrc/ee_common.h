@@ -312,7 +312,9 @@ struct SmallShape {
   int whole, halves;   // output tiles that are finished whole, and 16-row halves of the tiles behind them
   int wgs;             // set by the launcher
 };
-bool gemm_small_takes(int B, int d);
+// Whether they take an iteration of B rows (head_tiles: of the LM heads of its exit checks, 0 without), and an exit check on its own.
+bool gemm_small_takes(int B, int d, int head_tiles);
+bool gemm_small_takes_check(int B, int d, int head_tiles);
 void launch_small_qkv(const SmallShape& g, const QkvEpi& e, Pred pred, hipStream_t st, const CombineArgs* with_combine);
 // The first layer's, which begins the iteration as well (x unused; the embedding table starts on 16 bytes).
 void launch_small_begin_qkv(const BeginArgs& begin, const SmallShape& g, const QkvEpi& e, hipStream_t st);

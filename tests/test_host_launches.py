@@ -239,6 +239,24 @@ def test_gate_up_in_the_ring_kernel(program, rows, heads, tiles, ring):
     assert rc.strip() == "rc 0" and want not in launches
 
 
+@pytest.mark.parametrize("rows,heads,vocab,small", [
+    (1, 3, 32000, True), (2, 3, 8192, True), (2, 2, 32000, False), (4, 7, 32000, False), (8, 8, 32000, True), (8, 8, 8224, True), (8, 7, 8224, False),
+    (8, 7, 8192, True), (5, 25, 8192, False)])
+def test_exit_check_of_up_to_eight_rows_without_a_launch_for_its_operand(program, rows, heads, vocab, small):
+    """Where several tiles a workgroup and short contractions (heads of 128) do not make it the slower one."""
+    launches, rc = program("check", 0, rows, heads, 512, vocab)
+    assert rc.strip() == "rc 0"
+    assert any("gemm_small_kernel" in n for n in program.names) == small and len(launches) == (2 if small else 3)
+
+
+@pytest.mark.parametrize("rows,heads,vocab,small", [(8, 5, 1024, True), (8, 4, 1024, False), (5, 3, 1024, False), (4, 2, 8192, True), (4, 2, 8224, False),
+                                                    (3, 3, 32000, True), (2, 1, 32000, True), (8, 25, 1024, False)])
+def test_iteration_of_up_to_eight_rows_in_projections_that_normalise(program, rows, heads, vocab, small):
+    _, rc = program("per_sequence", 0, rows, heads, 512, vocab)
+    assert rc.strip() == "rc 0"
+    assert any("gemm_small_kernel" in n for n in program.names) == small
+
+
 FOUR_PIECES = "ELi4E"   # gemm_simple_kernel<.., PIECES = 4, ..>
 
 
