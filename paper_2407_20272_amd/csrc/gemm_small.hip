@@ -405,21 +405,21 @@ void launch_acc(SmallShape g, const AccEpi& e, Pred pred, hipStream_t st) {
 
 // Every workgroup builds the whole operand, so its rows times its channels are what this costs, and launches are what it saves.
 // Whole iterations, the other kernels' time over this one's: 1 and 2 rows 1.04 (d = 5120) to 1.4 (1024); 3 and 4 rows 1.09 (4096), 1.00
-// (5120), 1.05 (6144); 5 to 8 rows 0.90 (5120), 0.99 to 1.01 (4096), 1.01 (3584), 1.02 (3072), 1.10 (2048), 1.17 (640); 384 and 512 0.97 to 1.01
+// (5120), 1.05 (6144); 5 to 8 rows 0.90 (5120), 0.99 to 1.01 (4096), 1.01 (3584), 1.02 (3072), 1.10 (2048), 1.17 (640); 384 and 512 1.00 to 1.03
 // without exit checks, 0.98 to 1.00 with checks of 1280 words, 0.93 to 0.96 of 8000 and 0.90 to 0.95 of 32000 (few threads hold all rows, and the
 // head is a large part); 9 to 16 rows 0.84 (4096), 0.6 (256).
 // The head alone loses where a workgroup has several tiles of short contractions (each an end of its own: a meeting and one wavefront's
-// epilogue): 32000 words, 4 rows, exit check of 64 / 256 / 384 / 768 / 1024 / 2048 channels 0.84, 0.90, 0.97, 1.01, 1.07, 1.12, of 1 and 2 rows 0.88, 0.93,
-// 1.01, 1.02, 1.10, 1.12, of 8 rows from 384 on 0.93, 0.95, 1.04, 1.10; 8000 words, one tile each, 1.04 to 1.3 everywhere.  In an iteration it
-// saves no launch of its own: of 3 and 4 rows and 32000 words 0.93 (64 channels), 0.95 (192), 0.96 (256), 1.03 (320); 1 and 2 rows 0.99 to 1.05.
+// epilogue): 32000 words, exit check of 4 rows, 64 / 256 / 384 / 640 / 1024 / 2048 channels 0.86, 0.92, 1.02, 1.02, 1.10, 1.15, of 1 and 2 rows 0.90, 0.95,
+// 1.04, 1.03, 1.13, 1.15, of 8 rows from 384 on 0.97, 0.97, 1.06, 1.13; 8000 words, one tile each, 1.07 and more everywhere.  In an iteration it
+// saves no launch of its own: of 3 and 4 rows and 32000 words 0.95 (64 channels), 0.96 (192), 1.00 (256); of 1 and 2 rows 0.99 to 1.05.
 bool gemm_small_takes(int B, int d, int head_tiles) {
   const int R = B <= 2 ? B : B <= 4 ? 4 : 8;
-  if (R == 4 && d < 320 && head_tiles > SM_WGS) return false;
-  return B <= 8 && R * d <= SM_OPERAND && (R < 8 || d >= 640);   // (no more than 64 KiB of LDS)
+  if (R == 4 && d < 256 && head_tiles > SM_WGS) return false;
+  return B <= 8 && R * d <= SM_OPERAND && (R < 8 || d >= (head_tiles ? 640 : 384));   // (no more than 64 KiB of LDS)
 }
 bool gemm_small_takes_check(int B, int d, int head_tiles) {
   if (B > 8 || (B <= 2 ? B : B <= 4 ? 4 : 8) * d > SM_OPERAND) return false;
-  return head_tiles <= SM_WGS || d >= (B <= 2 ? 384 : 1024);
+  return head_tiles <= SM_WGS || d >= (B <= 4 ? 384 : 1024);
 }
 void launch_small_qkv(const SmallShape& g, const QkvEpi& e, Pred pred, hipStream_t st, const CombineArgs* with_combine) {
   if (!with_combine) {

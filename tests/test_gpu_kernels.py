@@ -440,9 +440,9 @@ def test_exit_check_of_up_to_eight_rows(batch, heads, vocab):
     run_exit_check(cfg, seed=batch + heads, layer=1, threshold=0.02)
 
 
-@pytest.mark.parametrize("batch,heads,vocab", [(2, 6, 8224), (2, 5, 8224), (3, 16, 8224), (3, 15, 8224), (8, 15, 8192), (5, 1, 8192)])
+@pytest.mark.parametrize("batch,heads,vocab", [(2, 6, 8224), (4, 5, 8224), (5, 16, 8224), (6, 15, 8224), (8, 15, 8192), (5, 1, 8192)])
 def test_exit_check_of_up_to_eight_rows_on_both_sides_of_its_rule(batch, heads, vocab):
-    """From more than 256 tiles on, one and two rows take that head from 384 channels on, more from 1024."""
+    """From more than 256 tiles on, up to four rows take that head from 384 channels on, more from 1024."""
     run_exit_check(cfg_of("bf16", 64, heads, vocab=vocab, logit_scale=2.0, batch=batch), seed=batch * heads, layer=1, threshold=0.3, hidden_scale=3.0)
 
 

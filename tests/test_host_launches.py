@@ -82,9 +82,9 @@ int main(int argc, char** argv) {
     rc = ee_decode_iteration(&m, &c, &b, 0, 0, EE_EXIT_NONE, p, p, p, 0, 0, p, n, 0);
   else if (!strcmp(argv[1], "float"))
     rc = ee_decode_iteration(&m, &c, &b, never, 0, EE_EXIT_BATCH, p, p, p, 0, 0, p, n, 0);
-  else if (!strcmp(argv[1], "per_sequence")) {
+  else if (!strcmp(argv[1], "per_sequence") || !strcmp(argv[1], "no_checks")) {
     b.row_table = 0;
-    rc = ee_decode_iteration(&m, &c, &b, never, 0, EE_EXIT_PER_SEQUENCE, p, p, p, 0, 0, p, n, 0);
+    rc = ee_decode_iteration(&m, &c, &b, never, 0, argv[1][0] == 'n' ? EE_EXIT_NONE : EE_EXIT_PER_SEQUENCE, p, p, p, 0, 0, p, n, 0);
   } else if (!strcmp(argv[1], "attention"))
     rc = ee_paged_attention_decode(&m.desc, &c, 1, p, &b, p, 0, 0, 0);
   else
@@ -240,7 +240,7 @@ def test_gate_up_in_the_ring_kernel(program, rows, heads, tiles, ring):
 
 
 @pytest.mark.parametrize("rows,heads,vocab,small", [
-    (1, 3, 32000, True), (2, 3, 8192, True), (2, 2, 32000, False), (4, 7, 32000, False), (8, 8, 32000, True), (8, 8, 8224, True), (8, 7, 8224, False),
+    (1, 3, 32000, True), (2, 3, 8192, True), (2, 2, 32000, False), (4, 2, 8224, False), (4, 3, 32000, True), (8, 8, 32000, True), (8, 8, 8224, True), (8, 7, 8224, False),
     (8, 7, 8192, True), (5, 25, 8192, False)])
 def test_exit_check_of_up_to_eight_rows_without_a_launch_for_its_operand(program, rows, heads, vocab, small):
     """Where several tiles a workgroup and short contractions (heads of 128) do not make it the slower one."""
@@ -249,10 +249,12 @@ def test_exit_check_of_up_to_eight_rows_without_a_launch_for_its_operand(program
     assert any("gemm_small_kernel" in n for n in program.names) == small and len(launches) == (2 if small else 3)
 
 
-@pytest.mark.parametrize("rows,heads,vocab,small", [(8, 5, 1024, True), (8, 4, 1024, False), (5, 3, 1024, False), (4, 2, 8192, True), (4, 2, 8224, False),
-                                                    (3, 3, 32000, True), (2, 1, 32000, True), (8, 25, 1024, False)])
-def test_iteration_of_up_to_eight_rows_in_projections_that_normalise(program, rows, heads, vocab, small):
-    _, rc = program("per_sequence", 0, rows, heads, 512, vocab)
+@pytest.mark.parametrize("call,rows,heads,vocab,small", [
+    ("per_sequence", 8, 5, 1024, True), ("per_sequence", 8, 4, 1024, False), ("per_sequence", 5, 3, 1024, False), ("per_sequence", 4, 1, 8192, True),
+    ("per_sequence", 4, 1, 8224, False), ("per_sequence", 4, 2, 8224, True), ("per_sequence", 3, 3, 32000, True), ("per_sequence", 2, 1, 32000, True),
+    ("per_sequence", 8, 25, 1024, False), ("no_checks", 8, 3, 32000, True), ("no_checks", 8, 2, 1024, False), ("no_checks", 4, 1, 32000, True)])
+def test_iteration_of_up_to_eight_rows_in_projections_that_normalise(program, call, rows, heads, vocab, small):
+    _, rc = program(call, 0, rows, heads, 512, vocab)
     assert rc.strip() == "rc 0"
     assert any("gemm_small_kernel" in n for n in program.names) == small
 
