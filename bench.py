@@ -26,15 +26,20 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 
 
+def elem_bytes(cfg):
+    """A weight, or a cached value."""
+    return 4 if cfg.dtype == "fp32" else 2
+
+
 def algorithmic_bytes(cfg, cls):
     """Bytes one launch of a projection class must move: its weights, once."""
-    d, f, V = cfg.d_model, cfg.d_ffn, cfg.vocab
-    return {"qkv": 3 * d * d * 2, "o_proj": d * d * 2, "gate_up": 2 * f * d * 2, "down": d * f * 2, "head": V * d * 2}.get(cls)
+    d, f, V, e = cfg.d_model, cfg.d_ffn, cfg.vocab, elem_bytes(cfg)
+    return {"qkv": 3 * d * d * e, "o_proj": d * d * e, "gate_up": 2 * f * d * e, "down": d * f * e, "head": V * d * e}.get(cls)
 
 
 def kv_bytes_per_position(cfg):
     """K and V of one cached position of one layer (what attention must read for it)."""
-    return 2 * cfg.d_model * 2
+    return 2 * cfg.d_model * elem_bytes(cfg)
 
 
 def layers_with_head(cfg, upto):
@@ -56,7 +61,7 @@ def iteration_bytes(cfg, kind, L, attended_layer_positions):
             total += algorithmic_bytes(cfg, "head")               # the final LM-head pass
     else:
         total += algorithmic_bytes(cfg, "head")                   # one LM-head pass for the tokens
-    total += (n - L) * 2 * d * d * 2                              # KV filling: K and V rows of every skipped layer
+    total += (n - L) * 2 * d * d * elem_bytes(cfg)                # KV filling: K and V rows of every skipped layer
     return total
 
 
@@ -361,8 +366,10 @@ def main():
             E_cpu, C_cpu = E_steps.cpu(), C_steps.cpu()
             per_iter = len(recs) // P
             agg = collections.defaultdict(lambda: [0, 0.0, 0.0])     # launches, milliseconds, algorithmic bytes
-            # up to 64 rows the projection that shares a launch with the decision has cached the first skipped layer
-            cached_ahead = 1 if cfg.dtype == "bf16" and Bsz <= 64 else 0
+            # up to 64 rows the projection that shares a launch with the decision, or runs ahead of it, has cached the first skipped
+            # layer (float path: softmax measures, up to 512 channels)
+            shares = cfg.dtype == "bf16" or (cfg.d_model <= 512 and base_mode not in ("sim", "cls"))
+            cached_ahead = 1 if shares and Bsz <= 64 else 0
             for it in range(P):
                 for cls, layer, ms in recs[it * per_iter:(it + 1) * per_iter]:
                     # kernels of layers above the batch exit layer return at once; KV filling only runs after an
@@ -373,7 +380,9 @@ def main():
                         executed = True
                     if not executed:
                         continue
-                    if cls == "kv_fill":      # K and V weight rows of every layer it fills
+                    if cfg.dtype == "fp32":   # its launches share work across classes: times only
+                        ab = 0.0
+                    elif cls == "kv_fill":    # K and V weight rows of every layer it fills
                         ab = (n - Lp[it] - cached_ahead) * 2.0 * cfg.d_model * cfg.d_model * 2
                     elif cls == "attention":  # cached K/V of the sequences that still attend in this layer
                         attends = (E_cpu[it] >= layer) if per_seq_mode else torch.ones(Bsz, dtype=torch.bool)

@@ -233,11 +233,15 @@ int ee_paged_attention_decode(const ee_model_desc* desc, const ee_kv_cache* cach
                               void* stream);
 
 /* ---- Measurement helpers (not part of the decode path) ------------------------------------------------------
- * While enabled, every later ee_* call brackets each kernel it enqueues with a pair of HIP events on the call's
+ * While enabled, every later ee_* call brackets the kernels it enqueues with pairs of HIP events on the call's
  * stream (the events add a few microseconds per kernel, so throughput is timed with profiling off).
  * ee_profile_read waits for the recorded events and returns, for up to max_records kernels in launch order,
  * the kernel class (EE_K_*), the 1-based layer it belongs to (0 = none) and its duration in milliseconds;
- * the records are then discarded.  Returns the number of records written, or a negative error code. */
+ * the records are then discarded.  Returns the number of records written, or a negative error code.
+ * Launches that are made together have one record (attention with the merge of its parts, KV filling with its operand).
+ * So has a launch that does the work of several kernels, under what it is named after: an exit decision or the start of an
+ * iteration inside a QKV projection is part of EE_K_QKV; in small float models the exit head of a layer is part of the next
+ * layer's EE_K_QKV, or of EE_K_KVFILL, and the exit decision and the output projection of EE_K_ATTN. */
 #define EE_K_NORM 0     /* sum of squares + normalised projection input                         */
 #define EE_K_QKV 1      /* QKV projection + rotary + cache write                                */
 #define EE_K_ATTN 2     /* paged decode attention                                               */

@@ -566,34 +566,34 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // (Small float models: in the launch of the first projection, which reads the embedding rows and forms the angles itself: four sequences 72.8 -> 70.6 us.)
   const bool begin_f32 = !bf && B <= kF32FewRows && d <= kF32FewWidth;
   BeginArgs ba{};
-  {
+  ba.s = s;
+  ba.conf_out = out_conf;
+  ba.context_lens = batch->context_lens;
+  ba.tokens = batch->tokens;
+  ba.rope = w.rope;
+  ba.h = w.h;
+  ba.snapshot = simmode ? w.hprev : nullptr;   // h_0, the "previous" hidden state of layer 1
+  ba.theta = D.rope_theta;
+  ba.eps = D.rms_eps;
+  ba.B = B;
+  ba.Mpad = Mpad;
+  ba.d = d;
+  ba.vocab = D.vocab;
+  ba.n_layers = n;
+  ba.head_dim = D.head_dim;
+  if (bf) {
+    ba.embed = reinterpret_cast<const bf16_t*>(model->embed);
+    ba.gain = reinterpret_cast<const bf16_t*>(model->layers[0].g_attn);
+    ba.x = w.xT;
+    ba.rowsq_out = rs(0);
+    ba.rm = rmap;
+  } else {
+    ba.embed_f32 = reinterpret_cast<const float*>(model->embed);
+  }
+  if (!(bf ? begin_small : begin_f32)) {
     ProfScope ps(EE_K_OTHER, 0, st);
-    ba.s = s;
-    ba.conf_out = out_conf;
-    ba.context_lens = batch->context_lens;
-    ba.tokens = batch->tokens;
-    ba.rope = w.rope;
-    ba.h = w.h;
-    ba.snapshot = simmode ? w.hprev : nullptr;   // h_0, the "previous" hidden state of layer 1
-    ba.theta = D.rope_theta;
-    ba.eps = D.rms_eps;
-    ba.B = B;
-    ba.Mpad = Mpad;
-    ba.d = d;
-    ba.vocab = D.vocab;
-    ba.n_layers = n;
-    ba.head_dim = D.head_dim;
-    if (bf) {
-      ba.embed = reinterpret_cast<const bf16_t*>(model->embed);
-      ba.gain = reinterpret_cast<const bf16_t*>(model->layers[0].g_attn);
-      ba.x = w.xT;
-      ba.rowsq_out = rs(0);
-      ba.rm = rmap;
-      if (!begin_small) launch_iter_begin(ba, st);
-    } else {
-      ba.embed_f32 = reinterpret_cast<const float*>(model->embed);
-      if (!begin_f32) launch_iter_begin_f32(ba, st);
-    }
+    if (bf) launch_iter_begin(ba, st);
+    else launch_iter_begin_f32(ba, st);
   }
   // bf16 path: the residual update of a projection and the RMSNorm that follows it are one launch (NormArgs):
   // it adds the projection's partial results (n_slices of them) to the residual rows, leaves the rows' sums of
