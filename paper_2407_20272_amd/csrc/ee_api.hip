@@ -86,7 +86,7 @@ struct Workspace {
   float4* partials;   // bf16: [Mpad][vocab/32]
   float* h;           // residual stream: bf16 [Mpad][d], fp32 [B][d]
   // bf16 path
-  float* y;           // [slices][Mpad][d] partial results of the output / down projection
+  float* y;           // [slices][Mpad][d] partial results of the output / down projection; up to eight rows: attention's result [B][d]
   bf16_t* xH;         // [Mpad][d] exit-head operand, directly followed by
   bf16_t* xT;         // [Mpad][d] layer operand
   bf16_t* aoT;        // [Mpad][d]
@@ -544,9 +544,10 @@ int ee_decode_iteration(const ee_model* model, const ee_kv_cache* cache, const e
   // residual columns.  The QKV projection keeps all rows in place (it does the KV filling of those that left).
   const bool compact = left && bf16_compactable(D, B);
   const RowMap rmap = compact ? w.rowmap : RowMap{};
-  // So does the last LM head, whose rows that have left have their tokens (a head-less measure has produced none).  7B shape, 256 rows of four
-  // layers with exits of their own 1791 -> 1770 us, 200 of three 895 -> 878, nobody leaving equal; at 300 to 500 rows 2 to 4 % faster with
-  // exits spread over the layers, but 2 % slower where nobody leaves: compacted rows do not go in blocks of as many.
+  // So does the last LM head, whose rows that have left have their tokens (a head-less measure has produced none): the same output from
+  // less work.  7B shape, 256 rows of four layers with exits of their own and 200 of three: 1 to 2 % less time, about what two runs of one
+  // side differ by; nobody leaving equal; at 300 to 500 rows 2 to 4 % faster with exits spread over the layers, but 2 % slower where nobody
+  // leaves: compacted rows do not go in blocks of as many.
   const bool compact_last = compact && !dotmode && B <= 256;
   // Kernels of the layer loop run only while the batch has not left.  It cannot have before the first check has been decided:
   // what is launched up to then takes no predicate (a kernel

@@ -36,7 +36,8 @@ void set_error(const char* fmt, ...);
 // The fp32 residual stream is plain row-major [Mpad][d].  The output and down projections do not add into it:
 //   each contraction slice writes its partial result to a slice of its own ([slices][Mpad][d], plain stores), and
 //   the normalisation kernel that follows sums the slices in slice order, adds them to the residual row and
-//   normalises it.  No float atomics anywhere, so the bf16 path is reproducible bit for bit.
+//   normalises it.  (Up to eight rows, gemm_small.hip, they do: a workgroup has whole contractions and adds each to its element
+//   of the residual rows, and activations are plain rows.)  No float atomics anywhere, so the bf16 path is reproducible bit for bit.
 // ---------------------------------------------------------------------------------------------------
 __host__ __device__ inline size_t xt_index(int m, int k, int K) {
   return ((size_t)(m >> 5) * (size_t)(K >> 4) + (size_t)(k >> 4)) * 512 + (size_t)((((k >> 3) & 1) << 5) + (m & 31)) * 8 +
@@ -95,12 +96,12 @@ __device__ inline bool kv_filled(const QkvEpi& e, int m) {
   return e.fill_from && !(e.fill_from[(size_t)m * e.fill_from_stride] + e.fill_lead < e.layer);
 }
 struct AccEpi {                 // residual update
-  float* h;                     // fp32 path: the residual stream [M][n_out], added to in place (one contributor per element).
-                                // bf16 path: partial results [slices][Mpad][n_out]; slice s receives the sum over the
+  float* h;                     // fp32 path and gemm_small.hip: the residual stream [M][n_out], added to in place (one contributor per element).
+                                // else: partial results [slices][Mpad][n_out]; slice s receives the sum over the
                                 // s-th part of the contraction (operand row m -> row m: compacted operands stay compacted)
-  int Mpad;                     // row count of a slice (bf16 path) or 0 (fp32 path)
+  int Mpad;                     // row count of a slice, or 0 (added in place)
   int n_out;
-  const int32_t* skip;          // fp32 path: nullptr, or [M]: rows with skip[m] != 0 keep their hidden state
+  const int32_t* skip;          // added in place: nullptr, or [M]: rows with skip[m] != 0 keep their hidden state
   const float* h_in;            // fp32 path: nullptr (added in place), or what is added to, with h the result
 };
 struct GateUpEpi {              // act = silu(gate) * up

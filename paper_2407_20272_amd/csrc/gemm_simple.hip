@@ -8,7 +8,8 @@
 // one.  So the launches are few (ee_decode_iteration) and what a launch reads is asked for at once, behind its predicate.
 // One iteration of four sequences and four layers of width 256, leaving at layer 3: 65 launches and 217 us with a launch a step, 27
 // and 98 us with norms and decisions inside the projections, 19 and 83 us with four launches a layer, 75 us with the operands asked for at once,
-// 73 with no second layer-4 projection in KV filling, 18 and 71 us with the start in the first projection's launch.
+// 73 with no second layer-4 projection in KV filling, 18 and 71 us with the start in the first projection's launch, 67 with
+// every predicate ahead of the operands.
 #include <type_traits>
 
 #include "ee_common.h"

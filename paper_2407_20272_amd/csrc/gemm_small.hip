@@ -5,9 +5,10 @@
 //     contractions of 16 or 32 output rows, its four wavefronts a quarter of each, so nothing is left for another launch to add.
 //   * Every wavefront walks its loads, over all of its tiles, as one stream SM_SETS - 1 groups ahead; sums of a tile meet in LDS and one
 //     wavefront finishes them while the others go on.  The first weights are asked for before the operand is built.
-// 7B shape, two layers: 1 sequence at 1000 positions 246 -> 217 us (QKV 21.4 -> 19.6, gate/up 31.2 -> 30, LM head 43.6 -> 42.9 us by trace, two
-// normalisations of 4 to 5 us a layer gone), 2 sequences of three layers 366 -> 332, 4 sequences 300 -> 275.  What bounds it: the weights,
-// 6.3 TB/s in the LM head, and the start of six launches a layer.
+// 7B shape, two layers: 1 sequence at 1000 positions 246 -> 217 us, 2 sequences of three layers 366 -> 332, 4 sequences 300 -> 275.  One trace of
+// the first, both sides: QKV 21.9 -> 19.0, gate/up 31.7 -> 29.5, LM head 43.6 -> 42.3, output 8.4 -> 7.7, two normalisations of 4 to 5 us a layer gone; the
+// down projection went 16.7 -> 17.4 (whole contractions in two passes of a workgroup, not eight slices), for the 5 us of the normalisation that
+// added its slices.  What bounds it: the weights, 6.2 TB/s in the LM head, and the start of six launches a layer.
 #include <type_traits>
 
 #include "ee_common.h"
