@@ -214,7 +214,7 @@ __device__ __forceinline__ void attn_decode(const AttnArgs& a, const Op& op, int
   if (lb + NW < lb_end) fetch(B, lb + NW);
   // The head's columns of this workgroup's rows of the output projection, LPT lanes a row, are on their way while the keys are
   // looked at.
-  constexpr int AHEAD = OPROJ ? 8 : 1, RPI = NW * TPL;
+  constexpr int RPI = NW * TPL, AHEAD = OPROJ ? 64 / RPI : 1;   // (256 channels at most: 64 rows a workgroup)
   float4 wo[AHEAD];
   [[maybe_unused]] const float* wrow = nullptr;
   [[maybe_unused]] int d_out = 0, rows = 0;
@@ -316,7 +316,6 @@ __device__ __forceinline__ void attn_decode(const AttnArgs& a, const Op& op, int
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i)
       if (i * RPI < rows) row(wo[i], i);
-    for (int i = AHEAD; i * RPI < rows; ++i) row(*reinterpret_cast<const float4*>(wrow + (size_t)i * RPI * d_out), i);
   }
 }
 

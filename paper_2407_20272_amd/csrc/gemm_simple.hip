@@ -167,7 +167,7 @@ __device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fi
     if constexpr (NORM) v.gn = *reinterpret_cast<const vec_t*>(g.gain + k);
 #pragma unroll
     for (int i = 0; i < MC; ++i) v.x[i] = *reinterpret_cast<const vec_t*>(x[i] + k);
-    if constexpr (PARTS) {   // the first four parts
+    if constexpr (PARTS) {   // (four at most: 256 channels, heads of 64 and more)
 #pragma unroll
       for (int q = 0; q < PN; ++q)
 #pragma unroll
@@ -183,7 +183,6 @@ __device__ __forceinline__ void simple_body(SimpleShape g, Epi e, const Fill& fi
         vec_t p = v.p[0][i];
 #pragma unroll
         for (int q = 1; q < PN; ++q) p = q < g.n_parts ? p + v.p[q][i] : p;
-        for (int q = PN; q < g.n_parts; ++q) p += *reinterpret_cast<const vec_t*>(g.parts + ((size_t)q * g.M + m) * g.K + k);
         if (!(g.left && ctl_load(g.left + m) != 0)) v.x[i] += p;   // (a sequence that has left: its parts may not have been written)
         if (pair == 0 && m0 + i < g.M) *reinterpret_cast<vec_t*>(g.x_out + (size_t)m * g.K + k) = v.x[i];
       }

@@ -81,14 +81,19 @@ def test_fp32_odd_widths(batch, d_ffn, vocab, conf_mode):
     (1, 1, 64, 62, 1, True),       # no layer behind the first: the only LM head runs beside KV filling
     (32, 2, 64, 130, 3, 2),        # 64 (sequence, head) pairs: attention multiplies by the output projection; contraction of 130, no 16-byte loads
     (33, 2, 64, 256, 3, True),     # 66: a launch of its own again
-    (12, 5, 64, 1028, 3, 2),       # 320 channels: a last iteration of 64 of them; five parts, four of them loaded ahead; past 1024 in a loop
-    (16, 4, 128, 1024, 3, True),   # 512 channels, 64 pairs, 1024 of a contraction ahead
+    (16, 4, 64, 1028, 3, 2),       # the widest, 64 pairs: four parts; the down projection past 1024 in a loop
+    (17, 4, 64, 1024, 3, True),    # 68 pairs; 1024 of a contraction at once, in 160 workgroups
+    (32, 2, 128, 1024, 3, 2),      # .. in 256
+    (36, 2, 128, 1024, 3, True),   # .. in 288: a loop
+    (3, 3, 64, 640, 3, 2),         # three parts, three pieces
     (64, 2, 128, 320, 2, 2),       # the last row count of the four-launch form ..
     (65, 2, 128, 320, 2, True),    # .. past it
-    (5, 9, 64, 576, 2, True),      # .. and past its width
+    (12, 5, 64, 1028, 3, 2),       # .. and past its width: 320 channels ..
+    (16, 4, 128, 1024, 3, True),   # .. 512, the last width of the decision inside QKV ..
+    (5, 9, 64, 576, 2, True),      # .. and past that
 ])
 def test_fp32_layers_in_four_launches(batch, heads, dh, d_ffn, layers, head_mode):
-    """Float layers of up to 64 rows and 512 channels, at the edges of the forms: the LM head beside the next QKV projection or KV filling,
+    """Float layers of up to 64 rows and 256 channels, at the edges of the forms: the LM head beside the next QKV projection or KV filling,
     the decision in front of attention, the output projection inside it; sequences leave together or one by one."""
     cfg = TINY.with_(batch=batch, n_heads=heads, head_dim=dh, d_model=heads * dh, d_ffn=d_ffn, vocab=130, n_layers=layers, prompt_len=20,
                      min_prompt_len=3, weight_std=0.05, logit_scale=1.0, threshold=0.3, shuffled_blocks=True, tied_head=False)
